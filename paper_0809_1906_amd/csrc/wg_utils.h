@@ -11,13 +11,17 @@ namespace wg {
 
 constexpr int PB = 256; // threads per workgroup
 
-// Workgroup barrier with device-scope ordering: per-source arrays are updated
-// by device atomics (performed in L2), so every phase change must make them
-// visible across the workgroup's waves.
+// Workgroup barrier between the phases of a per-source sweep.  The arrays it
+// orders (distances, counts, sums, queues in global memory) belong to one
+// workgroup, whose waves share a compute unit's L1: workgroup scope, which
+// __syncthreads carries, orders them, atomics included.  The wait makes every
+// atomic and store of the phase complete before any wave goes on.  With
+// agent-scope fences around it every barrier wrote back and invalidated the
+// XCD's L2: all sources of G(1024, 8/1023) took 2252 us instead of 578, and
+// 1024 sources of RMAT-16 with weights 1..255 304 ms instead of 27.5.
 __device__ __forceinline__ void bar() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
 __device__ __forceinline__ int wave_incl_scan(int x) {
