@@ -158,12 +158,17 @@ struct WeightedState {
 constexpr int MG_MAX_N = 4096; // largest graph a many-graph context takes
 struct MultiState {
     int32_t ngraphs = 0, nunits = 0, chunk = 64, grid = 0;
-    int32_t ncompact = 0;             // units [0, ncompact) go to the compact sweep first
+    int32_t nbig = 0, nsmall = 0;     // units [0, nbig) and the next nsmall go to the group sweep
     int32_t *voff = nullptr, *rpoff = nullptr, *rp = nullptr, *units = nullptr;
-    int32_t *redo = nullptr;          // compact units handed back to the full sweep
-    unsigned int *next = nullptr;     // queue counters: compact, full, redo; [3] = redo count
+    int32_t *redo = nullptr;          // group-sweep units handed back to the full sweep
+    unsigned int *next = nullptr;     // queue counters: big, full, redo; [3] = redo count; [4] = small
     std::vector<int32_t> h_voff;
     std::vector<int32_t> h_arcs;      // arcs of each graph
+    std::vector<uint8_t> h_group;     // graphs the group sweep takes
+    uint16_t *brp = nullptr;          // group sweep: row starts in bursts, burst offsets, padded columns
+    int64_t *boff = nullptr;
+    uint32_t *safe = nullptr;         // per graph: largest count whose sums need no wrap test
+    void *bursts = nullptr;
     std::vector<int32_t> h_order;     // graphs by n_g descending (stable)
     hipStream_t stream = nullptr;     // private stream the launch is captured on
     hipEvent_t ev = nullptr;

@@ -7,29 +7,22 @@
 // graph).
 //
 // The work is a device queue of units (graph, [s0, s1) of its sources) sorted
-// by n_g^2 descending, largest first (longest-processing-time order).  A grid
-// of persistent 512-thread workgroups pulls units with an atomic counter and
-// exits when the queue is drained.  For each source the workgroup runs the
-// level-synchronous forward sweep (distance, exact uint64 counts) and the
-// backward sweep (c(v) = (1 + delta(v)) / lambda(v) in FP32, sums in FP64)
-// entirely in LDS; each unit's dependencies are summed in an FP64 LDS vector
-// and added to BC once per unit.  The unit's columns are staged in LDS as
-// 16-bit local ids when they fit (n <= 4096), so that a level step waits on
-// LDS only; larger graphs read them from global memory.
-//
-// The level steps are latency-bound, so a compact sweep runs first with two
-// workgroups per compute unit.  Each takes under half of the LDS:
-// - 16-bit distances;
-// - 32-bit counts, each overwritten by c(v) in the backward once v's own
-//   dependency is known;
-// - at most LEVCAP levels;
-// - 16-bit row offsets and columns read through the caches.
-// It takes the graphs with at most 65535 arcs. A unit whose counts pass 2^32
-// - 1 or whose depth passes LEVCAP drops its partial sums and is handed to the
-// full sweep. The launches (counter reset, compact sweep, full sweep over the
-// remaining graphs, full sweep over the handed-back units) are captured once
-// into a HIP graph and replayed.
+// by n_g descending, largest first (longest-processing-time order).  A grid of
+// persistent workgroups pulls units with an atomic counter and exits when the
+// queue is drained.  Two sweeps:
+//   group sweep  (lds_sweep.h) as many sources at once as the LDS holds, 32-bit
+//                counts overwritten by FP32 c(v), at most LEVCAP levels; for
+//                graphs of fewer than 65536 bursts of eight columns;
+//   full sweep   one source at a time, 64-bit counts, any depth; for the other
+//                graphs, the units that the group sweep hands back (a count
+//                past 2^32 - 1, more levels) and the per-source readout.
+// In both, each unit's dependencies are summed in an FP64 LDS vector and added
+// to BC once per unit.  The full sweep's columns are staged in LDS as 16-bit
+// local ids when they fit.  The launches (counter reset, group sweeps, full
+// sweep over the remaining graphs, full sweep over the handed-back units) are
+// captured once into a HIP graph and replayed.
 #include "bc_internal.h"
+#include "lds_sweep.h"
 
 #include <algorithm>
 
@@ -39,8 +32,20 @@ constexpr int MT = 512;          // threads per workgroup
 constexpr int32_t MG_INF = 0x7FFFFFFF;
 constexpr int ABURST = 8;        // column reads issued together per vertex
 constexpr int32_t COL_CAP = 16320; // 16-bit columns staged in LDS
-constexpr int LEVCAP = 1024;       // levels per source in the compact sweep
-constexpr uint32_t D16_INF = 0xFFFF;
+constexpr int LEVCAP = 1024;       // levels per source in the group sweep
+// The group sweep is bound by VALU and LDS issue about equally (counters: each
+// busy 45-50% of the time, the rest barriers and latency), and gains from
+// every source that shares a barrier: one workgroup of 1024 threads with the
+// whole LDS (K = 4 at n = 4096).  256 Watts-Strogatz graphs, n = 64..4096:
+// 20.0 ms, against 23.0 with two workgroups of 512 and half the LDS each, and
+// 67.8 with one source at a time per workgroup, 32-bit columns and a
+// compare-and-swap per arc.  Tiny graphs fill a quarter of the LDS with all
+// their sources: 5000 graphs of 30 vertices 0.19 ms against 0.33, 3000 of 100
+// 0.49 against 0.56; even at 250, and slower from 1000 (8.3 against 6.8 ms).
+constexpr int BIG_T = 1024, BIG_BYTES = 163000, SMALL_T = 512, SMALL_BYTES = 40000;
+constexpr int32_t SMALL_N = 256;
+static_assert(lds_sweep::bytes_for<uint32_t>(MG_MAX_N, 1, LEVCAP) <= BIG_BYTES, "one source of the largest graph");
+static_assert(lds_sweep::bytes_for<uint32_t>(SMALL_N, 1, SMALL_N) <= SMALL_BYTES, "one source of a small graph");
 
 struct MultiArgs {
     const int32_t *voff;   // [ngraphs+1] first global vertex of each graph
@@ -51,7 +56,11 @@ struct MultiArgs {
     int32_t nunits;
     const unsigned int *nunits_dev; // if set, the unit count is read here instead
     unsigned int *next;    // queue counter
-    int32_t *redo;         // compact sweep: units handed to the full sweep
+    const uint16_t *brp;   // group sweep: first burst of each row, indexed as rp
+    const int64_t *boff;   // [ngraphs] first burst of each graph (-1: not in the group sweep)
+    const uint32_t *safe;  // [ngraphs] (2^32 - 1) / largest degree
+    const uint4 *bursts;   // columns as 16-bit ids, eight per burst
+    int32_t *redo;         // group sweep: units handed to the full sweep
     unsigned int *redo_count;
     double *bc;            // [sum n]
     uint32_t *status;
@@ -63,7 +72,7 @@ struct MultiArgs {
 };
 
 __global__ void k_mg_reset(unsigned int *next) {
-    if (threadIdx.x < 4) next[threadIdx.x] = 0;
+    if (threadIdx.x < 5) next[threadIdx.x] = 0;
 }
 
 struct MgShared {
@@ -219,147 +228,74 @@ __global__ __launch_bounds__(MT) void k_mg_sweep(MultiArgs a) {
     }
 }
 
-// ---- the compact sweep ------------------------------------------------------------
+// ---- the group sweep --------------------------------------------------------------
 
-struct MgCompact {
-    uint32_t dist2[MG_MAX_N / 2]; // two 16-bit distances per word, D16_INF = unreached
-    uint32_t sc[MG_MAX_N];        // the count (uint32) in the forward; c(v) (float bits) after v's backward step
-    uint16_t queue[MG_MAX_N];
-    uint16_t lev[LEVCAP + 2];
-    double bc[MG_MAX_N];
-    uint16_t rp[MG_MAX_N + 1];    // row offsets relative to the graph's first arc
-    int32_t unit, cnt[3];
-    uint32_t fail;                // counts or depth out of range: the full sweep redoes the unit
-};
-
-__device__ __forceinline__ uint32_t d16_get(const uint32_t *d2, int32_t v) {
-    return (d2[v >> 1] >> (16 * (v & 1))) & 0xFFFFu;
-}
-
-// Level of w, claiming it for level nl when it is unreached (*claimed says so).
-__device__ __forceinline__ uint32_t d16_claim(uint32_t *d2, int32_t w, uint32_t nl, bool &claimed) {
-    const int sh = 16 * (w & 1);
-    uint32_t word = d2[w >> 1];
-    for (;;) {
-        const uint32_t cur = (word >> sh) & 0xFFFFu;
-        if (cur != D16_INF) {
-            claimed = false;
-            return cur;
+// Columns of every graph the group sweep takes, padded to bursts (one block
+// per graph).
+__global__ __launch_bounds__(256) void k_mg_pad(const int32_t *__restrict__ voff, const int32_t *__restrict__ rpoff,
+                                                const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+                                                const uint16_t *__restrict__ brp, const int64_t *__restrict__ boff,
+                                                uint4 *__restrict__ bursts) {
+    const int32_t g = blockIdx.x;
+    if (boff[g] < 0) return;
+    const int32_t n = voff[g + 1] - voff[g];
+    const int32_t *r = rp + rpoff[g];
+    const uint16_t *br = brp + rpoff[g];
+    uint4 *out = bursts + boff[g];
+    for (int32_t v = threadIdx.x; v < n; v += 256) {
+        int32_t e = r[v];
+        for (int32_t b = br[v]; b < br[v + 1]; ++b) {
+            uint32_t x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t lo = e < r[v + 1] ? (uint32_t)col[e] : (uint32_t)n;
+                const uint32_t hi = e + 1 < r[v + 1] ? (uint32_t)col[e + 1] : (uint32_t)n;
+                x[q] = lo | hi << 16;
+                e += 2;
+            }
+            out[b] = make_uint4(x[0], x[1], x[2], x[3]);
         }
-        const uint32_t want = (word & ~(0xFFFFu << sh)) | (nl << sh);
-        const uint32_t old = atomicCAS(&d2[w >> 1], word, want);
-        if (old == word) {
-            claimed = true;
-            return nl;
-        }
-        word = old; // the other half changed, or another thread claimed w
     }
 }
 
-// The sources [s0, s1) of the unit in sh (graph of n vertices, columns col).
-__device__ void mg_unit_compact(MgCompact &sh, int32_t n, const int32_t *__restrict__ col, int32_t s0, int32_t s1) {
+template <int T, int BYTES>
+__global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
+    __shared__ __attribute__((aligned(16))) unsigned char raw[BYTES];
+    __shared__ int32_t s_unit, s_cnt[3];
+    __shared__ uint32_t s_fail;
     const int tid = threadIdx.x;
-    for (int32_t s = s0; s < s1 && !sh.fail; ++s) {
-        for (int32_t v = tid; v < (n + 1) / 2; v += MT) sh.dist2[v] = 0xFFFFFFFFu;
-        for (int32_t v = tid; v < n; v += MT) sh.sc[v] = 0;
-        __syncthreads();
+    for (;;) {
         if (tid == 0) {
-            sh.dist2[s >> 1] &= ~(0xFFFFu << (16 * (s & 1))); // level 0
-            sh.sc[s] = 1;
-            sh.queue[0] = (uint16_t)s;
-            sh.lev[0] = 0;
-            sh.lev[1] = 1;
-            sh.cnt[0] = sh.cnt[1] = sh.cnt[2] = 0;
+            s_unit = (int32_t)atomicAdd(a.next, 1u);
+            s_fail = 0;
         }
         __syncthreads();
-        // forward: as in the full sweep (three counters, one barrier per level)
-        int32_t qb = 0, qe = 1, L = 0;
-        while (qb < qe) {
-            const int cur = L % 3;
-            if (tid == 0) sh.cnt[(L + 1) % 3] = 0;
-            for (int32_t i = qb + tid; i < qe; i += MT) {
-                const int32_t v = sh.queue[i];
-                const uint32_t sv = sh.sc[v];
-                const int32_t rb = sh.rp[v], re = sh.rp[v + 1];
-                for (int32_t e0 = rb; e0 < re; e0 += ABURST) {
-                    int32_t ws[ABURST];
-#pragma unroll
-                    for (int j = 0; j < ABURST; ++j) ws[j] = e0 + j < re ? col[e0 + j] : -1;
-#pragma unroll
-                    for (int j = 0; j < ABURST; ++j) {
-                        const int32_t w = ws[j];
-                        if (w < 0) continue;
-                        bool claimed = false;
-                        const uint32_t dw = d16_claim(sh.dist2, w, (uint32_t)(L + 1), claimed);
-                        if (claimed) sh.queue[qe + atomicAdd(&sh.cnt[cur], 1)] = (uint16_t)w;
-                        if (dw == (uint32_t)(L + 1)) { // v in P_s(w)
-                            const uint32_t old = atomicAdd(&sh.sc[w], sv);
-                            if (old + sv < old) sh.fail = 1;
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-            qb = qe;
-            qe += sh.cnt[cur];
-            ++L;
-            if (L + 1 > LEVCAP) {
-                if (tid == 0) sh.fail = 1;
-                break;
-            }
-            if (tid == 0) sh.lev[L + 1] = (uint16_t)qe;
-        }
-        __syncthreads();
-        if (sh.fail) break;
-        const int32_t nlev = L;
-        // backward: deepest level first; one thread per vertex; c(v) replaces
-        // the count of v (read only by v's own thread, just before)
-        for (int32_t l = nlev - 1; l >= 1; --l) {
-            for (int32_t i = sh.lev[l] + tid; i < sh.lev[l + 1]; i += MT) {
-                const int32_t v = sh.queue[i];
-                double acc = 0.0;
-                if (l + 1 < nlev) {
-                    const int32_t rb = sh.rp[v], re = sh.rp[v + 1];
-                    for (int32_t e0 = rb; e0 < re; e0 += ABURST) {
-                        int32_t ws[ABURST];
-#pragma unroll
-                        for (int j = 0; j < ABURST; ++j) ws[j] = e0 + j < re ? col[e0 + j] : -1;
-#pragma unroll
-                        for (int j = 0; j < ABURST; ++j)
-                            if (ws[j] >= 0 && d16_get(sh.dist2, ws[j]) == (uint32_t)(l + 1))
-                                acc += (double)__uint_as_float(sh.sc[ws[j]]);
-                    }
-                }
-                const double sv = (double)sh.sc[v];
-                const double dl = sv * acc;
-                sh.sc[v] = __float_as_uint((float)((1.0 + dl) / sv));
-                if (v != s) sh.bc[v] += dl;
-            }
-            __syncthreads();
-        }
-    }
-}
-
-__global__ __launch_bounds__(MT, 2) void k_mg_sweep_compact(MultiArgs a) {
-    __shared__ MgCompact sh;
-    const int tid = threadIdx.x;
-    for (;;) {
-        if (tid == 0) sh.unit = (int32_t)atomicAdd(a.next, 1u);
-        __syncthreads();
-        const int32_t u = sh.unit;
+        const int32_t u = s_unit;
         if (u >= a.nunits) break;
         const int32_t g = a.units[3 * u], s0 = a.units[3 * u + 1], s1 = a.units[3 * u + 2];
         const int32_t vo = a.voff[g], n = a.voff[g + 1] - vo;
-        const int32_t *grp = a.rp + a.rpoff[g];
-        for (int32_t v = tid; v <= n; v += MT) sh.rp[v] = (uint16_t)(grp[v] - grp[0]);
-        for (int32_t v = tid; v < n; v += MT) sh.bc[v] = 0.0;
-        if (tid == 0) sh.fail = 0;
+        const int32_t levels = min(n, LEVCAP);
+        int32_t K = lds_sweep::group_size<uint32_t>(BYTES, n, levels, s1 - s0);
+        const int32_t groups = (s1 - s0 + K - 1) / K;
+        K = (s1 - s0 + groups - 1) / groups; // even groups
+        lds_sweep::Arrays<uint32_t> s(raw, n, K, levels);
+        const uint16_t *br = a.brp + a.rpoff[g];
+        const uint4 *cols = a.bursts + a.boff[g];
+        for (int32_t v = tid; v <= n; v += T) s.rp[v] = br[v];
+        for (int32_t v = tid; v < n; v += T) s.bc[v] = 0.0;
+        bool deep = false;
+        for (int32_t k0 = s0; k0 < s1; k0 += K) {
+            s.K = min(K, s1 - k0);
+            const int32_t nlev = lds_sweep::forward<uint32_t, T>(
+                s, cols, [&](int32_t k) { return k0 + k; }, a.safe[g], s_cnt, &s_fail);
+            deep = nlev < 0;
+            if (deep || s_fail) break; // uniform: the forward ends with a barrier
+            lds_sweep::backward<uint32_t, T>(s, cols, nlev, 1, [](int32_t, int32_t, double) {});
+        }
         __syncthreads();
-        mg_unit_compact(sh, n, a.col + grp[0], s0, s1);
-        __syncthreads();
-        if (!sh.fail) {
-            for (int32_t v = tid; v < n; v += MT)
-                if (sh.bc[v] != 0.0) unsafeAtomicAdd(&a.bc[vo + v], sh.bc[v]);
+        if (!deep && !s_fail) {
+            for (int32_t v = tid; v < n; v += T)
+                if (s.bc[v] != 0.0) unsafeAtomicAdd(&a.bc[vo + v], s.bc[v]);
         } else if (tid == 0) {
             const unsigned int k = atomicAdd(a.redo_count, 1u);
             a.redo[3 * k] = g;
@@ -389,6 +325,10 @@ MultiArgs args_of(bc_ctx *ctx, const int32_t *units, int32_t nunits) {
     a.col = ctx->col;
     a.units = units;
     a.nunits = nunits;
+    a.brp = m.brp;
+    a.boff = m.boff;
+    a.safe = m.safe;
+    a.bursts = (const uint4 *)m.bursts;
     a.next = m.next;
     a.bc = ctx->bc;
     a.status = ctx->status;
@@ -424,27 +364,68 @@ bc_status multigraph_prepare(bc_ctx *ctx, const std::vector<int32_t> &voff, cons
     if (!rpoff.empty())
         BC_HIP(ctx, hipMemcpy(m.rpoff, rpoff.data(), rpoff.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     if (!rp.empty()) BC_HIP(ctx, hipMemcpy(m.rp, rp.data(), rp.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    // the group sweep's padded columns: rows in bursts, 16-bit burst indices
+    std::vector<uint16_t> brp(rp.size());
+    std::vector<int64_t> boff((size_t)ng);
+    std::vector<uint32_t> safe((size_t)ng);
+    m.h_group.assign((size_t)ng, 0);
+    int64_t total = 0;
+    for (int32_t g = 0; g < ng; ++g) {
+        const int32_t *r = rp.data() + rpoff[(size_t)g];
+        uint16_t *b = brp.data() + rpoff[(size_t)g];
+        const int32_t n = voff[g + 1] - voff[g];
+        int64_t at = 0;
+        int32_t deg = 1;
+        for (int32_t v = 0; v < n && at < 65536; ++v) {
+            b[v] = (uint16_t)at;
+            deg = std::max(deg, r[v + 1] - r[v]);
+            at += (r[v + 1] - r[v] + lds_sweep::BURST - 1) / lds_sweep::BURST;
+        }
+        m.h_group[(size_t)g] = at < 65536;
+        safe[(size_t)g] = 0xFFFFFFFFu / (uint32_t)deg;
+        boff[(size_t)g] = at < 65536 ? total : -1;
+        if (at < 65536) {
+            b[n] = (uint16_t)at;
+            total += at;
+        }
+    }
+    m.brp = (uint16_t *)bc_dalloc(ctx, std::max<size_t>(brp.size(), 1) * sizeof(uint16_t));
+    m.boff = (int64_t *)bc_dalloc(ctx, std::max<size_t>(boff.size(), 1) * sizeof(int64_t));
+    m.safe = (uint32_t *)bc_dalloc(ctx, std::max<size_t>(safe.size(), 1) * sizeof(uint32_t));
+    m.bursts = bc_dalloc(ctx, (size_t)std::max<int64_t>(total, 1) * sizeof(uint4));
+    if (!m.brp || !m.boff || !m.safe || !m.bursts) return bc_fail(ctx, BC_ERR_NOMEM, "many graphs: allocation failed");
+    if (ng > 0) {
+        BC_HIP(ctx, hipMemcpy(m.brp, brp.data(), brp.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+        BC_HIP(ctx, hipMemcpy(m.boff, boff.data(), boff.size() * sizeof(int64_t), hipMemcpyHostToDevice));
+        BC_HIP(ctx, hipMemcpy(m.safe, safe.data(), safe.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+        hipLaunchKernelGGL(k_mg_pad, dim3(ng), dim3(256), 0, ctx->stream, m.voff, m.rpoff, m.rp, ctx->col, m.brp, m.boff,
+                           (uint4 *)m.bursts);
+        BC_HIP(ctx, hipGetLastError());
+        BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    }
     return multigraph_set_queue(ctx, nullptr, chunk > 0 ? chunk : 64);
 }
 
-// Units (graph, s0, s1) of `chunk` sources: the compact sweep's graphs (at
-// most 65535 arcs) first, then the others, each group largest first.
+// Units (graph, s0, s1) of `chunk` sources: the group sweep's graphs above
+// SMALL_N vertices first, then its others, then those for the full sweep, each
+// class largest graph first.
 bc_status multigraph_set_queue(bc_ctx *ctx, const std::vector<int32_t> *graphs, int32_t chunk) {
     MultiState &m = ctx->mg;
     const std::vector<int32_t> &order = graphs ? *graphs : m.h_order;
     std::vector<int32_t> units;
-    int32_t ncompact = 0;
-    for (int pass = 0; pass < 2; ++pass) {
+    int32_t end[3] = {0, 0, 0}; // units through each class
+    for (int pass = 0; pass < 3; ++pass) {
         for (int32_t g : order) {
             const int32_t n = m.h_voff[(size_t)g + 1] - m.h_voff[(size_t)g];
-            if ((m.h_arcs[(size_t)g] <= 65535) != (pass == 0)) continue;
+            const int cls = !m.h_group[(size_t)g] ? 2 : n > SMALL_N ? 0 : 1;
+            if (cls != pass) continue;
             for (int32_t s0 = 0; s0 < n; s0 += chunk) {
                 units.push_back(g);
                 units.push_back(s0);
                 units.push_back(std::min(n, s0 + chunk));
             }
         }
-        if (pass == 0) ncompact = (int32_t)(units.size() / 3);
+        end[pass] = (int32_t)(units.size() / 3);
     }
     if (m.exec) { // recorded with the old queue's addresses and sizes
         BC_HIP(ctx, hipStreamSynchronize(m.stream));
@@ -455,16 +436,17 @@ bc_status multigraph_set_queue(bc_ctx *ctx, const std::vector<int32_t> *graphs, 
     if (m.units) bc_dfree(ctx, m.units);
     if (m.redo) bc_dfree(ctx, m.redo);
     m.units = (int32_t *)bc_dalloc(ctx, std::max<size_t>(units.size(), 3) * sizeof(int32_t));
-    m.redo = (int32_t *)bc_dalloc(ctx, (size_t)std::max(ncompact, 1) * 3 * sizeof(int32_t));
+    m.redo = (int32_t *)bc_dalloc(ctx, (size_t)std::max(end[1], 1) * 3 * sizeof(int32_t));
     if (!m.units || !m.redo) return bc_fail(ctx, BC_ERR_NOMEM, "many graphs: allocation failed");
     if (!units.empty())
         BC_HIP(ctx, hipMemcpy(m.units, units.data(), units.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     m.chunk = chunk;
-    m.ncompact = ncompact;
+    m.nbig = end[0];
+    m.nsmall = end[1] - end[0];
     m.nunits = (int32_t)(units.size() / 3);
     int cus = 0;
     BC_HIP(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
-    m.grid = std::max(1, std::min(m.nunits, cus > 0 ? cus : 256));
+    m.grid = cus > 0 ? cus : 256; // compute units
     return BC_OK;
 }
 
@@ -474,13 +456,19 @@ bc_status multigraph_run(bc_ctx *ctx) {
     MultiState &m = ctx->mg;
     if (m.nunits == 0) return BC_OK;
     if (!m.exec) {
-        // compact sweep, full sweep over the other graphs, full sweep over the
-        // units the compact sweep handed back (its count read on the device)
-        MultiArgs ac = args_of(ctx, m.units, m.ncompact);
-        ac.next = m.next;
-        ac.redo = m.redo;
-        ac.redo_count = m.next + 3;
-        MultiArgs af = args_of(ctx, m.units + (size_t)3 * m.ncompact, m.nunits - m.ncompact);
+        // the group sweep over its two classes, the full sweep over the other
+        // graphs and over the units the group sweep handed back (their count
+        // read on the device)
+        const int32_t ngroup = m.nbig + m.nsmall;
+        MultiArgs ab = args_of(ctx, m.units, m.nbig);
+        ab.next = m.next;
+        ab.redo = m.redo;
+        ab.redo_count = m.next + 3;
+        MultiArgs as = args_of(ctx, m.units + (size_t)3 * m.nbig, m.nsmall);
+        as.next = m.next + 4;
+        as.redo = m.redo;
+        as.redo_count = m.next + 3;
+        MultiArgs af = args_of(ctx, m.units + (size_t)3 * ngroup, m.nunits - ngroup);
         af.next = m.next + 1;
         MultiArgs ar = args_of(ctx, m.redo, 0);
         ar.nunits_dev = m.next + 3;
@@ -488,11 +476,15 @@ bc_status multigraph_run(bc_ctx *ctx) {
         hipGraph_t graph = nullptr;
         BC_HIP(ctx, hipStreamBeginCapture(m.stream, hipStreamCaptureModeThreadLocal));
         hipLaunchKernelGGL(k_mg_reset, dim3(1), dim3(64), 0, m.stream, m.next);
-        if (m.ncompact > 0)
-            hipLaunchKernelGGL(k_mg_sweep_compact, dim3(std::min(m.ncompact, 2 * m.grid)), dim3(MT), 0, m.stream, ac);
-        if (m.nunits > m.ncompact)
-            hipLaunchKernelGGL(k_mg_sweep, dim3(std::min(m.nunits - m.ncompact, m.grid)), dim3(MT), 0, m.stream, af);
-        if (m.ncompact > 0) hipLaunchKernelGGL(k_mg_sweep, dim3(m.grid), dim3(MT), 0, m.stream, ar);
+        if (m.nbig > 0)
+            hipLaunchKernelGGL((k_mg_group<BIG_T, BIG_BYTES>), dim3(std::min(m.nbig, m.grid)), dim3(BIG_T), 0, m.stream,
+                               ab);
+        if (m.nsmall > 0)
+            hipLaunchKernelGGL((k_mg_group<SMALL_T, SMALL_BYTES>), dim3(std::min(m.nsmall, 4 * m.grid)), dim3(SMALL_T), 0,
+                               m.stream, as);
+        if (m.nunits > ngroup)
+            hipLaunchKernelGGL(k_mg_sweep, dim3(std::min(m.nunits - ngroup, m.grid)), dim3(MT), 0, m.stream, af);
+        if (ngroup > 0) hipLaunchKernelGGL(k_mg_sweep, dim3(m.grid), dim3(MT), 0, m.stream, ar);
         BC_HIP(ctx, hipStreamEndCapture(m.stream, &graph));
         const hipError_t e = hipGraphInstantiate(&m.exec, graph, nullptr, nullptr, 0);
         (void)hipGraphDestroy(graph);

@@ -557,8 +557,8 @@ bc_status tune_prepare(bc_ctx *ctx, const bc_options &opt, bc_form form) {
 // launches.  The calibration runs a sample of the graphs (every k-th by size,
 // k chosen so that one launch takes about kManySampleWork of n_g (n_g +
 // arcs_g)) once per unit size to warm up and record the launch, then kReps
-// times timed; the fastest mean wins.  The compact sweep's workgroups per
-// compute unit are fixed at two by its LDS (each takes just under half).
+// times timed; the fastest mean wins.  Workgroups per compute unit are fixed
+// by the group sweep's LDS (multigraph.hip).
 bc_status tune_many(bc_ctx *ctx, const bc_options &opt, const std::vector<int32_t> &voff,
                     const std::vector<int32_t> &rpoff, const std::vector<int32_t> &rp) {
     ctx->hy = HybridState{};
