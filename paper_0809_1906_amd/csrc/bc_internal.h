@@ -154,6 +154,24 @@ struct WeightedState {
     int32_t grid = 0;             // requested workgroups (0 = default)
 };
 
+// Columns of small graphs as 16-bit ids in padded bursts of eight (lds_sweep.h).
+struct LdsColumns {
+    uint16_t *brp = nullptr;  // first burst of each row, one array laid out as the row offsets
+    int64_t *boff = nullptr;  // [graphs] first burst of each graph; -1: 65536 bursts or more, left out
+    uint32_t *safe = nullptr; // [graphs] (2^32 - 1) / largest degree
+    void *bursts = nullptr;   // uint4 per burst
+};
+
+// State of a small graph's LDS sweeps (small.hip).
+struct SmallState {
+    bool on = false;
+    int cus = 0;
+    LdsColumns cols;
+    uint32_t *count = nullptr;  // [0] units handed back by the 32-bit sweep, [1] most levels seen
+    int32_t *redo = nullptr;    // those units
+    int64_t redo_cap = 0;
+};
+
 // State of a many-graph context (bc_create_many).
 constexpr int MG_MAX_N = 4096; // largest graph a many-graph context takes
 struct MultiState {
@@ -165,10 +183,7 @@ struct MultiState {
     std::vector<int32_t> h_voff;
     std::vector<int32_t> h_arcs;      // arcs of each graph
     std::vector<uint8_t> h_group;     // graphs the group sweep takes
-    uint16_t *brp = nullptr;          // group sweep: row starts in bursts, burst offsets, padded columns
-    int64_t *boff = nullptr;
-    uint32_t *safe = nullptr;         // per graph: largest count whose sums need no wrap test
-    void *bursts = nullptr;
+    LdsColumns cols;                  // the group sweep's padded columns
     std::vector<int32_t> h_order;     // graphs by n_g descending (stable)
     hipStream_t stream = nullptr;     // private stream the launch is captured on
     hipEvent_t ev = nullptr;
@@ -229,6 +244,7 @@ struct bc_ctx {
     PlainState pl;
     WeightedState wt;
     MultiState mg;
+    SmallState sm;
     HybridState hy;
     bool many = false;
 
@@ -305,6 +321,20 @@ bc_status edges_to_caller_order(bc_ctx *ctx, double *out);
 bc_status plain_prepare(bc_ctx *ctx);
 bc_status plain_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool accumulate,
                     double *delta_dump, int32_t *dist_dump, uint64_t *sigma_dump);
+
+// Padded columns of `voff.size() - 1` graphs; taken[g] says whether graph g's
+// bursts fit 16-bit indices.  voff, rpoff and rp as in a many-graph context.
+bc_status lds_columns(bc_ctx *ctx, const std::vector<int32_t> &voff, const std::vector<int32_t> &rpoff,
+                      const std::vector<int32_t> &rp, const int32_t *d_voff, const int32_t *d_rpoff,
+                      const int32_t *d_rp, LdsColumns &out, std::vector<uint8_t> &taken);
+// Small unweighted graphs without edge terms: can the LDS hold a source's state?
+bool small_fits(const bc_ctx *ctx);
+bc_status small_prepare(bc_ctx *ctx);
+// wide: 64-bit counts and FP64 c(v) throughout; else 32-bit counts and FP32
+// c(v), groups whose counts pass 32 bits again in 64 bits.  With dist_dump,
+// rows of n per source instead of BC (delta_dump may be null: forward only).
+bc_status small_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool wide, double *delta_dump,
+                    int32_t *dist_dump, uint64_t *sigma_dump);
 
 bc_status weighted_prepare(bc_ctx *ctx);
 bc_status weighted_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool accumulate,

@@ -1,0 +1,82 @@
+// Columns of small graphs for the LDS sweeps (lds_sweep.h): 16-bit ids in
+// bursts of eight, rows padded with the id n.
+#include "bc_internal.h"
+#include "lds_sweep.h"
+
+#include <algorithm>
+
+namespace {
+
+// One block per graph.
+__global__ __launch_bounds__(256) void k_pad_columns(const int32_t *__restrict__ voff, const int32_t *__restrict__ rpoff,
+                                                     const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+                                                     const uint16_t *__restrict__ brp, const int64_t *__restrict__ boff,
+                                                     uint4 *__restrict__ bursts) {
+    const int32_t g = blockIdx.x;
+    if (boff[g] < 0) return;
+    const int32_t n = voff[g + 1] - voff[g];
+    const int32_t *r = rp + rpoff[g];
+    const uint16_t *br = brp + rpoff[g];
+    uint4 *out = bursts + boff[g];
+    for (int32_t v = threadIdx.x; v < n; v += 256) {
+        int32_t e = r[v];
+        for (int32_t b = br[v]; b < br[v + 1]; ++b) {
+            uint32_t x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t lo = (uint32_t)(e < r[v + 1] ? col[e] : n);
+                const uint32_t hi = (uint32_t)(e + 1 < r[v + 1] ? col[e + 1] : n);
+                x[q] = lo | hi << 16;
+                e += 2;
+            }
+            out[b] = make_uint4(x[0], x[1], x[2], x[3]);
+        }
+    }
+}
+
+} // namespace
+
+bc_status lds_columns(bc_ctx *ctx, const std::vector<int32_t> &voff, const std::vector<int32_t> &rpoff,
+                      const std::vector<int32_t> &rp, const int32_t *d_voff, const int32_t *d_rpoff,
+                      const int32_t *d_rp, LdsColumns &out, std::vector<uint8_t> &taken) {
+    const int32_t ng = (int32_t)voff.size() - 1;
+    std::vector<uint16_t> brp(std::max<size_t>(rp.size(), 1));
+    std::vector<int64_t> boff((size_t)std::max(ng, 1));
+    std::vector<uint32_t> safe((size_t)std::max(ng, 1));
+    taken.assign((size_t)ng, 0);
+    int64_t total = 0;
+    for (int32_t g = 0; g < ng; ++g) {
+        const int32_t *r = rp.data() + rpoff[(size_t)g];
+        uint16_t *b = brp.data() + rpoff[(size_t)g];
+        const int32_t n = voff[(size_t)g + 1] - voff[(size_t)g];
+        int64_t at = 0;
+        int32_t deg = 1;
+        for (int32_t v = 0; v < n && at < 65536; ++v) {
+            b[v] = (uint16_t)at;
+            deg = std::max(deg, r[v + 1] - r[v]);
+            at += (r[v + 1] - r[v] + lds_sweep::BURST - 1) / lds_sweep::BURST;
+        }
+        taken[(size_t)g] = at < 65536; // 16-bit burst indices
+        safe[(size_t)g] = 0xFFFFFFFFu / (uint32_t)deg;
+        boff[(size_t)g] = at < 65536 ? total : -1;
+        if (at < 65536) {
+            b[n] = (uint16_t)at;
+            total += at;
+        }
+    }
+    out.brp = (uint16_t *)bc_dalloc(ctx, brp.size() * sizeof(uint16_t));
+    out.boff = (int64_t *)bc_dalloc(ctx, boff.size() * sizeof(int64_t));
+    out.safe = (uint32_t *)bc_dalloc(ctx, safe.size() * sizeof(uint32_t));
+    out.bursts = bc_dalloc(ctx, (size_t)std::max<int64_t>(total, 1) * sizeof(uint4));
+    if (!out.brp || !out.boff || !out.safe || !out.bursts)
+        return bc_fail(ctx, BC_ERR_NOMEM, "padded columns: allocation failed");
+    if (ng == 0) return BC_OK;
+    BC_HIP(ctx, hipMemcpy(out.brp, brp.data(), brp.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+    BC_HIP(ctx, hipMemcpy(out.boff, boff.data(), boff.size() * sizeof(int64_t), hipMemcpyHostToDevice));
+    BC_HIP(ctx, hipMemcpy(out.safe, safe.data(), safe.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(k_pad_columns, dim3(ng), dim3(256), 0, ctx->stream, d_voff, d_rpoff, d_rp, ctx->col, out.brp,
+                       out.boff, (uint4 *)out.bursts);
+    BC_HIP(ctx, hipGetLastError());
+    BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    return BC_OK;
+}

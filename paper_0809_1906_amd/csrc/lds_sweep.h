@@ -26,6 +26,11 @@
 namespace lds_sweep {
 
 constexpr int BURST = 8; // columns per 16-byte load
+// Rows of more bursts than this are taken by a whole wave, a burst per lane,
+// one such row after the other; the others by one lane each.  HV = false
+// compiles that out, for graphs without such a row (10% faster on Watts-
+// Strogatz graphs of mean degree 6).
+constexpr int HEAVY = 8;
 constexpr uint32_t UNREACHED = 8, NOBODY = 16; // states; levels are 1 << (l % 3)
 
 __host__ __device__ inline uint32_t level_bit(int32_t l) { return 1u << (l % 3); }
@@ -101,7 +106,7 @@ __device__ __forceinline__ void unpack(const uint4 c, uint32_t (&w)[BURST]) {
 // count that no vertex's neighbours can add up past the range of ST (that
 // range over the largest degree): only a wave that meets a larger one tests
 // its sums, setting *ovf in LDS when one wraps.
-template <typename ST, int T, typename Src>
+template <typename ST, int T, bool HV, typename Src>
 __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__restrict__ cols, Src src, ST safe,
                                            int32_t *cnt, uint32_t *ovf) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -133,62 +138,79 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
     int32_t qb = 0, qe = a.K, L = 0, c0 = 0;
     while (qb < qe) {
         const int32_t c1 = c0 == 2 ? 0 : c0 + 1; // (L + 1) % 3
-        const uint32_t next = 1u << c1, open = UNREACHED | next;
+        const uint32_t next = 1u << c1;
         if (tid == 0) cnt[c1] = 0;
+        // one burst per lane (every lane of the wave calls): the arcs to
+        // `mask` states take sv, the vertices found first are appended
+        auto burst = [&](const uint4 c, uint32_t mask, ST sv, int32_t base, bool test) {
+            ST *sc = a.sc + base;
+            uint8_t *st = a.st + base;
+            uint32_t w[BURST], t[BURST];
+            unpack(c, w);
+#pragma unroll
+            for (int j = 0; j < BURST; ++j) t[j] = st[w[j]];
+            ST old[BURST];
+#pragma unroll
+            for (int j = 0; j < BURST; ++j) {
+                old[j] = 1; // an arc not added claims nothing
+                if (t[j] & mask) old[j] = add_count(&sc[w[j]], sv); // v in P_s(w)
+            }
+            if (__builtin_expect(test, 0)) {
+                bool wrap = false;
+#pragma unroll
+                for (int j = 0; j < BURST; ++j) wrap |= (t[j] & mask) && (ST)(old[j] + sv) < sv;
+                if (wrap) *ovf = 1;
+            }
+            uint64_t claim[BURST];
+            int total = 0;
+#pragma unroll
+            for (int j = 0; j < BURST; ++j) {
+                claim[j] = __ballot(old[j] == 0);
+                total += __popcll(claim[j]);
+            }
+            if (total == 0) return;
+            int32_t at = 0;
+            if (lane == 0) at = atomicAdd(cnt + c0, total);
+            at = qe + __builtin_amdgcn_readfirstlane(at);
+            // at most one claim per entry, unless a count wrapped to zero
+            // (then *ovf is set and the queue's contents do not matter)
+#pragma unroll
+            for (int j = 0; j < BURST; ++j) {
+                if (old[j] == 0) {
+                    st[w[j]] = (uint8_t)next;
+                    const int32_t p = at + lanes_below(claim[j]);
+                    if (p < E) a.queue[p] = (uint16_t)(base + (int32_t)w[j]);
+                }
+                at += __popcll(claim[j]);
+            }
+        };
         for (int32_t i0 = qb + (tid & ~63); i0 < qe; i0 += T) {
             const bool act = i0 + lane < qe;
             const int32_t id = act ? (int32_t)a.queue[i0 + lane] : 0;
             const int32_t base = a.source_of(id) * n1;
             const int32_t v = id - base;
             const ST sv = a.sc[id];
-            ST *sc = a.sc + base;
-            uint8_t *st = a.st + base;
             int32_t b = act ? (int32_t)a.rp[v] : 0;
             const int32_t e = act ? (int32_t)a.rp[v + 1] : 0;
             const bool test = __any(act && sv > safe);
-            while (__any(b < e)) {
+            uint64_t heavy = HV ? __ballot(e - b > HEAVY) : 0;
+            const bool light = !HV || e - b <= HEAVY;
+            while (__any(light && b < e)) {
+                const bool more = light && b < e;
                 uint4 c = make_uint4(0, 0, 0, 0);
-                const bool more = b < e;
-                if (more) c = cols[b];
-                ++b;
-                const uint32_t mask = more ? open : 0u;
-                uint32_t w[BURST], t[BURST];
-                unpack(c, w);
-#pragma unroll
-                for (int j = 0; j < BURST; ++j) t[j] = st[w[j]];
-                ST old[BURST];
-#pragma unroll
-                for (int j = 0; j < BURST; ++j) {
-                    old[j] = 1; // an arc not added claims nothing
-                    if (t[j] & mask) old[j] = add_count(&sc[w[j]], sv); // v in P_s(w)
-                }
-                if (__builtin_expect(test, 0)) {
-                    bool wrap = false;
-#pragma unroll
-                    for (int j = 0; j < BURST; ++j) wrap |= (t[j] & mask) && (ST)(old[j] + sv) < sv;
-                    if (wrap) *ovf = 1;
-                }
-                uint64_t claim[BURST];
-                int total = 0;
-#pragma unroll
-                for (int j = 0; j < BURST; ++j) {
-                    claim[j] = __ballot(old[j] == 0);
-                    total += __popcll(claim[j]);
-                }
-                if (total == 0) continue;
-                int32_t at = 0;
-                if (lane == 0) at = atomicAdd(cnt + c0, total);
-                at = qe + __builtin_amdgcn_readfirstlane(at);
-                // at most one claim per entry, unless a count wrapped to zero
-                // (then *ovf is set and the queue's contents do not matter)
-#pragma unroll
-                for (int j = 0; j < BURST; ++j) {
-                    if (old[j] == 0) {
-                        st[w[j]] = (uint8_t)next;
-                        const int32_t p = at + lanes_below(claim[j]);
-                        if (p < E) a.queue[p] = (uint16_t)(base + (int32_t)w[j]);
-                    }
-                    at += __popcll(claim[j]);
+                if (more) c = cols[b++]; // a heavy row keeps its first burst
+                burst(c, more ? UNREACHED | next : 0u, sv, base, test);
+            }
+            while (HV && heavy) {
+                const int j = __ffsll((unsigned long long)heavy) - 1;
+                heavy &= heavy - 1;
+                const int32_t hbase = __shfl(base, j, 64), he = __shfl(e, j, 64);
+                const ST hsv = __shfl(sv, j, 64);
+                for (int32_t hb = __shfl(b, j, 64); hb < he; hb += 64) {
+                    const bool more = hb + lane < he;
+                    uint4 c = make_uint4(0, 0, 0, 0);
+                    if (more) c = cols[hb + lane];
+                    burst(c, more ? UNREACHED | next : 0u, hsv, hbase, test);
                 }
             }
         }
@@ -207,37 +229,54 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
 // Backward sweep, deepest level first, down to level `lowest`: delta(v) =
 // lambda_sv * sum of c(w) over successors w (Theorem 1.1), BC sums in LDS for
 // every level but 0.  put(k, v, delta) receives every dependency.
-template <typename ST, int T, typename Put>
+template <typename ST, int T, bool HV, typename Put>
 __device__ __forceinline__ void backward(const Arrays<ST> &a, const uint4 *__restrict__ cols, int32_t nlev,
                                          int32_t lowest, Put put) {
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int32_t n1 = a.n + 1;
     for (int32_t l = nlev - 1; l >= lowest; --l) {
         const uint32_t next = level_bit(l + 1);
-        const int32_t le = a.lev[l + 1];
-        for (int32_t i = a.lev[l] + tid; i < le; i += T) {
-            const int32_t id = a.queue[i];
+        const int32_t lb = a.lev[l], le = a.lev[l + 1];
+        // sum += c over the successors among one burst's columns
+        auto burst = [&](const uint4 c, int32_t base, double &sum) {
+            const ST *sc = a.sc + base;
+            const uint8_t *st = a.st + base;
+            uint32_t w[BURST], t[BURST];
+            unpack(c, w);
+#pragma unroll
+            for (int j = 0; j < BURST; ++j) t[j] = st[w[j]];
+            // straight-line reads, the successors selected afterwards: the
+            // reads of a burst are in flight together
+            ST x[BURST];
+#pragma unroll
+            for (int j = 0; j < BURST; ++j) x[j] = sc[w[j]];
+#pragma unroll
+            for (int j = 0; j < BURST; ++j) sum += coef(t[j] & next ? x[j] : (ST)0);
+        };
+        for (int32_t i0 = lb + (tid & ~63); i0 < le; i0 += T) {
+            const bool act = i0 + lane < le;
+            const int32_t id = act ? (int32_t)a.queue[i0 + lane] : 0;
             const int32_t k = a.source_of(id), base = k * n1;
             const int32_t v = id - base;
             double acc = 0.0;
             if (l + 1 < nlev) {
-                const ST *sc = a.sc + base;
-                const uint8_t *st = a.st + base;
-                const int32_t e = a.rp[v + 1];
-                for (int32_t b = a.rp[v]; b < e; ++b) {
-                    uint32_t w[BURST], t[BURST];
-                    unpack(cols[b], w);
+                int32_t b = act ? (int32_t)a.rp[v] : 0;
+                const int32_t e = act ? (int32_t)a.rp[v + 1] : 0;
+                uint64_t heavy = HV ? __ballot(e - b > HEAVY) : 0;
+                if (!HV || e - b <= HEAVY)
+                    for (; b < e; ++b) burst(cols[b], base, acc);
+                while (HV && heavy) {
+                    const int j = __ffsll((unsigned long long)heavy) - 1;
+                    heavy &= heavy - 1;
+                    const int32_t hbase = __shfl(base, j, 64), he = __shfl(e, j, 64);
+                    double sum = 0.0;
+                    for (int32_t hb = __shfl(b, j, 64) + lane; hb < he; hb += 64) burst(cols[hb], hbase, sum);
 #pragma unroll
-                    for (int j = 0; j < BURST; ++j) t[j] = st[w[j]];
-                    // straight-line reads, the successors selected afterwards:
-                    // the reads of a burst are in flight together
-                    ST x[BURST];
-#pragma unroll
-                    for (int j = 0; j < BURST; ++j) x[j] = sc[w[j]];
-#pragma unroll
-                    for (int j = 0; j < BURST; ++j) acc += coef(t[j] & next ? x[j] : (ST)0);
+                    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+                    if (lane == j) acc = sum;
                 }
             }
+            if (!act) continue;
             const double sv = (double)a.sc[id];
             const double dl = sv * acc;
             set_coef(&a.sc[id], (1.0 + dl) / sv);

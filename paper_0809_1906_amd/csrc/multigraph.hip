@@ -25,6 +25,7 @@
 #include "lds_sweep.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -230,34 +231,6 @@ __global__ __launch_bounds__(MT) void k_mg_sweep(MultiArgs a) {
 
 // ---- the group sweep --------------------------------------------------------------
 
-// Columns of every graph the group sweep takes, padded to bursts (one block
-// per graph).
-__global__ __launch_bounds__(256) void k_mg_pad(const int32_t *__restrict__ voff, const int32_t *__restrict__ rpoff,
-                                                const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-                                                const uint16_t *__restrict__ brp, const int64_t *__restrict__ boff,
-                                                uint4 *__restrict__ bursts) {
-    const int32_t g = blockIdx.x;
-    if (boff[g] < 0) return;
-    const int32_t n = voff[g + 1] - voff[g];
-    const int32_t *r = rp + rpoff[g];
-    const uint16_t *br = brp + rpoff[g];
-    uint4 *out = bursts + boff[g];
-    for (int32_t v = threadIdx.x; v < n; v += 256) {
-        int32_t e = r[v];
-        for (int32_t b = br[v]; b < br[v + 1]; ++b) {
-            uint32_t x[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t lo = e < r[v + 1] ? (uint32_t)col[e] : (uint32_t)n;
-                const uint32_t hi = e + 1 < r[v + 1] ? (uint32_t)col[e + 1] : (uint32_t)n;
-                x[q] = lo | hi << 16;
-                e += 2;
-            }
-            out[b] = make_uint4(x[0], x[1], x[2], x[3]);
-        }
-    }
-}
-
 template <int T, int BYTES>
 __global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char raw[BYTES];
@@ -283,17 +256,23 @@ __global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
         const uint4 *cols = a.bursts + a.boff[g];
         for (int32_t v = tid; v <= n; v += T) s.rp[v] = br[v];
         for (int32_t v = tid; v < n; v += T) s.bc[v] = 0.0;
-        bool deep = false;
-        for (int32_t k0 = s0; k0 < s1; k0 += K) {
-            s.K = min(K, s1 - k0);
-            const int32_t nlev = lds_sweep::forward<uint32_t, T>(
-                s, cols, [&](int32_t k) { return k0 + k; }, a.safe[g], s_cnt, &s_fail);
-            deep = nlev < 0;
-            if (deep || s_fail) break; // uniform: the forward ends with a barrier
-            lds_sweep::backward<uint32_t, T>(s, cols, nlev, 1, [](int32_t, int32_t, double) {});
-        }
+        const uint32_t safe = a.safe[g];
+        auto sweep = [&](auto heavy) { // false when the unit must be handed back (uniform)
+            constexpr bool HV = decltype(heavy)::value;
+            for (int32_t k0 = s0; k0 < s1; k0 += K) {
+                s.K = min(K, s1 - k0);
+                const int32_t nlev = lds_sweep::forward<uint32_t, T, HV>(
+                    s, cols, [&](int32_t k) { return k0 + k; }, safe, s_cnt, &s_fail);
+                if (nlev < 0 || s_fail) return false;
+                lds_sweep::backward<uint32_t, T, HV>(s, cols, nlev, 1, [](int32_t, int32_t, double) {});
+            }
+            return true;
+        };
+        // a row of more than HEAVY bursts
+        const bool hv = safe < 0xFFFFFFFFu / (lds_sweep::HEAVY * lds_sweep::BURST);
+        const bool done = hv ? sweep(std::true_type()) : sweep(std::false_type());
         __syncthreads();
-        if (!deep && !s_fail) {
+        if (done) {
             for (int32_t v = tid; v < n; v += T)
                 if (s.bc[v] != 0.0) unsafeAtomicAdd(&a.bc[vo + v], s.bc[v]);
         } else if (tid == 0) {
@@ -325,10 +304,10 @@ MultiArgs args_of(bc_ctx *ctx, const int32_t *units, int32_t nunits) {
     a.col = ctx->col;
     a.units = units;
     a.nunits = nunits;
-    a.brp = m.brp;
-    a.boff = m.boff;
-    a.safe = m.safe;
-    a.bursts = (const uint4 *)m.bursts;
+    a.brp = m.cols.brp;
+    a.boff = m.cols.boff;
+    a.safe = m.cols.safe;
+    a.bursts = (const uint4 *)m.cols.bursts;
     a.next = m.next;
     a.bc = ctx->bc;
     a.status = ctx->status;
@@ -364,45 +343,8 @@ bc_status multigraph_prepare(bc_ctx *ctx, const std::vector<int32_t> &voff, cons
     if (!rpoff.empty())
         BC_HIP(ctx, hipMemcpy(m.rpoff, rpoff.data(), rpoff.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     if (!rp.empty()) BC_HIP(ctx, hipMemcpy(m.rp, rp.data(), rp.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    // the group sweep's padded columns: rows in bursts, 16-bit burst indices
-    std::vector<uint16_t> brp(rp.size());
-    std::vector<int64_t> boff((size_t)ng);
-    std::vector<uint32_t> safe((size_t)ng);
-    m.h_group.assign((size_t)ng, 0);
-    int64_t total = 0;
-    for (int32_t g = 0; g < ng; ++g) {
-        const int32_t *r = rp.data() + rpoff[(size_t)g];
-        uint16_t *b = brp.data() + rpoff[(size_t)g];
-        const int32_t n = voff[g + 1] - voff[g];
-        int64_t at = 0;
-        int32_t deg = 1;
-        for (int32_t v = 0; v < n && at < 65536; ++v) {
-            b[v] = (uint16_t)at;
-            deg = std::max(deg, r[v + 1] - r[v]);
-            at += (r[v + 1] - r[v] + lds_sweep::BURST - 1) / lds_sweep::BURST;
-        }
-        m.h_group[(size_t)g] = at < 65536;
-        safe[(size_t)g] = 0xFFFFFFFFu / (uint32_t)deg;
-        boff[(size_t)g] = at < 65536 ? total : -1;
-        if (at < 65536) {
-            b[n] = (uint16_t)at;
-            total += at;
-        }
-    }
-    m.brp = (uint16_t *)bc_dalloc(ctx, std::max<size_t>(brp.size(), 1) * sizeof(uint16_t));
-    m.boff = (int64_t *)bc_dalloc(ctx, std::max<size_t>(boff.size(), 1) * sizeof(int64_t));
-    m.safe = (uint32_t *)bc_dalloc(ctx, std::max<size_t>(safe.size(), 1) * sizeof(uint32_t));
-    m.bursts = bc_dalloc(ctx, (size_t)std::max<int64_t>(total, 1) * sizeof(uint4));
-    if (!m.brp || !m.boff || !m.safe || !m.bursts) return bc_fail(ctx, BC_ERR_NOMEM, "many graphs: allocation failed");
-    if (ng > 0) {
-        BC_HIP(ctx, hipMemcpy(m.brp, brp.data(), brp.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
-        BC_HIP(ctx, hipMemcpy(m.boff, boff.data(), boff.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-        BC_HIP(ctx, hipMemcpy(m.safe, safe.data(), safe.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-        hipLaunchKernelGGL(k_mg_pad, dim3(ng), dim3(256), 0, ctx->stream, m.voff, m.rpoff, m.rp, ctx->col, m.brp, m.boff,
-                           (uint4 *)m.bursts);
-        BC_HIP(ctx, hipGetLastError());
-        BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    }
+    bc_status st = lds_columns(ctx, voff, rpoff, rp, m.voff, m.rpoff, m.rp, m.cols, m.h_group);
+    if (st != BC_OK) return st;
     return multigraph_set_queue(ctx, nullptr, chunk > 0 ? chunk : 64);
 }
 

@@ -1,4 +1,6 @@
-// Plain FP64 form: one workgroup per source, per-source state in HBM.
+// Plain FP64 form: one workgroup per source, per-source state in HBM.  Graphs
+// whose state fits the LDS go to small.hip instead, unless the caller asks for
+// a grid of workgroups or for edge terms.
 //
 // For each source s (Brandes's algorithm, Sec. 1.1):
 //   forward   level-synchronous breadth-first search from s (the parallel BFS
@@ -170,6 +172,7 @@ __global__ __launch_bounds__(PB) void k_plain_sweep(
 bc_status plain_prepare(bc_ctx *ctx) {
     if (ctx->weighted) return weighted_prepare(ctx);
     PlainState &p = ctx->pl;
+    if (p.grid == 0 && small_fits(ctx)) return small_prepare(ctx);
     const size_t n = (size_t)std::max(ctx->n, 1);
     const size_t per_group = n * (4 + 8 + 8 + 4) + (n + 2) * 4;
     const size_t budget = size_t(16) << 30;
@@ -190,6 +193,12 @@ bc_status plain_prepare(bc_ctx *ctx) {
 bc_status plain_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool accumulate,
                     double *delta_dump, int32_t *dist_dump, uint64_t *sigma_dump) {
     if (ctx->weighted) return weighted_run(ctx, d_sources, count, accumulate, delta_dump, dist_dump, sigma_dump);
+    if (ctx->sm.on) {
+        LaunchTimer t(ctx, "plain_sweep");
+        bc_status st = small_run(ctx, d_sources, count, true, accumulate ? nullptr : delta_dump, dist_dump, sigma_dump);
+        t.done();
+        return st;
+    }
     PlainState &p = ctx->pl;
     BC_HIP(ctx, hipMemsetAsync(p.next, 0, sizeof(unsigned long long), ctx->stream));
     const int grid = (int)std::min<int64_t>(count, p.groups);

@@ -19,6 +19,8 @@ CASES = {
     "class-edges": lambda: [gg.path(1), gg.path(2)] + [gg.watts_strogatz(n, 6, 0.1, n) for n in (255, 256, 257)],
     # degrees 7, 8 and 9: one burst short, full, and one column over
     "burst-edges": lambda: [gg.complete(8), gg.complete(9), gg.complete(10), gg.star(9), gg.star(10), gg.star(3000)],
+    # rows of more than eight bursts beside short ones in a wave
+    "hubs": lambda: [gg.rmat(12, 16, 7), gg.rmat(8, 16, 8)],
     # unreached vertices, isolated ones among them
     "disconnected": lambda: [gg.disjoint_union(gg.path(300), gg.cycle(7), gg.path(1)), gg.disjoint_union(gg.path(1), gg.star(5))],
     # C(34,17) = 2.3e9: no 32-bit sum wraps, but a neighbour's count times the

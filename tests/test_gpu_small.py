@@ -1,0 +1,45 @@
+"""Sweeps of small graphs with their state in LDS: sizes at the edges of the
+route and of a group, hubs, depth up to n, counts near the limits, and the
+readout, against the oracle."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+GRAPHS = {
+    "one": lambda: gg.path(1),
+    "two": lambda: gg.path(2),
+    "isolated": lambda: gg.disjoint_union(gg.path(1), gg.cycle(9), gg.path(1), gg.path(70)),
+    "deep": lambda: gg.path(2100),
+    "hubs": lambda: gg.rmat(12, 16, 3),
+    "counts": lambda: gg.grid(34, 34),  # C(66,33) = 7.2e18
+    "last": lambda: gg.er_plus_tree(7084, 3.0, 5),  # the largest that fits
+    "past": lambda: gg.er_plus_tree(7085, 3.0, 5),
+}
+
+
+def rel_err(x, y):
+    return float(np.max(np.abs(x - y) / np.maximum(np.abs(y), 1.0))) if y.size else 0.0
+
+
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_plain_small(gpu_lib, name):
+    g = GRAPHS[name]()
+    print(f"small plain {name} n={g.n}", flush=True)
+    src = gg.sample_sources(g.n, min(g.n, 700), 11)  # groups of three, the last ragged
+    src = np.concatenate([src, src[:1]]).astype(np.int32)  # a multiset
+    want = oracle.bc(g, sources=src, threads=8)
+    with gpu_lib.BC(g, form="plain") as ctx:
+        ctx.run(src)
+        assert rel_err(ctx.read(), want) <= 1e-12  # FP64 throughout
+        ctx.run(src[:1])
+        assert rel_err(ctx.read(), want + oracle.bc(g, sources=src[:1])) <= 1e-12
+        pick = src[:: max(1, src.size // 5)]
+        dist, sigma, delta = ctx.sssp(pick)
+    for i, s in enumerate(pick):
+        d, sg, dl = oracle.sssp_u64(g, int(s))
+        assert np.array_equal(dist[i], d) and np.array_equal(sigma[i], sg)
+        assert rel_err(delta[i], dl) <= 1e-12
