@@ -102,10 +102,12 @@ __device__ __forceinline__ void unpack(const uint4 c, uint32_t (&w)[BURST]) {
 
 // Forward sweep of the group from sources src(0) .. src(K - 1) by the T
 // threads of the workgroup; cnt[0..2] is LDS scratch.  Returns the number of
-// levels, or -1 when there were more than a.levels.  `safe` is the largest
-// count that no vertex's neighbours can add up past the range of ST (that
-// range over the largest degree): only a wave that meets a larger one tests
-// its sums, setting *ovf in LDS when one wraps.
+// levels, or -1 when there were more than a.levels.  *ovf in LDS is set when a
+// count may have passed the range of ST.  64-bit counts: every add is tested,
+// so it is set exactly when a sum wrapped.  32-bit counts: it is set when a
+// vertex with a count above `safe`, that range over the largest degree, is
+// expanded; no sum of smaller counts can wrap.  (Testing only the adds of
+// such vertices would not do: a small count can be the one that wraps.)
 template <typename ST, int T, bool HV, typename Src>
 __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__restrict__ cols, Src src, ST safe,
                                            int32_t *cnt, uint32_t *ovf) {
@@ -142,7 +144,7 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
         if (tid == 0) cnt[c1] = 0;
         // one burst per lane (every lane of the wave calls): the arcs to
         // `mask` states take sv, the vertices found first are appended
-        auto burst = [&](const uint4 c, uint32_t mask, ST sv, int32_t base, bool test) {
+        auto burst = [&](const uint4 c, uint32_t mask, ST sv, int32_t base) {
             ST *sc = a.sc + base;
             uint8_t *st = a.st + base;
             uint32_t w[BURST], t[BURST];
@@ -155,7 +157,7 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
                 old[j] = 1; // an arc not added claims nothing
                 if (t[j] & mask) old[j] = add_count(&sc[w[j]], sv); // v in P_s(w)
             }
-            if (__builtin_expect(test, 0)) {
+            if (sizeof(ST) == 8) {
                 bool wrap = false;
 #pragma unroll
                 for (int j = 0; j < BURST; ++j) wrap |= (t[j] & mask) && (ST)(old[j] + sv) < sv;
@@ -192,14 +194,14 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
             const ST sv = a.sc[id];
             int32_t b = act ? (int32_t)a.rp[v] : 0;
             const int32_t e = act ? (int32_t)a.rp[v + 1] : 0;
-            const bool test = __any(act && sv > safe);
+            if (sizeof(ST) == 4 && act && sv > safe) *ovf = 1;
             uint64_t heavy = HV ? __ballot(e - b > HEAVY) : 0;
             const bool light = !HV || e - b <= HEAVY;
             while (__any(light && b < e)) {
                 const bool more = light && b < e;
                 uint4 c = make_uint4(0, 0, 0, 0);
                 if (more) c = cols[b++]; // a heavy row keeps its first burst
-                burst(c, more ? UNREACHED | next : 0u, sv, base, test);
+                burst(c, more ? UNREACHED | next : 0u, sv, base);
             }
             while (HV && heavy) {
                 const int j = __ffsll((unsigned long long)heavy) - 1;
@@ -210,7 +212,7 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
                     const bool more = hb + lane < he;
                     uint4 c = make_uint4(0, 0, 0, 0);
                     if (more) c = cols[hb + lane];
-                    burst(c, more ? UNREACHED | next : 0u, hsv, hbase, test);
+                    burst(c, more ? UNREACHED | next : 0u, hsv, hbase);
                 }
             }
         }

@@ -11,15 +11,15 @@
 // persistent workgroups pulls units with an atomic counter and exits when the
 // queue is drained.  Two sweeps:
 //   group sweep  (lds_sweep.h) as many sources at once as the LDS holds, 32-bit
-//                counts overwritten by FP32 c(v), at most LEVCAP levels; for
-//                graphs of fewer than 65536 bursts of eight columns;
+//                counts overwritten by FP32 c(v), at most LEVCAP levels; units
+//                it cannot finish again with 64-bit counts, FP64 c(v) and any
+//                depth; for graphs of fewer than 65536 bursts of eight columns;
 //   full sweep   one source at a time, 64-bit counts, any depth; for the other
-//                graphs, the units that the group sweep hands back (a count
-//                past 2^32 - 1, more levels) and the per-source readout.
+//                graphs and the per-source readout.
 // In both, each unit's dependencies are summed in an FP64 LDS vector and added
 // to BC once per unit.  The full sweep's columns are staged in LDS as 16-bit
 // local ids when they fit.  The launches (counter reset, group sweeps, full
-// sweep over the remaining graphs, full sweep over the handed-back units) are
+// sweep over the remaining graphs, group sweep over the handed-back units) are
 // captured once into a HIP graph and replayed.
 #include "bc_internal.h"
 #include "lds_sweep.h"
@@ -46,6 +46,7 @@ constexpr int LEVCAP = 1024;       // levels per source in the group sweep
 constexpr int BIG_T = 1024, BIG_BYTES = 163000, SMALL_T = 512, SMALL_BYTES = 40000;
 constexpr int32_t SMALL_N = 256;
 static_assert(lds_sweep::bytes_for<uint32_t>(MG_MAX_N, 1, LEVCAP) <= BIG_BYTES, "one source of the largest graph");
+static_assert(lds_sweep::bytes_for<uint64_t>(MG_MAX_N, 1, MG_MAX_N) <= BIG_BYTES, "the same in 64 bits, any depth");
 static_assert(lds_sweep::bytes_for<uint32_t>(SMALL_N, 1, SMALL_N) <= SMALL_BYTES, "one source of a small graph");
 
 struct MultiArgs {
@@ -231,12 +232,16 @@ __global__ __launch_bounds__(MT) void k_mg_sweep(MultiArgs a) {
 
 // ---- the group sweep --------------------------------------------------------------
 
-template <int T, int BYTES>
+// ST = uint32_t hands units it cannot finish to a.redo; ST = uint64_t finishes
+// any (it has room for as many levels as vertices).
+template <typename ST, int T, int BYTES>
 __global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char raw[BYTES];
     __shared__ int32_t s_unit, s_cnt[3];
     __shared__ uint32_t s_fail;
+    constexpr bool WIDE = sizeof(ST) == 8;
     const int tid = threadIdx.x;
+    const int32_t nunits = a.nunits_dev ? (int32_t)*a.nunits_dev : a.nunits;
     for (;;) {
         if (tid == 0) {
             s_unit = (int32_t)atomicAdd(a.next, 1u);
@@ -244,14 +249,14 @@ __global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
         }
         __syncthreads();
         const int32_t u = s_unit;
-        if (u >= a.nunits) break;
+        if (u >= nunits) break;
         const int32_t g = a.units[3 * u], s0 = a.units[3 * u + 1], s1 = a.units[3 * u + 2];
         const int32_t vo = a.voff[g], n = a.voff[g + 1] - vo;
-        const int32_t levels = min(n, LEVCAP);
-        int32_t K = lds_sweep::group_size<uint32_t>(BYTES, n, levels, s1 - s0);
+        const int32_t levels = WIDE ? n : min(n, LEVCAP);
+        int32_t K = lds_sweep::group_size<ST>(BYTES, n, levels, s1 - s0);
         const int32_t groups = (s1 - s0 + K - 1) / K;
         K = (s1 - s0 + groups - 1) / groups; // even groups
-        lds_sweep::Arrays<uint32_t> s(raw, n, K, levels);
+        lds_sweep::Arrays<ST> s(raw, n, K, levels);
         const uint16_t *br = a.brp + a.rpoff[g];
         const uint4 *cols = a.bursts + a.boff[g];
         for (int32_t v = tid; v <= n; v += T) s.rp[v] = br[v];
@@ -261,10 +266,10 @@ __global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
             constexpr bool HV = decltype(heavy)::value;
             for (int32_t k0 = s0; k0 < s1; k0 += K) {
                 s.K = min(K, s1 - k0);
-                const int32_t nlev = lds_sweep::forward<uint32_t, T, HV>(
-                    s, cols, [&](int32_t k) { return k0 + k; }, safe, s_cnt, &s_fail);
-                if (nlev < 0 || s_fail) return false;
-                lds_sweep::backward<uint32_t, T, HV>(s, cols, nlev, 1, [](int32_t, int32_t, double) {});
+                const int32_t nlev = lds_sweep::forward<ST, T, HV>(
+                    s, cols, [&](int32_t k) { return k0 + k; }, (ST)safe, s_cnt, &s_fail);
+                if (nlev < 0 || (!WIDE && s_fail)) return false;
+                lds_sweep::backward<ST, T, HV>(s, cols, nlev, 1, [](int32_t, int32_t, double) {});
             }
             return true;
         };
@@ -275,6 +280,7 @@ __global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
         if (done) {
             for (int32_t v = tid; v < n; v += T)
                 if (s.bc[v] != 0.0) unsafeAtomicAdd(&a.bc[vo + v], s.bc[v]);
+            if (WIDE && tid == 0 && s_fail) atomicOr(a.status, (uint32_t)BC_DEV_SIGMA_OVERFLOW);
         } else if (tid == 0) {
             const unsigned int k = atomicAdd(a.redo_count, 1u);
             a.redo[3 * k] = g;
@@ -399,8 +405,8 @@ bc_status multigraph_run(bc_ctx *ctx) {
     if (m.nunits == 0) return BC_OK;
     if (!m.exec) {
         // the group sweep over its two classes, the full sweep over the other
-        // graphs and over the units the group sweep handed back (their count
-        // read on the device)
+        // graphs, and the group sweep with 64-bit counts over the units handed
+        // back (their count read on the device)
         const int32_t ngroup = m.nbig + m.nsmall;
         MultiArgs ab = args_of(ctx, m.units, m.nbig);
         ab.next = m.next;
@@ -419,14 +425,16 @@ bc_status multigraph_run(bc_ctx *ctx) {
         BC_HIP(ctx, hipStreamBeginCapture(m.stream, hipStreamCaptureModeThreadLocal));
         hipLaunchKernelGGL(k_mg_reset, dim3(1), dim3(64), 0, m.stream, m.next);
         if (m.nbig > 0)
-            hipLaunchKernelGGL((k_mg_group<BIG_T, BIG_BYTES>), dim3(std::min(m.nbig, m.grid)), dim3(BIG_T), 0, m.stream,
+            hipLaunchKernelGGL((k_mg_group<uint32_t, BIG_T, BIG_BYTES>), dim3(std::min(m.nbig, m.grid)), dim3(BIG_T), 0, m.stream,
                                ab);
         if (m.nsmall > 0)
-            hipLaunchKernelGGL((k_mg_group<SMALL_T, SMALL_BYTES>), dim3(std::min(m.nsmall, 4 * m.grid)), dim3(SMALL_T), 0,
+            hipLaunchKernelGGL((k_mg_group<uint32_t, SMALL_T, SMALL_BYTES>), dim3(std::min(m.nsmall, 4 * m.grid)), dim3(SMALL_T), 0,
                                m.stream, as);
         if (m.nunits > ngroup)
             hipLaunchKernelGGL(k_mg_sweep, dim3(std::min(m.nunits - ngroup, m.grid)), dim3(MT), 0, m.stream, af);
-        if (ngroup > 0) hipLaunchKernelGGL(k_mg_sweep, dim3(m.grid), dim3(MT), 0, m.stream, ar);
+        if (ngroup > 0)
+            hipLaunchKernelGGL((k_mg_group<uint64_t, BIG_T, BIG_BYTES>), dim3(std::min(ngroup, m.grid)), dim3(BIG_T), 0,
+                               m.stream, ar);
         BC_HIP(ctx, hipStreamEndCapture(m.stream, &graph));
         const hipError_t e = hipGraphInstantiate(&m.exec, graph, nullptr, nullptr, 0);
         (void)hipGraphDestroy(graph);

@@ -14,7 +14,36 @@ def rel_err(x, y):
     return float(np.max(np.abs(x - y) / np.maximum(np.abs(y), 1.0))) if y.size else 0.0
 
 
+def fans(*widths, then=0):
+    """A chain of fans: the count multiplies by each width; `then` more edges."""
+    edges, at, new = [], 0, 1
+    for w in widths:
+        mids = list(range(new, new + w))
+        new += w + 1
+        edges += [(at, x) for x in mids] + [(x, new - 1) for x in mids]
+        at = new - 1
+    for _ in range(then):
+        edges.append((at, new))
+        at, new = new, new + 1
+    return edges, at, new
+
+
+def wrapping_sum(more=0):
+    """From vertex 0 a vertex has predecessors with 255 * 2^24 and 2^25
+    shortest paths (times 2^more): either is below 2^32, their sum is not, and
+    the smaller one is below 2^32 over the largest degree."""
+    a, ea, na = fans(15, 17, *[2] * (24 + more))
+    b, eb, nb = fans(*[2] * (25 + more), then=2)
+    move = lambda x: 0 if x == 0 else x + na - 1  # noqa: E731
+    e = a + [(move(x), move(y)) for x, y in b]
+    n = na + nb - 1
+    e += [(ea, n), (move(eb), n), (n, n + 1)]
+    u, v = np.array(e).T
+    return gg.from_edges(n + 2, u, v, name="wrapping-sum")
+
+
 CASES = {
+    "wrapping-sum": lambda: [wrapping_sum()] * 40,
     # one vertex, one edge, and both sides of the small-graph class
     "class-edges": lambda: [gg.path(1), gg.path(2)] + [gg.watts_strogatz(n, 6, 0.1, n) for n in (255, 256, 257)],
     # degrees 7, 8 and 9: one burst short, full, and one column over

@@ -43,3 +43,16 @@ def test_plain_small(gpu_lib, name):
         d, sg, dl = oracle.sssp_u64(g, int(s))
         assert np.array_equal(dist[i], d) and np.array_equal(sigma[i], sg)
         assert rel_err(delta[i], dl) <= 1e-12
+
+
+def test_plain_small_overflow(gpu_lib):
+    """Paths of 255 * 2^56 and 2^57 meet: their sum passes 2^64, whichever of
+    the two is added last."""
+    from test_gpu_many_groups import wrapping_sum
+    for _ in range(8):
+        with gpu_lib.BC(wrapping_sum(32), form="plain") as ctx:
+            ctx.run()
+            with pytest.raises(gpu_lib.BCError) as ei:
+                ctx.read()
+            assert ei.value.status == gpu_lib.BC_ERR_OVERFLOW
+            ctx.reset()
