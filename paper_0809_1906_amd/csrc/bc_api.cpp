@@ -495,6 +495,7 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
     if (form == BC_FORM_PLAIN_FP64) ps = plain_prepare(ctx);
     else if (form == BC_FORM_SPARSE || form == BC_FORM_HYBRID || form == BC_FORM_ALGEBRAIC)
         ps = tune_prepare(ctx, opt, form);
+    if (ps == BC_OK && small_takes_batches(ctx)) ps = small_prepare(ctx);
     if (ps != BC_OK) return bail(ps, ctx->err);
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return bail(BC_ERR_DEVICE, "stream synchronisation failed");
     *out = ctx;
@@ -878,7 +879,7 @@ bc_status bc_get_info(const bc_ctx *ctx, bc_info *out) {
     out->weighted = ctx->weighted ? 1 : 0;
     out->form = ctx->form;
     out->batch = ctx->many ? ctx->mg.chunk : ctx->form == BC_FORM_PLAIN_FP64 ? 1 : ctx->sp.batch;
-    out->max_levels = ctx->max_levels;
+    out->max_levels = std::max(ctx->max_levels, ctx->poisoned ? 0 : small_levels(const_cast<bc_ctx *>(ctx), 1));
     out->sources_run = ctx->sources_run;
     out->device_bytes = ctx->device_bytes;
     const bool every = ctx->form == BC_FORM_ALGEBRAIC;

@@ -167,7 +167,8 @@ struct SmallState {
     bool on = false;
     int cus = 0;
     LdsColumns cols;
-    uint32_t *count = nullptr;  // [0] units handed back by the 32-bit sweep, [1] most levels seen
+    uint32_t *count = nullptr;  // [0] units handed back by the 32-bit sweep, [1] most levels seen,
+                                // [2] by the last allocation-free call
     int32_t *redo = nullptr;    // those units
     int64_t redo_cap = 0;
 };
@@ -329,7 +330,13 @@ bc_status lds_columns(bc_ctx *ctx, const std::vector<int32_t> &voff, const std::
                       const int32_t *d_rp, LdsColumns &out, std::vector<uint8_t> &taken);
 // Small unweighted graphs without edge terms: can the LDS hold a source's state?
 bool small_fits(const bc_ctx *ctx);
+// Do the sparse and hybrid forms run their sources that way?
+bool small_takes_batches(const bc_ctx *ctx);
 bc_status small_prepare(bc_ctx *ctx);
+// Most levels any source had: slot 1 by ordinary calls, 2 in the last
+// allocation-free one (synchronises); 0 off this route.
+int32_t small_levels(bc_ctx *ctx, int slot);
+bc_status small_check_room(bc_ctx *ctx);
 // wide: 64-bit counts and FP64 c(v) throughout; else 32-bit counts and FP32
 // c(v), groups whose counts pass 32 bits again in 64 bits.  With dist_dump,
 // rows of n per source instead of BC (delta_dump may be null: forward only).

@@ -12,7 +12,7 @@
 // queue is drained.  Two sweeps:
 //   group sweep  (lds_sweep.h) as many sources at once as the LDS holds, 32-bit
 //                counts overwritten by FP32 c(v), at most LEVCAP levels; units
-//                it cannot finish again with 64-bit counts, FP64 c(v) and any
+//                it cannot finish again with 64-bit counts and any
 //                depth; for graphs of fewer than 65536 bursts of eight columns;
 //   full sweep   one source at a time, 64-bit counts, any depth; for the other
 //                graphs and the per-source readout.
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
                 const int32_t nlev = lds_sweep::forward<ST, T, HV>(
                     s, cols, [&](int32_t k) { return k0 + k; }, (ST)safe, s_cnt, &s_fail);
                 if (nlev < 0 || (!WIDE && s_fail)) return false;
-                lds_sweep::backward<ST, T, HV>(s, cols, nlev, 1, [](int32_t, int32_t, double) {});
+                lds_sweep::backward<ST, T, HV, true>(s, cols, nlev, 1, [](int32_t, int32_t, double) {});
             }
             return true;
         };

@@ -1,7 +1,7 @@
 // Small unweighted graphs: per-source sweeps with all per-source state in LDS
 // (lds_sweep.h), for one graph and a list of sources.  The plain form takes
 // 64-bit counts and FP64 c(v); the sparse and hybrid forms 32-bit counts and
-// FP32 c(v), sources whose counts pass 32 bits again in 64.
+// FP32 c(v), and the sources whose counts pass 32 bits again with 64-bit ones.
 #include "bc_internal.h"
 #include "lds_sweep.h"
 
@@ -40,11 +40,11 @@ struct SmallArgs {
     double *delta_dump;     // may be null: forward only
 };
 
-__global__ void k_small_reset(uint32_t *redo_count) {
-    if (threadIdx.x == 0) *redo_count = 0;
+__global__ void k_small_reset(uint32_t *count) {
+    if (threadIdx.x == 0) count[0] = count[2] = 0;
 }
 
-template <typename ST, bool HV, bool DUMP>
+template <typename ST, bool F32, bool HV, bool DUMP>
 __global__ __launch_bounds__(ST_T) void k_small_sweep(SmallArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char raw[ST_BYTES];
     __shared__ int32_t s_cnt[3];
@@ -93,11 +93,11 @@ __global__ __launch_bounds__(ST_T) void k_small_sweep(SmallArgs a) {
                     }
                 __syncthreads(); // the backward overwrites the counts
                 if (!a.delta_dump) continue;
-                lds_sweep::backward<ST, ST_T, HV>(s, a.bursts, nlev, 0, [&](int32_t k, int32_t v, double d) {
+                lds_sweep::backward<ST, ST_T, HV, F32>(s, a.bursts, nlev, 0, [&](int32_t k, int32_t v, double d) {
                     a.delta_dump[(size_t)(k0 + k) * n + v] = d;
                 });
             } else {
-                lds_sweep::backward<ST, ST_T, HV>(s, a.bursts, nlev, 1, [](int32_t, int32_t, double) {});
+                lds_sweep::backward<ST, ST_T, HV, F32>(s, a.bursts, nlev, 1, [](int32_t, int32_t, double) {});
             }
         }
     }
@@ -108,10 +108,10 @@ __global__ __launch_bounds__(ST_T) void k_small_sweep(SmallArgs a) {
     if (tid == 0 && a.depth && depth > 0) atomicMax(a.depth, (uint32_t)depth);
 }
 
-template <typename ST>
+template <typename ST, bool F32>
 void launch(bc_ctx *ctx, const SmallArgs &a, bool heavy, bool dump, int grid) {
-    const auto k = dump ? (heavy ? k_small_sweep<ST, true, true> : k_small_sweep<ST, false, true>)
-                        : (heavy ? k_small_sweep<ST, true, false> : k_small_sweep<ST, false, false>);
+    const auto k = dump ? (heavy ? k_small_sweep<ST, F32, true, true> : k_small_sweep<ST, F32, false, true>)
+                        : (heavy ? k_small_sweep<ST, F32, true, false> : k_small_sweep<ST, F32, false, false>);
     hipLaunchKernelGGL(k, dim3(grid), dim3(ST_T), 0, ctx->stream, a);
 }
 
@@ -124,6 +124,47 @@ bool small_fits(const bc_ctx *ctx) {
     for (int32_t v = 0; v < ctx->n; ++v)
         bursts += (ctx->h_row_ptr[(size_t)v + 1] - ctx->h_row_ptr[(size_t)v] + lds_sweep::BURST - 1) / lds_sweep::BURST;
     return bursts < 65536;
+}
+
+// The sparse and hybrid forms' line.  A batch pays two launches per level and
+// pulls every row at every level; the LDS sweep pays per arc and source.
+// Microseconds for one source / milliseconds for all, LDS against batches of
+// 256 (of 512 faster by a fifth): a path of 1000 1680 / 1.71 against 7620 /
+// 39; a ring lattice of 6001 213 / 2.1 against 1050 / 38; G(4000) degree 10
+// 90 / 0.39 against 176 / 2.8; RMAT-12 (97 thousand arcs) 140 / 1.1 against
+// 213 / 2.8; G(6500) degree 26 (170) 121 / 1.7 against 168 / 5.2.  Past the
+// line the batches catch up: RMAT-13 (204) 237 / 5.4 against 219 / 6.6 and
+// 4.9 at 512; G(4000) degree 66 (265) 229 / 2.2 against 166 / 3.0 and 2.3.
+// Hubs cost the LDS sweep more, so the last stretch is for graphs without.
+// Edge terms, kernel timing, host-driven batches and levels by products ask
+// for the batched kernels themselves.
+bool small_takes_batches(const bc_ctx *ctx) {
+    if (ctx->form != BC_FORM_SPARSE && ctx->form != BC_FORM_HYBRID) return false;
+    if (ctx->host_driven || ctx->timing || !small_fits(ctx)) return false;
+    if (ctx->hy.products && (ctx->al.every_level || ctx->hy.theta_fwd <= 1.0 || ctx->hy.theta_bwd <= 1.0)) return false;
+    return ctx->nnz <= 131072 || (ctx->nnz <= 196608 && ctx->max_degree <= 256);
+}
+
+int32_t small_levels(bc_ctx *ctx, int slot) {
+    if (!ctx->sm.on || ctx->form == BC_FORM_PLAIN_FP64) return 0;
+    uint32_t x = 0;
+    if (hipMemcpyAsync(&x, ctx->sm.count + slot, sizeof x, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess)
+        return 0;
+    return (int32_t)x;
+}
+
+// An allocation-free readout of sources deeper than the frontier levels that
+// the batched kernels would hold by now (16, doubled as earlier calls needed
+// more) is refused, as it is where those kernels run: whichever route a graph
+// takes, a context answers alike.
+bc_status small_check_room(bc_ctx *ctx) {
+    const int32_t seen = small_levels(ctx, 1), now = small_levels(ctx, 2);
+    int32_t cap = 16;
+    while (cap < seen + 1) cap *= 2;
+    if (now > seen && now + 2 > cap)
+        return bc_fail(ctx, BC_ERR_NOMEM, "the sources are deeper than any earlier call's: run them by an ordinary call first");
+    return BC_OK;
 }
 
 bc_status small_prepare(bc_ctx *ctx) {
@@ -140,6 +181,9 @@ bc_status small_prepare(bc_ctx *ctx) {
     bc_dfree(ctx, d);
     if (st != BC_OK) return st;
     BC_HIP(ctx, hipDeviceGetAttribute(&m.cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    m.redo_cap = std::max(ctx->n, 4096);
+    m.redo = (int32_t *)bc_dalloc(ctx, (size_t)m.redo_cap * sizeof(int32_t));
+    if (!m.redo) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation failed");
     m.on = taken[0] != 0;
     return BC_OK;
 }
@@ -158,7 +202,7 @@ bc_status small_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool w
     a.count = count;
     a.bc = ctx->bc;
     a.status = ctx->status;
-    a.depth = wide ? nullptr : m.count + 1;
+    a.depth = wide ? nullptr : m.count + (ctx->no_alloc ? 2 : 1);
     a.dist_dump = dist_dump;
     a.sigma_dump = sigma_dump;
     a.delta_dump = delta_dump;
@@ -169,7 +213,7 @@ bc_status small_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool w
         a.K = a.unit = k64;
         a.nunits = (count + a.unit - 1) / a.unit;
         a.safe = ~0ull / deg;
-        launch<uint64_t>(ctx, a, heavy, dump, (int)std::min<int64_t>(a.nunits, cus));
+        launch<uint64_t, false>(ctx, a, heavy, dump, (int)std::min<int64_t>(a.nunits, cus));
         BC_HIP(ctx, hipGetLastError());
         return BC_OK;
     }
@@ -186,13 +230,13 @@ bc_status small_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool w
     a.redo = m.redo;
     a.redo_count = m.count;
     hipLaunchKernelGGL(k_small_reset, dim3(1), dim3(64), 0, ctx->stream, m.count);
-    launch<uint32_t>(ctx, a, heavy, dump, (int)std::min<int64_t>(a.nunits, cus));
+    launch<uint32_t, true>(ctx, a, heavy, dump, (int)std::min<int64_t>(a.nunits, cus));
     SmallArgs r = a;
     r.K = std::min(k64, a.unit);
     r.list = m.redo;
     r.list_count = m.count;
     r.safe = ~0ull / deg;
-    launch<uint64_t>(ctx, r, heavy, dump, (int)std::min<int64_t>(a.nunits, cus));
+    launch<uint64_t, true>(ctx, r, heavy, dump, (int)std::min<int64_t>(a.nunits, cus));
     BC_HIP(ctx, hipGetLastError());
     return BC_OK;
 }

@@ -1,5 +1,5 @@
 // Batched sparse form: B sources at once (B = 64 NW, NW in {1, 2, 4, 8}),
-// unit weights.
+// unit weights.  (Small sparse graphs run their sources in LDS: small.hip.)
 //
 // State is batch-minor.  For level l the frontier is a bitmap
 // front[l][v][q] (uint64): bit b of word q is set iff d(s_{64q+b}, v) = l,
@@ -1485,6 +1485,7 @@ bc_status sparse_release(bc_ctx *ctx) {
 }
 
 bc_status sparse_run(bc_ctx *ctx, const int32_t *d_src, int64_t count) {
+    if (ctx->sm.on) return small_run(ctx, d_src, count, false, nullptr, nullptr, nullptr);
     SparseState &s = ctx->sp;
     const int32_t B = s.batch;
     const bool replay = !ctx->weighted && !ctx->host_driven && count < (int64_t(1) << 31) - B;
@@ -1565,6 +1566,10 @@ void sparse_graphs_release(bc_ctx *ctx) {
 
 bc_status sparse_dump(bc_ctx *ctx, const int32_t *d_src, int32_t count,
                       int32_t *dist_dump, uint64_t *sigma_dump, double *delta_dump) {
+    if (ctx->sm.on) {
+        bc_status st = small_run(ctx, d_src, count, false, delta_dump, dist_dump, sigma_dump);
+        return st == BC_OK && ctx->no_alloc ? small_check_room(ctx) : st;
+    }
     SparseState &s = ctx->sp;
     int32_t nlev = 0;
     bc_status st = run_batch(ctx, d_src, count, false, &nlev, delta_dump != nullptr, delta_dump);

@@ -56,3 +56,59 @@ def test_plain_small_overflow(gpu_lib):
                 ctx.read()
             assert ei.value.status == gpu_lib.BC_ERR_OVERFLOW
             ctx.reset()
+
+
+BATCHED = {
+    "one": lambda: gg.path(1),
+    "isolated": lambda: gg.disjoint_union(gg.path(1), gg.cycle(9), gg.path(1), gg.path(70)),
+    "deep": lambda: gg.path(1500),
+    "hubs": lambda: gg.rmat(12, 16, 3),
+    # C(34,17) fits 32 bits with a sum that could wrap; C(38,19) and C(66,33)
+    # are run again in 64
+    "counts32": lambda: gg.grid(18, 18),
+    "counts64": lambda: gg.disjoint_union(gg.grid(34, 34), gg.grid(20, 20), gg.path(3)),
+    "last": lambda: gg.er_plus_tree(7084, 3.0, 5),
+    "past": lambda: gg.er_plus_tree(7085, 3.0, 5),
+}
+
+
+@pytest.mark.parametrize("form,batch", [("sparse", 64), ("sparse", 512), ("hybrid", 256)])
+@pytest.mark.parametrize("name", list(BATCHED))
+def test_batched_small(gpu_lib, name, form, batch):
+    """The batched forms on small graphs: the LDS sweep against the oracle, and
+    against the batched kernels (a host-driven context)."""
+    g = BATCHED[name]()
+    print(f"small {form} {batch} {name} n={g.n}", flush=True)
+    src = gg.sample_sources(g.n, min(g.n, 700), 11)
+    src = np.concatenate([src, src[:1]]).astype(np.int32)
+    want = oracle.bc(g, sources=src, threads=8)
+    pick = src[:: max(1, src.size // 5)][:6]
+    with gpu_lib.BC(g, form=form, batch=batch, host_driven=True) as ctx:
+        ctx.run(src)
+        host, levels = ctx.read(), ctx.info().max_levels
+    with gpu_lib.BC(g, form=form, batch=batch) as ctx:
+        ctx.run(src)
+        assert rel_err(ctx.read(), want) <= 1e-5  # FP32 c(v)
+        assert rel_err(ctx.read(), host) <= 1e-5
+        assert ctx.info().max_levels == levels and ctx.info().sources_run == src.size
+        ctx.reset()
+        ctx.run()
+        assert rel_err(ctx.read(), oracle.bc(g, threads=8)) <= 1e-5
+        dist, sigma, delta = ctx.sssp(pick)
+    for i, s in enumerate(pick):
+        d, sg, dl = oracle.sssp_u64(g, int(s))
+        assert np.array_equal(dist[i], d) and np.array_equal(sigma[i], sg)
+        assert rel_err(delta[i], dl) <= 1e-5
+
+
+@pytest.mark.parametrize("form", ["plain", "sparse"])
+def test_small_overflow(gpu_lib, form):
+    g = gg.grid(35, 35)  # C(68,34) > 2^64 - 1
+    with gpu_lib.BC(g, form=form) as ctx:
+        ctx.run()
+        with pytest.raises(gpu_lib.BCError) as ei:
+            ctx.read()
+        assert ei.value.status == gpu_lib.BC_ERR_OVERFLOW
+        ctx.reset()
+        ctx.run(np.array([600], np.int32))  # near the middle: counts fit
+        assert rel_err(ctx.read(), oracle.bc(g, sources=np.array([600], np.int32))) <= 1e-5
