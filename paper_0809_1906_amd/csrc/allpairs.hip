@@ -9,27 +9,39 @@
 // the Brandes backward.
 //
 // The context's forward kernels write D (int32, -1 = unreachable) and Lambda
-// (uint64) [n][n], row = source, internal numbering.  A preparation pass turns
-// them into
-//   Dp  uint32 [n][ld], ld = n rounded up to 64: d(s,t) where 0 < d, else FAR
-//       (t = s, t unreachable, and the padding columns)
+// (uint64) [n][n], row = source, internal numbering.  The graph is undirected,
+// so every matrix is symmetric.  A preparation pass turns them into
 //   R   double [n][n]: 1 / lambda_st where 0 < d(s,t), else 0
-// The graph is undirected, so every matrix is symmetric: d(v,t) is row t of Dp
-// and lambda_vt is row v of Lambda.
+//   D8  uint8 [n][l8], l8 = n rounded up to 256: d(s,t), NO8 for t = s, no path
+//       and the padding (unit weights with distances up to MAX8)
+//   P   uint32 [n][ld], ld = n rounded up to 64: d(s,t) of the pairs (s,t) that
+//       the triple sum below takes, else FAR
+//   Q   uint32 [n][ld]: the distances it takes for d(s,v) and d(v,t), else FAR
 //
-// The mask d(s,v) + d(v,t) = d(s,t) holds for a small share of triples (about
-// (L - 1) / n of them for mean distance L), so the sum is organised around
-// testing it cheaply.  A block takes VT vertices v and SC sources s; each
-// thread owns targets t and keeps d(v,t) for its VT vertices in registers; per
-// source the VT distances d(s,v) are uniform across the wave and come in by
-// scalar loads.  A triple costs one three-operand add, x = d(s,v) + d(v,t) -
-// d(s,t) (mod 2^32), and half a three-operand minimum; a group of 8 vertices is
-// tested once, by a ballot on its minimum.  Groups with a hit (x = 0) are
-// queued and their terms added into the block's LDS accumulators later.  FAR = 2^31 makes
-// the one compare exact: real distances are below 2^31, so a sum of two stays
-// below 2^32, FAR plus a real distance lies in (2^31, 2^32), FAR + FAR wraps to
-// 0, and no Dp entry is 0; x = 0 is the same test.  A sum of two real distances
-// equal to 2^31 could meet dst = FAR; R is 0 there, so such a term adds nothing.
+// Unit weights: near and far triples.  A triple with d(v,t) = 1 has v next to t
+// and lambda_vt = 1, so for each arc (v, u) and every x with d(x,u) = d(x,v) + 1
+// the two triples (x, v, u) and (u, v, x) add lambda_xv / lambda_xu each; where
+// d(x,v) = 1 they are near at both ends and each arrives twice, over (v, u) and
+// over (v, x), so they count half (k_alg2_near).  What is left has d(s,v) >= 2
+// and d(v,t) >= 2, so d(s,t) >= 4: P holds only those pairs and Q only
+// distances from 2, and the triple sum (k_alg2) is skipped where no pair is
+// that far apart.  Weighted graphs, and deeper ones, take every triple there:
+// P = Q = the distances.
+//
+// The triple sum.  The mask d(s,v) + d(v,t) = d(s,t) holds for a small share of
+// triples, so it is organised around testing it cheaply.  A block takes VT
+// vertices v and SC sources s; each thread owns targets t and keeps d(v,t) for
+// its VT vertices in registers; per source the VT distances d(s,v) are uniform
+// across the wave and come in by scalar loads.  A triple costs one
+// three-operand add, x = d(s,v) + d(v,t) - d(s,t) (mod 2^32), and half a
+// three-operand minimum; a group of 8 vertices is tested once, by a ballot on
+// its minimum.  Groups with a hit (x = 0) are queued and their terms added into
+// the block's LDS accumulators later.  FAR = 2^31 makes the one compare exact:
+// real distances are below 2^31, so a sum of two stays below 2^32, FAR plus a
+// real distance lies in (2^31, 2^32), FAR + FAR wraps to 0, and no entry of P is
+// 0; x = 0 is the same test.  A sum of two real distances equal to 2^31 could
+// meet P = FAR; R is 0 there, or the pair was left to the near sum and its wave
+// skips it, so such a term adds nothing.
 #include "bc_internal.h"
 
 #include <type_traits>
@@ -41,19 +53,104 @@ constexpr int VT = 64;                // vertices v per block
 constexpr int SC = 256;               // sources s per block
 constexpr uint32_t FAR = 0x80000000u; // t = s, no path, or padding
 
-__global__ __launch_bounds__(256) void k_alg2_prep(int32_t n, int32_t ld, const int32_t *__restrict__ D,
-                                                   const uint64_t *__restrict__ Lam, uint32_t *__restrict__ Dp,
-                                                   double *__restrict__ R) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (size_t)n * ld) return;
-    const int32_t s = (int32_t)(i / ld), c = (int32_t)(i % ld);
+constexpr uint8_t NO8 = 255;          // no entry of D8
+constexpr int32_t MAX8 = 250;         // largest distance D8 holds
+
+// R and, when D8 is wanted, D8; *far = the largest distance (one block per row
+// and 256 columns).
+__global__ __launch_bounds__(256) void k_alg2_prep(int32_t n, int32_t l8, const int32_t *__restrict__ D,
+                                                   const uint64_t *__restrict__ Lam, double *__restrict__ R,
+                                                   uint8_t *__restrict__ D8, int32_t *__restrict__ far) {
+    const int32_t s = blockIdx.y, c = blockIdx.x * 256 + threadIdx.x;
+    int32_t d = 0;
     if (c < n) {
         const size_t k = (size_t)s * n + c;
-        const int32_t d = D[k];
-        Dp[i] = d > 0 ? (uint32_t)d : FAR;
+        d = D[k];
         R[k] = d > 0 ? 1.0 / (double)Lam[k] : 0.0;
-    } else {
-        Dp[i] = FAR;
+    }
+    if (D8 && c < l8) D8[(size_t)s * l8 + c] = d > 0 && d <= MAX8 ? (uint8_t)d : NO8;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) d = max(d, __shfl_xor(d, off, 64));
+    if ((threadIdx.x & 63) == 0 && d > __hip_atomic_load(far, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(far, d);
+}
+
+// P: the distances of at least dmin, Q: those of at least qmin, else FAR.
+__global__ __launch_bounds__(256) void k_alg2_far(int32_t n, int32_t ld, const int32_t *__restrict__ D, int32_t dmin,
+                                                  int32_t qmin, uint32_t *__restrict__ P, uint32_t *__restrict__ Q) {
+    const int32_t s = blockIdx.y, c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= ld) return;
+    const int32_t d = c < n ? D[(size_t)s * n + c] : 0;
+    P[(size_t)s * ld + c] = d >= dmin ? (uint32_t)d : FAR;
+    if (Q != P) Q[(size_t)s * ld + c] = d >= qmin ? (uint32_t)d : FAR;
+}
+
+// The near triples.  A block takes vertex v and 256 columns x; its four waves
+// share v's arcs, each lane four columns: for an arc (v, u) the bytes of row u
+// are compared with those of row v plus one, four at a time, and only a lane
+// with a match loads the 1/lambda_xu.  What bounds it is the L2 traffic of the
+// rows u (n bytes per arc, and 8 n where distances grow), so the blocks of one
+// XCD (every eighth) take one column range after the other: 256 columns of
+// every row of D8 fit its L2 up to n = 16384.  Whole call, against the triple
+// sum alone: G(6001, 64/6000), distances up to 3, 7.3 against 90.4 ms (this
+// kernel 2.4); G(16384, 256/16383) 77 against 492; where far triples remain,
+// G(6001, 8/6000) 41 against 57 and RMAT-13 70 against 111.
+__global__ __launch_bounds__(256) void k_alg2_near(int32_t n, int32_t l8, const int32_t *__restrict__ rp,
+                                                   const int32_t *__restrict__ col, const uint8_t *__restrict__ D8,
+                                                   const double *__restrict__ R, const uint64_t *__restrict__ Lam,
+                                                   int32_t xcds, double *__restrict__ bc) {
+    __shared__ double s_sum[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t tiles = l8 / 256;
+    // XCD g takes column ranges g, g + xcds, ...; within a range every vertex
+    const int64_t g = blockIdx.x % xcds, r = blockIdx.x / xcds;
+    const int32_t tile = (int32_t)(g + xcds * (r / n)), v = (int32_t)(r % n);
+    if (tile >= tiles) return;
+    const int32_t b = rp[v], e = rp[v + 1];
+    if (b == e) return;
+    const int32_t x0 = tile * 256 + 4 * lane;
+    const uint32_t dv = *reinterpret_cast<const uint32_t *>(D8 + (size_t)v * l8 + x0);
+    // row v plus one, 0 (which no byte of D8 equals) where there is no entry
+    uint32_t want = 0;
+    double lam[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t d = (dv >> (8 * k)) & 0xFFu;
+        lam[k] = 0.0;
+        if (d != NO8) {
+            want |= (d + 1) << (8 * k);
+            // near at both ends: each of the two triples is met twice
+            lam[k] = d == 1 ? 1.0 : 2.0 * (double)Lam[(size_t)v * n + x0 + k];
+        }
+    }
+    double acc = 0.0;
+    constexpr int U = 8; // rows in flight
+    for (int32_t a0 = b + wave; a0 < e; a0 += 4 * U) {
+        uint32_t du[U];
+        int32_t u[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) u[j] = a0 + 4 * j < e ? col[a0 + 4 * j] : -1;
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            du[j] = u[j] >= 0 ? *reinterpret_cast<const uint32_t *>(D8 + (size_t)u[j] * l8 + x0) : 0xFFFFFFFFu;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const uint32_t z = du[j] ^ want;
+            const uint32_t hit = (z - 0x01010101u) & ~z & 0x80808080u; // exact below the lowest zero byte
+            if (hit == 0) continue;
+            const double *row = R + (size_t)u[j] * n + x0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (((z >> (8 * k)) & 0xFFu) == 0) acc += lam[k] * row[k];
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (lane == 0) s_sum[wave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double sum = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+        if (sum != 0.0) unsafeAtomicAdd(&bc[v], sum);
     }
 }
 
@@ -67,8 +164,8 @@ __global__ __launch_bounds__(256) void k_alg2_prep(int32_t n, int32_t ld, const 
 // test loop.
 constexpr int QK = 24; // queue entries per thread
 
-__global__ __launch_bounds__(AT) void k_alg2(int32_t n, int32_t ld, const uint32_t *__restrict__ Dp,
-                                             const double *__restrict__ R, const uint64_t *__restrict__ Lam,
+__global__ __launch_bounds__(AT) void k_alg2(int32_t n, int32_t ld, const uint32_t *__restrict__ P,
+                                             const uint32_t *__restrict__ Q, const double *__restrict__ R, const uint64_t *__restrict__ Lam,
                                              double *__restrict__ bc) {
     __shared__ double s_acc[VT];
     __shared__ uint16_t s_q[QK][AT];  // source slot << 3 | group
@@ -84,7 +181,7 @@ __global__ __launch_bounds__(AT) void k_alg2(int32_t n, int32_t ld, const uint32
     // step, so that their loads are in flight together; inside it, one.
     auto drain = [&](int32_t t, int32_t cnt, auto unroll) {
         constexpr int U = decltype(unroll)::value;
-        const uint32_t *trow = Dp + (size_t)t * ld + v0;
+        const uint32_t *trow = Q + (size_t)t * ld + v0;
         const uint64_t *ltrow = Lam + (size_t)t * n + v0;
         for (int32_t i = 0; i < cnt; i += U) {
             int32_t sv[U], gv[U];
@@ -98,7 +195,7 @@ __global__ __launch_bounds__(AT) void k_alg2(int32_t n, int32_t ld, const uint32
                 sv[u] = sa + (int32_t)(code >> 3);
                 gv[u] = (int32_t)(code & 7);
                 ndv[u] = s_nd[e][tid];
-                const uint4 *sp = reinterpret_cast<const uint4 *>(Dp + (size_t)sv[u] * ld + v0 + 8 * gv[u]);
+                const uint4 *sp = reinterpret_cast<const uint4 *>(Q + (size_t)sv[u] * ld + v0 + 8 * gv[u]);
                 const uint4 *tp = reinterpret_cast<const uint4 *>(trow + 8 * gv[u]);
                 p0[u] = sp[0];
                 p1[u] = sp[1];
@@ -128,7 +225,7 @@ __global__ __launch_bounds__(AT) void k_alg2(int32_t n, int32_t ld, const uint32
     };
     for (int32_t t = tid; t < n; t += AT) {
         uint32_t dvt[VT];
-        const uint4 *row = reinterpret_cast<const uint4 *>(Dp + (size_t)t * ld + v0);
+        const uint4 *row = reinterpret_cast<const uint4 *>(Q + (size_t)t * ld + v0);
 #pragma unroll
         for (int q = 0; q < VT / 4; ++q) {
             const uint4 x = row[q];
@@ -138,14 +235,16 @@ __global__ __launch_bounds__(AT) void k_alg2(int32_t n, int32_t ld, const uint32
             dvt[4 * q + 3] = x.w;
         }
         int32_t cnt = 0;
-        uint32_t dnext = Dp[(size_t)sa * ld + t]; // d(s,t), one source ahead
+        uint32_t dnext = P[(size_t)sa * ld + t]; // d(s,t), one source ahead
         for (int32_t sl = 0; sl < ns; ++sl) {
             const int32_t s = sa + sl;
-            const uint32_t *srow = Dp + (size_t)s * ld; // uniform
+            const uint32_t *srow = Q + (size_t)s * ld; // uniform
             // -d(s,t), opaque so that x below stays one three-operand add
             uint32_t ndst = 0u - dnext;
             __asm__ volatile("" : "+v"(ndst));
-            if (sl + 1 < ns) dnext = srow[(size_t)ld + t];
+            const bool none = __builtin_amdgcn_ballot_w64(dnext != FAR) == 0;
+            if (sl + 1 < ns) dnext = P[(size_t)(s + 1) * ld + t];
+            if (none) continue; // no pair of this source and the wave's targets
 #pragma unroll
             for (int h = 0; h < VT / 32; ++h) {
                 // d(s,v) for 32 vertices: uniform, loaded before any test
@@ -212,14 +311,19 @@ bc_status allpairs_bc(bc_ctx *ctx, double *bc_internal) {
     // forward only
     double *dtmp = plain ? (double *)bc_dalloc(ctx, (size_t)chunk * n * sizeof(double)) : nullptr;
     int32_t *src = (int32_t *)bc_dalloc(ctx, (size_t)chunk * sizeof(int32_t));
-    uint32_t *Dp = nullptr;
+    uint32_t *P = nullptr, *Q = nullptr;
+    uint8_t *D8 = nullptr;
+    int32_t *far = nullptr;
     double *R = nullptr;
     auto cleanup = [&]() {
         bc_dfree(ctx, D);
         bc_dfree(ctx, Lam);
         bc_dfree(ctx, dtmp);
         bc_dfree(ctx, src);
-        bc_dfree(ctx, Dp);
+        if (Q != P) bc_dfree(ctx, Q);
+        bc_dfree(ctx, P);
+        bc_dfree(ctx, D8);
+        bc_dfree(ctx, far);
         bc_dfree(ctx, R);
     };
     if (!D || !Lam || (plain && !dtmp) || !src) {
@@ -240,22 +344,46 @@ bc_status allpairs_bc(bc_ctx *ctx, double *bc_internal) {
     }
     bc_dfree(ctx, dtmp);
     dtmp = nullptr;
-    Dp = (uint32_t *)bc_dalloc(ctx, (size_t)n * ld * sizeof(uint32_t));
+    const int32_t l8 = (n + 255) / 256 * 256;
     R = (double *)bc_dalloc(ctx, nn * sizeof(double));
-    if (!Dp || !R) {
+    far = (int32_t *)bc_dalloc(ctx, sizeof(int32_t));
+    if (!ctx->weighted) D8 = (uint8_t *)bc_dalloc(ctx, (size_t)n * l8);
+    if (!R || !far || (!ctx->weighted && !D8)) {
         cleanup();
         return bc_fail(ctx, BC_ERR_NOMEM, "all pairs: allocation of the prepared matrices failed");
     }
-    const size_t cells = (size_t)n * ld;
-    hipLaunchKernelGGL(k_alg2_prep, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, ctx->stream, n, ld, D, Lam,
-                       Dp, R);
     hipLaunchKernelGGL(k_zero_f64, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, bc_internal, n);
-    const dim3 grid(ld / VT, (n + SC - 1) / SC);
-    {
-        LaunchTimer tm(ctx, "all_pairs");
-        hipLaunchKernelGGL(k_alg2, grid, dim3(AT), 0, ctx->stream, n, ld, Dp, R, Lam, bc_internal);
-        tm.done();
+    int32_t deepest = 0;
+    hipError_t pe = hipMemsetAsync(far, 0, sizeof(int32_t), ctx->stream);
+    hipLaunchKernelGGL(k_alg2_prep, dim3(l8 / 256, n), dim3(256), 0, ctx->stream, n, l8, D, Lam, R, D8, far);
+    if (pe == hipSuccess) pe = hipMemcpyAsync(&deepest, far, sizeof deepest, hipMemcpyDeviceToHost, ctx->stream);
+    if (pe == hipSuccess) pe = hipStreamSynchronize(ctx->stream);
+    if (pe != hipSuccess) {
+        cleanup();
+        return bc_hip(ctx, pe, "all pairs: preparation");
     }
+    const bool near = D8 && deepest <= MAX8;
+    LaunchTimer tm(ctx, "all_pairs");
+    if (near) {
+        const int32_t xcds = 8, tiles = l8 / 256;
+        const unsigned blocks = (unsigned)((size_t)xcds * ((tiles + xcds - 1) / xcds) * n);
+        hipLaunchKernelGGL(k_alg2_near, dim3(blocks), dim3(256), 0, ctx->stream, n, l8, ctx->row_ptr, ctx->col, D8, R, Lam,
+                           xcds, bc_internal);
+    }
+    if (!near || deepest >= 4) {
+        P = (uint32_t *)bc_dalloc(ctx, (size_t)n * ld * sizeof(uint32_t));
+        Q = near ? (uint32_t *)bc_dalloc(ctx, (size_t)n * ld * sizeof(uint32_t)) : P;
+        if (!P || !Q) {
+            (void)hipStreamSynchronize(ctx->stream);
+            cleanup();
+            return bc_fail(ctx, BC_ERR_NOMEM, "all pairs: allocation of the prepared matrices failed");
+        }
+        hipLaunchKernelGGL(k_alg2_far, dim3((ld + 255) / 256, n), dim3(256), 0, ctx->stream, n, ld, D, near ? 4 : 1,
+                           near ? 2 : 1, P, Q);
+        const dim3 grid(ld / VT, (n + SC - 1) / SC);
+        hipLaunchKernelGGL(k_alg2, grid, dim3(AT), 0, ctx->stream, n, ld, P, Q, R, Lam, bc_internal);
+    }
+    tm.done();
     const hipError_t e = hipGetLastError();
     const hipError_t sy = hipStreamSynchronize(ctx->stream);
     cleanup();
