@@ -90,10 +90,10 @@ struct GemmArgs {
     int32_t npad, n, B, NW;
     int32_t K;             // M * npad: the class matrices side by side
     size_t plane_elems;    // K * B
-    int32_t ksplit;        // forward: 1, or 2 blocks per tile, each over half of K
+    int32_t ksplit;        // blocks per tile, each over every ksplit-th non-zero stage of K
     int32_t ntiles;        // grid_blocks<BM>(npad, B): tiles of one product
-    float *ws;             // split tiles' partial sums, [8][ntiles][2][64][forward block threads]
-    uint32_t *arrive;      // [8][ntiles]
+    float *ws;             // split tiles' partial sums, [limbs][ntiles][ksplit][64][block threads]
+    uint32_t *arrive;      // [limbs][ntiles]
     unsigned long long *ktiles; // [0] k-tiles multiplied, [1] k-tiles in the blocks' ranges (per direction)
     const uint32_t *gate;  // backward of a replayed batch: flag of level l, whose vertices it
                            // writes; zero = every block exits
@@ -175,7 +175,7 @@ constexpr int FWD_KC = 16;
 constexpr int BWD_KS = 64;
 // Forward block rows: 128 or 256, whichever the tuner measured faster on the
 // graph (AlgebraicState::fwd_rows); the backward takes 128.
-constexpr int BWD_BM = 128;
+// or, where those leave compute units idle, 64 (AlgebraicState::bwd_rows).
 
 // A stage's plane tile held in registers between its global loads and its LDS
 // stores: the block's T threads cover T / GN k-groups of GN sources at a time,
@@ -191,11 +191,11 @@ struct Stage {
 // words of row (lane % 32) of that tile that the wave multiplies: the stage's
 // KS / 32, or with the stage's k range split between the two waves of a row
 // pair (KH), the KS / 64 of the wave's half.
-template <int KS, bool KH>
+template <int KS, bool KH, int R = RT>
 struct ABits {
     static constexpr int W = KH ? KS / 64 : KS / 32;
     static_assert(W == 2 || W == 4, "stage depth");
-    uint32_t w[RT][W];
+    uint32_t w[R][W];
 };
 
 template <int NP, int KS, int TT, int KC>
@@ -214,13 +214,13 @@ __device__ __forceinline__ void load_stage(const GemmArgs &g, const __bf16 *plan
 // rows0: the wave's first row.  The wave's columns of stage ks start at k0 =
 // ks KS (+ KS / 2 for the second half with KH), word (k0 % 128) / 32 of panel
 // k0 / 128: 16 B or 8 B, aligned.  I8: the bits in the int8 operand order.
-template <int KS, bool KH, bool I8 = false>
+template <int KS, bool KH, bool I8 = false, int R = RT>
 __device__ __forceinline__ void load_abits(const GemmArgs &g, int ks, int rows0, int lane, int half,
-                                           ABits<KS, KH> &ab) {
-    constexpr int W = ABits<KS, KH>::W;
+                                           ABits<KS, KH, R> &ab) {
+    constexpr int W = ABits<KS, KH, R>::W;
     const int k0 = ks * KS + (KH ? half * (KS / 2) : 0);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
+    for (int rt = 0; rt < R; ++rt) {
         const uint32_t *p = (I8 ? g.abits8 : g.abits) +
                             ((size_t)(k0 / 128) * g.npad + rows0 + rt * 32 + (lane & 31)) * 4 + (k0 % 128) / 32;
         if constexpr (W == 4) {
@@ -278,9 +278,9 @@ __device__ __forceinline__ i32x4 expand_i8(uint32_t w, int h) {
 // Without KH the wave multiplies the stage's KS / 16 k-steps for 64 sources
 // (CT = 2); with KH, its half of them (from k-step half KS / 32) for all 128
 // sources (CT = 4).
-template <int NP, int KS, bool KH, bool I8 = false>
-__device__ __forceinline__ void mma_stage(const __bf16 *sX, const ABits<KS, KH> &ab, int lane, int wn, int half,
-                                          f32x16 (&acc)[RT][KH ? 4 : 2]) {
+template <int NP, int KS, bool KH, bool I8 = false, int R = RT>
+__device__ __forceinline__ void mma_stage(const __bf16 *sX, const ABits<KS, KH, R> &ab, int lane, int wn, int half,
+                                          f32x16 (&acc)[R][KH ? 4 : 2]) {
     // k-steps of 16 (BF16) or 32 (int8) k: two cell rows of 16 B each
     constexpr int KC = I8 ? 16 : 8, KSTEP = 2 * KC;
     constexpr int CT = KH ? 4 : 2, STEPS = KH ? KS / KSTEP / 2 : KS / KSTEP;
@@ -308,27 +308,27 @@ __device__ __forceinline__ void mma_stage(const __bf16 *sX, const ABits<KS, KH> 
         __builtin_amdgcn_sched_barrier(0); // the reads stay ahead of this step's products
         if constexpr (I8) {
             // int32 sums kept in the FP32-typed accumulators' bits
-            i32x4 a[RT];
+            i32x4 a[R];
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) a[rt] = expand_i8(ab.w[rt][kh], lane >> 5);
+            for (int rt = 0; rt < R; ++rt) a[rt] = expand_i8(ab.w[rt][kh], lane >> 5);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
+                for (int rt = 0; rt < R; ++rt)
                     acc[rt][ct] = __builtin_bit_cast(
                         f32x16, __builtin_amdgcn_mfma_i32_32x32x32_i8(a[rt], __builtin_bit_cast(i32x4, b[cur][0][ct]),
                                                                       __builtin_bit_cast(i32x16, acc[rt][ct]), 0, 0,
                                                                       0));
         } else {
-            bf16x8 a[RT];
+            bf16x8 a[R];
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) a[rt] = expand_bits(ab.w[rt][kh >> 1], hs + 8 * (kh & 1));
+            for (int rt = 0; rt < R; ++rt) a[rt] = expand_bits(ab.w[rt][kh >> 1], hs + 8 * (kh & 1));
 #pragma unroll
             for (int p = 0; p < NP; ++p)
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-                    for (int rt = 0; rt < RT; ++rt)
+                    for (int rt = 0; rt < R; ++rt)
                         acc[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                             a[rt], __builtin_bit_cast(bf16x8, b[cur][p][ct]), acc[rt][ct], 0, 0, 0);
         }
@@ -353,13 +353,13 @@ __device__ __forceinline__ Tile tile_of(int B) {
 template <int BM>
 inline unsigned grid_blocks(int npad, int B) { return (unsigned)(((npad / BM + 7) / 8) * 8 * (B / GN)); }
 
-// With K split in two: blocks L and L + 8 (the same XCD) take the two halves
+// With K split: the ksplit blocks L, L + 8, ... (the same XCD) take the parts
 // of one tile; otherwise as tile_of.  *tile is the tile's index in
 // [0, grid_blocks).
-__device__ __forceinline__ Tile tile_of_split(int B, int &half, int &tile) {
+__device__ __forceinline__ Tile tile_of_split(int B, int ksplit, int &part, int &tile) {
     const int C = B / GN;
-    const int L = blockIdx.x, x = L & 7, t = L >> 3, tt = t >> 1;
-    half = __builtin_amdgcn_readfirstlane(t & 1);
+    const int L = blockIdx.x, x = L & 7, t = L >> 3, tt = t / ksplit;
+    part = __builtin_amdgcn_readfirstlane(t - tt * ksplit);
     const int row = (tt / C) * 8 + x, col = tt % C;
     tile = __builtin_amdgcn_readfirstlane(row * C + col);
     return Tile{__builtin_amdgcn_readfirstlane(row), __builtin_amdgcn_readfirstlane(col)};
@@ -401,35 +401,42 @@ __device__ __forceinline__ int next_stage(const uint32_t *flags, int ntn, int ks
 // (from w0) and GN sources (from b0); wave wv holds rows w0 + WM (wv / WC) +
 // [0, WM) and sources b0 + WN (wv % WC) + [0, WN).  The next stage's planes
 // and bits are loaded (into registers) during the current stage's products.
-// kt0 and kt1 are k-tiles, multiples of the stage's k-tiles.  I8: int8
-// planes and products (exact int32 sums, returned converted to FP32).
-template <int NP, int KS, int BM, bool KH = false, bool I8 = false>
+// Block `part` of the tile's g.ksplit takes every ksplit-th of those stages,
+// starting with the part-th: equal shares however the zero k-tiles lie.  I8:
+// int8 planes and products (exact int32 sums, returned converted to FP32).
+template <int NP, int KS, int BM, bool KH = false, bool I8 = false, int R = RT>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &g, const __bf16 *planes, int w0, int b0, int tid,
-                                          __bf16 (*sX)[lds_x<NP, KS, I8 ? 16 : 8>()], f32x16 (&acc)[RT][KH ? 4 : 2],
-                                          int kt0 = 0, int kt1 = -1) {
+                                          __bf16 (*sX)[lds_x<NP, KS, I8 ? 16 : 8>()], f32x16 (&acc)[R][KH ? 4 : 2],
+                                          int part = 0) {
     constexpr int KC = I8 ? 16 : 8;
     constexpr int TPS = KS / GK; // k-tiles per stage
     const int lane = tid & 63, wv = tid >> 6, half = wv & 1;
-    const int rows0 = w0 + (wv >> 1) * WM, wn = KH ? 0 : half * 64;
-    const int nks = (kt1 < 0 ? g.K / GK : kt1) / TPS, ks0 = kt0 / TPS, ntn = g.B / GN;
+    const int rows0 = w0 + (wv >> 1) * (32 * R), wn = KH ? 0 : half * 64;
+    const int nks = g.K / GK / TPS, ntn = g.B / GN;
     const uint32_t *flags = g.kflags + b0 / GN;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int rt = 0; rt < R; ++rt)
 #pragma unroll
         for (int c = 0; c < (KH ? 4 : 2); ++c)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[rt][c][r] = 0.f;
 
-    int wbase = ks0 - 64; // empty window
+    int wbase = -64; // empty window
     uint64_t wbits = 0;
-    int ks = next_stage<TPS>(flags, ntn, ks0, nks, lane, wbase, wbits);
-    int kn = ks < nks ? next_stage<TPS>(flags, ntn, ks + 1, nks, lane, wbase, wbits) : nks;
+    // the times-th non-zero stage from k on
+    auto advance = [&](int k, int times) {
+        k = next_stage<TPS>(flags, ntn, k, nks, lane, wbase, wbits);
+        for (; times > 1 && k < nks; --times) k = next_stage<TPS>(flags, ntn, k + 1, nks, lane, wbase, wbits);
+        return k;
+    };
+    int ks = advance(0, part + 1);
+    int kn = ks < nks ? advance(ks + 1, g.ksplit) : nks;
     int buf = 0, done = 0;
-    Stage<NP, KS, 2 * BM, KC> st;
-    ABits<KS, KH> ab, abn;
+    Stage<NP, KS, 4 * BM / R, KC> st;
+    ABits<KS, KH, R> ab, abn;
     if (ks < nks) {
         // bits first: the planes' stores then wait for them too
-        load_abits<KS, KH, I8>(g, ks, rows0, lane, half, ab);
+        load_abits<KS, KH, I8, R>(g, ks, rows0, lane, half, ab);
         load_stage(g, planes, ks, b0, tid, st);
         store_stage(sX[0], tid, st);
     }
@@ -440,9 +447,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, const __bf16 *plane
         // after this stage's products.
         const int kl = kn < nks ? kn : ks;
         load_stage(g, planes, kl, b0, tid, st);
-        load_abits<KS, KH, I8>(g, kl, rows0, lane, half, abn);
+        load_abits<KS, KH, I8, R>(g, kl, rows0, lane, half, abn);
         __builtin_amdgcn_sched_barrier(0); // issued before the products, not sunk below them
-        mma_stage<NP, KS, KH, I8>(sX[buf], ab, lane, wn, half, acc);
+        mma_stage<NP, KS, KH, I8, R>(sX[buf], ab, lane, wn, half, acc);
         if constexpr (stages<NP, KS, BM, KC>() == 2) {
             if (kn < nks) store_stage(sX[buf ^ 1], tid, st);
             __syncthreads();
@@ -454,46 +461,54 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, const __bf16 *plane
         }
         ab = abn;
         ks = kn;
-        kn = kn < nks ? next_stage<TPS>(flags, ntn, kn + 1, nks, lane, wbase, wbits) : nks;
+        kn = kn < nks ? advance(kn + 1, g.ksplit) : nks;
         ++done;
     }
     if (tid == 0 && g.ktiles) {
         // in units of one plane's 32 x 128 x 128 (k, rows, sources): 2^20 flops
-        constexpr unsigned long long U = (unsigned long long)NP * (BM / 128);
-        atomicAdd(&g.ktiles[0], (unsigned long long)done * TPS * U);
-        atomicAdd(&g.ktiles[1], (unsigned long long)(nks - ks0) * TPS * U);
+        constexpr unsigned long long U = (unsigned long long)NP * BM;
+        const unsigned long long run = (unsigned long long)done * TPS * U, all = (unsigned long long)nks * TPS * U;
+        // a 64-row block's half units: the two blocks of a 128-row pair run
+        // the same stages, so the upper one counts for both
+        if (BM >= 128) {
+            atomicAdd(&g.ktiles[0], run / 128);
+            if (part == 0) atomicAdd(&g.ktiles[1], all / 128);
+        } else if ((w0 & 64) == 0) {
+            atomicAdd(&g.ktiles[0], run / 64);
+            atomicAdd(&g.ktiles[1], all / 64);
+        }
     }
     if constexpr (I8) {
         // whole vectors: a bit cast of one vector element reads element 0
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
+        for (int rt = 0; rt < R; ++rt)
 #pragma unroll
             for (int c = 0; c < (KH ? 4 : 2); ++c)
                 acc[rt][c] = __builtin_convertvector(__builtin_bit_cast(i32x16, acc[rt][c]), f32x16);
     }
 }
 
-// The two halves of a split tile meet here after their products for limb k.
-// Each stores its partial sums (agent-scope stores, coherent across XCDs) to
-// its own slot for limb k; the second to arrive adds the other's and returns
-// true, the first returns false.  One slot per limb: a half never waits, so
-// it may be several limbs ahead of the other.
+// The parts of a split tile meet here after their products for limb k.  Each
+// stores its partial sums (agent-scope stores, coherent across XCDs) to its
+// own slot for limb k; the last to arrive adds them up, in the parts' order
+// whichever came last, and returns true, the others return false.  One slot
+// per limb: a part never waits, so it may be several limbs ahead of another.
 template <int T>
-__device__ __forceinline__ bool split_meet(const GemmArgs &g, int k, int tile, int half, int tid, int &s_last,
+__device__ __forceinline__ bool split_meet(const GemmArgs &g, int k, int tile, int part, int tid, int &s_last,
                                            f32x16 (&acc)[RT][2]) {
     constexpr int V = RT * 2 * 16; // sums per thread
-    float *slot = g.ws + (((size_t)k * g.ntiles + tile) * 2) * V * T;
+    float *slot = g.ws + ((size_t)k * g.ntiles + tile) * g.ksplit * V * T;
 #pragma unroll
     for (int i = 0; i < RT * 2; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            __hip_atomic_store(&slot[((size_t)half * V + i * 16 + r) * T + tid], acc[i / 2][i % 2][r],
+            __hip_atomic_store(&slot[((size_t)part * V + i * 16 + r) * T + tid], acc[i / 2][i % 2][r],
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __asm__ __volatile__("s_waitcnt vmcnt(0)" ::: "memory"); // this thread's stores are done
     __syncthreads();
     if (tid == 0) {
         uint32_t *cnt = &g.arrive[(size_t)k * g.ntiles + tile];
-        s_last = atomicAdd(cnt, 1u) == 1u;
+        s_last = atomicAdd(cnt, 1u) == (uint32_t)g.ksplit - 1;
         if (s_last) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
@@ -501,9 +516,16 @@ __device__ __forceinline__ bool split_meet(const GemmArgs &g, int k, int tile, i
 #pragma unroll
     for (int i = 0; i < RT * 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            acc[i / 2][i % 2][r] += __hip_atomic_load(&slot[((size_t)(1 - half) * V + i * 16 + r) * T + tid],
-                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int r = 0; r < 16; ++r) acc[i / 2][i % 2][r] = 0.f;
+    for (int p = 0; p < g.ksplit; ++p) {
+        const float *from = slot + (size_t)p * V * T + tid;
+#pragma unroll
+        for (int i = 0; i < RT * 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[i / 2][i % 2][r] += __hip_atomic_load(&from[(size_t)(i * 16 + r) * T], __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT);
+    }
     return true;
 }
 
@@ -626,18 +648,14 @@ __global__ __launch_bounds__(2 * BM, BM == 128 ? 2 : 1) void k_mfma_fwd(GemmArgs
     __shared__ __align__(16) unsigned char smem[PLANE_BYTES > XCHG_BYTES ? PLANE_BYTES : XCHG_BYTES];
     auto sX = reinterpret_cast<__bf16 (*)[lds_x<1, KS, KC>()]>(smem);
     __shared__ int s_last;
-    int half = 0, tile = 0;
-    const Tile tl = g.ksplit == 2 ? tile_of_split(g.B, half, tile) : tile_of(g.B);
+    int part = 0, tile = 0;
+    const Tile tl = g.ksplit > 1 ? tile_of_split(g.B, g.ksplit, part, tile) : tile_of(g.B);
     if (tl.row >= g.npad / BM || (e.reach && e.reach[2] != 0)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int w0 = tl.row * BM + (wv >> 1) * WM, b0 = tl.col * GN;
     const int q = (b0 >> 6) + (wv & 1); // bitmap word of this wave's sources
     const int L = limbs_feeding(e.lvmax_cur, e.level, e.classes);
     if (blockIdx.x == 0 && tid == 0) atomicAdd(e.planes_issued, (unsigned long long)L);
-    // split K at a stage boundary (K is a multiple of 256, the stages' depth)
-    constexpr int TPS = KS / GK;
-    const int nst = g.K / KS, hst = nst / 2;
-    const int kt0 = g.ksplit == 2 && half ? hst * TPS : 0, kt1 = g.ksplit == 2 && !half ? hst * TPS : nst * TPS;
     f32x16 acc[RT][2];
 #pragma nounroll
     for (int k = 0; k < L; ++k) {
@@ -645,7 +663,7 @@ __global__ __launch_bounds__(2 * BM, BM == 128 ? 2 : 1) void k_mfma_fwd(GemmArgs
         const __bf16 *planes_k = g.planes + (size_t)k * (g.plane_elems / 2);
         if constexpr (KH) {
             f32x16 acc4[RT][4];
-            gemm_tile<1, KS, BM, true, true>(g, planes_k, tl.row * BM, b0, tid, sX, acc4, kt0, kt1);
+            gemm_tile<1, KS, BM, true, true>(g, planes_k, tl.row * BM, b0, tid, sX, acc4, part);
             // wave wv keeps sources 64 h .. 64 h + 63 (h = wv & 1, its bitmap
             // word) and hands the other 64 to its partner wv ^ 1; the tile
             // loop ended at a barrier, so the plane buffers are free
@@ -688,10 +706,9 @@ __global__ __launch_bounds__(2 * BM, BM == 128 ? 2 : 1) void k_mfma_fwd(GemmArgs
                             acc[rt][c][r] = acc4[rt][c][r] + theirs[((rt * 2 + c) * 16 + r) * 64];
             }
         } else {
-            gemm_tile<1, KS, BM, false, true>(g, planes_k, tl.row * BM, b0, tid, sX, acc, kt0, kt1);
+            gemm_tile<1, KS, BM, false, true>(g, planes_k, tl.row * BM, b0, tid, sX, acc, part);
         }
-        if (g.ksplit == 2 && !split_meet<2 * BM>(g, k, tile, half, tid, s_last, acc))
-            continue; // the other half finishes it
+        if (g.ksplit > 1 && !split_meet<2 * BM>(g, k, tile, part, tid, s_last, acc)) continue; // another part finishes it
         const int mode = L == 1 ? EPI_ONLY : k == 0 ? EPI_FIRST : k + 1 < L ? EPI_MID : EPI_LAST;
         // The epilogue's row addresses do not depend on k; an opaque copy of
         // the block's first row keeps the compiler from computing all of them
@@ -706,40 +723,41 @@ __global__ __launch_bounds__(2 * BM, BM == 128 ? 2 : 1) void k_mfma_fwd(GemmArgs
 // Backward level l: acc = A . (hi + mid + lo planes of C_{l+1}), then
 // delta(v,b) = lambda(v,b) * acc for v at level l, c(v,b) = (1 + delta) / lambda,
 // and BC(v) += delta summed over the block's sources (v != s_b).
-template <typename S>
-__global__ __launch_bounds__(2 * BWD_BM, BWD_BM == 128 ? 2 : 1) void k_mfma_bwd(GemmArgs g, EpiArgs e) {
-    __shared__ __align__(16) __bf16 sX[stages<3, BWD_KS, BWD_BM>()][lds_x<3, BWD_KS>()];
-    // one block per tile: its stages of three planes are long enough already
-    // (split in two halves of K it measured slower)
+template <typename S, int R>
+__global__ __launch_bounds__(256, R == 2 ? 2 : 3) void k_mfma_bwd(GemmArgs g, EpiArgs e) {
+    constexpr int BM = 64 * R; // four waves of 32 R x 64
+    __shared__ __align__(16) __bf16 sX[1][lds_x<3, BWD_KS>()];
+    // one block per tile, whole K: the order of the FP32 sums is part of the
+    // result
     if (g.gate && *g.gate == 0) return; // level l is empty (or the batch was handed back)
     const Tile tl = tile_of(g.B);
-    if (tl.row >= g.npad / BWD_BM) return;
+    if (tl.row >= g.npad / BM) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b0 = tl.col * GN;
-    f32x16 acc[RT][2];
+    f32x16 acc[R][2];
     if (g.gate && g.gate[1] == 0) {
         // the deepest level of a replayed batch: no successor, so delta = 0
         // and c = 1 / lambda, without products (their flag scan alone would
         // cost a dependent load per stage)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
+        for (int rt = 0; rt < R; ++rt)
 #pragma unroll
             for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[rt][ct][r] = 0.f;
     } else {
         if (blockIdx.x == 0 && tid == 0) atomicAdd(e.planes_issued, 3ull);
-        gemm_tile<3, BWD_KS, BWD_BM>(g, g.planes, tl.row * BWD_BM, b0, tid, sX, acc);
+        gemm_tile<3, BWD_KS, BM, false, false, R>(g, g.planes, tl.row * BM, b0, tid, sX, acc);
     }
 
-    const int w0 = tl.row * BWD_BM + (wv >> 1) * WM;
+    const int w0 = tl.row * BM + (wv >> 1) * (32 * R);
     const int q = (b0 >> 6) + (wv & 1);
     const int half = lane >> 5, col = lane & 31;
     S *sigma = reinterpret_cast<S *>(e.sigma);
-    // level-l words of the wave's 64 rows, one load per lane (as in the forward)
-    const uint64_t f_lane = w0 + lane < g.n ? e.fcur[(size_t)(w0 + lane) * g.NW + q] : 0;
+    // level-l words of the wave's rows, one load per lane (as in the forward)
+    const uint64_t f_lane = lane < 32 * R && w0 + lane < g.n ? e.fcur[(size_t)(w0 + lane) * g.NW + q] : 0;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
+    for (int rt = 0; rt < R; ++rt) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int lr = rt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
@@ -905,8 +923,8 @@ GemmArgs gemm_args(bc_ctx *ctx, const __bf16 *planes, bool forward) {
     g.NW = ctx->sp.words;
     g.K = a.classes * a.npad;
     g.plane_elems = (size_t)g.K * ctx->sp.batch;
-    g.ksplit = a.ksplit;
-    g.ntiles = (int32_t)(!forward           ? grid_blocks<BWD_BM>(a.npad, ctx->sp.batch)
+    g.ksplit = forward ? a.ksplit : 1;
+    g.ntiles = (int32_t)(!forward           ? grid_blocks<128>(a.npad, ctx->sp.batch)
                          : a.fwd_rows == 256 ? grid_blocks<256>(a.npad, ctx->sp.batch)
                                              : grid_blocks<128>(a.npad, ctx->sp.batch));
     g.ws = a.ws;
@@ -942,28 +960,36 @@ bc_status algebraic_prepare(bc_ctx *ctx) {
     a.part = (uint64_t *)bc_dalloc(ctx, (size_t)a.npad * B * sizeof(uint64_t));
     a.kflags = (uint32_t *)bc_dalloc(ctx, (K / GK) * (B / GN) * sizeof(uint32_t));
     a.planes_issued = (unsigned long long *)bc_dalloc(ctx, 256);
-    // Unweighted forward products over a long K (one npad per limb) with
-    // fewer tiles than the compute units hold blocks at once (256 units, LDS
-    // for 256 / BM blocks each): two blocks per output tile, each over half
-    // of K, so that the grid fills the chip.  With a full chip of tiles the
-    // split measured slower (ER-16384, B = 512: 124 against 116 ms per step),
-    // and with weight classes too (K is M npad; 0.43 of BF16 against 0.50).
-    // The decision is the same for 128- and 256-row blocks (tiles halve as
-    // the blocks per unit do); the workspace takes the larger of the two
-    // (grids are rounded up to whole rounds of the eight XCDs).
     a.fwd_rows = 128;
+    // Forward products with fewer tiles than the compute units hold blocks at
+    // once (256 units, two blocks each): two blocks per tile, each over every
+    // second stage (the sums are exact integers, so any split gives the same).
+    // Up to 256 tiles and from K = 4096 they gain 1 to 4% of a run over all
+    // sources (G(5003, 128/5002), weights 1..4, batch 512: 13.5 -> 13.2 ms;
+    // G(12000, 150/11999), batch 256: 46.5 -> 44.8); with 376 tiles they lose 5%,
+    // below K = 4096 1%.  The decision is the same for 128- and 256-row blocks
+    // (tiles halve as the blocks per unit do); the workspace takes the larger
+    // of the two (grids are rounded up to whole rounds of the eight XCDs).
     const size_t ntiles = grid_blocks<128>(a.npad, B), ntiles256 = grid_blocks<256>(a.npad, B);
-    const size_t ws_elems = std::max(ntiles * 2 * (RT * 2 * 16) * (2 * 128), ntiles256 * 2 * (RT * 2 * 16) * (2 * 256));
-    const size_t ntiles_max = std::max(ntiles, ntiles256);
-    a.ksplit = a.classes == 1 && K / GK >= 256 && ntiles < (size_t)256 * (256 / 128) ? 2 : 1;
-    if (a.ksplit == 2) {
-        a.ws = (float *)bc_dalloc(ctx, (size_t)8 * ws_elems * sizeof(float));
-        a.arrive = (uint32_t *)bc_dalloc(ctx, (size_t)8 * ntiles_max * sizeof(uint32_t));
+    a.ksplit = (size_t)(a.npad / 128) * (B / GN) <= 256 && K >= 4096 ? 2 : 1;
+    // Backward blocks of 64 rows up to 256 tiles of 128 x 128: twice the blocks
+    // where a unit would hold one, the same sums in the same order.  All
+    // sources, ms with 128 / 64 rows, batch 512: G(5003, 128/5002) weights 1..4
+    // 13.2 / 12.0, G(5003, 50/5002) 5.8 / 5.0, G(8000, 80/7999) (256 tiles) 12.5 /
+    // 11.1, G(12000, 150/11999) (376) 30.4 / 30.9; batch 256: 25.2 / 20.1, 11.0 /
+    // 8.7 and 23.2 / 18.4 for the first three.
+    a.bwd_rows = (size_t)(a.npad / 128) * (B / GN) <= 256 ? 64 : 128;
+    const size_t per_tile = (size_t)(RT * 2 * 16) * sizeof(float); // one thread's sums
+    const size_t ws = a.ksplit > 1 ? (size_t)10 * a.ksplit * per_tile * std::max(ntiles * 256, ntiles256 * 512) : 0;
+    const size_t narrive = (size_t)10 * std::max(ntiles, ntiles256);
+    if (ws > 0) {
+        a.ws = (float *)bc_dalloc(ctx, ws);
+        a.arrive = (uint32_t *)bc_dalloc(ctx, narrive * sizeof(uint32_t));
     }
     if (!a.abits || !a.abits8 || !a.planes || !a.part || !a.kflags || !a.planes_issued ||
-        (a.ksplit == 2 && (!a.ws || !a.arrive)))
+        (ws > 0 && (!a.ws || !a.arrive)))
         return bc_fail(ctx, BC_ERR_NOMEM, "algebraic form: allocation failed");
-    if (a.ksplit == 2) BC_HIP(ctx, hipMemsetAsync(a.arrive, 0, (size_t)8 * ntiles_max * sizeof(uint32_t), ctx->stream));
+    if (ws > 0) BC_HIP(ctx, hipMemsetAsync(a.arrive, 0, narrive * sizeof(uint32_t), ctx->stream));
     BC_HIP(ctx, hipMemsetAsync(a.abits, 0, adj_bytes, ctx->stream));
     BC_HIP(ctx, hipMemsetAsync(a.abits8, 0, adj_bytes, ctx->stream));
     BC_HIP(ctx, hipMemsetAsync(a.planes_issued, 0, 5 * sizeof(unsigned long long), ctx->stream));
@@ -1066,8 +1092,10 @@ bc_status algebraic_backward_level_t(bc_ctx *ctx, const uint64_t *fcur, const ui
     GemmArgs g = gemm_args(ctx, a.planes, false);
     g.gate = gate;
     LaunchTimer tm(ctx, "mfma_bwd");
-    hipLaunchKernelGGL(k_mfma_bwd<S>, dim3(grid_blocks<BWD_BM>(a.npad, s.batch)), dim3(2 * BWD_BM), 0, ctx->stream,
-                       g, e);
+    if (a.bwd_rows == 64)
+        hipLaunchKernelGGL((k_mfma_bwd<S, 1>), dim3(grid_blocks<64>(a.npad, s.batch)), dim3(256), 0, ctx->stream, g, e);
+    else
+        hipLaunchKernelGGL((k_mfma_bwd<S, 2>), dim3(grid_blocks<128>(a.npad, s.batch)), dim3(256), 0, ctx->stream, g, e);
     tm.done();
     BC_HIP(ctx, hipGetLastError());
     return BC_OK;

@@ -95,8 +95,9 @@ struct AlgebraicState {
     unsigned long long *planes_issued = nullptr; // products issued (limb or coefficient planes)
     int32_t ksplit = 1;                // forward products: blocks per output tile, each over a share of K
     int32_t fwd_rows = 128;            // forward products: rows per block, 128 or 256 (tuned)
-    float *ws = nullptr;               // [8 limbs][tiles][2 halves][64][256] partial sums of split tiles
-    uint32_t *arrive = nullptr;        // [8 limbs][tiles] halves arrived
+    int32_t bwd_rows = 128;            // backward products: rows per block, 128 or 64
+    float *ws = nullptr;               // [10 limbs][tiles][parts][64][threads] partial sums of split tiles
+    uint32_t *arrive = nullptr;        // [10 limbs][tiles] parts arrived
     bool every_level = false;          // the algebraic form: every level l >= 1 by products
 };
 
