@@ -174,7 +174,7 @@ constexpr int FWD_KS = 256;
 constexpr int FWD_KC = 16;
 constexpr int BWD_KS = 64;
 // Forward block rows: 128 or 256, whichever the tuner measured faster on the
-// graph (AlgebraicState::fwd_rows); the backward takes 128.
+// graph (AlgebraicState::fwd_rows); the backward takes 128
 // or, where those leave compute units idle, 64 (AlgebraicState::bwd_rows).
 
 // A stage's plane tile held in registers between its global loads and its LDS
@@ -937,30 +937,17 @@ GemmArgs gemm_args(bc_ctx *ctx, const __bf16 *planes, bool forward) {
 
 } // namespace
 
-bc_status algebraic_prepare(bc_ctx *ctx) {
+// The buffers a batch in flight writes, and the launch shapes.
+static bc_status algebraic_scratch(bc_ctx *ctx) {
     AlgebraicState &a = ctx->al;
     const int32_t B = ctx->sp.batch;
-    if (ctx->weighted && ctx->max_weight > BC_ALGEBRAIC_MAX_WEIGHT)
-        return bc_fail(ctx, BC_ERR_UNSUPPORTED, "algebraic form: weights above 8 (one product class per weight)");
-    if (B % GN != 0) return bc_fail(ctx, BC_ERR_UNSUPPORTED, "algebraic form: batch must be 256 or 512");
-    if (ctx->max_degree > BC_ALGEBRAIC_MAX_DEGREE)
-        return bc_fail(ctx, BC_ERR_UNSUPPORTED,
-                       "algebraic form: degrees above 65792 are not taken (exact FP32 copies of the products' sums)");
-    a.npad = std::max(NPAD, (ctx->n + NPAD - 1) / NPAD * NPAD);
-    a.classes = ctx->weighted ? (int32_t)ctx->max_weight : 1;
     const size_t K = (size_t)a.classes * a.npad;
-    const size_t adj_bytes = (size_t)a.npad * K / 8;
     const size_t plane_elems = K * B;
-    if (2 * adj_bytes + 8 * plane_elems * sizeof(__bf16) > (size_t(96) << 30))
-        return bc_fail(ctx, BC_ERR_UNSUPPORTED, "algebraic form: the adjacency bits and planes would exceed 96 GiB");
-    a.abits = (uint32_t *)bc_dalloc(ctx, adj_bytes);
-    a.abits8 = (uint32_t *)bc_dalloc(ctx, adj_bytes);
     // up to ten int8 limb planes (10 plane_elems bytes), or 3 BF16 coefficient planes
     a.planes = (__bf16 *)bc_dalloc(ctx, 8 * plane_elems * sizeof(__bf16));
     a.part = (uint64_t *)bc_dalloc(ctx, (size_t)a.npad * B * sizeof(uint64_t));
     a.kflags = (uint32_t *)bc_dalloc(ctx, (K / GK) * (B / GN) * sizeof(uint32_t));
     a.planes_issued = (unsigned long long *)bc_dalloc(ctx, 256);
-    a.fwd_rows = 128;
     // Forward products with fewer tiles than the compute units hold blocks at
     // once (256 units, two blocks each): two blocks per tile, each over every
     // second stage (the sums are exact integers, so any split gives the same).
@@ -986,13 +973,47 @@ bc_status algebraic_prepare(bc_ctx *ctx) {
         a.ws = (float *)bc_dalloc(ctx, ws);
         a.arrive = (uint32_t *)bc_dalloc(ctx, narrive * sizeof(uint32_t));
     }
-    if (!a.abits || !a.abits8 || !a.planes || !a.part || !a.kflags || !a.planes_issued ||
-        (ws > 0 && (!a.ws || !a.arrive)))
+    if (!a.planes || !a.part || !a.kflags || !a.planes_issued || (ws > 0 && (!a.ws || !a.arrive)))
         return bc_fail(ctx, BC_ERR_NOMEM, "algebraic form: allocation failed");
     if (ws > 0) BC_HIP(ctx, hipMemsetAsync(a.arrive, 0, narrive * sizeof(uint32_t), ctx->stream));
+    BC_HIP(ctx, hipMemsetAsync(a.planes_issued, 0, 5 * sizeof(unsigned long long), ctx->stream));
+    return BC_OK;
+}
+
+bc_status algebraic_share(bc_ctx *ctx, const bc_ctx *from) {
+    AlgebraicState &a = ctx->al;
+    const AlgebraicState &f = from->al;
+    a.npad = f.npad;
+    a.classes = f.classes;
+    a.abits = f.abits;
+    a.abits8 = f.abits8;
+    return algebraic_scratch(ctx);
+}
+
+bc_status algebraic_prepare(bc_ctx *ctx) {
+    AlgebraicState &a = ctx->al;
+    const int32_t B = ctx->sp.batch;
+    if (ctx->weighted && ctx->max_weight > BC_ALGEBRAIC_MAX_WEIGHT)
+        return bc_fail(ctx, BC_ERR_UNSUPPORTED, "algebraic form: weights above 8 (one product class per weight)");
+    if (B % GN != 0) return bc_fail(ctx, BC_ERR_UNSUPPORTED, "algebraic form: batch must be 256 or 512");
+    if (ctx->max_degree > BC_ALGEBRAIC_MAX_DEGREE)
+        return bc_fail(ctx, BC_ERR_UNSUPPORTED,
+                       "algebraic form: degrees above 65792 are not taken (exact FP32 copies of the products' sums)");
+    a.npad = std::max(NPAD, (ctx->n + NPAD - 1) / NPAD * NPAD);
+    a.classes = ctx->weighted ? (int32_t)ctx->max_weight : 1;
+    const size_t K = (size_t)a.classes * a.npad;
+    const size_t adj_bytes = (size_t)a.npad * K / 8;
+    const size_t plane_elems = K * B;
+    if (2 * adj_bytes + 8 * plane_elems * sizeof(__bf16) > (size_t(96) << 30))
+        return bc_fail(ctx, BC_ERR_UNSUPPORTED, "algebraic form: the adjacency bits and planes would exceed 96 GiB");
+    a.abits = (uint32_t *)bc_dalloc(ctx, adj_bytes);
+    a.abits8 = (uint32_t *)bc_dalloc(ctx, adj_bytes);
+    if (!a.abits || !a.abits8) return bc_fail(ctx, BC_ERR_NOMEM, "algebraic form: allocation failed");
+    a.fwd_rows = 128;
+    bc_status st = algebraic_scratch(ctx);
+    if (st != BC_OK) return st;
     BC_HIP(ctx, hipMemsetAsync(a.abits, 0, adj_bytes, ctx->stream));
     BC_HIP(ctx, hipMemsetAsync(a.abits8, 0, adj_bytes, ctx->stream));
-    BC_HIP(ctx, hipMemsetAsync(a.planes_issued, 0, 5 * sizeof(unsigned long long), ctx->stream));
     if (ctx->n > 0)
         hipLaunchKernelGGL(k_build_adj, dim3(ctx->n), dim3(PB), 0, ctx->stream, ctx->n, a.npad,
                            ctx->row_ptr, ctx->col, ctx->weighted ? (const uint8_t *)ctx->weight : nullptr, a.abits,

@@ -103,6 +103,7 @@ void release_all(bc_ctx *ctx) {
     ctx->mg.exec = nullptr;
     ctx->mg.ev = nullptr;
     ctx->mg.stream = nullptr;
+    lanes_release(ctx);
     sparse_graphs_release(ctx);
     bc_timers_clear(ctx);
     for (hipEvent_t e : ctx->event_pool) hipEventDestroy(e);
@@ -662,8 +663,13 @@ extern "C" {
 
 static bc_status check_overflow(bc_ctx *ctx) {
     BC_HIP(ctx, hipMemcpyAsync(ctx->status_host, ctx->status, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
+    for (size_t i = 0; i < ctx->lanes.size(); ++i)
+        BC_HIP(ctx, hipMemcpyAsync(ctx->status_host + 2 + i, ctx->lanes[i]->status, sizeof(uint32_t),
+                                   hipMemcpyDeviceToHost, ctx->stream));
     BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    if (*ctx->status_host & BC_DEV_SIGMA_OVERFLOW) {
+    uint32_t bits = *ctx->status_host;
+    for (size_t i = 0; i < ctx->lanes.size(); ++i) bits |= ctx->status_host[2 + i];
+    if (bits & BC_DEV_SIGMA_OVERFLOW) {
         ctx->overflow_seen = true;
         return bc_fail(ctx, BC_ERR_OVERFLOW, "a shortest-path count exceeded 2^64 - 1");
     }
@@ -735,6 +741,10 @@ bc_status bc_reset(bc_ctx *ctx) {
     BC_HIP(ctx, hipMemsetAsync(ctx->bc, 0, sizeof(double) * (size_t)std::max(ctx->n, 1), ctx->stream));
     if (ctx->eb) BC_HIP(ctx, hipMemsetAsync(ctx->eb, 0, sizeof(double) * (size_t)std::max(ctx->nnz, 1), ctx->stream));
     BC_HIP(ctx, hipMemsetAsync(ctx->status, 0, 256, ctx->stream));
+    for (bc_ctx *t : ctx->lanes) {
+        BC_HIP(ctx, hipMemsetAsync(t->status, 0, 256, ctx->stream));
+        algebraic_reset_counters(t);
+    }
     BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     bc_timers_clear(ctx);
     algebraic_reset_counters(ctx);
@@ -893,6 +903,16 @@ bc_status bc_get_info(const bc_ctx *ctx, bc_info *out) {
     if (!ctx->poisoned && !algebraic_ktiles(const_cast<bc_ctx *>(ctx), &out->mfma_ktiles_run, &out->mfma_ktiles_dense,
                                             &out->mfma_ktiles_run_fwd, &out->mfma_ktiles_dense_fwd))
         out->mfma_ktiles_run = out->mfma_ktiles_dense = out->mfma_ktiles_run_fwd = out->mfma_ktiles_dense_fwd = -1;
+    for (bc_ctx *t : ctx->lanes) {
+        out->device_bytes += t->device_bytes;
+        int64_t run = 0, dense = 0, run_fwd = 0, dense_fwd = 0;
+        if (ctx->poisoned || !algebraic_ktiles(t, &run, &dense, &run_fwd, &dense_fwd)) continue;
+        out->mfma_planes += algebraic_planes_issued(t);
+        out->mfma_ktiles_run += run;
+        out->mfma_ktiles_dense += dense;
+        out->mfma_ktiles_run_fwd += run_fwd;
+        out->mfma_ktiles_dense_fwd += dense_fwd;
+    }
     return BC_OK;
 }
 

@@ -250,6 +250,15 @@ struct bc_ctx {
     HybridState hy;
     bool many = false;
 
+    // Batches in flight at once (sparse.hip): the lanes beside this context's
+    // own state.  A lane is a context with its own batch state on the same
+    // graph, BC and stream; only its recorded batches run on its own stream,
+    // between the fork and the join of a run.
+    std::vector<bc_ctx *> lanes;
+    std::vector<hipStream_t> lane_streams;
+    std::vector<hipEvent_t> lane_events; // the fork, then each lane's join
+    bool lanes_refused = false;          // their memory was not to be had
+
     // bookkeeping
     int64_t sources_run = 0;
     int32_t max_levels = 0;
@@ -375,6 +384,8 @@ bc_status algebraic_forward_level(bc_ctx *ctx, bool wide, int32_t l);
 bc_status algebraic_backward_level(bc_ctx *ctx, bool wide, const uint64_t *fcur, const uint64_t *fnext,
                                    int32_t deeper, double *delta_dump, bool accumulate,
                                    const uint32_t *gate = nullptr);
+// A lane's products: `from`'s adjacency bits, buffers of its own.
+bc_status algebraic_share(bc_ctx *ctx, const bc_ctx *from);
 int64_t algebraic_planes_issued(bc_ctx *ctx); // synchronises; -1 on a device error
 // k-tiles the products multiplied and those a dense product would have;
 // synchronises; false on a device error
@@ -390,6 +401,7 @@ bc_status sparse_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count);
 // back (on the host-driven path); synchronises.  A no-op when nothing is
 // pending.  Every entry point calls it before touching the context's state.
 bc_status sparse_settle(bc_ctx *ctx);
+void lanes_release(bc_ctx *ctx); // synchronises
 // Destroys the recorded batch graphs and their capture stream; synchronises.
 void sparse_graphs_release(bc_ctx *ctx);
 // delta_dump = nullptr runs the forward only (distances and counts).

@@ -33,6 +33,8 @@
 #include "bc_internal.h"
 
 #include <algorithm>
+#include <cstring>
+#include <new>
 #include <type_traits>
 
 namespace {
@@ -1484,6 +1486,204 @@ bc_status sparse_release(bc_ctx *ctx) {
     return BC_OK;
 }
 
+namespace {
+
+// ---- batches in flight at once --------------------------------------------------
+//
+// A batch is a chain of some twenty launches, each waiting for the one before:
+// a short level leaves most of the chip idle, and every launch has a head and
+// a tail.  A run of several batches is therefore dealt to lanes, each with its
+// own batch state and its own stream, that replay their share at the same
+// time; BC and the edge terms are sums by atomics either way.
+
+constexpr int MAX_LANES = 3;
+
+// Lanes for a run of nb replayed batches.  Three while what they write stays
+// in the memory-side cache (256 MB), else two.  All sources, ms with 1 / 2 / 3
+// lanes: RMAT-13 with edge terms, batch 256, 10.2 / 6.7 / 5.5; RMAT-14 23.1 / 16.1
+// / 14.1, batch 512 19.1 / 14.2 / 12.9; RMAT-16 (108 MB a lane) 199 / 164 / 165;
+// G(5003, 50/5002) by products, batch 512, 4.5 / 3.3 / 3.2; G(16384, 256/16383)
+// (117 MB) 52.6 / 51.0 / 53.8.  Setting a lane up costs about a millisecond
+// once, so a first run of fewer than four batches goes without.  Kernel timing
+// counts launches of one chain; weighted batches are driven from the host.
+int lanes_for(const bc_ctx *ctx, int64_t nb) {
+    if (ctx->timing || ctx->weighted || ctx->host_driven || ctx->lanes_refused) return 1;
+    if (nb < (ctx->lanes.empty() ? 4 : 2)) return 1;
+    const size_t cells = (size_t)ctx->n * ctx->sp.batch;
+    if (cells * 12 > size_t(8) << 30) return 1; // its memory
+    const size_t written = cells * 8 + cells / 8 * 8 + (ctx->al.planes ? cells * 6 : 0);
+    return (int)std::min<int64_t>(nb, 3 * written <= size_t(256) << 20 ? 3 : 2);
+}
+
+void lane_failed(bc_ctx *ctx, const bc_ctx *lane) {
+    ctx->err = lane->err;
+    ctx->poisoned = ctx->poisoned || lane->poisoned;
+}
+
+void lane_free(bc_ctx *t) {
+    sparse_graphs_release(t);
+    auto owned = t->owned;
+    for (auto &pr : owned) bc_dfree(t, pr.first);
+    if (t->sp.any_host) hipHostFree(t->sp.any_host);
+    if (t->status_host) hipHostFree(t->status_host);
+    delete t;
+}
+
+bc_status lane_prepare(bc_ctx *t, const bc_ctx *ctx) {
+    t->n = ctx->n;
+    t->nnz = ctx->nnz;
+    t->max_degree = ctx->max_degree;
+    t->h_row_ptr = ctx->h_row_ptr;
+    t->device = ctx->device;
+    t->stream = ctx->stream;
+    t->alloc = ctx->alloc;
+    t->row_ptr = ctx->row_ptr;
+    t->col = ctx->col;
+    t->comp_size = ctx->comp_size;
+    t->bc = ctx->bc;
+    t->eb = ctx->eb;
+    t->edges = ctx->edges;
+    t->form = ctx->form;
+    t->status = (uint32_t *)bc_dalloc(t, 256);
+    if (!t->status || hipHostMalloc((void **)&t->status_host, 256) != hipSuccess)
+        return bc_fail(t, BC_ERR_NOMEM, "batch lane: allocation failed");
+    BC_HIP(t, hipMemsetAsync(t->status, 0, 256, t->stream));
+    bc_status st = sparse_prepare(t, ctx->sp.batch, ctx->sp.split);
+    if (st == BC_OK && ctx->al.planes) st = algebraic_share(t, ctx);
+    return st;
+}
+
+// `lanes` lanes, this context's state being the first; false (and none kept
+// from this call) when their memory or streams cannot be had.
+bool ensure_lanes(bc_ctx *ctx, int lanes) {
+    if (ctx->lane_events.empty()) {
+        hipEvent_t e = nullptr;
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return false;
+        ctx->lane_events.push_back(e);
+    }
+    while ((int)ctx->lanes.size() < lanes - 1) {
+        bc_ctx *t = new (std::nothrow) bc_ctx();
+        if (!t) return false;
+        hipStream_t q = nullptr;
+        hipEvent_t e = nullptr;
+        if (lane_prepare(t, ctx) != BC_OK || hipStreamCreateWithFlags(&q, hipStreamNonBlocking) != hipSuccess ||
+            hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+            if (q) hipStreamDestroy(q);
+            if (t->poisoned) lane_failed(ctx, t);
+            lane_free(t);
+            return false;
+        }
+        ctx->lanes.push_back(t);
+        ctx->lane_streams.push_back(q);
+        ctx->lane_events.push_back(e);
+    }
+    return true;
+}
+
+// The recorded batch is ready and the device holds the run's control block.
+bc_status start_replays(bc_ctx *ctx, const int32_t *d_src, int64_t count, hipStream_t stream) {
+    SparseState &s = ctx->sp;
+    const int64_t nb = (count + s.batch - 1) / s.batch;
+    if (nb > s.redo_cap) {
+        int32_t *r = (int32_t *)bc_dalloc(ctx, (size_t)nb * sizeof(int32_t));
+        if (!r) return bc_fail(ctx, BC_ERR_NOMEM, "sparse form: allocation of the handed-back list failed");
+        bc_dfree(ctx, s.redo);
+        s.redo = r;
+        s.redo_cap = nb;
+    }
+    bc_status st = ensure_replay(ctx);
+    if (st != BC_OK) return st;
+    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(64), 0, stream, s.ctl, d_src, (int32_t)count, s.redo);
+    BC_HIP(ctx, hipGetLastError());
+    s.g_pending = true; // from here on the device holds checks the host must read
+    return BC_OK;
+}
+
+// The run's batches over the lanes: each takes a contiguous share.
+bc_status run_lanes(bc_ctx *ctx, int lanes, const int32_t *d_src, int64_t count) {
+    const int64_t B = ctx->sp.batch, nb = (count + B - 1) / B;
+    if (!ensure_lanes(ctx, lanes)) {
+        if (ctx->poisoned) return BC_ERR_DEVICE;
+        ctx->lanes_refused = ctx->lanes.empty();
+        lanes = 1 + (int)ctx->lanes.size();
+    }
+    std::vector<bc_ctx *> all{ctx};
+    all.insert(all.end(), ctx->lanes.begin(), ctx->lanes.begin() + (lanes - 1));
+    std::vector<int64_t> first((size_t)lanes + 1);
+    for (int i = 0; i <= lanes; ++i) first[(size_t)i] = nb * i / lanes;
+    auto stream = [&](int i) { return i == 0 ? ctx->stream : ctx->lane_streams[(size_t)i - 1]; };
+    // What a lane needs is allocated and recorded before the fork, in the order
+    // of the context's own stream.
+    for (int i = 1; i < lanes; ++i) {
+        bc_ctx *t = all[(size_t)i];
+        t->sp.depth_max = ctx->sp.depth_max;
+        t->sp.depth_guess = ctx->sp.depth_guess;
+        t->sp.wide = ctx->sp.wide;
+        t->hy.products = ctx->hy.products;
+        t->hy.theta_fwd = ctx->hy.theta_fwd;
+        t->hy.theta_bwd = ctx->hy.theta_bwd;
+        t->hy.prev_density = ctx->hy.prev_density;
+        t->al.every_level = ctx->al.every_level;
+        t->al.fwd_rows = ctx->al.fwd_rows;
+    }
+    for (int i = 0; i < lanes; ++i) {
+        const int64_t b = first[(size_t)i] * B, e = std::min(first[(size_t)i + 1] * B, count);
+        const bc_status st = start_replays(all[(size_t)i], d_src + b, e - b, ctx->stream);
+        if (st != BC_OK) {
+            if (i > 0) lane_failed(ctx, all[(size_t)i]);
+            return st;
+        }
+    }
+    BC_HIP(ctx, hipEventRecord(ctx->lane_events[0], ctx->stream));
+    for (int i = 1; i < lanes; ++i) BC_HIP(ctx, hipStreamWaitEvent(stream(i), ctx->lane_events[0], 0));
+    hipError_t e = hipSuccess;
+    for (int64_t k = 0; k < (nb + lanes - 1) / lanes + 1 && e == hipSuccess; ++k)
+        for (int i = 0; i < lanes && e == hipSuccess; ++i)
+            if (first[(size_t)i] + k < first[(size_t)i + 1]) e = hipGraphLaunch(all[(size_t)i]->sp.gexec, stream(i));
+    // join, whatever happened: nothing of a lane outlives the call unordered
+    for (int i = 1; i < lanes; ++i) {
+        hipError_t j = hipEventRecord(ctx->lane_events[(size_t)i], stream(i));
+        if (j == hipSuccess) j = hipStreamWaitEvent(ctx->stream, ctx->lane_events[(size_t)i], 0);
+        if (j != hipSuccess) {
+            (void)hipStreamSynchronize(stream(i));
+            if (e == hipSuccess) e = j;
+        }
+    }
+    BC_HIP(ctx, e);
+    return BC_OK;
+}
+
+// Takes in what a lane's replays found (c, read from its control block) and
+// runs the batches they handed back.
+bc_status settle_one(bc_ctx *ctx, const BatchCtl &c) {
+    SparseState &s = ctx->sp;
+    s.depth_max = std::max(s.depth_max, (int32_t)c.max_nlev);
+    s.depth_guess = std::max(s.depth_guess, (int32_t)c.max_nlev);
+    ctx->max_levels = std::max(ctx->max_levels, (int32_t)c.max_nlev);
+    if (c.redo_count == 0) return BC_OK;
+    std::vector<int32_t> redo(c.redo_count);
+    BC_HIP(ctx, hipMemcpy(redo.data(), s.redo, redo.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    if (c.need_wide) s.wide = true; // sticky, as on the host-driven path
+    for (const int32_t b0 : redo) {
+        int32_t nlev = 0;
+        bc_status st = run_batch(ctx, c.src + b0, std::min(s.batch, c.total - b0), true, &nlev);
+        if (st != BC_OK) return st;
+    }
+    return BC_OK;
+}
+
+} // namespace
+
+void lanes_release(bc_ctx *ctx) {
+    for (hipStream_t q : ctx->lane_streams) hipStreamSynchronize(q);
+    for (bc_ctx *t : ctx->lanes) lane_free(t);
+    for (hipStream_t q : ctx->lane_streams) hipStreamDestroy(q);
+    for (hipEvent_t e : ctx->lane_events) hipEventDestroy(e);
+    ctx->lanes.clear();
+    ctx->lane_streams.clear();
+    ctx->lane_events.clear();
+}
+
 bc_status sparse_run(bc_ctx *ctx, const int32_t *d_src, int64_t count) {
     if (ctx->sm.on) return small_run(ctx, d_src, count, false, nullptr, nullptr, nullptr);
     SparseState &s = ctx->sp;
@@ -1500,19 +1700,11 @@ bc_status sparse_run(bc_ctx *ctx, const int32_t *d_src, int64_t count) {
         if (st != BC_OK) return st;
     }
     if (b0 >= count) return BC_OK;
-    bc_status st = ensure_replay(ctx);
-    if (st != BC_OK) return st;
     const int64_t rest = count - b0, nb = (rest + B - 1) / B;
-    if (nb > s.redo_cap) {
-        int32_t *r = (int32_t *)bc_dalloc(ctx, (size_t)nb * sizeof(int32_t));
-        if (!r) return bc_fail(ctx, BC_ERR_NOMEM, "sparse form: allocation of the handed-back list failed");
-        bc_dfree(ctx, s.redo);
-        s.redo = r;
-        s.redo_cap = nb;
-    }
-    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(64), 0, ctx->stream, s.ctl, d_src + b0, (int32_t)rest, s.redo);
-    BC_HIP(ctx, hipGetLastError());
-    s.g_pending = true; // from here on the device holds checks the host must read
+    const int lanes = lanes_for(ctx, nb);
+    if (lanes > 1) return run_lanes(ctx, lanes, d_src + b0, rest);
+    bc_status st = start_replays(ctx, d_src + b0, rest, ctx->stream);
+    if (st != BC_OK) return st;
     for (int64_t i = 0; i < nb; ++i) {
         bc_timing_batch(ctx);
         if (ctx->timing && ctx->timing_sel) {
@@ -1534,25 +1726,36 @@ bc_status sparse_run(bc_ctx *ctx, const int32_t *d_src, int64_t count) {
 }
 
 bc_status sparse_settle(bc_ctx *ctx) {
-    SparseState &s = ctx->sp;
-    if (!s.g_pending) return BC_OK;
-    s.g_pending = false;
-    BatchCtl c{};
-    BC_HIP(ctx, hipMemcpyAsync(&c, s.ctl, sizeof c, hipMemcpyDeviceToHost, ctx->stream));
-    BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    s.depth_max = std::max(s.depth_max, (int32_t)c.max_nlev);
-    s.depth_guess = std::max(s.depth_guess, (int32_t)c.max_nlev);
-    ctx->max_levels = std::max(ctx->max_levels, (int32_t)c.max_nlev);
-    if (c.redo_count == 0) return BC_OK;
-    std::vector<int32_t> redo(c.redo_count);
-    BC_HIP(ctx, hipMemcpy(redo.data(), s.redo, redo.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-    if (c.need_wide) s.wide = true; // sticky, as on the host-driven path
-    for (const int32_t b0 : redo) {
-        int32_t nlev = 0;
-        bc_status st = run_batch(ctx, c.src + b0, std::min(s.batch, c.total - b0), true, &nlev);
-        if (st != BC_OK) return st;
+    // every control block in one round trip
+    std::vector<bc_ctx *> all{ctx};
+    all.insert(all.end(), ctx->lanes.begin(), ctx->lanes.end());
+    bool pending = false;
+    for (size_t i = 0; i < all.size(); ++i) {
+        if (!all[i]->sp.g_pending) continue;
+        pending = true;
+        BC_HIP(ctx, hipMemcpyAsync(ctx->status_host + 16 * (i + 1), all[i]->sp.ctl, sizeof(BatchCtl),
+                                   hipMemcpyDeviceToHost, ctx->stream));
     }
-    return BC_OK;
+    if (!pending) return BC_OK;
+    BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    BatchCtl ctls[MAX_LANES];
+    for (size_t i = 0; i < all.size(); ++i) std::memcpy(&ctls[i], ctx->status_host + 16 * (i + 1), sizeof(BatchCtl));
+    bc_status st = BC_OK;
+    for (size_t i = 0; i < all.size(); ++i) {
+        if (!all[i]->sp.g_pending) continue;
+        all[i]->sp.g_pending = false;
+        const bc_status one = settle_one(all[i], ctls[i]);
+        if (i > 0) {
+            SparseState &s = ctx->sp;
+            s.depth_max = std::max(s.depth_max, all[i]->sp.depth_max);
+            s.depth_guess = std::max(s.depth_guess, all[i]->sp.depth_guess);
+            s.wide = s.wide || all[i]->sp.wide;
+            ctx->max_levels = std::max(ctx->max_levels, all[i]->max_levels);
+            if (one != BC_OK) lane_failed(ctx, all[i]);
+        }
+        if (st == BC_OK) st = one;
+    }
+    return st;
 }
 
 void sparse_graphs_release(bc_ctx *ctx) {
