@@ -1689,28 +1689,43 @@ bc_status sparse_run(bc_ctx *ctx, const int32_t *d_src, int64_t count) {
     SparseState &s = ctx->sp;
     const int32_t B = s.batch;
     const bool replay = !ctx->weighted && !ctx->host_driven && count < (int64_t(1) << 31) - B;
-    int64_t b0 = 0;
-    // Host-driven batches: every batch without replay; with replay the first
-    // batch a state runs, which gives the depth and the level densities.
-    for (; b0 < count && (!replay || s.depth_max == 0); b0 += B) {
-        int32_t nlev = 0;
-        bc_timing_batch(ctx); // with sampled timing, this batch's launches are timed or not as a whole
-        bc_timing_eager(ctx);
-        bc_status st = run_batch(ctx, d_src + b0, (int32_t)std::min<int64_t>(B, count - b0), true, &nlev);
-        if (st != BC_OK) return st;
+    if (!replay) {
+        for (int64_t b0 = 0; b0 < count; b0 += B) {
+            int32_t nlev = 0;
+            bc_timing_batch(ctx); // with sampled timing, this batch's launches are timed or not as a whole
+            bc_timing_eager(ctx);
+            bc_status st = run_batch(ctx, d_src + b0, (int32_t)std::min<int64_t>(B, count - b0), true, &nlev);
+            if (st != BC_OK) return st;
+        }
+        return BC_OK;
     }
-    if (b0 >= count) return BC_OK;
-    const int64_t rest = count - b0, nb = (rest + B - 1) / B;
+    if (s.depth_max == 0 && count > 0) {
+        // The first batch a state runs is driven from the host and gives the
+        // depth and the level densities: the last B sources, which in a run
+        // over every vertex are those of the lowest degrees and so the
+        // deepest.  Recorded for the depth of the hubs' batch, most replays
+        // handed their batches back (RMAT-16, a context's first run over all
+        // sources: 198 against 145 ms).
+        const int64_t first = std::min<int64_t>(B, count);
+        int32_t nlev = 0;
+        bc_timing_batch(ctx);
+        bc_timing_eager(ctx);
+        bc_status st = run_batch(ctx, d_src + count - first, (int32_t)first, true, &nlev);
+        if (st != BC_OK) return st;
+        count -= first;
+    }
+    if (count <= 0) return BC_OK;
+    const int64_t nb = (count + B - 1) / B;
     const int lanes = lanes_for(ctx, nb);
-    if (lanes > 1) return run_lanes(ctx, lanes, d_src + b0, rest);
-    bc_status st = start_replays(ctx, d_src + b0, rest, ctx->stream);
+    if (lanes > 1) return run_lanes(ctx, lanes, d_src, count);
+    bc_status st = start_replays(ctx, d_src, count, ctx->stream);
     if (st != BC_OK) return st;
     for (int64_t i = 0; i < nb; ++i) {
         bc_timing_batch(ctx);
         if (ctx->timing && ctx->timing_sel) {
             // a timed batch runs host-driven, so that its launches carry events
             bc_timing_eager(ctx);
-            const int64_t off = b0 + i * B;
+            const int64_t off = i * B;
             int32_t nlev = 0;
             st = run_batch(ctx, d_src + off, (int32_t)std::min<int64_t>(B, count - off), true, &nlev);
             if (st != BC_OK) return st;
