@@ -196,9 +196,11 @@ struct MultiState {
 struct PlainState {
     int32_t grid = 0;         // requested workgroups (0 = default)
     int32_t groups = 0;       // persistent workgroups
-    int32_t *dist = nullptr;  // [groups][n]
-    uint64_t *sigma = nullptr;// [groups][n]
-    double *acc = nullptr;    // [groups][n]
+    int32_t cus = 0;          // compute units
+    int32_t threads = 0;      // threads per workgroup of the sweep with its states in LDS; 0: they do not fit
+    int32_t *dist = nullptr;  // [groups][n], states in memory only
+    uint64_t *sigma = nullptr;// [groups][n] (states in LDS: replaced by c in the backward)
+    double *acc = nullptr;    // [groups][n], states in memory only
     int32_t *queue = nullptr; // [groups][n]
     int32_t *lev = nullptr;   // [groups][n + 2] level starts in the queue
     uint32_t *next = nullptr; // work counter

@@ -9,7 +9,7 @@
 
 namespace wg {
 
-constexpr int PB = 256; // threads per workgroup
+constexpr int PB = 256; // threads per workgroup, where not given as T
 
 // Workgroup barrier between the phases of a per-source sweep.  The arrays it
 // orders (distances, counts, sums, queues in global memory) belong to one
@@ -35,6 +35,7 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
 }
 
 // Exclusive prefix sum over the workgroup; *total receives the sum.
+template <int T = PB>
 __device__ __forceinline__ int block_excl_scan(int x, int *wsum, int *total) {
     const int incl = wave_incl_scan(x);
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -42,7 +43,7 @@ __device__ __forceinline__ int block_excl_scan(int x, int *wsum, int *total) {
     __syncthreads();
     int off = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < PB / 64; ++i) {
+    for (int i = 0; i < T / 64; ++i) {
         int s = wsum[i];
         if (i < wid) off += s;
         tot += s;
@@ -52,9 +53,10 @@ __device__ __forceinline__ int block_excl_scan(int x, int *wsum, int *total) {
     return off + incl - x;
 }
 
-// Largest k in [0, PB) with off[k] <= e, given off[0] = 0 <= e < off[PB].
+// Largest k in [0, T) with off[k] <= e, given off[0] = 0 <= e < off[T].
+template <int T = PB>
 __device__ __forceinline__ int owner(const int *off, int e) {
-    int lo = 0, hi = PB;
+    int lo = 0, hi = T;
     while (hi - lo > 1) {
         int mid = (lo + hi) >> 1;
         if (off[mid] <= e) lo = mid;
@@ -63,51 +65,22 @@ __device__ __forceinline__ int owner(const int *off, int e) {
     return lo;
 }
 
-// LDS staging for one chunk of up to PB vertices.
-struct Chunk {
-    int32_t v[PB];
-    int32_t rp[PB];
-    int32_t off[PB + 1];
-    int32_t wsum[PB / 64];
+// LDS staging for one chunk of up to T vertices.
+template <int T>
+struct ChunkOf {
+    int32_t v[T];
+    int32_t rp[T];
+    int32_t off[T + 1];
+    int32_t wsum[T / 64];
 };
+using Chunk = ChunkOf<PB>;
 
-// Calls f(k, v, arc) for every arc of the vertices list[lb..le), PB vertices
-// at a time, one arc per thread: hubs are spread over the whole workgroup.
-// k is the vertex's slot in the chunk (for per-vertex values a caller staged).
-// pre(k, v) runs once per staged vertex before its arcs.  Ends with bar().
-template <typename Pre, typename F>
-__device__ __forceinline__ void for_arcs(const int32_t *list, int32_t lb, int32_t le, const int32_t *__restrict__ rp,
-                                         Chunk &c, Pre pre, F f) {
-    const int tid = threadIdx.x;
-    for (int32_t cb = lb; cb < le; cb += PB) {
-        const int32_t i = cb + tid;
-        int32_t v = -1, r = 0, d = 0;
-        if (i < le) {
-            v = list[i];
-            r = rp[v];
-            d = rp[v + 1] - r;
-        }
-        int tot;
-        const int off = block_excl_scan(d, c.wsum, &tot);
-        c.v[tid] = v;
-        c.rp[tid] = r;
-        c.off[tid] = off;
-        if (tid == 0) c.off[PB] = tot;
-        if (v >= 0) pre(tid, v);
-        __syncthreads();
-        for (int e = tid; e < tot; e += PB) {
-            const int k = owner(c.off, e);
-            f(k, c.v[k], c.rp[k] + (e - c.off[k]));
-        }
-        bar();
-    }
-}
-
-// Stages the vertices list[cb .. min(cb + PB, le)) in c (vertex, row offset,
-// exclusive degree prefix; c.off[PB] = total) and returns their total degree.
+// Stages the vertices list[cb .. min(cb + T, le)) in c (vertex, row offset,
+// exclusive degree prefix; c.off[T] = total) and returns their total degree.
 // Every thread of the workgroup calls; ends with __syncthreads().
+template <int T>
 __device__ __forceinline__ int stage_chunk(const int32_t *list, int32_t cb, int32_t le,
-                                           const int32_t *__restrict__ rp, Chunk &c) {
+                                           const int32_t *__restrict__ rp, ChunkOf<T> &c) {
     const int tid = threadIdx.x;
     const int32_t i = cb + tid;
     int32_t v = -1, r = 0, d = 0;
@@ -117,27 +90,27 @@ __device__ __forceinline__ int stage_chunk(const int32_t *list, int32_t cb, int3
         d = rp[v + 1] - r;
     }
     int tot;
-    const int off = block_excl_scan(d, c.wsum, &tot);
+    const int off = block_excl_scan<T>(d, c.wsum, &tot);
     c.v[tid] = v;
     c.rp[tid] = r;
     c.off[tid] = off;
-    if (tid == 0) c.off[PB] = tot;
+    if (tid == 0) c.off[T] = tot;
     __syncthreads();
     return tot;
 }
 
-// Arc positions e0 + j * PB (j < U) of a staged chunk with `tot` arcs: slot
+// Arc positions e0 + j * T (j < U) of a staged chunk with `tot` arcs: slot
 // k[j] of the owning vertex and arc index a[j] (-1 past the end).  The U
 // owner searches are independent, so they overlap.
-template <int U>
-__device__ __forceinline__ void arc_burst(const Chunk &c, int e0, int tot, int (&k)[U], int32_t (&a)[U]) {
+template <int U, int T>
+__device__ __forceinline__ void arc_burst(const ChunkOf<T> &c, int e0, int tot, int (&k)[U], int32_t (&a)[U]) {
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-        const int e = e0 + j * PB;
+        const int e = e0 + j * T;
         k[j] = 0;
         a[j] = -1;
         if (e < tot) {
-            k[j] = owner(c.off, e);
+            k[j] = owner<T>(c.off, e);
             a[j] = c.rp[k[j]] + (e - c.off[k[j]]);
         }
     }
