@@ -77,7 +77,7 @@ __global__ __launch_bounds__(PB) void k_plain_sweep(
                 for (int e0 = tid; e0 < tot; e0 += PB * U) {
                     int k[U];
                     int32_t a[U], w[U], dw[U];
-                    wg::arc_burst<U, PB>(ch, e0, tot, k, a);
+                    wg::arc_burst<U, PB>(ch, e0, tot, PB, k, a);
 #pragma unroll
                     for (int j = 0; j < U; ++j) w[j] = a[j] >= 0 ? col[a[j]] : 0;
 #pragma unroll
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(PB) void k_plain_sweep(
                     for (int e0 = tid; e0 < tot; e0 += PB * U) {
                         int k[U];
                         int32_t a[U], w[U], dw[U];
-                        wg::arc_burst<U, PB>(ch, e0, tot, k, a);
+                        wg::arc_burst<U, PB>(ch, e0, tot, PB, k, a);
 #pragma unroll
                         for (int j = 0; j < U; ++j) w[j] = a[j] >= 0 ? col[a[j]] : 0;
 #pragma unroll
@@ -176,10 +176,10 @@ __global__ __launch_bounds__(PB) void k_plain_sweep(
 // one accumulator per vertex of the chunk (no atomic in memory), and the
 // workgroups are as many as fit the LDS: 12 bytes a vertex each, not 24 times
 // 2048.  Up to a source per compute unit a workgroup has 1024 threads.  ms for
-// 1 / 2048 sources, against the sweep with the state in memory: RMAT-15 2.2 /
-// 22.4 and 9.1 / 61; RMAT-16 4.4 / 47 and 18 / 136; G(30000, 8/29999) 0.96 / 10.7
+// 1 / 2048 sources, against the sweep with the state in memory: RMAT-15 2.0 /
+// 19.9 and 9.1 / 61; RMAT-16 4.0 / 42 and 18 / 136; G(30000, 8/29999) 1.0 / 10.5
 // and 3.3 / 39.  At n = 90208 one workgroup per unit is left: RMAT-17, 1024
-// sources, 51 against 142.
+// sources, 48 against 142.
 template <int T>
 __global__ __launch_bounds__(T) void k_plain_state(
     int32_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(T) void k_plain_state(
                     int k[U];
                     int32_t a[U], w[U];
                     bool in[U];
-                    wg::arc_burst<U, T>(ch, e0, tot, k, a);
+                    wg::arc_burst<U, T>(ch, e0, tot, min(T, qe - cb), k, a);
 #pragma unroll
                     for (int j = 0; j < U; ++j) w[j] = a[j] >= 0 ? col[a[j]] : 0;
 #pragma unroll
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(T) void k_plain_state(
                         int k[U];
                         int32_t a[U], w[U];
                         bool in[U];
-                        wg::arc_burst<U, T>(ch, e0, tot, k, a);
+                        wg::arc_burst<U, T>(ch, e0, tot, min(T, le - cb), k, a);
 #pragma unroll
                         for (int j = 0; j < U; ++j) w[j] = a[j] >= 0 ? col[a[j]] : 0;
 #pragma unroll
@@ -352,9 +352,11 @@ bc_status plain_prepare(bc_ctx *ctx) {
     cus = std::max(cus, 1);
     const size_t per_cu = std::min<size_t>(LDS_BYTES / (fixed_lds<ST_T>() + state_lds(ctx->n)), 2048 / ST_T);
     p.threads = per_cu >= 2 ? ST_T : fixed_lds<WIDE_T>() + state_lds(ctx->n) <= LDS_BYTES ? WIDE_T : 0;
-    for (const void *k : {(const void *)k_plain_state<ST_T>, (const void *)k_plain_state<WIDE_T>})
-        if (p.threads)
-            BC_HIP(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)state_lds(ctx->n)));
+    // the kernels' limit, the same for every context
+    BC_HIP(ctx, hipFuncSetAttribute((const void *)k_plain_state<ST_T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)(LDS_BYTES - fixed_lds<ST_T>())));
+    BC_HIP(ctx, hipFuncSetAttribute((const void *)k_plain_state<WIDE_T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)(LDS_BYTES - fixed_lds<WIDE_T>())));
     p.cus = cus;
     const size_t per_group = (p.threads ? n * (8 + 4) : n * (4 + 8 + 8 + 4)) + (n + 2) * 4;
     const size_t budget = size_t(16) << 30;

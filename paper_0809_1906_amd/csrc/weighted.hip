@@ -191,7 +191,7 @@ __global__ __launch_bounds__(PB) void k_weighted_sweep(
                 for (int e0 = tid; e0 < tot; e0 += PB * U) {
                     int k[U];
                     int32_t a[U], x[U], c[U], dx[U];
-                    wg::arc_burst<U, PB>(ch, e0, tot, k, a);
+                    wg::arc_burst<U, PB>(ch, e0, tot, PB, k, a);
 #pragma unroll
                     for (int j = 0; j < U; ++j) {
                         x[j] = a[j] >= 0 ? col[a[j]] : 0;
