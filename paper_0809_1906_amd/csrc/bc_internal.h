@@ -143,13 +143,17 @@ struct WeightedBuffers {
     double *acc = nullptr;
 };
 struct WeightedState {
+    WeightedBuffers lds;          // the sweep with its distances in LDS
+    int32_t lds_threads = 0;      // its threads per workgroup; 0: the distances do not fit
+    int32_t lds_few = 0;          // up to this many sources its workgroups have 1024 threads
+    bool lds_off = false;         // most sources' distances pass 16 bits
     WeightedBuffers main;         // many workgroups, arena of max(4n, 2^16)
     WeightedBuffers big;          // few workgroups, arena of nnz (allocated on first need)
     uint32_t *next = nullptr;
-    int32_t *retry = nullptr;     // rows whose live bins outgrew the main arena
+    int32_t *retry = nullptr;     // rows to run again in the next larger workspace
     uint32_t *retry_count = nullptr;
     uint32_t *host = nullptr;     // pinned
-    int64_t retry_cap = 0;
+    int32_t *again = nullptr;     // the sources to run again, then their rows
     int64_t retried = 0;
     int32_t arena_log2 = 0;       // requested main arena size (0 = default)
     int32_t grid = 0;             // requested workgroups (0 = default)

@@ -65,7 +65,8 @@ struct WeightedWork {
     int64_t cap;     // arena entries per workgroup, a power of two
     int64_t icap;    // improvement-list entries per workgroup
     int64_t dcap;    // DAG-arc entries per workgroup
-    int32_t *retry;  // sources (positions in the source list) whose live bins outgrew the arena
+    int32_t *retry;  // rows of the sources to run again: their live bins outgrew the arena, or
+                     // the sweep with its distances in LDS does not hold them
     uint32_t *retry_count;
     const int32_t *comp_size; // [n] vertices in each vertex's connected component
 };
@@ -334,12 +335,313 @@ __global__ __launch_bounds__(PB) void k_weighted_sweep(
     }
 }
 
+// The same order with every distance in LDS, 16 bits each.  Measured against
+// the sweep above, ms for 1 / 1024 sources: RMAT-16 with weights up to 255 5.1 /
+// 21.1 against 13.1 / 26.1, up to 10 2.7 / 13.8 against 10.8 / 23.5; RMAT-13 2.1 /
+// 4.9 against 3.2 / 5.8; G(60000, 10/59999) 5.8 / 25.4 against 11.0 / 28.9.
+// What bounds the sweep is each phase's chain of dependent accesses and its
+// barriers (counters: waves wait 67% of their time, vector units busy 47%), so:
+//   - a phase finds its vertices, and the least distance above its own, by a
+//     scan of the distances (two per instruction): no bins to read, search and
+//     file in memory, and no phase without a vertex.  The thread that finds a
+//     vertex loads its row and takes its place among the phase's arcs by one
+//     LDS atomic on (vertices, arcs); then one pass over the arcs.
+//   - an add into a count whose result nobody needs does not wait for it:
+//     counts up to `safe`, 2^63 over the largest degree, cannot sum past 2^63,
+//     and a larger one that brings a sum there hands the source back;
+//   - the backward takes c(w) = 1 / lambda_sw + the sum over w's successors
+//     straight from the two, one barrier per phase with the next phase's arcs
+//     loaded before it; BC is added for all vertices at the end.
+// A source is handed to the sweep above when a distance reaches 65535, its
+// DAG arcs outgrow W.dcap, or a count comes near 2^64.
+__device__ __forceinline__ uint32_t pk_sub16(uint32_t a, uint32_t b) {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_min16(uint32_t a, uint32_t b) {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t,
+                              __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
+constexpr uint32_t FAR16 = 0xFFFF; // not reached
+
+template <int T>
+__global__ __launch_bounds__(T, 4) void k_weighted_lds(
+    int32_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const uint8_t *__restrict__ wt,
+    const int32_t *__restrict__ sources, int64_t count, unsigned long long *next_counter, WeightedWork W, uint64_t safe,
+    double *bc, int accumulate, double *delta_dump, int32_t *dist_dump, uint64_t *sigma_dump, double *eb) {
+    constexpr int U = 4; // eight arcs in flight take more than a quarter of the registers
+    extern __shared__ uint4 s_dist8[]; // [(n + 7) / 8] eight distances each
+    __shared__ wg::ChunkOf<T> ch;
+    __shared__ long long s_idx;
+    // phase p uses entry p % 3 and clears the next phase's, last used two
+    // phases before
+    __shared__ unsigned long long s_found[3]; // vertices << 32 | arcs
+    __shared__ uint32_t s_next[3];
+    __shared__ int32_t s_ndag;
+    __shared__ uint32_t s_abort;
+
+    const int tid = threadIdx.x;
+    const size_t g = blockIdx.x;
+    uint32_t *dist2 = reinterpret_cast<uint32_t *>(s_dist8);
+    const uint16_t *dist = reinterpret_cast<const uint16_t *>(s_dist8);
+    const int32_t n8 = (n + 7) / 8;
+    uint64_t *sigma = W.sigma + g * (size_t)n;
+    double *acc = W.acc + g * (size_t)n;
+    int32_t *order = W.order + g * (size_t)n; // a phase's vertices past the first T
+    int32_t *gdag = W.gdag + g * ((size_t)n + 1);
+    int32_t *dag_p = W.dag_p + g * (size_t)W.dcap;
+    int32_t *dag_s = W.dag_s + g * (size_t)W.dcap;
+    int32_t *dag_a = W.dag_a + g * (size_t)W.dcap;
+
+    for (;;) {
+        if (tid == 0) {
+            s_idx = (long long)atomicAdd(next_counter, 1ull);
+            // where most sources so far were handed back, so is the rest
+            const uint32_t back = __hip_atomic_load(W.retry_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_abort = s_idx >= gridDim.x && 2 * (long long)back > s_idx;
+        }
+        __syncthreads();
+        const long long idx = s_idx;
+        if (idx >= count) break;
+        if (s_abort) {
+            if (tid == 0) W.retry[atomicAdd(W.retry_count, 1u)] = (int32_t)idx;
+            __syncthreads(); // s_idx and s_abort are read above
+            continue;
+        }
+        const int32_t s = sources[idx];
+        for (int32_t i = tid; i < n8; i += T) s_dist8[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+        for (int32_t v = tid; v < n; v += T) {
+            sigma[v] = 0;
+            acc[v] = 0.0;
+        }
+        wg::bar();
+        if (tid == 0) {
+            dist2[s >> 1] = s & 1 ? 0x0000FFFFu : 0xFFFF0000u; // distance 0
+            sigma[s] = 1;
+            s_ndag = 0;
+            gdag[0] = 0;
+            s_found[0] = 0;
+            s_next[0] = FAR16;
+        }
+        wg::bar();
+
+        // ---- forward: phases at the distances that occur ----
+        int32_t nsettled = 0, ngroups = 0;
+        uint32_t d = 0;
+        const int32_t all = W.comp_size[s];
+        for (int ph = 0;; ph = ph == 2 ? 0 : ph + 1) {
+            // the vertices at distance d, and the least distance above it:
+            // x - (d + 1) mod 2^16 is largest for the distances up to d
+            uint32_t gap = 0xFFFFFFFFu;
+            const uint32_t here = d | d << 16, above = (d + 1) | (d + 1) << 16;
+            for (int32_t i = tid; i < n8; i += T) {
+                const uint4 x4 = s_dist8[i];
+                const uint32_t x[4] = {x4.x, x4.y, x4.z, x4.w};
+                uint32_t hit = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    gap = pk_min16(gap, pk_sub16(x[q], above));
+                    const uint32_t z = x[q] ^ here;
+                    hit |= (z - 0x00010001u) & ~z & 0x80008000u; // some half is zero
+                }
+                if (hit == 0) continue;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (((x[j >> 1] >> (16 * (j & 1))) & 0xFFFFu) == d) {
+                        const int32_t v = 8 * i + j;
+                        const int32_t r = rp[v], deg = rp[v + 1] - r;
+                        const unsigned long long at = atomicAdd(&s_found[ph], 1ull << 32 | (unsigned long long)deg);
+                        const int32_t slot = (int32_t)(at >> 32);
+                        if (slot <= T) ch.off[slot] = (int32_t)(uint32_t)at;
+                        if (slot < T) {
+                            ch.v[slot] = v;
+                            ch.rp[slot] = r;
+                        } else {
+                            order[slot] = v;
+                        }
+                    }
+            }
+            gap = min(gap & 0xFFFFu, gap >> 16);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) gap = min(gap, (uint32_t)__shfl_xor((int)gap, off, 64));
+            // with no distance above d, d + 1 + gap = FAR16
+            if ((tid & 63) == 0) atomicMin(&s_next[ph], d + 1 + gap);
+            __syncthreads();
+            const unsigned long long found = s_found[ph];
+            const int32_t cnt = (int32_t)(found >> 32);
+            if (tid == 0) {
+                s_found[ph == 2 ? 0 : ph + 1] = 0;
+                s_next[ph == 2 ? 0 : ph + 1] = FAR16;
+            }
+            nsettled += cnt;
+            // one pass over their arcs pulls the counts from the predecessors
+            // and relaxes
+            uint32_t low = FAR16;
+            auto arcs = [&](int slots, int tot) {
+                for (int e0 = tid * U; e0 < tot; e0 += T * U) {
+                    int k[U];
+                    int32_t a[U], x[U];
+                    uint32_t c[U], dx[U], was[U];
+                    wg::arc_run<U, T>(ch, e0, tot, slots, k, a);
+#pragma unroll
+                    for (int j = 0; j < U; ++j) {
+                        x[j] = a[j] >= 0 ? col[a[j]] : 0;
+                        c[j] = a[j] >= 0 ? (uint32_t)wt[a[j]] : 0;
+                    }
+#pragma unroll
+                    for (int j = 0; j < U; ++j) was[j] = dist2[x[j] >> 1];
+#pragma unroll
+                    for (int j = 0; j < U; ++j) dx[j] = a[j] >= 0 ? (was[j] >> (16 * (x[j] & 1))) & 0xFFFFu : 0u;
+                    // the counts of the predecessors (x in P_s(w)), loaded together
+                    bool in[U];
+                    uint64_t sx[U];
+                    bool any = false;
+#pragma unroll
+                    for (int j = 0; j < U; ++j) {
+                        in[j] = a[j] >= 0 && d > 0 && dx[j] + c[j] == d;
+                        sx[j] = in[j] ? sigma[x[j]] : 0;
+                        any |= in[j];
+                    }
+                    // lower x's half of its word where the arc improves it: one
+                    // attempt each, then those that met another change again
+                    uint32_t todo = 0;
+#pragma unroll
+                    for (int j = 0; j < U; ++j) {
+                        const uint32_t nd = d + c[j];
+                        if (dx[j] == FAR16 && nd >= FAR16) s_abort = 1; // past 16 bits
+                        if (nd >= dx[j]) continue;
+                        const int sh = 16 * (x[j] & 1);
+                        const uint32_t seen = atomicCAS(&dist2[x[j] >> 1], was[j], (was[j] & ~(0xFFFFu << sh)) | nd << sh);
+                        if (seen == was[j]) low = min(low, nd);
+                        else todo |= 1u << j;
+                        was[j] = seen;
+                    }
+                    if (todo) {
+#pragma unroll
+                        for (int j = 0; j < U; ++j) {
+                            if (!((todo >> j) & 1)) continue;
+                            const uint32_t nd = d + c[j];
+                            const int sh = 16 * (x[j] & 1);
+                            while (nd < ((was[j] >> sh) & 0xFFFFu)) {
+                                const uint32_t seen =
+                                    atomicCAS(&dist2[x[j] >> 1], was[j], (was[j] & ~(0xFFFFu << sh)) | nd << sh);
+                                if (seen == was[j]) {
+                                    low = min(low, nd);
+                                    break;
+                                }
+                                was[j] = seen;
+                            }
+                        }
+                    }
+                    if (any) {
+                        int mine = 0;
+#pragma unroll
+                        for (int j = 0; j < U; ++j) mine += in[j];
+                        int32_t pos = atomicAdd(&s_ndag, mine);
+#pragma unroll
+                        for (int j = 0; j < U; ++j) {
+                            if (!in[j]) continue;
+                            const int32_t w = ch.v[k[j]];
+                            if (sx[j] <= safe) {
+                                (void)__hip_atomic_fetch_add(&sigma[w], sx[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            } else {
+                                const uint64_t old = atomicAdd((unsigned long long *)&sigma[w], (unsigned long long)sx[j]);
+                                if (old + sx[j] < old || old + sx[j] >= 1ull << 63) s_abort = 1;
+                            }
+                            if (pos < W.dcap) {
+                                dag_p[pos] = x[j];
+                                dag_s[pos] = w;
+                                if (eb) dag_a[pos] = a[j];
+                            } else {
+                                s_abort = 1;
+                            }
+                            ++pos;
+                        }
+                    }
+                }
+            };
+            arcs(min(cnt, T), cnt <= T ? (int)(uint32_t)found : ch.off[T]);
+            for (int32_t cb = T; cb < cnt; cb += T) {
+                __syncthreads(); // the chunk's LDS is restaged
+                const int tot = wg::stage_chunk<T>(order, cb, cnt, rp, ch);
+                arcs(min(cnt - cb, T), tot);
+            }
+            if (low < FAR16) atomicMin(&s_next[ph], low);
+            __syncthreads();
+            ++ngroups;
+            if (tid == 0) gdag[ngroups] = s_ndag; // the next arcs are listed a barrier later
+            const uint32_t nd = s_next[ph];
+            if (s_abort || nsettled == all || nd >= FAR16) break; // uniform
+            d = nd;
+        }
+        wg::bar();
+        if (s_abort) {
+            if (tid == 0) W.retry[atomicAdd(W.retry_count, 1u)] = (int32_t)idx;
+            wg::bar();
+            continue;
+        }
+
+        // ---- backward: phases from the last down; phase 0 is the source's,
+        // phase 1's arcs lead to it (its sum is the readout's only) ----
+        {
+            int32_t de = gdag[ngroups], db = gdag[ngroups - 1];
+            int32_t p = -1, w = 0;
+            double inv = 0.0;
+            auto fetch = [&](int32_t i) {
+                p = -1;
+                if (i < de) {
+                    p = dag_p[i];
+                    w = dag_s[i];
+                    inv = 1.0 / (double)sigma[w];
+                }
+            };
+            fetch(db + tid);
+            for (int32_t gi = ngroups - 1; gi >= 1; --gi) {
+                for (int32_t i = db + tid;;) {
+                    if (p >= 0) {
+                        const double cw = inv + acc[w];
+                        unsafeAtomicAdd(&acc[p], cw);
+                        // edge term of the DAG arc p -> w: lambda(p) c(w)
+                        if (eb) unsafeAtomicAdd(&eb[dag_a[i]], (double)sigma[p] * cw);
+                    }
+                    i += T;
+                    if (i >= de) break;
+                    fetch(i);
+                }
+                de = db;
+                db = gdag[gi - 1];
+                fetch(db + tid);
+                __syncthreads();
+            }
+        }
+        for (int32_t v = tid; v < n; v += T) {
+            const uint32_t dv = dist[v];
+            const uint64_t sv = dv == FAR16 ? 0 : sigma[v];
+            const double dl = sv ? (double)sv * acc[v] : 0.0;
+            if (accumulate && v != s && dl != 0.0) unsafeAtomicAdd(&bc[v], dl);
+            if (dist_dump) {
+                const size_t at = (size_t)idx * n + v;
+                dist_dump[at] = dv == FAR16 ? -1 : (int32_t)dv;
+                sigma_dump[at] = sv;
+                delta_dump[at] = dl;
+            }
+        }
+        wg::bar();
+    }
+}
+
 // Main workspaces list a quarter of the ring's size in improvements per phase
 // and half of it in DAG arcs, and send a source that needs more to the retry
 // workspace; the retry workspace (ring of nnz + 1 entries or more) holds every
 // improvement of a phase and every DAG arc, so it never needs a retry itself.
 int64_t imp_cap(int64_t cap, bool retry_ws) { return retry_ws ? cap : std::max<int64_t>(cap / 4, 1); }
 int64_t dag_cap(int64_t cap) { return std::max<int64_t>(cap / 2, 1); }
+// the arena; the improvement list (5 B per entry); the DAG list (12 B per arc)
+size_t list_bytes(int64_t cap, bool retry_ws) {
+    return (size_t)cap * 4 + (size_t)imp_cap(cap, retry_ws) * 5 + (size_t)dag_cap(cap) * 12;
+}
 
 bc_status alloc_work(bc_ctx *ctx, WeightedBuffers &b, int64_t cap, int groups, bool retry_ws) {
     const size_t n = (size_t)std::max(ctx->n, 1);
@@ -354,28 +656,34 @@ bc_status alloc_work(bc_ctx *ctx, WeightedBuffers &b, int64_t cap, int groups, b
     b.order = (int32_t *)bc_dalloc(ctx, G * n * 4);
     b.gstart = (int32_t *)bc_dalloc(ctx, G * (n + 1) * 4);
     b.gdist = (int32_t *)bc_dalloc(ctx, G * n * 4);
-    b.arena = (int32_t *)bc_dalloc(ctx, G * (size_t)cap * 4);
     b.bstart = (int32_t *)bc_dalloc(ctx, G * RING * RING * 4);
     b.bcount = (int32_t *)bc_dalloc(ctx, G * RING * RING * 4);
     b.pstart = (int32_t *)bc_dalloc(ctx, G * RING * 4);
-    b.imp_x = (int32_t *)bc_dalloc(ctx, G * (size_t)b.icap * 4);
-    b.imp_c = (uint8_t *)bc_dalloc(ctx, G * (size_t)b.icap);
-    b.dag_p = (int32_t *)bc_dalloc(ctx, G * (size_t)b.dcap * 4);
-    b.dag_s = (int32_t *)bc_dalloc(ctx, G * (size_t)b.dcap * 4);
-    b.dag_a = (int32_t *)bc_dalloc(ctx, G * (size_t)b.dcap * 4);
+    // the lists, in one piece: the sweep with its distances in LDS divides it
+    // otherwise
+    b.arena = (int32_t *)bc_dalloc(ctx, G * list_bytes(cap, retry_ws));
+    b.dag_p = b.arena + G * (size_t)cap;
+    b.dag_s = b.dag_p + G * (size_t)b.dcap;
+    b.dag_a = b.dag_s + G * (size_t)b.dcap;
+    b.imp_x = b.dag_a + G * (size_t)b.dcap;
+    b.imp_c = reinterpret_cast<uint8_t *>(b.imp_x + G * (size_t)b.icap);
     b.gdag = (int32_t *)bc_dalloc(ctx, G * (n + 1) * 4);
     if (!b.dist || !b.sigma || !b.acc || !b.order || !b.gstart || !b.gdist || !b.arena || !b.bstart || !b.bcount ||
-        !b.pstart || !b.imp_x || !b.imp_c || !b.dag_p || !b.dag_s || !b.dag_a || !b.gdag)
+        !b.pstart || !b.gdag)
         return bc_fail(ctx, BC_ERR_NOMEM, "weighted form: workspace allocation failed");
     return BC_OK;
 }
 
+constexpr size_t LDS_BYTES = 160 << 10;
+constexpr int64_t RETRY_CAP = 4096;
+template <int T>
+constexpr size_t fixed_lds() { return sizeof(wg::ChunkOf<T>) + 64; }
+size_t dist_lds(int32_t n) { return ((size_t)n + 7) / 8 * 16; }
+
 size_t per_group_bytes(bc_ctx *ctx, int64_t cap, bool retry_ws) {
     const size_t n = (size_t)std::max(ctx->n, 1);
-    // per vertex: dist, sigma, acc, order, gstart, gdist, gdag; the arena; the
-    // improvement list (5 B per entry); the DAG list (12 B per arc); the bins
-    return n * (4 + 8 + 8 + 4 + 4 + 4 + 4) + 8 + (size_t)cap * 4 + (size_t)imp_cap(cap, retry_ws) * 5 +
-           (size_t)dag_cap(cap) * 12 + (2 * (size_t)RING + 1) * RING * 4;
+    // per vertex: dist, sigma, acc, order, gstart, gdist, gdag; the lists; the bins
+    return n * (4 + 8 + 8 + 4 + 4 + 4 + 4) + 8 + list_bytes(cap, retry_ws) + (2 * (size_t)RING + 1) * RING * 4;
 }
 
 int64_t pow2_at_least(int64_t x) {
@@ -393,7 +701,8 @@ WeightedWork work_of(bc_ctx *ctx, const WeightedBuffers &b) {
 
 } // namespace
 
-// Workgroups get an arena ring of max(4n, 2^16) entries (rounded up to a power
+// The sweep with its distances in LDS takes every source first, where it
+// applies; what it hands back goes to the main workspace.  Workgroups get an arena ring of max(4n, 2^16) entries (rounded up to a power
 // of two); a source whose live bins outgrow it is re-run with an arena of nnz
 // entries, which always suffices (a vertex settles once, so at most one entry
 // per arc is ever filed).
@@ -409,47 +718,120 @@ bc_status weighted_prepare(bc_ctx *ctx) {
     while (groups > 1 && per_group_bytes(ctx, cap, false) * (size_t)groups > budget) groups /= 2;
     bc_status st = alloc_work(ctx, w.main, cap, groups, false);
     if (st != BC_OK) return st;
+    // The sweep with its distances in LDS, unless a grid or an arena of the
+    // other was asked for: 512 threads where two workgroups' distances fit a
+    // compute unit, else 1024, and 1024 up to a source per compute unit.  ms
+    // with 512 / 1024 threads: RMAT-15, 1024 sources 10.3 / 13.8, one 4.4 / 3.5;
+    // RMAT-13 with weights up to 10, 1024 sources 1.8 / 2.1, one 0.70 / 0.51.
+    if (w.grid == 0 && w.arena_log2 == 0 && ctx->n > 0) {
+        int cus = 0;
+        BC_HIP(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
+        const size_t lds = dist_lds(ctx->n);
+        const size_t per_cu = std::min<size_t>(LDS_BYTES / (fixed_lds<512>() + lds), 4);
+        w.lds_threads = per_cu >= 2 ? 512 : fixed_lds<1024>() + lds <= LDS_BYTES ? 1024 : 0;
+        w.lds_few = std::max(cus, 1);
+        if (w.lds_threads) {
+            // the kernels' limit, the same for every context
+            BC_HIP(ctx, hipFuncSetAttribute((const void *)k_weighted_lds<512>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)(LDS_BYTES - fixed_lds<512>())));
+            BC_HIP(ctx, hipFuncSetAttribute((const void *)k_weighted_lds<1024>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)(LDS_BYTES - fixed_lds<1024>())));
+            // The two never run together and share their arrays.  All the
+            // lists' bytes go to this one's DAG arcs: with no room for a
+            // source's arcs it is handed back, and one with few distinct
+            // weights has many (RMAT-14, weights up to 3, 1024 sources:
+            // 45 ms handed back, 4.6 with room).
+            w.lds = w.main;
+            w.lds.groups = std::min(groups, w.lds_few * (w.lds_threads == 512 ? (int)per_cu : 1));
+            const size_t bytes = (size_t)groups * list_bytes(cap, false) / (size_t)w.lds.groups;
+            w.lds.dcap = std::min<int64_t>((int64_t)(bytes / (ctx->edges ? 12 : 8)), INT32_MAX);
+            w.lds.dag_p = w.main.arena;
+            w.lds.dag_s = w.lds.dag_p + (size_t)w.lds.groups * (size_t)w.lds.dcap;
+            w.lds.dag_a = w.lds.dag_s + (size_t)w.lds.groups * (size_t)w.lds.dcap; // with edge terms only
+        }
+    }
     w.next = (uint32_t *)bc_dalloc(ctx, 256);
     w.retry_count = (uint32_t *)bc_dalloc(ctx, 256);
-    w.retry = (int32_t *)bc_dalloc(ctx, (size_t)4096 * 4);
-    w.retry_cap = 4096;
-    if (!w.next || !w.retry_count || !w.retry || hipHostMalloc((void **)&w.host, 256) != hipSuccess)
+    w.retry = (int32_t *)bc_dalloc(ctx, (size_t)RETRY_CAP * 4);
+    w.again = (int32_t *)bc_dalloc(ctx, (size_t)RETRY_CAP * 8);
+    if (!w.next || !w.retry_count || !w.retry || !w.again || hipHostMalloc((void **)&w.host, 256) != hipSuccess)
         return bc_fail(ctx, BC_ERR_NOMEM, "weighted form: allocation failed");
     return BC_OK;
 }
 
-static bc_status launch(bc_ctx *ctx, const WeightedBuffers &b, const int32_t *d_sources, const int32_t *slot_of,
-                        int64_t count, bool accumulate, double *delta_dump, int32_t *dist_dump, uint64_t *sigma_dump) {
+namespace {
+
+struct Outputs {
+    bool accumulate;
+    double *delta;
+    int32_t *dist;
+    uint64_t *sigma;
+};
+
+// One launch over `count` sources (slot_of: their rows of the outputs); *left
+// receives how many it put on the retry list.
+bc_status launch(bc_ctx *ctx, const WeightedBuffers &b, const int32_t *d_sources, const int32_t *slot_of,
+                 int64_t count, const Outputs &o, uint32_t *left) {
     WeightedState &w = ctx->wt;
     BC_HIP(ctx, hipMemsetAsync(w.next, 0, sizeof(unsigned long long), ctx->stream));
+    BC_HIP(ctx, hipMemsetAsync(w.retry_count, 0, sizeof(uint32_t), ctx->stream));
     const int grid = (int)std::min<int64_t>(count, b.groups);
+    double *eb = o.accumulate && ctx->edges ? ctx->eb : nullptr;
     LaunchTimer t(ctx, "weighted_sweep");
-    hipLaunchKernelGGL(k_weighted_sweep, dim3(grid), dim3(PB), 0, ctx->stream, ctx->n, ctx->row_ptr, ctx->col,
-                       ctx->weight, d_sources, slot_of, count, (unsigned long long *)w.next, work_of(ctx, b),
-                       ctx->bc, ctx->status, accumulate ? 1 : 0, delta_dump, dist_dump, sigma_dump,
-                       accumulate && ctx->edges ? ctx->eb : nullptr);
+    if (&b == &w.lds) {
+        const int T = count <= w.lds_few ? 1024 : w.lds_threads;
+        const auto k = T == 512 ? k_weighted_lds<512> : k_weighted_lds<1024>;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(T), dist_lds(ctx->n), ctx->stream, ctx->n, ctx->row_ptr,
+                           ctx->col, ctx->weight, d_sources, count, (unsigned long long *)w.next, work_of(ctx, b),
+                           (uint64_t(1) << 63) / (uint64_t)std::max(ctx->max_degree, 1), ctx->bc, o.accumulate ? 1 : 0,
+                           o.delta, o.dist, o.sigma, eb);
+    } else {
+        hipLaunchKernelGGL(k_weighted_sweep, dim3(grid), dim3(PB), 0, ctx->stream, ctx->n, ctx->row_ptr, ctx->col,
+                           ctx->weight, d_sources, slot_of, count, (unsigned long long *)w.next, work_of(ctx, b),
+                           ctx->bc, ctx->status, o.accumulate ? 1 : 0, o.delta, o.dist, o.sigma, eb);
+    }
     t.done();
     BC_HIP(ctx, hipGetLastError());
+    BC_HIP(ctx, hipMemcpyAsync(w.host, w.retry_count, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
+    BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    *left = *w.host;
     return BC_OK;
 }
+
+// The `left` sources on the retry list and their rows, into w.again.
+bc_status gather_left(bc_ctx *ctx, const int32_t *d_sources, int64_t count, uint32_t left) {
+    WeightedState &w = ctx->wt;
+    std::vector<int32_t> both(2 * (size_t)left), all((size_t)count);
+    BC_HIP(ctx, hipMemcpy(both.data() + left, w.retry, left * sizeof(int32_t), hipMemcpyDeviceToHost));
+    BC_HIP(ctx, hipMemcpy(all.data(), d_sources, (size_t)count * sizeof(int32_t), hipMemcpyDeviceToHost));
+    for (uint32_t i = 0; i < left; ++i) both[i] = all[(size_t)both[left + i]];
+    BC_HIP(ctx, hipMemcpy(w.again, both.data(), both.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    return BC_OK;
+}
+
+} // namespace
 
 bc_status weighted_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool accumulate,
                        double *delta_dump, int32_t *dist_dump, uint64_t *sigma_dump) {
     WeightedState &w = ctx->wt;
     // the retry list holds at most one entry per source in flight: run in chunks
-    for (int64_t c0 = 0; c0 < count; c0 += w.retry_cap) {
-        const int64_t cnt = std::min<int64_t>(w.retry_cap, count - c0);
-        BC_HIP(ctx, hipMemsetAsync(w.retry_count, 0, sizeof(uint32_t), ctx->stream));
+    for (int64_t c0 = 0; c0 < count; c0 += RETRY_CAP) {
+        const int64_t cnt = std::min<int64_t>(RETRY_CAP, count - c0);
+        const int32_t *src = d_sources + c0;
         // per-source output rows are positions in the whole list
-        bc_status st = launch(ctx, w.main, d_sources + c0, nullptr, cnt, accumulate,
-                              delta_dump ? delta_dump + (size_t)c0 * ctx->n : nullptr,
-                              dist_dump ? dist_dump + (size_t)c0 * ctx->n : nullptr,
-                              sigma_dump ? sigma_dump + (size_t)c0 * ctx->n : nullptr);
+        const size_t row = (size_t)c0 * ctx->n;
+        const Outputs o{accumulate, delta_dump ? delta_dump + row : nullptr, dist_dump ? dist_dump + row : nullptr,
+                        sigma_dump ? sigma_dump + row : nullptr};
+        const bool lds = w.lds_threads && !w.lds_off;
+        uint32_t left = 0;
+        bc_status st = launch(ctx, lds ? w.lds : w.main, src, nullptr, cnt, o, &left);
         if (st != BC_OK) return st;
-        BC_HIP(ctx, hipMemcpyAsync(w.host, w.retry_count, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
-        BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        const uint32_t nretry = *w.host;
-        if (nretry == 0) continue;
+        if (left && lds) {
+            w.lds_off = 2 * (int64_t)left > cnt; // long distances: the other sweep straight away from now on
+            if ((st = gather_left(ctx, src, cnt, left)) != BC_OK) return st;
+            if ((st = launch(ctx, w.main, w.again, w.again + left, left, o, &left)) != BC_OK) return st;
+        }
+        if (left == 0) continue;
         if (!w.big.dist) {
             const int64_t cap = pow2_at_least((int64_t)std::max(ctx->nnz, 1) + 1);
             int groups = 64;
@@ -457,28 +839,12 @@ bc_status weighted_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, boo
             st = alloc_work(ctx, w.big, cap, groups, true);
             if (st != BC_OK) return st;
         }
-        // sources of the retried rows, gathered on the host
-        std::vector<int32_t> rows(nretry), srcs(nretry);
-        BC_HIP(ctx, hipMemcpy(rows.data(), w.retry, nretry * sizeof(int32_t), hipMemcpyDeviceToHost));
-        std::vector<int32_t> all((size_t)cnt);
-        BC_HIP(ctx, hipMemcpy(all.data(), d_sources + c0, (size_t)cnt * sizeof(int32_t), hipMemcpyDeviceToHost));
-        for (uint32_t i = 0; i < nretry; ++i) srcs[i] = all[(size_t)rows[i]];
-        int32_t *dev = (int32_t *)bc_dalloc(ctx, 2 * (size_t)nretry * sizeof(int32_t));
-        if (!dev) return bc_fail(ctx, BC_ERR_NOMEM, "weighted form: retry allocation failed");
-        BC_HIP(ctx, hipMemcpy(dev, srcs.data(), nretry * sizeof(int32_t), hipMemcpyHostToDevice));
-        BC_HIP(ctx, hipMemcpy(dev + nretry, rows.data(), nretry * sizeof(int32_t), hipMemcpyHostToDevice));
-        BC_HIP(ctx, hipMemsetAsync(w.retry_count, 0, sizeof(uint32_t), ctx->stream));
-        st = launch(ctx, w.big, dev, dev + nretry, nretry, accumulate,
-                    delta_dump ? delta_dump + (size_t)c0 * ctx->n : nullptr,
-                    dist_dump ? dist_dump + (size_t)c0 * ctx->n : nullptr,
-                    sigma_dump ? sigma_dump + (size_t)c0 * ctx->n : nullptr);
-        BC_HIP(ctx, hipMemcpyAsync(w.host, w.retry_count, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
-        BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        bc_dfree(ctx, dev);
-        if (st != BC_OK) return st;
-        if (*w.host != 0) // cannot happen: the retry workspace holds any source's lists
+        if ((st = gather_left(ctx, src, cnt, left)) != BC_OK) return st;
+        const uint32_t outgrown = left;
+        if ((st = launch(ctx, w.big, w.again, w.again + left, left, o, &left)) != BC_OK) return st;
+        if (left != 0) // cannot happen: the retry workspace holds any source's lists
             return bc_fail(ctx, BC_ERR_DEVICE, "weighted form: a source outgrew the retry workspace");
-        ctx->wt.retried += nretry;
+        ctx->wt.retried += outgrown;
     }
     return BC_OK;
 }
