@@ -497,6 +497,7 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
     else if (form == BC_FORM_SPARSE || form == BC_FORM_HYBRID || form == BC_FORM_ALGEBRAIC)
         ps = tune_prepare(ctx, opt, form);
     if (ps == BC_OK && small_takes_batches(ctx)) ps = small_prepare(ctx);
+    if (ps == BC_OK) ps = fold_prepare(ctx, ucol);
     if (ps != BC_OK) return bail(ps, ctx->err);
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return bail(BC_ERR_DEVICE, "stream synchronisation failed");
     *out = ctx;
@@ -695,7 +696,7 @@ bc_status bc_run(bc_ctx *ctx, const int32_t *sources, int64_t count, bc_mem mem)
     if (cnt == 0 || ctx->n == 0) return BC_OK;
     if (ctx->form == BC_FORM_PLAIN_FP64) s = plain_run(ctx, d_src, cnt, true, nullptr, nullptr, nullptr);
     else if (ctx->form == BC_FORM_SPARSE || ctx->form == BC_FORM_ALGEBRAIC || ctx->form == BC_FORM_HYBRID)
-        s = sparse_run(ctx, d_src, cnt);
+        s = sparse_run(ctx, d_src, cnt, sources == nullptr);
     else s = bc_fail(ctx, BC_ERR_UNSUPPORTED, "form not available");
     if (s == BC_OK) ctx->sources_run += cnt;
     return s;

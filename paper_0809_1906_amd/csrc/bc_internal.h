@@ -32,11 +32,23 @@ struct BatchCtl {
     int32_t total;          // sources in the run
     const int32_t *src;     // the run's internal source ids
     int32_t *redo;          // [batches] first source of each batch handed back to the host
+    int64_t wt_off;         // from a source to its weight (0: all 1)
     uint32_t redo_count;
     uint32_t max_nlev;      // deepest level count among the batches that completed
     uint32_t need_wide;     // a handed-back batch needs uint64 counts
     uint32_t deep;          // a handed-back batch went past the captured depth
     uint32_t arrived;       // blocks of the current batch check that have finished
+    int32_t leafy;          // batches of sources that stand for their leaves too
+    uint32_t seen;          // deepest level count, leaves as sources included
+};
+static_assert(sizeof(BatchCtl) <= 64, "its pinned copy");
+
+// The sources of a run over every vertex, without the leaves (vertices of one
+// neighbour): a leaf's sweep is its neighbour's, one level deeper.
+struct FoldState {
+    int32_t *src = nullptr; // [2][count]: sources (-1: none), then how many sources each stands for
+    int64_t count = 0;      // 0: every vertex is its own source
+    int64_t leafy = 0;      // the first entries, whole batches, have leaves
 };
 
 // State of the batched sparse form (per-level frontier bitmaps).
@@ -51,7 +63,8 @@ struct SparseState {
     uint64_t *visited = nullptr; // [n][words]
     uint64_t *sigma = nullptr;   // [n][batch] as uint64, or uint32 in its first half
     float *cval = nullptr;       // [n][batch]  c(v) = (1 + delta(v)) / sigma(v)
-    int32_t *src = nullptr;      // [batch] sources of the current batch (-1 = empty lane)
+    int32_t *src = nullptr;      // [2][batch] sources of the current batch (-1 = empty lane), their weights
+    int64_t wt_off = 0;          // the current run's: from a source to its weight (0: all 1)
     unsigned long long *reach = nullptr; // [0] the batch's sources' component sizes summed,
                                          // [1] (vertex, source) pairs reached so far
     uint32_t *any_host = nullptr; // pinned mirror of any, read once per batch
@@ -251,6 +264,7 @@ struct bc_ctx {
     AlgebraicState al;
     PlainState pl;
     WeightedState wt;
+    FoldState fold;
     MultiState mg;
     SmallState sm;
     HybridState hy;
@@ -402,7 +416,9 @@ bc_status algebraic_release(bc_ctx *ctx);
 // One batch of at most sp.batch internal source ids (device memory) through
 // the batched forms; accumulate = false leaves BC untouched.
 bc_status sparse_batch(bc_ctx *ctx, const int32_t *d_sources, int32_t count, bool accumulate);
-bc_status sparse_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count);
+// all: the sources are every vertex
+bc_status sparse_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool all);
+bc_status fold_prepare(bc_ctx *ctx, const int32_t *h_col);
 // Reads back what replayed batches found and re-runs the batches they handed
 // back (on the host-driven path); synchronises.  A no-op when nothing is
 // pending.  Every entry point calls it before touching the context's state.
