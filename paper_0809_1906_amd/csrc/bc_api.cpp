@@ -497,7 +497,7 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
     else if (form == BC_FORM_SPARSE || form == BC_FORM_HYBRID || form == BC_FORM_ALGEBRAIC)
         ps = tune_prepare(ctx, opt, form);
     if (ps == BC_OK && small_takes_batches(ctx)) ps = small_prepare(ctx);
-    if (ps == BC_OK) ps = fold_prepare(ctx, ucol);
+    if (ps == BC_OK) ps = order_prepare(ctx, ucol, new_of_old);
     if (ps != BC_OK) return bail(ps, ctx->err);
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return bail(BC_ERR_DEVICE, "stream synchronisation failed");
     *out = ctx;
@@ -600,7 +600,8 @@ bc_status bc_create_many(const bc_graph *gs, int32_t count, const bc_options *op
     return BC_OK;
 }
 
-static bc_status stage_sources(bc_ctx *ctx, const int32_t *sources, int64_t count, bc_mem mem,
+// any_order: the sources may be dealt to batches in another order than given.
+static bc_status stage_sources(bc_ctx *ctx, const int32_t *sources, int64_t count, bc_mem mem, bool any_order,
                                const int32_t **d_out, int64_t *count_out) {
     if (count == -1 && sources == nullptr) count = ctx->n;
     else if (count < 0 || (count > 0 && !sources)) return bc_fail(ctx, BC_ERR_INVALID_ARG, "bad sources/count");
@@ -632,6 +633,19 @@ static bc_status stage_sources(bc_ctx *ctx, const int32_t *sources, int64_t coun
             snprintf(buf, sizeof buf, "source %d at position %lld is outside [0,%d)", hs[i], (long long)i, ctx->n);
             return bc_fail(ctx, BC_ERR_INVALID_ARG, buf);
         }
+    std::vector<int32_t> ordered;
+    if (any_order && count > ctx->sp.batch && count <= INT32_MAX && !ctx->place.empty()) {
+        // by their places, in one counting pass
+        std::vector<int32_t> at((size_t)ctx->n + 1, 0);
+        for (int64_t i = 0; i < count; ++i) ++at[(size_t)ctx->place[(size_t)hs[i]] + 1];
+        for (int32_t p = 0; p < ctx->n; ++p) at[(size_t)p + 1] += at[(size_t)p];
+        ordered.resize((size_t)count);
+        for (int64_t i = 0; i < count; ++i) {
+            int32_t &to = at[(size_t)ctx->place[(size_t)hs[i]]];
+            ordered[(size_t)to++] = hs[i];
+        }
+        hs = ordered.data();
+    }
     if (count > 0)
         BC_HIP(ctx, hipMemcpyAsync(ctx->sources, hs, sizeof(int32_t) * (size_t)count, hipMemcpyHostToDevice, ctx->stream));
     // the caller's (or our) host array must stay alive until the copy is done
@@ -691,7 +705,7 @@ bc_status bc_run(bc_ctx *ctx, const int32_t *sources, int64_t count, bc_mem mem)
     }
     const int32_t *d_src = nullptr;
     int64_t cnt = 0;
-    s = stage_sources(ctx, sources, count, mem, &d_src, &cnt);
+    s = stage_sources(ctx, sources, count, mem, true, &d_src, &cnt);
     if (s != BC_OK) return s;
     if (cnt == 0 || ctx->n == 0) return BC_OK;
     if (ctx->form == BC_FORM_PLAIN_FP64) s = plain_run(ctx, d_src, cnt, true, nullptr, nullptr, nullptr);
@@ -788,7 +802,7 @@ bc_status bc_read_sssp(bc_ctx *ctx, const int32_t *sources, int32_t count,
     if (!sources || count < 1 || count > maxc) return bc_fail(ctx, BC_ERR_INVALID_ARG, "count must be in [1, batch]");
     const int32_t *d_src = nullptr;
     int64_t cnt = 0;
-    s = stage_sources(ctx, sources, count, BC_MEM_HOST, &d_src, &cnt);
+    s = stage_sources(ctx, sources, count, BC_MEM_HOST, false, &d_src, &cnt);
     if (s != BC_OK) return s;
     size_t cells = (size_t)count * (size_t)std::max(ctx->n, 1);
     int32_t *dd = (int32_t *)bc_dalloc(ctx, cells * sizeof(int32_t));

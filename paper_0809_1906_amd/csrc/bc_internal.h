@@ -43,11 +43,12 @@ struct BatchCtl {
 };
 static_assert(sizeof(BatchCtl) <= 64, "its pinned copy");
 
-// The sources of a run over every vertex, without the leaves (vertices of one
-// neighbour): a leaf's sweep is its neighbour's, one level deeper.
+// The sources of a run over every vertex, sources of one neighbourhood next to
+// each other, without the leaves (vertices of one neighbour): a leaf's sweep is
+// its neighbour's, one level deeper.
 struct FoldState {
     int32_t *src = nullptr; // [2][count]: sources (-1: none), then how many sources each stands for
-    int64_t count = 0;      // 0: every vertex is its own source
+    int64_t count = 0;      // 0: every vertex, by its number
     int64_t leafy = 0;      // the first entries, whole batches, have leaves
 };
 
@@ -265,6 +266,7 @@ struct bc_ctx {
     PlainState pl;
     WeightedState wt;
     FoldState fold;
+    std::vector<int32_t> place; // batched pulls: each vertex's place in the order of the sources (caller's numbers)
     MultiState mg;
     SmallState sm;
     HybridState hy;
@@ -418,7 +420,7 @@ bc_status algebraic_release(bc_ctx *ctx);
 bc_status sparse_batch(bc_ctx *ctx, const int32_t *d_sources, int32_t count, bool accumulate);
 // all: the sources are every vertex
 bc_status sparse_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool all);
-bc_status fold_prepare(bc_ctx *ctx, const int32_t *h_col);
+bc_status order_prepare(bc_ctx *ctx, const int32_t *h_col, const std::vector<int32_t> &new_of_old);
 // Reads back what replayed batches found and re-runs the batches they handed
 // back (on the host-driven path); synchronises.  A no-op when nothing is
 // pending.  Every entry point calls it before touching the context's state.

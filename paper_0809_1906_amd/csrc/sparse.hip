@@ -1359,7 +1359,7 @@ bc_status record_batch_t(bc_ctx *ctx, int32_t L, const std::vector<uint8_t> &pla
     for (int32_t lv = L - 1; lv >= lowest && st == BC_OK; --lv)
         st = launch_bwd_level<NW, S>(ctx, b, lv, lv >= 1 && (plan[(size_t)lv] & 2), true, true, nullptr, true);
     if (st != BC_OK) return st;
-    if (ctx->fold.count) launch_fold_sources(ctx, s.lvflag);
+    if (ctx->fold.leafy) launch_fold_sources(ctx, s.lvflag);
     BC_HIP(ctx, hipGetLastError());
     return BC_OK;
 }
@@ -1800,47 +1800,76 @@ bc_status sparse_run(bc_ctx *ctx, const int32_t *d_src, int64_t count, bool all)
     return st;
 }
 
+// The order in which batched pulls take their sources: by the neighbour of
+// the highest degree.  What bounds a level is the (row, word) pairs with a
+// source at it and the gathers for them, and sources that share a hub reach
+// the same rows at the same levels: of a word's 64 sources more are active at
+// once, and fewer words are.  ms by degree / by
+// that neighbour: RMAT-16 103 / 88, RMAT-14 8.6 / 7.5, RMAT-13 with edge terms
+// 5.5 / 4.9; a random graph of 20000 vertices and degree 10 26.7 / 26.9.  The
+// second neighbour as well gained nothing more (RMAT-16 85.3 / 84.9 as lists).
+//
 // A leaf s with neighbour p: every shortest path from s goes through p, so for
 // v other than p its dependencies, from the same counts and c in the same
 // order, are p's, and a run over every vertex need not sweep from s.  Entries
 // that stand for leaves come first, in whole batches, so that a batch's depth
 // tells its leaves' depth: one more.  (Two vertices joined to each other only
 // stay as they are.)  RMAT-16, of whose 46630 vertices 8595 are leaves, batch
-// 256, all sources: 135 ms without, 103 with.  Edge terms take every source.
-bc_status fold_prepare(bc_ctx *ctx, const int32_t *h_col) {
+// 256, all sources by degree: 135 ms with the leaves, 103 without.  Edge terms
+// take every source.
+bc_status order_prepare(bc_ctx *ctx, const int32_t *h_col, const std::vector<int32_t> &new_of_old) {
     if (ctx->form != BC_FORM_SPARSE && ctx->form != BC_FORM_HYBRID) return BC_OK;
     // levels by products sum in FP32, in an order of their own
     if (ctx->hy.products && (ctx->al.every_level || ctx->hy.theta_fwd <= 1.0 || ctx->hy.theta_bwd <= 1.0)) return BC_OK;
-    if (ctx->weighted || ctx->edges || ctx->sm.on) return BC_OK;
+    if (ctx->weighted || ctx->sm.on || ctx->n <= ctx->sp.batch) return BC_OK;
     const std::vector<int32_t> &rp = ctx->h_row_ptr;
     const int32_t n = ctx->n;
     const int64_t B = ctx->sp.batch;
     auto degree = [&](int32_t v) { return rp[(size_t)v + 1] - rp[(size_t)v]; };
+    // the vertices by that neighbour, those without one last
+    std::vector<int32_t> hub((size_t)n, n), order((size_t)n), at((size_t)n + 2, 0);
+    for (int32_t v = 0; v < n; ++v) {
+        int32_t best = 0;
+        for (int32_t e = rp[(size_t)v]; e < rp[(size_t)v + 1]; ++e) {
+            if (degree(h_col[e]) <= best) continue;
+            hub[(size_t)v] = h_col[e];
+            best = degree(h_col[e]);
+            if (!new_of_old.empty()) break; // rows list their neighbours by degree
+        }
+        ++at[(size_t)hub[(size_t)v] + 1];
+    }
+    for (int32_t p = 0; p <= n; ++p) at[(size_t)p + 1] += at[(size_t)p];
+    for (int32_t v = 0; v < n; ++v) order[(size_t)at[(size_t)hub[(size_t)v]]++] = v;
+    ctx->place.resize((size_t)n);
+    {
+        std::vector<int32_t> place((size_t)n);
+        for (int32_t i = 0; i < n; ++i) place[(size_t)order[(size_t)i]] = i;
+        for (int32_t v = 0; v < n; ++v) ctx->place[(size_t)v] = place[(size_t)(new_of_old.empty() ? v : new_of_old[(size_t)v])];
+    }
     std::vector<int32_t> weight((size_t)n, 1);
-    for (int32_t v = 0; v < n; ++v) {
-        if (degree(v) != 1) continue;
-        const int32_t p = h_col[rp[(size_t)v]];
-        if (degree(p) == 1) continue;
+    int64_t leafy = 0, rest = n;
+    for (int32_t v = 0; v < n && !ctx->edges; ++v) {
+        if (degree(v) != 1 || degree(hub[(size_t)v]) == 1) continue;
         weight[(size_t)v] = 0;
-        ++weight[(size_t)p];
+        --rest;
+        if (++weight[(size_t)hub[(size_t)v]] == 2) ++leafy, --rest;
     }
-    int64_t leafy = 0, rest = 0;
-    for (int32_t v = 0; v < n; ++v) {
-        leafy += weight[(size_t)v] > 1;
-        rest += weight[(size_t)v] == 1;
+    const int64_t front = (leafy + B - 1) / B;
+    if (32 * (front + (rest + B - 1) / B) > 31 * ((n + B - 1) / B)) { // no batches saved to speak of
+        std::fill(weight.begin(), weight.end(), 1);
+        leafy = 0;
+        rest = n;
     }
-    const int64_t before = (n + B - 1) / B, front = (leafy + B - 1) / B, after = front + (rest + B - 1) / B;
-    if (32 * after > 31 * before) return BC_OK; // not worth the other list
     FoldState f;
-    f.leafy = front * B;
+    f.leafy = leafy ? front * B : 0;
     f.count = f.leafy + rest;
     std::vector<int32_t> both(2 * (size_t)f.count, -1);
     size_t a = 0, b = (size_t)f.leafy;
-    for (int32_t v = 0; v < n; ++v) {
+    for (const int32_t v : order) {
         if (weight[(size_t)v] == 0) continue;
-        const size_t at = weight[(size_t)v] > 1 ? a++ : b++;
-        both[at] = v;
-        both[(size_t)f.count + at] = weight[(size_t)v];
+        const size_t to = weight[(size_t)v] > 1 ? a++ : b++;
+        both[to] = v;
+        both[(size_t)f.count + to] = weight[(size_t)v];
     }
     f.src = (int32_t *)bc_dalloc(ctx, both.size() * sizeof(int32_t));
     if (!f.src) return bc_fail(ctx, BC_ERR_NOMEM, "source list allocation failed");

@@ -56,6 +56,18 @@ def test_leaf_sources(gpu_lib, name, form, batch):
         assert rel_err(ctx.read(), oracle.bc(g) + oracle.bc(g, sources=every[:batch + 3])) <= 1e-5
 
 
+def test_lists_with_repeats(gpu_lib):
+    g = GRAPHS["hubs"]()
+    src = np.concatenate([gg.sample_sources(g.n, 700, 3), gg.sample_sources(g.n, 90, 4), np.full(50, 5)]).astype(np.int32)
+    want = oracle.edge_bc(g, sources=src, threads=8)
+    for edges in (False, True):
+        with gpu_lib.BC(g, form="sparse", batch=256, edges=edges) as ctx:
+            ctx.run(src)
+            assert rel_err(ctx.read(), want[0]) <= 1e-5
+            if edges:
+                assert rel_err(ctx.read_edges(), want[1]) <= 1e-5
+
+
 def test_leaf_sources_host_driven(gpu_lib):
     g = gg.rmat(13, 16, 2)
     want = oracle.bc(g)
