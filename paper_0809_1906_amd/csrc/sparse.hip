@@ -132,6 +132,17 @@ __device__ __forceinline__ double wave_sum8(const double (&p)[8], int lane) {
     return y;
 }
 
+// The lane's bit of a mask that the whole wave shares: the mask is the
+// condition register, where a shift by the lane number would be a vector
+// operation or two.
+__device__ __forceinline__ bool in_mask(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// p[lane] of a p that the whole wave shares: a scalar base and a 32-bit offset.
+template <typename T>
+__device__ __forceinline__ T at_lane(const T *p, int lane) {
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + (uint32_t)lane * (uint32_t)sizeof(T));
+}
+
 // Last-arriver protocol for split rows: every segment wave of heavy row h adds
 // its partial sums into hacc with device-scope atomics, waits until they have
 // completed, then counts itself in arrive[h]; the wave that brings the count to
@@ -161,7 +172,6 @@ __device__ __forceinline__ void fwd_scan(const Topo &t, int32_t beg, int32_t end
                                          const uint32_t *__restrict__ any_cur, const uint64_t *__restrict__ fcur,
                                          const G *__restrict__ sigma, int lane, uint64_t (&acc)[NW], bool &ovf) {
     constexpr int ARCS = NW >= GDEPTH ? 1 : GDEPTH / NW; // arcs per round, ARCS * NW gathers in flight
-    const G *sig = sigma + lane;
     for (int32_t base = beg; base < end; base += 64) {
         const int32_t e = base + lane;
         int32_t v = 0;
@@ -180,46 +190,59 @@ __device__ __forceinline__ void fwd_scan(const Topo &t, int32_t beg, int32_t end
         for (int q = 0; q < NW; ++q) nz |= f[q];
         uint64_t act = __ballot(nz != 0);
         if constexpr (UNIT) {
+            uint32_t ones[NW] = {};
             while (act) {
                 const int j = pop_lowest(act);
 #pragma unroll
-                for (int q = 0; q < NW; ++q) acc[q] += (rl64(f[q], j) >> lane) & 1;
+                for (int q = 0; q < NW; ++q) ones[q] += in_mask(rl64(f[q], j)) ? 1u : 0u;
             }
+#pragma unroll
+            for (int q = 0; q < NW; ++q) acc[q] += ones[q];
             continue;
         }
-        // Straight-line loads, the lane's bit selecting after all are issued:
-        // a load under a per-lane branch was compiled with a wait for its own
-        // result, so the gathers of a round ran one after another.  An arc
-        // slot past the last active arc, or a word with no source of this
-        // lane's mask, reads row 0 instead: a valid, cached address whose
-        // value is then dropped.
+        // What bounds the scan is the vector instructions of an (arc, word)
+        // pair as much as its gather (they were 58% of the kernel's time): so
+        // the word is the gather's mask as it stands, a word without sources
+        // costs a branch, 64 arcs of 16-bit counts sum in 32 bits, and 32-bit
+        // counts, which cannot overflow a 64-bit sum, are not tested.  Thirteen
+        // vector instructions a pair are now five; with the same mask in the
+        // backward (ten, now seven), all sources, ms before / now: RMAT-16
+        // batch 256 85.8 / 76.4, 512 88.2 / 79.4; RMAT-14 7.7 / 6.8; a random
+        // graph of 20000 vertices and degree 10 27.2 / 25.6.
         using X = typename std::conditional<sizeof(G) == 8, uint64_t, uint32_t>::type;
+        using P = typename std::conditional<sizeof(G) == 2, uint32_t, uint64_t>::type;
+        P part[NW];
+#pragma unroll
+        for (int q = 0; q < NW; ++q) part[q] = sizeof(G) == 2 ? 0 : (P)acc[q];
         while (act) {
             X x[ARCS][NW];
-            uint64_t m[ARCS][NW];
 #pragma unroll
             for (int a = 0; a < ARCS; ++a) {
-                const bool live = act != 0;
-                const int j = live ? pop_lowest(act) : 0;
-                const size_t row = live ? (size_t)rl32(v, j) * t.B : 0;
 #pragma unroll
-                for (int q = 0; q < NW; ++q) {
-                    m[a][q] = live ? rl64(f[q], j) : 0;
-                    x[a][q] = sig[m[a][q] != 0 ? row + (size_t)q * 64 : 0];
+                for (int q = 0; q < NW; ++q) x[a][q] = 0;
+                if (act) {
+                    const int j = pop_lowest(act);
+                    const G *row = sigma + (size_t)rl32(v, j) * t.B;
+#pragma unroll
+                    for (int q = 0; q < NW; ++q)
+                        if (in_mask(rl64(f[q], j))) x[a][q] = at_lane(row + (size_t)q * 64, lane);
                 }
             }
 #pragma unroll
             for (int a = 0; a < ARCS; ++a) {
 #pragma unroll
                 for (int q = 0; q < NW; ++q) {
-                    if ((m[a][q] >> lane) & 1) {
-                        const uint64_t s = acc[q] + (uint64_t)x[a][q];
-                        ovf |= s < acc[q];
-                        acc[q] = s;
-                    }
+                    // the widening stays here: moved up under the load's mask,
+                    // it made each gather wait for its own result
+                    __asm__("" : "+v"(x[a][q]));
+                    const P s = part[q] + (P)x[a][q];
+                    if (sizeof(G) == 8) ovf |= s < part[q];
+                    part[q] = s;
                 }
             }
         }
+#pragma unroll
+        for (int q = 0; q < NW; ++q) acc[q] = sizeof(G) == 2 ? acc[q] + part[q] : (uint64_t)part[q];
     }
 }
 
@@ -230,7 +253,6 @@ __device__ __forceinline__ void bwd_scan(const Topo &t, int32_t beg, int32_t end
                                          const uint32_t *__restrict__ any_next, const uint64_t *__restrict__ fnext,
                                          const float *__restrict__ cval, int lane, double (&acc)[NW]) {
     constexpr int ARCS = NW >= GDEPTH ? 1 : GDEPTH / NW;
-    const float *c = cval + lane;
     for (int32_t base = beg; base < end; base += 64) {
         const int32_t e = base + lane;
         int32_t w = 0;
@@ -260,7 +282,7 @@ __device__ __forceinline__ void bwd_scan(const Topo &t, int32_t beg, int32_t end
 #pragma unroll
                     for (int q = 0; q < NW; ++q) {
                         const uint64_t gj = rl64(g[q], j);
-                        if (gj != 0 && ((gj >> lane) & 1)) x[a][q] = c[row + (size_t)q * 64];
+                        if (gj != 0 && in_mask(gj)) x[a][q] = at_lane(cval + row + (size_t)q * 64, lane);
                     }
                 }
             }
@@ -688,7 +710,7 @@ __device__ __forceinline__ void bwd_item_w(const Topo &t, int64_t wid, const uin
     }
     {
         // the single-word scan over word q: shift the row base by q words
-        const float *c = cval + (size_t)q * 64 + lane;
+        const float *c = cval + (size_t)q * 64;
         // edge betweenness: arc v -> w carries sum over this word's sources of
         // lambda(v) c(w) (the per-arc term of Theorem 1.1)
         const double sv = eb && ((F >> lane) & 1) ? (double)sigma[(size_t)v * t.B + (size_t)q * 64 + lane] : 0.0;
@@ -720,7 +742,8 @@ __device__ __forceinline__ void bwd_item_w(const Topo &t, int64_t wid, const uin
                     if (act) {
                         const int j = pop_lowest(act);
                         jj[u] = j;
-                        if ((rl64(g, j) >> lane) & 1) x[u] = c[(size_t)rl32(w, j) * t.B];
+                        const float *row = c + (size_t)rl32(w, j) * t.B;
+                        if (in_mask(rl64(g, j))) x[u] = at_lane(row, lane);
                     }
                 }
 #pragma unroll
