@@ -500,28 +500,17 @@ __device__ __forceinline__ void fwd_commit(int32_t w, const uint64_t (&vis)[NW],
 //   sig16: half the bytes of a uint32 row.
 enum { FWD_GENERAL = 0, FWD_UNIT = 1, FWD_HALF = 2 };
 template <int NW, typename S, int MODE>
-__device__ __forceinline__ void fwd_item(const Topo &t, int64_t wid, const uint32_t *__restrict__ any_cur,
-                                         const uint64_t *__restrict__ fcur, uint64_t *__restrict__ fnext,
-                                         uint64_t *__restrict__ visited, S *__restrict__ sigma,
-                                         uint16_t *__restrict__ sig16, unsigned long long *__restrict__ hacc,
-                                         uint32_t *__restrict__ arrive, uint32_t *__restrict__ any_next,
-                                         uint32_t *__restrict__ status, unsigned long long *__restrict__ lvmax_next,
-                                         int lane) {
-    Item it;
-    if (!item_of(t, wid, it)) return;
+__device__ __forceinline__ void fwd_row(const Topo &t, const Item &it, const uint64_t (&vis)[NW],
+                                        const uint32_t *__restrict__ any_cur, const uint64_t *__restrict__ fcur,
+                                        uint64_t *__restrict__ fnext, uint64_t *__restrict__ visited,
+                                        S *__restrict__ sigma, uint16_t *__restrict__ sig16,
+                                        unsigned long long *__restrict__ hacc, uint32_t *__restrict__ arrive,
+                                        uint32_t *__restrict__ any_next, uint32_t *__restrict__ status,
+                                        unsigned long long *__restrict__ lvmax_next, int lane) {
     const int32_t w = it.v;
-    uint64_t vis[NW], U[NW];
-    load_words<NW>(visited + (size_t)w * NW, lane, vis);
-    uint64_t anyU = 0;
+    uint64_t U[NW];
 #pragma unroll
-    for (int q = 0; q < NW; ++q) {
-        U[q] = ~vis[q];
-        anyU |= U[q];
-    }
-    if (anyU == 0) {
-        if (it.first && lane < NW) fnext[(size_t)w * NW + lane] = 0;
-        return;
-    }
+    for (int q = 0; q < NW; ++q) U[q] = ~vis[q];
     uint64_t acc[NW];
 #pragma unroll
     for (int q = 0; q < NW; ++q) acc[q] = 0;
@@ -576,29 +565,88 @@ __device__ __forceinline__ void fwd_item(const Topo &t, int64_t wid, const uint3
     if (__any(wide) && lane == 0) atomicOr(&status[1], 1u);
 }
 
-// The launches.  k_fwd_pull: each wave takes rows (or segments) wave, wave +
-// waves, ... of the n + nseg, eight waves per SIMD (the loop's extra live
-// values fit 64 registers for up to four words).  k_fwd_pull_row: one wave
-// per row or segment, for eight words per row, whose registers leave no room
-// for the loop.
+template <int NW, typename S, int MODE>
+__device__ __forceinline__ void fwd_item(const Topo &t, int64_t wid, const uint32_t *__restrict__ any_cur,
+                                         const uint64_t *__restrict__ fcur, uint64_t *__restrict__ fnext,
+                                         uint64_t *__restrict__ visited, S *__restrict__ sigma,
+                                         uint16_t *__restrict__ sig16, unsigned long long *__restrict__ hacc,
+                                         uint32_t *__restrict__ arrive, uint32_t *__restrict__ any_next,
+                                         uint32_t *__restrict__ status, unsigned long long *__restrict__ lvmax_next,
+                                         int lane) {
+    Item it;
+    if (!item_of(t, wid, it)) return;
+    uint64_t vis[NW];
+    load_words<NW>(visited + (size_t)it.v * NW, lane, vis);
+    uint64_t all = ~0ull;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) all &= vis[q];
+    if (~all == 0) {
+        if (it.first && lane < NW) fnext[(size_t)it.v * NW + lane] = 0;
+        return;
+    }
+    fwd_row<NW, S, MODE>(t, it, vis, any_cur, fcur, fnext, visited, sigma, sig16, hacc, arrive, any_next, status,
+                         lvmax_next, lane);
+}
+
+// The launches.  k_fwd_pull: each wave takes R light rows at a time (a lane a
+// word: most rows of most levels have nothing left to reach, and a wave that
+// looks at one row pays its chain of loads for that), then segments one by
+// one, eight waves per SIMD (the loop's extra live values fit 64 registers for
+// up to four words).  k_fwd_pull_row: one wave per row or segment, for eight
+// words per row, whose registers leave no room for the loop (batch 512, RMAT-16:
+// 71.5 ms, with the loop 80.0).  The R rows' results with k_bwd_pull_w's below.
 template <int NW, typename S, int MODE>
 __global__ __launch_bounds__(SB) __attribute__((amdgpu_waves_per_eu(8))) void k_fwd_pull(
     Topo t, const uint32_t *__restrict__ any_cur, const uint64_t *__restrict__ fcur, uint64_t *__restrict__ fnext,
     uint64_t *__restrict__ visited, S *__restrict__ sigma, uint16_t *__restrict__ sig16,
     unsigned long long *__restrict__ hacc, uint32_t *__restrict__ arrive, uint32_t *__restrict__ any_next,
-    uint32_t *__restrict__ status, unsigned long long *__restrict__ lvmax_next) {
+    uint32_t *__restrict__ status, unsigned long long *__restrict__ lvmax_next, int R) {
     const int lane = threadIdx.x & 63;
-    const int64_t items = (int64_t)t.n + t.nseg, waves = (int64_t)gridDim.x * WPB;
-    for (int64_t wid = (int64_t)blockIdx.x * WPB + (threadIdx.x >> 6); wid < items; wid += waves)
-        fwd_item<NW, S, MODE>(t, wid, any_cur, fcur, fnext, visited, sigma, sig16, hacc, arrive, any_next, status,
-                              lvmax_next, lane);
+    const int64_t light = ((int64_t)t.n + R - 1) / R, waves = (int64_t)gridDim.x * WPB;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (int64_t wid = (int64_t)blockIdx.x * WPB + wave; wid < light + t.nseg; wid += waves) {
+        if (wid >= light) {
+            fwd_item<NW, S, MODE>(t, t.n + (wid - light), any_cur, fcur, fnext, visited, sigma, sig16, hacc, arrive,
+                                  any_next, status, lvmax_next, lane);
+            continue;
+        }
+        // a lane per word of R rows
+        const int32_t v0 = (int32_t)(wid * R), v = v0 + lane / NW;
+        const bool mine = lane < R * NW && v < t.n;
+        uint64_t vis1 = 0;
+        int32_t hv = 0, b = 0, e = 0;
+        if (mine) {
+            vis1 = visited[(size_t)v0 * NW + lane];
+            hv = t.heavy_id[v];
+            b = t.rp[v];
+            e = t.rp[v + 1];
+        }
+        uint64_t act = __ballot(mine && hv < 0 && ~vis1 != 0);
+        constexpr uint64_t ROW = (1ull << NW) - 1;
+        if (mine && hv < 0 && ((act >> (lane / NW * NW)) & ROW) == 0) fnext[(size_t)v0 * NW + lane] = 0;
+        while (act) {
+            const int j = __builtin_ctzll(act) / NW * NW; // the row's first lane
+            act &= ~(ROW << j);
+            Item it;
+            it.v = v0 + j / NW;
+            it.beg = rl32(b, j);
+            it.end = rl32(e, j);
+            it.h = -1;
+            it.first = true;
+            uint64_t vis[NW];
+#pragma unroll
+            for (int q = 0; q < NW; ++q) vis[q] = rl64(vis1, j + q);
+            fwd_row<NW, S, MODE>(t, it, vis, any_cur, fcur, fnext, visited, sigma, sig16, hacc, arrive, any_next,
+                                 status, lvmax_next, lane);
+        }
+    }
 }
 template <int NW, typename S, int MODE>
 __global__ __launch_bounds__(SB) void k_fwd_pull_row(
     Topo t, const uint32_t *__restrict__ any_cur, const uint64_t *__restrict__ fcur, uint64_t *__restrict__ fnext,
     uint64_t *__restrict__ visited, S *__restrict__ sigma, uint16_t *__restrict__ sig16,
     unsigned long long *__restrict__ hacc, uint32_t *__restrict__ arrive, uint32_t *__restrict__ any_next,
-    uint32_t *__restrict__ status, unsigned long long *__restrict__ lvmax_next) {
+    uint32_t *__restrict__ status, unsigned long long *__restrict__ lvmax_next, int) {
     const int64_t wid = (int64_t)blockIdx.x * WPB + (threadIdx.x >> 6);
     if (wid < (int64_t)t.n + t.nseg)
         fwd_item<NW, S, MODE>(t, wid, any_cur, fcur, fnext, visited, sigma, sig16, hacc, arrive, any_next, status,
@@ -667,35 +715,12 @@ __global__ __launch_bounds__(SB) void k_bwd_pull(Topo t, const uint64_t *__restr
 // levels this keeps NW times more waves in flight than a wave per row, and a
 // word with no sources at this level costs its wave a single load.
 template <int NW, typename S, bool EB>
-__device__ __forceinline__ void bwd_item_w(const Topo &t, int64_t wid, const uint64_t *__restrict__ fcur,
-                                           const uint32_t *__restrict__ any_next, const uint64_t *__restrict__ fnext,
-                                           const S *__restrict__ sigma, float *__restrict__ cval,
-                                           const int32_t *__restrict__ src_lane, double *__restrict__ bc,
-                                           double *__restrict__ hacc, uint32_t *__restrict__ arrive,
-                                           double *__restrict__ delta_dump, int accumulate, double *__restrict__ eb,
-                                           int lane) {
-    (void)any_next; // the per-word pull reads successors' words directly
-    const int q = (int)(wid % NW);
-    Item it;
-    const int64_t r = wid / NW;
-    uint64_t F;
-    if (r < t.n) {
-        // a light row: its bounds, its heavy mark and its frontier word are
-        // independent loads, issued together
-        const int32_t v0 = (int32_t)r;
-        const int32_t hv = t.heavy_id[v0], b0 = t.rp[v0], e0 = t.rp[v0 + 1];
-        F = fcur[(size_t)v0 * NW + q];
-        if (hv >= 0 || F == 0) return;
-        it.v = v0;
-        it.beg = b0;
-        it.end = e0;
-        it.h = -1;
-        it.first = true;
-    } else {
-        if (!item_of(t, r, it)) return;
-        F = fcur[(size_t)it.v * NW + q];
-        if (F == 0) return;
-    }
+__device__ __forceinline__ void bwd_word(const Topo &t, const Item &it, int q, uint64_t F,
+                                         const uint64_t *__restrict__ fnext, const S *__restrict__ sigma,
+                                         float *__restrict__ cval, const int32_t *__restrict__ src_lane,
+                                         double *__restrict__ bc, double *__restrict__ hacc,
+                                         uint32_t *__restrict__ arrive, double *__restrict__ delta_dump,
+                                         int accumulate, double *__restrict__ eb, int lane) {
     const int32_t v = it.v;
     const uint64_t F1[1] = {F};
     double acc[1] = {0.0};
@@ -784,31 +809,92 @@ __device__ __forceinline__ void bwd_item_w(const Topo &t, int64_t wid, const uin
     }
 }
 
-// The launches.  k_bwd_pull_w: each wave takes items wave, wave + waves, ...
-// of the (n + nseg) * NW, eight waves per SIMD; a grid smaller than one wave
-// per item makes a launch whose level turns out empty (replayed batches) cost
-// a few thousand waves' flag reads instead of one wave per item.  With edge
-// terms the loop's extra live values would spill: one item per wave.
+template <int NW, typename S, bool EB>
+__device__ __forceinline__ void bwd_item_w(const Topo &t, int64_t wid, const uint64_t *__restrict__ fcur,
+                                           const uint64_t *__restrict__ fnext, const S *__restrict__ sigma,
+                                           float *__restrict__ cval, const int32_t *__restrict__ src_lane,
+                                           double *__restrict__ bc, double *__restrict__ hacc,
+                                           uint32_t *__restrict__ arrive, double *__restrict__ delta_dump,
+                                           int accumulate, double *__restrict__ eb, int lane) {
+    Item it;
+    const int64_t r = wid / NW;
+    const int q = (int)(wid % NW);
+    uint64_t F;
+    if (r < t.n) {
+        // a light row: its bounds, its heavy mark and its frontier word are
+        // independent loads, issued together
+        const int32_t v0 = (int32_t)r;
+        const int32_t hv = t.heavy_id[v0], b0 = t.rp[v0], e0 = t.rp[v0 + 1];
+        F = fcur[(size_t)v0 * NW + q];
+        if (hv >= 0 || F == 0) return;
+        it.v = v0;
+        it.beg = b0;
+        it.end = e0;
+        it.h = -1;
+        it.first = true;
+    } else {
+        if (!item_of(t, r, it)) return;
+        F = fcur[(size_t)it.v * NW + q];
+        if (F == 0) return;
+    }
+    bwd_word<NW, S, EB>(t, it, q, F, fnext, sigma, cval, src_lane, bc, hacc, arrive, delta_dump, accumulate, eb, lane);
+}
+
+// The launches.  k_bwd_pull_w: each wave takes C words of the light rows at a
+// time, loaded together with the rows' bounds, and goes on with those that
+// have sources at the level; then words of segments one by one; eight waves
+// per SIMD.  A grid smaller than one wave per item makes a launch whose level
+// turns out empty (replayed batches) cost a few thousand waves' flag reads
+// instead of one wave per item.  With edge terms the loop's extra live values
+// would spill: one item per wave.
+// R = C = 1 against R = 8, C = 16 on RMAT-16, batch 256, all sources: 76.4 and
+// 66.7 ms (C alone 70.9, R alone 73.6); on a ring lattice of 20000 (R = 4, C =
+// 8) 130 and 114.
 template <int NW, typename S>
 __global__ __launch_bounds__(SB) __attribute__((amdgpu_waves_per_eu(8))) void k_bwd_pull_w(
-    Topo t, const uint64_t *__restrict__ fcur, const uint32_t *__restrict__ any_next,
-    const uint64_t *__restrict__ fnext, const S *__restrict__ sigma, float *__restrict__ cval,
+    Topo t, const uint64_t *__restrict__ fcur, const uint64_t *__restrict__ fnext, const S *__restrict__ sigma, float *__restrict__ cval,
     const int32_t *__restrict__ src_lane, double *__restrict__ bc, double *__restrict__ hacc,
-    uint32_t *__restrict__ arrive, double *__restrict__ delta_dump, int accumulate, const uint32_t *__restrict__ lvf) {
+    uint32_t *__restrict__ arrive, double *__restrict__ delta_dump, int accumulate, const uint32_t *__restrict__ lvf, int C) {
     // lvf as in k_bwd_pull
     if (lvf) {
         if (lvf[0] == 0) return;
         if (lvf[1] == 0) fnext = nullptr;
     }
     const int lane = threadIdx.x & 63;
-    const int64_t items = ((int64_t)t.n + t.nseg) * NW, waves = (int64_t)gridDim.x * WPB;
-    for (int64_t wid = (int64_t)blockIdx.x * WPB + (threadIdx.x >> 6); wid < items; wid += waves)
-        bwd_item_w<NW, S, false>(t, wid, fcur, any_next, fnext, sigma, cval, src_lane, bc, hacc, arrive, delta_dump,
-                                 accumulate, nullptr, lane);
+    const int64_t words = (int64_t)t.n * NW, light = (words + C - 1) / C, waves = (int64_t)gridDim.x * WPB;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (int64_t wid = (int64_t)blockIdx.x * WPB + wave; wid < light + (int64_t)t.nseg * NW; wid += waves) {
+        if (wid >= light) {
+            bwd_item_w<NW, S, false>(t, words + (wid - light), fcur, fnext, sigma, cval, src_lane, bc, hacc, arrive,
+                                     delta_dump, accumulate, nullptr, lane);
+            continue;
+        }
+        const int64_t i0 = wid * C, i = i0 + lane;
+        uint64_t F1 = 0;
+        int32_t hv = 0, b = 0, e = 0;
+        if (lane < C && i < words) {
+            const int32_t v = (int32_t)(i / NW);
+            F1 = fcur[i];
+            hv = t.heavy_id[v];
+            b = t.rp[v];
+            e = t.rp[v + 1];
+        }
+        uint64_t act = __ballot(F1 != 0 && hv < 0);
+        while (act) {
+            const int j = pop_lowest(act);
+            Item it;
+            it.v = (int32_t)((i0 + j) / NW);
+            it.beg = rl32(b, j);
+            it.end = rl32(e, j);
+            it.h = -1;
+            it.first = true;
+            bwd_word<NW, S, false>(t, it, (int)((i0 + j) % NW), rl64(F1, j), fnext, sigma, cval, src_lane, bc, hacc,
+                                   arrive, delta_dump, accumulate, nullptr, lane);
+        }
+    }
 }
 template <int NW, typename S>
 __global__ __launch_bounds__(SB) void k_bwd_pull_we(Topo t, const uint64_t *__restrict__ fcur,
-                                                    const uint32_t *__restrict__ any_next,
                                                     const uint64_t *__restrict__ fnext, const S *__restrict__ sigma,
                                                     float *__restrict__ cval, const int32_t *__restrict__ src_lane,
                                                     double *__restrict__ bc, double *__restrict__ hacc,
@@ -821,7 +907,7 @@ __global__ __launch_bounds__(SB) void k_bwd_pull_we(Topo t, const uint64_t *__re
     }
     const int64_t wid = (int64_t)blockIdx.x * WPB + (threadIdx.x >> 6);
     if (wid < ((int64_t)t.n + t.nseg) * NW)
-        bwd_item_w<NW, S, true>(t, wid, fcur, any_next, fnext, sigma, cval, src_lane, bc, hacc, arrive, delta_dump,
+        bwd_item_w<NW, S, true>(t, wid, fcur, fnext, sigma, cval, src_lane, bc, hacc, arrive, delta_dump,
                                 accumulate, eb, threadIdx.x & 63);
 }
 
@@ -1042,6 +1128,17 @@ bc_status launch_batch_init(bc_ctx *ctx, const BatchShape &b, const int32_t *d_s
     return BC_OK;
 }
 
+// Rows (words) a wave of a pull looks at together: a power of two that leaves
+// `waves` waves, as a smaller graph needs them to fill the chip.  RMAT-16, RMAT-14
+// and RMAT-13, batch 256, ms: 4 rows and 16 words everywhere 65.7 / 8.3 / 3.6;
+// leaving 8192 waves 67.0 / 6.7 / 2.6; the rows 4096 waves 66.7 / 6.3 / 2.6; the
+// words 4096 waves 69.5 / 6.9 / 2.6.
+int at_once(int64_t items, int most, int waves) {
+    int k = 1;
+    while (2 * k <= most && items / (2 * k) >= waves) k *= 2;
+    return k;
+}
+
 // Forward level l -> l+1 of an unweighted batch.  products: this level goes
 // by products; next_products: level l+1 will (so its largest count is
 // recorded).  *l1_pulled tracks whether level 1 -> 2 filled the 16-bit counts.
@@ -1074,7 +1171,7 @@ bc_status launch_fwd_level(bc_ctx *ctx, const BatchShape &b, int32_t l, bool pro
     hipLaunchKernelGGL(kern, dim3(grid), dim3(SB), 0, ctx->stream, b.t, s.any + (size_t)l * b.aw,
                        s.front + (size_t)l * b.words, s.front + (size_t)(l + 1) * b.words, s.visited,
                        reinterpret_cast<S *>(s.sigma), sig16, (unsigned long long *)s.hacc, s.arrive,
-                       s.any + (size_t)(l + 1) * b.aw, ctx->status, next_products ? s.lvmax + l + 1 : nullptr);
+                       s.any + (size_t)(l + 1) * b.aw, ctx->status, next_products ? s.lvmax + l + 1 : nullptr, at_once(ctx->n, 64 / NW, 4096));
     tm.done();
     return BC_OK;
 }
@@ -1096,12 +1193,12 @@ bc_status launch_bwd_level(bc_ctx *ctx, const BatchShape &b, int32_t lv, bool pr
     LaunchTimer tm(ctx, "bwd_pull");
     const S *sigma = reinterpret_cast<const S *>(s.sigma);
     if (ctx->edges && accumulate) // edge terms come from the per-word pull, one wave per item
-        hipLaunchKernelGGL((k_bwd_pull_we<NW, S>), dim3(b.word_blocks), dim3(SB), 0, ctx->stream, b.t, fcur, anext, fnext,
+        hipLaunchKernelGGL((k_bwd_pull_we<NW, S>), dim3(b.word_blocks), dim3(SB), 0, ctx->stream, b.t, fcur, fnext,
                            sigma, s.cval, s.src, ctx->bc, s.hacc, s.arrive_w, ddump, 1, ctx->eb, lvf);
     else if (s.bwd_per_word || ctx->edges) {
         const int grid = s.bwd_grid > 0 ? std::min(b.word_blocks, s.bwd_grid) : b.word_blocks;
-        hipLaunchKernelGGL((k_bwd_pull_w<NW, S>), dim3(grid), dim3(SB), 0, ctx->stream, b.t, fcur, anext, fnext, sigma,
-                           s.cval, s.src, ctx->bc, s.hacc, s.arrive_w, ddump, accumulate ? 1 : 0, lvf);
+        hipLaunchKernelGGL((k_bwd_pull_w<NW, S>), dim3(grid), dim3(SB), 0, ctx->stream, b.t, fcur, fnext, sigma,
+                           s.cval, s.src, ctx->bc, s.hacc, s.arrive_w, ddump, accumulate ? 1 : 0, lvf, at_once((int64_t)ctx->n * NW, 64, 8192));
     } else
         hipLaunchKernelGGL((k_bwd_pull<NW, S>), dim3(b.pull_blocks), dim3(SB), 0, ctx->stream, b.t, fcur, anext, fnext,
                            sigma, s.cval, s.src, ctx->bc, s.hacc, s.arrive, ddump, accumulate ? 1 : 0, lvf);
@@ -1471,11 +1568,9 @@ bc_status sparse_prepare(bc_ctx *ctx, int32_t batch, int32_t split_degree) {
     s.words = batch / 64;
     s.split = split_degree > 0 ? split_degree : 128;
     {
-        // launch shapes of the pulls: 32 blocks of four waves per compute
-        // unit, each wave striding over the items.  Measured on RMAT-16 at
-        // batch 256 against one wave per item: the backward took a step from
-        // 181 to 173 ms host-driven and 182 to 171 ms replayed, the forward
-        // then to 172 and 169 ms; 16 and 64 blocks per unit were slower.
+        // launch shapes of the pulls: at most 32 blocks of four waves per
+        // compute unit, each wave striding over the items; 16 and 64 were
+        // slower (RMAT-16, batch 256).
         int cus = 0;
         BC_HIP(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
         s.bwd_grid = 32 * std::max(cus, 1);
