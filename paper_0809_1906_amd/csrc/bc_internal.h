@@ -85,7 +85,6 @@ struct SparseState {
     BatchCtl *ctl = nullptr;
     int32_t *redo = nullptr;
     int64_t redo_cap = 0;
-    hipStream_t cap_stream = nullptr;  // private stream the batch is captured on
     hipGraphExec_t gexec = nullptr;    // the recorded batch
     int32_t g_levels = 0;              // forward levels the graph holds
     bool g_wide = false;
@@ -277,7 +276,7 @@ struct bc_ctx {
     // graph, BC and stream; only its recorded batches run on its own stream,
     // between the fork and the join of a run.
     std::vector<bc_ctx *> lanes;
-    std::vector<hipStream_t> lane_streams;
+    std::vector<hipStream_t> lane_streams; // the device's, shared by its contexts
     std::vector<hipEvent_t> lane_events; // the fork, then each lane's join
     bool lanes_refused = false;          // their memory was not to be had
 

@@ -34,6 +34,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <type_traits>
 
@@ -1510,22 +1511,26 @@ void destroy_graphs(bc_ctx *ctx) {
 bc_status capture_batch(bc_ctx *ctx, int32_t L, const std::vector<uint8_t> &plan) {
     SparseState &s = ctx->sp;
     destroy_graphs(ctx);
-    if (!s.cap_stream) BC_HIP(ctx, hipStreamCreateWithFlags(&s.cap_stream, hipStreamNonBlocking));
+    // a stream of its own, kept no longer than the capture: a stream that lives
+    // counts when later ones are given their hardware queue
+    hipStream_t cap = nullptr;
+    BC_HIP(ctx, hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     hipStream_t saved = ctx->stream;
     hipGraph_t graph = nullptr;
     bc_status st = BC_OK;
-    hipError_t e = hipStreamBeginCapture(s.cap_stream, hipStreamCaptureModeThreadLocal);
+    hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        ctx->stream = s.cap_stream;
+        ctx->stream = cap;
         ctx->recording = true;
         st = record_batch(ctx, L, plan);
         ctx->stream = saved;
         ctx->recording = false;
-        const hipError_t e2 = hipStreamEndCapture(s.cap_stream, &graph);
+        const hipError_t e2 = hipStreamEndCapture(cap, &graph);
         if (e2 != hipSuccess) e = e2;
     }
     if (st == BC_OK && e == hipSuccess) e = hipGraphInstantiate(&s.gexec, graph, nullptr, nullptr, 0);
     if (graph) hipGraphDestroy(graph);
+    hipStreamDestroy(cap);
     if (st != BC_OK || e != hipSuccess) {
         s.gexec = nullptr;
         return st != BC_OK ? st : bc_hip(ctx, e, "recording a batch into a HIP graph");
@@ -1677,6 +1682,55 @@ int lanes_for(const bc_ctx *ctx, int64_t nb) {
     return (int)std::min<int64_t>(nb, 3 * written <= size_t(256) << 20 ? 3 : 2);
 }
 
+// The streams lanes run on, one set per device, shared by its contexts and
+// destroyed with the last context that uses them.  A process has four hardware
+// queues, and streams beyond that share them: with streams of their own, the
+// third context on a device had a lane in its caller's queue, and its lanes
+// ran one after another (RMAT-16 95 against 68 ms).  Work of different contexts
+// on one stream is in the order of its submission, as it would be on streams
+// that share a queue.
+struct LaneStreams {
+    std::mutex lock;
+    int users = 0;
+    std::vector<hipStream_t> streams;
+};
+LaneStreams &lane_streams_of(int device) {
+    static std::mutex lock;
+    static auto *all = new std::map<int, LaneStreams>; // a context may be destroyed after the statics
+    std::lock_guard<std::mutex> hold(lock);
+    return (*all)[device];
+}
+
+bool lane_streams_take(bc_ctx *ctx) {
+    if (!ctx->lane_streams.empty()) return true;
+    LaneStreams &p = lane_streams_of(ctx->device);
+    std::lock_guard<std::mutex> hold(p.lock);
+    while ((int)p.streams.size() < MAX_LANES) {
+        hipStream_t q = nullptr;
+        if (hipStreamCreateWithFlags(&q, hipStreamNonBlocking) != hipSuccess) {
+            if (p.users == 0) {
+                for (hipStream_t s : p.streams) hipStreamDestroy(s);
+                p.streams.clear();
+            }
+            return false;
+        }
+        p.streams.push_back(q);
+    }
+    ++p.users;
+    ctx->lane_streams = p.streams;
+    return true;
+}
+
+void lane_streams_give(bc_ctx *ctx) {
+    if (ctx->lane_streams.empty()) return;
+    LaneStreams &p = lane_streams_of(ctx->device);
+    std::lock_guard<std::mutex> hold(p.lock);
+    ctx->lane_streams.clear();
+    if (--p.users > 0) return;
+    for (hipStream_t q : p.streams) hipStreamDestroy(q);
+    p.streams.clear();
+}
+
 void lane_failed(bc_ctx *ctx, const bc_ctx *lane) {
     ctx->err = lane->err;
     ctx->poisoned = ctx->poisoned || lane->poisoned;
@@ -1719,26 +1773,21 @@ bc_status lane_prepare(bc_ctx *t, const bc_ctx *ctx) {
 // `lanes` lanes, this context's state being the first; false (and none kept
 // from this call) when their memory or streams cannot be had.
 bool ensure_lanes(bc_ctx *ctx, int lanes) {
-    if (ctx->lane_events.empty()) {
+    while (ctx->lane_events.size() < 1 + MAX_LANES) {
         hipEvent_t e = nullptr;
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return false;
         ctx->lane_events.push_back(e);
     }
+    if (!lane_streams_take(ctx)) return false;
     while ((int)ctx->lanes.size() < lanes - 1) {
         bc_ctx *t = new (std::nothrow) bc_ctx();
         if (!t) return false;
-        hipStream_t q = nullptr;
-        hipEvent_t e = nullptr;
-        if (lane_prepare(t, ctx) != BC_OK || hipStreamCreateWithFlags(&q, hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-            if (q) hipStreamDestroy(q);
+        if (lane_prepare(t, ctx) != BC_OK) {
             if (t->poisoned) lane_failed(ctx, t);
             lane_free(t);
             return false;
         }
         ctx->lanes.push_back(t);
-        ctx->lane_streams.push_back(q);
-        ctx->lane_events.push_back(e);
     }
     return true;
 }
@@ -1776,7 +1825,8 @@ bc_status run_lanes(bc_ctx *ctx, int lanes, const int32_t *d_src, int64_t count)
     all.insert(all.end(), ctx->lanes.begin(), ctx->lanes.begin() + (lanes - 1));
     std::vector<int64_t> first((size_t)lanes + 1);
     for (int i = 0; i <= lanes; ++i) first[(size_t)i] = nb * i / lanes;
-    auto stream = [&](int i) { return i == 0 ? ctx->stream : ctx->lane_streams[(size_t)i - 1]; };
+    auto stream = [&](int i) { return lanes > 1 ? ctx->lane_streams[(size_t)i] : ctx->stream; };
+    const int forked = lanes > 1 ? lanes : 0;
     // What a lane needs is allocated and recorded before the fork, in the order
     // of the context's own stream.
     for (int i = 1; i < lanes; ++i) {
@@ -1800,16 +1850,16 @@ bc_status run_lanes(bc_ctx *ctx, int lanes, const int32_t *d_src, int64_t count)
             return st;
         }
     }
-    BC_HIP(ctx, hipEventRecord(ctx->lane_events[0], ctx->stream));
-    for (int i = 1; i < lanes; ++i) BC_HIP(ctx, hipStreamWaitEvent(stream(i), ctx->lane_events[0], 0));
+    if (forked) BC_HIP(ctx, hipEventRecord(ctx->lane_events[0], ctx->stream));
+    for (int i = 0; i < forked; ++i) BC_HIP(ctx, hipStreamWaitEvent(stream(i), ctx->lane_events[0], 0));
     hipError_t e = hipSuccess;
     for (int64_t k = 0; k < (nb + lanes - 1) / lanes + 1 && e == hipSuccess; ++k)
         for (int i = 0; i < lanes && e == hipSuccess; ++i)
             if (first[(size_t)i] + k < first[(size_t)i + 1]) e = hipGraphLaunch(all[(size_t)i]->sp.gexec, stream(i));
     // join, whatever happened: nothing of a lane outlives the call unordered
-    for (int i = 1; i < lanes; ++i) {
-        hipError_t j = hipEventRecord(ctx->lane_events[(size_t)i], stream(i));
-        if (j == hipSuccess) j = hipStreamWaitEvent(ctx->stream, ctx->lane_events[(size_t)i], 0);
+    for (int i = 0; i < forked; ++i) {
+        hipError_t j = hipEventRecord(ctx->lane_events[(size_t)i + 1], stream(i));
+        if (j == hipSuccess) j = hipStreamWaitEvent(ctx->stream, ctx->lane_events[(size_t)i + 1], 0);
         if (j != hipSuccess) {
             (void)hipStreamSynchronize(stream(i));
             if (e == hipSuccess) e = j;
@@ -1843,13 +1893,12 @@ bc_status settle_one(bc_ctx *ctx, const BatchCtl &c) {
 } // namespace
 
 void lanes_release(bc_ctx *ctx) {
-    for (hipStream_t q : ctx->lane_streams) hipStreamSynchronize(q);
+    hipStreamSynchronize(ctx->stream); // the lanes' work is joined to it
     for (bc_ctx *t : ctx->lanes) lane_free(t);
-    for (hipStream_t q : ctx->lane_streams) hipStreamDestroy(q);
     for (hipEvent_t e : ctx->lane_events) hipEventDestroy(e);
     ctx->lanes.clear();
-    ctx->lane_streams.clear();
     ctx->lane_events.clear();
+    lane_streams_give(ctx);
 }
 
 static bc_status run_list(bc_ctx *ctx, const int32_t *d_src, int64_t count) {
@@ -2033,8 +2082,6 @@ void sparse_graphs_release(bc_ctx *ctx) {
     SparseState &s = ctx->sp;
     hipStreamSynchronize(ctx->stream); // no replay is in flight
     destroy_graphs(ctx);
-    if (s.cap_stream) hipStreamDestroy(s.cap_stream);
-    s.cap_stream = nullptr;
     s.g_pending = false;
 }
 
