@@ -1667,12 +1667,13 @@ constexpr int MAX_LANES = 3;
 
 // Lanes for a run of nb replayed batches.  Three while what they write stays
 // in the memory-side cache (256 MB), else two.  All sources, ms with 1 / 2 / 3
-// lanes: RMAT-13 with edge terms, batch 256, 10.2 / 6.7 / 5.5; RMAT-14 23.1 / 16.1
-// / 14.1, batch 512 19.1 / 14.2 / 12.9; RMAT-16 (108 MB a lane) 199 / 164 / 165;
-// G(5003, 50/5002) by products, batch 512, 4.5 / 3.3 / 3.2; G(16384, 256/16383)
-// (117 MB) 52.6 / 51.0 / 53.8.  Setting a lane up costs about a millisecond
-// once, so a first run of fewer than four batches goes without.  Kernel timing
-// counts launches of one chain; weighted batches are driven from the host.
+// lanes: RMAT-13 with edge terms, batch 256, 6.4 / 4.3 / 3.7; RMAT-14 11.3 / 7.6
+// / 6.5, batch 512 9.7 / 6.9 / 6.1; RMAT-16 (108 MB a lane) 94 / 67.5 / 66.0;
+// a ring lattice of 20000 204 / 136 / 116; G(5003, 50/5002) by products, batch
+// 512, 5.0 / 3.3 / 3.2; G(16384, 256/16383) (117 MB) 52.9 / 51.3 / 53.6.  Setting
+// a lane up costs about a millisecond once, so a first run of fewer than four
+// batches goes without.  Kernel timing counts launches of one chain; weighted
+// batches are driven from the host.
 int lanes_for(const bc_ctx *ctx, int64_t nb) {
     if (ctx->timing || ctx->weighted || ctx->host_driven || ctx->lanes_refused) return 1;
     if (nb < (ctx->lanes.empty() ? 4 : 2)) return 1;
