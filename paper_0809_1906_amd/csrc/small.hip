@@ -129,13 +129,13 @@ bool small_fits(const bc_ctx *ctx) {
 // The sparse and hybrid forms' line.  A batch pays two launches per level and
 // pulls every row at every level; the LDS sweep pays per arc and source.
 // Microseconds for one source / milliseconds for all, LDS against batches of
-// 256 (of 512 faster by a fifth): a path of 1000 1680 / 1.71 against 7620 /
-// 39; a ring lattice of 6001 213 / 2.1 against 1050 / 38; G(4000) degree 10
-// 90 / 0.39 against 176 / 2.8; RMAT-12 (97 thousand arcs) 140 / 1.1 against
-// 213 / 2.8; G(6500) degree 26 (170) 121 / 1.7 against 168 / 5.2.  Past the
-// line the batches catch up: RMAT-13 (204) 237 / 5.4 against 219 / 6.6 and
-// 4.9 at 512; G(4000) degree 66 (265) 229 / 2.2 against 166 / 3.0 and 2.3.
-// Hubs cost the LDS sweep more, so the last stretch is for graphs without.
+// 256 (of 512 faster by a fifth): a path of 1000 1930 / 1.74 against 8350 /
+// 24.7; a ring lattice of 6001 295 / 2.3 against 1180 / 22; G(4000) degree 10
+// 170 / 0.38 against 274 / 1.75; RMAT-12 (97 thousand arcs) 293 / 1.10 against
+// 291 / 1.21; G(6500) degree 26 (170) 193 / 1.7 against 273 / 3.4.  Past the
+// line the batches catch up: R-MAT of 5960 vertices (135) 267 / 2.9 against 310
+// / 2.2, RMAT-13 (204) / 5.4 against / 2.6 and 2.1 at 512.  Hubs cost the LDS
+// sweep more, so the last stretch is for graphs without.
 // Edge terms, kernel timing, host-driven batches and levels by products ask
 // for the batched kernels themselves.
 bool small_takes_batches(const bc_ctx *ctx) {
