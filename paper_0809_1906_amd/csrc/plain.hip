@@ -16,7 +16,7 @@
 //
 // Each level's frontier is expanded in chunks of 256 vertices whose degree
 // prefix sums are staged in LDS, so a thread takes arcs, not vertices: hub
-// vertices are spread over the whole workgroup.  Each thread keeps eight
+// vertices are spread over the whole workgroup.  Each thread keeps up to eight
 // arcs' loads in flight.
 #include "bc_internal.h"
 #include "wg_utils.h"
@@ -36,8 +36,11 @@ __global__ __launch_bounds__(PB) void k_plain_sweep(
     __shared__ int32_t s_tail;
     __shared__ long long s_idx;
     __shared__ uint32_t s_ovf;
+    __shared__ uint32_t s_run[PB / 64 * 2 * U]; // wg::arcs_of's bits, a wave's each
 
     const int tid = threadIdx.x;
+    uint32_t *run = s_run + (tid >> 6) * 2 * U;
+    if (tid < PB / 64 * 2 * U) s_run[tid] = 0; // read after a barrier
     const size_t g = blockIdx.x;
     int32_t *dist = dist_all + g * (size_t)n;
     uint64_t *sigma = sigma_all + g * (size_t)n;
@@ -74,10 +77,11 @@ __global__ __launch_bounds__(PB) void k_plain_sweep(
         while (qb < qe) {
             for (int32_t cb = qb; cb < qe; cb += PB) {
                 const int tot = wg::stage_chunk(queue, cb, qe, rp, ch);
-                for (int e0 = tid; e0 < tot; e0 += PB * U) {
+                const int u = wg::arcs_each<U, PB>(tot);
+                for (int e0 = wg::first_arc(u); e0 < tot; e0 += PB * u) {
                     int k[U];
                     int32_t a[U], w[U], dw[U];
-                    wg::arc_burst<U, PB>(ch, e0, tot, PB, k, a);
+                    wg::arcs_of<U, PB>(ch, run, e0, u, tot, min(PB, qe - cb), k, a);
 #pragma unroll
                     for (int j = 0; j < U; ++j) w[j] = a[j] >= 0 ? col[a[j]] : 0;
 #pragma unroll
@@ -122,10 +126,11 @@ __global__ __launch_bounds__(PB) void k_plain_sweep(
                 // acc[v] = sum of c(w) = acc[w] over successors w (level l + 1)
                 for (int32_t cb = lb; cb < le; cb += PB) {
                     const int tot = wg::stage_chunk(queue, cb, le, rp, ch);
-                    for (int e0 = tid; e0 < tot; e0 += PB * U) {
+                    const int u = wg::arcs_each<U, PB>(tot);
+                    for (int e0 = wg::first_arc(u); e0 < tot; e0 += PB * u) {
                         int k[U];
                         int32_t a[U], w[U], dw[U];
-                        wg::arc_burst<U, PB>(ch, e0, tot, PB, k, a);
+                        wg::arcs_of<U, PB>(ch, run, e0, u, tot, min(PB, le - cb), k, a);
 #pragma unroll
                         for (int j = 0; j < U; ++j) w[j] = a[j] >= 0 ? col[a[j]] : 0;
 #pragma unroll
@@ -176,10 +181,10 @@ __global__ __launch_bounds__(PB) void k_plain_sweep(
 // one accumulator per vertex of the chunk (no atomic in memory), and the
 // workgroups are as many as fit the LDS: 12 bytes a vertex each, not 24 times
 // 2048.  Up to a source per compute unit a workgroup has 1024 threads.  ms for
-// 1 / 2048 sources, against the sweep with the state in memory: RMAT-15 2.0 /
-// 19.9 and 9.1 / 61; RMAT-16 4.0 / 42 and 18 / 136; G(30000, 8/29999) 1.0 / 10.5
+// 1 / 2048 sources, against the sweep with the state in memory: RMAT-15 1.3 /
+// 17.3 and 9.1 / 61; RMAT-16 2.5 / 37 and 18 / 136; G(30000, 8/29999) 0.8 / 10.2
 // and 3.3 / 39.  At n = 90208 one workgroup per unit is left: RMAT-17, 1024
-// sources, 48 against 142.
+// sources, 39 against 142.
 template <int T>
 __global__ __launch_bounds__(T) void k_plain_state(
     int32_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
@@ -192,6 +197,7 @@ __global__ __launch_bounds__(T) void k_plain_state(
     __shared__ int32_t s_tail;
     __shared__ long long s_idx;
     __shared__ uint32_t s_ovf;
+    __shared__ uint32_t s_run[T / 64 * 2 * U]; // wg::arcs_of's bits, a wave's each
     constexpr uint32_t UNREACHED = 8;
 
     const int tid = threadIdx.x;
@@ -201,6 +207,8 @@ __global__ __launch_bounds__(T) void k_plain_state(
     int32_t *queue = queue_all + g * (size_t)n;
     int32_t *lev = lev_all + g * ((size_t)n + 2);
 
+    uint32_t *run = s_run + (tid >> 6) * 2 * U;
+    if (tid < T / 64 * 2 * U) s_run[tid] = 0; // read after a barrier
     for (;;) {
         if (tid == 0) s_idx = (long long)atomicAdd(next_counter, 1ull);
         __syncthreads();
@@ -227,11 +235,12 @@ __global__ __launch_bounds__(T) void k_plain_state(
             const uint32_t next = 1u << ((L + 1) % 3), open = UNREACHED | next;
             for (int32_t cb = qb; cb < qe; cb += T) {
                 const int tot = wg::stage_chunk<T>(queue, cb, qe, rp, ch);
-                for (int e0 = tid; e0 < tot; e0 += T * U) {
+                const int u = wg::arcs_each<U, T>(tot);
+                for (int e0 = wg::first_arc(u); e0 < tot; e0 += T * u) {
                     int k[U];
                     int32_t a[U], w[U];
                     bool in[U];
-                    wg::arc_burst<U, T>(ch, e0, tot, min(T, qe - cb), k, a);
+                    wg::arcs_of<U, T>(ch, run, e0, u, tot, min(T, qe - cb), k, a);
 #pragma unroll
                     for (int j = 0; j < U; ++j) w[j] = a[j] >= 0 ? col[a[j]] : 0;
 #pragma unroll
@@ -292,11 +301,12 @@ __global__ __launch_bounds__(T) void k_plain_state(
                 s_sum[tid] = 0.0;
                 if (l < nlev - 1) {
                     const int tot = wg::stage_chunk<T>(queue, cb, le, rp, ch);
-                    for (int e0 = tid; e0 < tot; e0 += T * U) {
+                    const int u = wg::arcs_each<U, T>(tot);
+                    for (int e0 = wg::first_arc(u); e0 < tot; e0 += T * u) {
                         int k[U];
                         int32_t a[U], w[U];
                         bool in[U];
-                        wg::arc_burst<U, T>(ch, e0, tot, min(T, le - cb), k, a);
+                        wg::arcs_of<U, T>(ch, run, e0, u, tot, min(T, le - cb), k, a);
 #pragma unroll
                         for (int j = 0; j < U; ++j) w[j] = a[j] >= 0 ? col[a[j]] : 0;
 #pragma unroll
@@ -335,7 +345,7 @@ __global__ __launch_bounds__(T) void k_plain_state(
 constexpr int ST_T = 512, WIDE_T = 1024;
 constexpr size_t LDS_BYTES = 160 << 10;
 template <int T>
-constexpr size_t fixed_lds() { return sizeof(wg::ChunkOf<T>) + T * sizeof(double) + 64; }
+constexpr size_t fixed_lds() { return sizeof(wg::ChunkOf<T>) + T * sizeof(double) + T / 64 * 2 * U * sizeof(uint32_t) + 64; }
 size_t state_lds(int32_t n) { return ((size_t)n + 3) / 4 * 4; }
 
 } // namespace

@@ -86,8 +86,11 @@ __global__ __launch_bounds__(PB) void k_weighted_sweep(
     __shared__ uint32_t s_ovf, s_abort;
     __shared__ int32_t s_top;
     __shared__ int32_t s_hd[KH]; // dist[v] for v < KH
+    __shared__ uint32_t s_run[PB / 64 * 2 * U]; // wg::arcs_of's bits, a wave's each
 
     const int tid = threadIdx.x;
+    uint32_t *run = s_run + (tid >> 6) * 2 * U;
+    if (tid < PB / 64 * 2 * U) s_run[tid] = 0; // read after a barrier
     const size_t g = blockIdx.x;
     int32_t *dist = W.dist + g * (size_t)n;
     uint64_t *sigma = W.sigma + g * (size_t)n;
@@ -189,10 +192,11 @@ __global__ __launch_bounds__(PB) void k_weighted_sweep(
             __syncthreads();
             for (int32_t cb = lb; cb < le; cb += PB) {
                 const int tot = wg::stage_chunk(order, cb, le, rp, ch);
-                for (int e0 = tid; e0 < tot; e0 += PB * U) {
+                const int u = wg::arcs_each<U, PB>(tot);
+                for (int e0 = wg::first_arc(u); e0 < tot; e0 += PB * u) {
                     int k[U];
                     int32_t a[U], x[U], c[U], dx[U];
-                    wg::arc_burst<U, PB>(ch, e0, tot, PB, k, a);
+                    wg::arcs_of<U, PB>(ch, run, e0, u, tot, min(PB, le - cb), k, a);
 #pragma unroll
                     for (int j = 0; j < U; ++j) {
                         x[j] = a[j] >= 0 ? col[a[j]] : 0;
@@ -336,9 +340,9 @@ __global__ __launch_bounds__(PB) void k_weighted_sweep(
 }
 
 // The same order with every distance in LDS, 16 bits each.  Measured against
-// the sweep above, ms for 1 / 1024 sources: RMAT-16 with weights up to 255 5.1 /
-// 21.1 against 13.1 / 26.1, up to 10 2.7 / 13.8 against 10.8 / 23.5; RMAT-13 2.1 /
-// 4.9 against 3.2 / 5.8; G(60000, 10/59999) 5.8 / 25.4 against 11.0 / 28.9.
+// the sweep above, ms for 1 / 1024 sources: RMAT-16 with weights up to 255 4.6 /
+// 19.4 against 12.9 / 25.7, up to 10 2.5 / 13.3 against 10.8 / 23.5; RMAT-13 1.7 /
+// 4.2 against 3.2 / 5.7; G(60000, 10/59999) 5.2 / 23.1 against 11.0 / 28.9.
 // What bounds the sweep is each phase's chain of dependent accesses and its
 // barriers (counters: waves wait 67% of their time, vector units busy 47%), so:
 //   - a phase finds its vertices, and the least distance above its own, by a
@@ -382,7 +386,10 @@ __global__ __launch_bounds__(T, 4) void k_weighted_lds(
     __shared__ int32_t s_ndag;
     __shared__ uint32_t s_abort;
 
+    __shared__ uint32_t s_run[T / 64 * 2 * U]; // wg::arcs_of's bits, a wave's each
     const int tid = threadIdx.x;
+    uint32_t *run = s_run + (tid >> 6) * 2 * U;
+    if (tid < T / 64 * 2 * U) s_run[tid] = 0; // read after a barrier
     const size_t g = blockIdx.x;
     uint32_t *dist2 = reinterpret_cast<uint32_t *>(s_dist8);
     const uint16_t *dist = reinterpret_cast<const uint16_t *>(s_dist8);
@@ -457,7 +464,7 @@ __global__ __launch_bounds__(T, 4) void k_weighted_lds(
                         if (slot <= T) ch.off[slot] = (int32_t)(uint32_t)at;
                         if (slot < T) {
                             ch.v[slot] = v;
-                            ch.rp[slot] = r;
+                            ch.rp[slot] = r - (int32_t)(uint32_t)at;
                         } else {
                             order[slot] = v;
                         }
@@ -480,11 +487,12 @@ __global__ __launch_bounds__(T, 4) void k_weighted_lds(
             // and relaxes
             uint32_t low = FAR16;
             auto arcs = [&](int slots, int tot) {
-                for (int e0 = tid * U; e0 < tot; e0 += T * U) {
+                const int u = wg::arcs_each<U, T>(tot);
+                for (int e0 = wg::first_arc(u); e0 < tot; e0 += T * u) {
                     int k[U];
                     int32_t a[U], x[U];
                     uint32_t c[U], dx[U], was[U];
-                    wg::arc_run<U, T>(ch, e0, tot, slots, k, a);
+                    wg::arcs_of<U, T>(ch, run, e0, u, tot, slots, k, a);
 #pragma unroll
                     for (int j = 0; j < U; ++j) {
                         x[j] = a[j] >= 0 ? col[a[j]] : 0;
@@ -677,7 +685,7 @@ bc_status alloc_work(bc_ctx *ctx, WeightedBuffers &b, int64_t cap, int groups, b
 constexpr size_t LDS_BYTES = 160 << 10;
 constexpr int64_t RETRY_CAP = 4096;
 template <int T>
-constexpr size_t fixed_lds() { return sizeof(wg::ChunkOf<T>) + 64; }
+constexpr size_t fixed_lds() { return sizeof(wg::ChunkOf<T>) + T / 64 * 2 * 4 * sizeof(uint32_t) + 64; }
 size_t dist_lds(int32_t n) { return ((size_t)n + 7) / 8 * 16; }
 
 size_t per_group_bytes(bc_ctx *ctx, int64_t cap, bool retry_ws) {
@@ -721,7 +729,7 @@ bc_status weighted_prepare(bc_ctx *ctx) {
     // The sweep with its distances in LDS, unless a grid or an arena of the
     // other was asked for: 512 threads where two workgroups' distances fit a
     // compute unit, else 1024, and 1024 up to a source per compute unit.  ms
-    // with 512 / 1024 threads: RMAT-15, 1024 sources 10.3 / 13.8, one 4.4 / 3.5;
+    // with 512 / 1024 threads: RMAT-15, 1024 sources 10.3 / 13.8, one 4.4 / 3.5 (9.4 and 3.0 by now);
     // RMAT-13 with weights up to 10, 1024 sources 1.8 / 2.1, one 0.70 / 0.51.
     if (w.grid == 0 && w.arena_log2 == 0 && ctx->n > 0) {
         int cus = 0;

@@ -1,5 +1,5 @@
 // Workgroup-level helpers shared by the per-source forms (plain.hip,
-// weighted.hip): barriers with device-scope ordering, prefix sums, and the
+// weighted.hip): barriers, prefix sums, and the
 // LDS-staged, per-arc balanced expansion of a vertex list's adjacency.
 #pragma once
 
@@ -69,7 +69,7 @@ __device__ __forceinline__ int owner(const int *off, int e) {
 template <int T>
 struct ChunkOf {
     int32_t v[T];
-    int32_t rp[T];
+    int32_t rp[T];  // row offset less off[]: position e of the chunk is arc rp[k] + e
     int32_t off[T + 1];
     int32_t wsum[T / 64];
 };
@@ -92,71 +92,79 @@ __device__ __forceinline__ int stage_chunk(const int32_t *list, int32_t cb, int3
     int tot;
     const int off = block_excl_scan<T>(d, c.wsum, &tot);
     c.v[tid] = v;
-    c.rp[tid] = r;
+    c.rp[tid] = r - off;
     c.off[tid] = off;
     if (tid == 0) c.off[T] = tot;
     __syncthreads();
     return tot;
 }
 
-// Arc positions e0 + j * T (j < U) of a staged chunk of `slots` vertices with
-// `tot` arcs: slot k[j] of the owning vertex (the last that starts at or before
-// the arc) and arc index a[j] (-1 past the end).  The U searches go step by step
-// together, so that their LDS reads overlap, and take log2(slots) steps: with
-// each its own search over T slots the plain sweep took 22.4 ms on RMAT-15 with
-// 2048 sources, now 19.9.  A chunk that gives a thread one arc needs one search
-// (ring of 20000, 1024 sources: 2.40 ms, with all U 2.56).
+// A staged chunk's arcs are dealt in rounds of T u, 64 u in a row to each wave,
+// with u <= U such that a chunk of less than a full round is spread over the
+// waves evenly.
 template <int U, int T>
-__device__ __forceinline__ void arc_burst(const ChunkOf<T> &c, int e0, int tot, int slots, int (&k)[U],
-                                          int32_t (&a)[U]) {
-#pragma unroll
-    for (int j = 0; j < U; ++j) k[j] = 0;
-    const int h0 = slots > 1 ? 1 << (31 - __builtin_clz((uint32_t)(slots - 1))) : 0;
-    if (__builtin_amdgcn_readfirstlane(tot) <= T) { // a narrow level: one arc a thread
-        for (int h = h0; h > 0; h >>= 1)
-            if (k[0] + h < slots && c.off[k[0] + h] <= e0) k[0] += h;
-    } else {
-        for (int h = h0; h > 0; h >>= 1) {
-            int at[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) at[j] = c.off[min(k[j] + h, T)];
-#pragma unroll
-            for (int j = 0; j < U; ++j)
-                if (k[j] + h < slots && at[j] <= e0 + j * T) k[j] += h;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-        const int e = e0 + j * T;
-        a[j] = -1;
-        if (e < tot) a[j] = c.rp[k[j]] + (e - c.off[k[j]]);
-        else k[j] = 0;
-    }
+__device__ __forceinline__ int arcs_each(int tot) {
+    return __builtin_amdgcn_readfirstlane(min(U, max(1, (tot + T - 1) / T)));
 }
+// The wave's first arc (u > 1), or the thread's (u = 1).
+__device__ __forceinline__ int first_arc(int u) { return u > 1 ? (int)(threadIdx.x & ~63u) * u : (int)threadIdx.x; }
 
-// Arc positions e0 .. e0 + U - 1 of a staged chunk of `slots` vertices, each
-// with an arc, and `tot` arcs: slot k[j] of the owning vertex (the last that
-// starts at or before the arc) and arc index a[j] (-1 past the end).  One
-// search for a thread's U arcs, which mostly share a row: fewer instructions
-// than arc_burst, whose neighbouring threads read neighbouring columns.
+// A thread's u arcs of the round at e0 (from first_arc on), of a chunk of `slots`
+// vertices, each with an arc, and `tot` arcs: slot k[j] of the owning vertex
+// (the last that starts at or before the arc) and arc index a[j] (-1: none).
+// Neighbouring threads have neighbouring arcs.  One search serves a wave's
+// round, by its 64 lanes in two reads: the rows that start in its 64 u
+// positions each set a bit of `run` (2 U words of the wave, zero before and
+// after), and a lane counts the bits before its own position.  With a search
+// an arc, its steps were most of the sweeps' instructions and LDS reads.  Plain
+// form, ms for 1 / 2048 sources, a search an arc in step with a thread's others
+// / now: RMAT-15 2.0 / 19.9 and 1.3 / 17.3, RMAT-16 4.0 / 42.4 and 2.5 / 37.4;
+// one arc a thread takes its own search (a ring of 20000, 1024 sources: 2.40
+// and 2.13).  Weighted form, ms for 1 / 1024 sources, consecutive arcs and one
+// search a thread / now: RMAT-16 5.0 / 21.1 and 4.6 / 19.4, G(60000, 10/59999)
+// 5.7 / 25.5 and 5.2 / 23.1.
 template <int U, int T>
-__device__ __forceinline__ void arc_run(const ChunkOf<T> &c, int e0, int tot, int slots, int (&k)[U],
-                                        int32_t (&a)[U]) {
-    int lo = 0;
-    for (int h = slots > 1 ? 1 << (31 - __builtin_clz((uint32_t)(slots - 1))) : 0; h > 0; h >>= 1)
-        if (lo + h < slots && c.off[lo + h] <= e0) lo += h;
-    int32_t row = c.rp[lo] - c.off[lo]; // arc index of position 0, were it in this row
-    int end = lo + 1 < slots ? c.off[lo + 1] : tot;
+__device__ __forceinline__ void arcs_of(const ChunkOf<T> &c, uint32_t *run, int e0, int u, int tot, int slots,
+                                        int (&k)[U], int32_t (&a)[U]) {
+    const int lane = threadIdx.x & 63;
+    if (u == 1) {
+        k[0] = 0;
+        for (int h = slots > 1 ? 1 << (31 - __builtin_clz((uint32_t)(slots - 1))) : 0; h > 0; h >>= 1)
+            if (k[0] + h < slots && c.off[k[0] + h] <= e0) k[0] += h;
+        a[0] = c.rp[k[0]] + e0;
+#pragma unroll
+        for (int j = 1; j < U; ++j) {
+            k[j] = 0;
+            a[j] = -1;
+        }
+        return;
+    }
+    constexpr int G = T / 64;
+    const int r0 = __builtin_amdgcn_readfirstlane(e0);
+    const int g = __popcll(__ballot(lane * G < slots && c.off[lane * G] <= r0)) - 1;
+    const int f = g * G + (lane & (G - 1));
+    const int first = g * G + __popcll(__ballot(lane < G && f < slots && c.off[f] <= r0)) - 1;
+    for (int i = first + 1;; i += 64) {
+        // a row's bit is one below its start: the count is of starts up to a position
+        const int p = i + lane < slots ? c.off[i + lane] - 1 - r0 : 64 * U;
+        if (p < 64 * u) atomicOr(&run[p >> 5], 1u << (p & 31));
+        if (~__ballot(p < 64 * u) != 0) break;
+    }
+    __builtin_amdgcn_wave_barrier();
+    uint32_t m[2 * U];
+#pragma unroll
+    for (int i = 0; i < 2 * U; ++i) m[i] = run[i];
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 2 * U) run[lane] = 0;
+    uint32_t base = (uint32_t)first;
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-        const int e = e0 + j;
-        if (e >= end && e < tot) { // the next row
-            ++lo;
-            row = c.rp[lo] - c.off[lo];
-            end = lo + 1 < slots ? c.off[lo + 1] : tot;
-        }
-        k[j] = lo;
-        a[j] = e < tot ? row + e : -1;
+        const int e = r0 + 64 * j + lane;
+        k[j] = (int)__builtin_amdgcn_mbcnt_hi(m[2 * j + 1], __builtin_amdgcn_mbcnt_lo(m[2 * j], base));
+        base += (uint32_t)(__popc(m[2 * j]) + __popc(m[2 * j + 1]));
+        a[j] = -1;
+        if (j < u && e < tot) a[j] = c.rp[k[j]] + e;
+        else k[j] = 0;
     }
 }
 
