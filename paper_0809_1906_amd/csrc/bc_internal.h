@@ -187,7 +187,7 @@ struct SmallState {
     LdsColumns cols;
     uint32_t *count = nullptr;  // [0] units handed back by the 32-bit sweep, [1] most levels seen,
                                 // [2] by the last allocation-free call
-    int32_t *redo = nullptr;    // those units
+    int32_t *redo = nullptr;    // those units (the first list: behind count)
     int64_t redo_cap = 0;
 };
 
@@ -356,6 +356,7 @@ bc_status plain_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool a
 
 // Padded columns of `voff.size() - 1` graphs; taken[g] says whether graph g's
 // bursts fit 16-bit indices.  voff, rpoff and rp as in a many-graph context.
+// d_voff, d_rpoff: voff and rpoff on the device, or null.
 bc_status lds_columns(bc_ctx *ctx, const std::vector<int32_t> &voff, const std::vector<int32_t> &rpoff,
                       const std::vector<int32_t> &rp, const int32_t *d_voff, const int32_t *d_rpoff,
                       const int32_t *d_rp, LdsColumns &out, std::vector<uint8_t> &taken);

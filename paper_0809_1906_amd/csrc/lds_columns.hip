@@ -4,6 +4,7 @@
 #include "lds_sweep.h"
 
 #include <algorithm>
+#include <cstring>
 
 namespace {
 
@@ -64,16 +65,31 @@ bc_status lds_columns(bc_ctx *ctx, const std::vector<int32_t> &voff, const std::
             total += at;
         }
     }
-    out.brp = (uint16_t *)bc_dalloc(ctx, brp.size() * sizeof(uint16_t));
-    out.boff = (int64_t *)bc_dalloc(ctx, boff.size() * sizeof(int64_t));
-    out.safe = (uint32_t *)bc_dalloc(ctx, safe.size() * sizeof(uint32_t));
+    // the tables in one piece, one copy: a small context's preparation is mostly
+    // allocations and copies
+    auto rounded = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t safe_at = rounded(boff.size() * sizeof(int64_t));
+    const size_t voff_at = safe_at + rounded(safe.size() * sizeof(uint32_t));
+    const size_t rpoff_at = voff_at + (d_voff ? 0 : rounded(voff.size() * sizeof(int32_t)));
+    const size_t brp_at = rpoff_at + (d_voff ? 0 : rounded(rpoff.size() * sizeof(int32_t)));
+    std::vector<char> host(brp_at + brp.size() * sizeof(uint16_t));
+    char *d = (char *)bc_dalloc(ctx, host.size());
     out.bursts = bc_dalloc(ctx, (size_t)std::max<int64_t>(total, 1) * sizeof(uint4));
-    if (!out.brp || !out.boff || !out.safe || !out.bursts)
-        return bc_fail(ctx, BC_ERR_NOMEM, "padded columns: allocation failed");
+    if (!d || !out.bursts) return bc_fail(ctx, BC_ERR_NOMEM, "padded columns: allocation failed");
+    out.boff = (int64_t *)d;
+    out.safe = (uint32_t *)(d + safe_at);
+    out.brp = (uint16_t *)(d + brp_at);
     if (ng == 0) return BC_OK;
-    BC_HIP(ctx, hipMemcpy(out.brp, brp.data(), brp.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
-    BC_HIP(ctx, hipMemcpy(out.boff, boff.data(), boff.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-    BC_HIP(ctx, hipMemcpy(out.safe, safe.data(), safe.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+    std::memcpy(host.data(), boff.data(), boff.size() * sizeof(int64_t));
+    std::memcpy(host.data() + safe_at, safe.data(), safe.size() * sizeof(uint32_t));
+    std::memcpy(host.data() + brp_at, brp.data(), brp.size() * sizeof(uint16_t));
+    if (!d_voff) {
+        std::memcpy(host.data() + voff_at, voff.data(), voff.size() * sizeof(int32_t));
+        std::memcpy(host.data() + rpoff_at, rpoff.data(), rpoff.size() * sizeof(int32_t));
+        d_voff = (const int32_t *)(d + voff_at);
+        d_rpoff = (const int32_t *)(d + rpoff_at);
+    }
+    BC_HIP(ctx, hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice));
     hipLaunchKernelGGL(k_pad_columns, dim3(ng), dim3(256), 0, ctx->stream, d_voff, d_rpoff, d_rp, ctx->col, out.brp,
                        out.boff, (uint4 *)out.bursts);
     BC_HIP(ctx, hipGetLastError());

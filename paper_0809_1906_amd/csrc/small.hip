@@ -170,20 +170,15 @@ bc_status small_check_room(bc_ctx *ctx) {
 bc_status small_prepare(bc_ctx *ctx) {
     SmallState &m = ctx->sm;
     const std::vector<int32_t> voff{0, ctx->n}, rpoff{0};
-    int32_t *d = (int32_t *)bc_dalloc(ctx, 3 * sizeof(int32_t));
-    m.count = (uint32_t *)bc_dalloc(ctx, 256);
-    if (!d || !m.count) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation failed");
-    const int32_t h[3] = {0, ctx->n, 0}; // voff, then rpoff
-    BC_HIP(ctx, hipMemcpy(d, h, sizeof h, hipMemcpyHostToDevice));
+    m.redo_cap = std::max(ctx->n, 4096);
+    m.count = (uint32_t *)bc_dalloc(ctx, 256 + (size_t)m.redo_cap * sizeof(int32_t)); // and the first list
+    if (!m.count) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation failed");
+    m.redo = (int32_t *)(m.count + 64);
     BC_HIP(ctx, hipMemsetAsync(m.count, 0, 256, ctx->stream));
     std::vector<uint8_t> taken;
-    bc_status st = lds_columns(ctx, voff, rpoff, ctx->h_row_ptr, d, d + 2, ctx->row_ptr, m.cols, taken);
-    bc_dfree(ctx, d);
+    bc_status st = lds_columns(ctx, voff, rpoff, ctx->h_row_ptr, nullptr, nullptr, ctx->row_ptr, m.cols, taken);
     if (st != BC_OK) return st;
     BC_HIP(ctx, hipDeviceGetAttribute(&m.cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
-    m.redo_cap = std::max(ctx->n, 4096);
-    m.redo = (int32_t *)bc_dalloc(ctx, (size_t)m.redo_cap * sizeof(int32_t));
-    if (!m.redo) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation failed");
     m.on = taken[0] != 0;
     return BC_OK;
 }
@@ -223,7 +218,7 @@ bc_status small_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool w
     if (a.nunits > m.redo_cap) {
         int32_t *r = (int32_t *)bc_dalloc(ctx, (size_t)a.nunits * sizeof(int32_t));
         if (!r) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation of the handed-back list failed");
-        bc_dfree(ctx, m.redo);
+        if (m.redo != (int32_t *)(m.count + 64)) bc_dfree(ctx, m.redo);
         m.redo = r;
         m.redo_cap = a.nunits;
     }
