@@ -166,10 +166,13 @@ typedef struct {
                              process).  NULL = this process only. */
     int32_t grid;         /* plain form (unit and integer weights): persistent
                              workgroups, each running one source at a time;
-                             0 = default (the most that fit a workspace budget,
-                             at most 2048 unweighted, 1024 weighted; the budget
-                             is 16 GB unweighted, 96 GB weighted, 192 GB weighted
-                             with an explicit grid) */
+                             0 = default: sweeps whose state fits the compute
+                             units' LDS where it does, as many workgroups as
+                             fit; else, and with a grid, the sweeps with their
+                             state in memory (the most workgroups that fit a
+                             workspace budget, at most 2048 unweighted, 1024
+                             weighted; the budget is 16 GB unweighted, 96 GB
+                             weighted, 192 GB weighted with an explicit grid) */
     int32_t edges;        /* nonzero: also accumulate edge betweenness (read with
                              bc_read_edges).  Plain, sparse and hybrid forms
                              (the hybrid form then takes every backward level
@@ -179,7 +182,10 @@ typedef struct {
                              records one source batch's launches (every level of
                              the forward and backward sweeps, up to the deepest
                              level seen so far plus one) into a HIP graph once
-                             and replays it for every batch, with no host
+                             and replays it for every batch, two or three
+                             batches at a time on streams of the library's
+                             own, forked from the context's stream and joined
+                             to it, with no host
                              synchronisation between batches; a batch that
                              goes deeper, or whose counts need 64 bits, is
                              handed back and re-run when the context is next
@@ -289,8 +295,9 @@ bc_status bc_read_sssp(bc_ctx *ctx, const int32_t *sources, int32_t count,
  * backward pass.  The result equals all-source BC (bc_run over every vertex)
  * and serves as an independent check of it and of the forward outputs.
  * Writes n doubles in the caller's vertex order to bc_out (host or device per
- * mem), computed in FP64; the running BC is left untouched.  Holds 12 n^2
- * bytes of device memory during the call (n <= BC_ALL_PAIRS_MAX_N: 12.9 GB).
+ * mem), computed in FP64; the running BC is left untouched.  Holds up
+ * to 29 n^2 bytes of device memory during the call (n <= BC_ALL_PAIRS_MAX_N:
+ * 31 GB), 24 n^2 where no more can be had.
  * Synchronises.
  * Errors: BC_ERR_UNSUPPORTED (context of many graphs, n above the limit),
  * BC_ERR_OVERFLOW (a path count exceeded 2^64 - 1; the running BC's own

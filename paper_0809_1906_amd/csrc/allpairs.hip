@@ -362,7 +362,7 @@ bc_status allpairs_bc(bc_ctx *ctx, double *bc_internal) {
         cleanup();
         return bc_hip(ctx, pe, "all pairs: preparation");
     }
-    const bool near = D8 && deepest <= MAX8;
+    bool near = D8 && deepest <= MAX8;
     LaunchTimer tm(ctx, "all_pairs");
     if (near) {
         const int32_t xcds = 8, tiles = l8 / 256;
@@ -373,7 +373,19 @@ bc_status allpairs_bc(bc_ctx *ctx, double *bc_internal) {
     if (!near || deepest >= 4) {
         P = (uint32_t *)bc_dalloc(ctx, (size_t)n * ld * sizeof(uint32_t));
         Q = near ? (uint32_t *)bc_dalloc(ctx, (size_t)n * ld * sizeof(uint32_t)) : P;
-        if (!P || !Q) {
+        if (near && (!P || !Q)) {
+            // not the memory for both matrices: every triple by the triple sum,
+            // which needs one and no D8
+            (void)hipStreamSynchronize(ctx->stream);
+            bc_dfree(ctx, Q);
+            bc_dfree(ctx, D8);
+            D8 = nullptr;
+            near = false;
+            if (!P) P = (uint32_t *)bc_dalloc(ctx, (size_t)n * ld * sizeof(uint32_t));
+            Q = P;
+            hipLaunchKernelGGL(k_zero_f64, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, bc_internal, n);
+        }
+        if (!P) {
             (void)hipStreamSynchronize(ctx->stream);
             cleanup();
             return bc_fail(ctx, BC_ERR_NOMEM, "all pairs: allocation of the prepared matrices failed");
