@@ -273,7 +273,7 @@ KERNELS = ("fwd_pull", "bwd_pull", "fwd_push0", "batch_init", "batch_check", "li
            "coef_split", "mfma_bwd", "plain_sweep", "weighted_sweep", "multigraph_sweep")
 
 
-def roofline(name, wl, kern, info, steps):
+def roofline(name, wl, kern, info, steps, edges=False):
     """Roofline of the dominant kernel: algorithmic bytes (or flops) per
     launch over its average launch time from HIP events in the timed region."""
     dom = max(kern, key=lambda k: kern[k][0])
@@ -318,7 +318,15 @@ def roofline(name, wl, kern, info, steps):
     elif dom == "plain_sweep":
         total = float(S) * steps * 2 * pass_bytes(n, m)
     else:
-        total = float(S) * steps * pass_bytes(n, m)
+        # a run over every vertex sweeps from its leaves' neighbours only
+        # (edge terms take every source)
+        swept = S
+        if S == n and not edges:
+            deg = np.diff(wl["graph"].row_ptr)
+            leaf = np.flatnonzero(deg == 1)
+            swept = S - int(np.count_nonzero(deg[wl["graph"].col[wl["graph"].row_ptr[leaf]]] > 1))
+            base["sources_swept"] = swept
+        total = float(swept) * steps * pass_bytes(n, m)
     ach = total / (ms * 1e-3) / 1e9
     traffic = measured_traffic(dom, name)
     extra = {}
@@ -607,7 +615,7 @@ def main():
         if launches:
             kern[k] = (ms, launches)
     log("kernel times (ms, launches):", kern)
-    roof = roofline(args.workload, wl, kern, info, args.steps) if kern else None
+    roof = roofline(args.workload, wl, kern, info, args.steps, args.edges) if kern else None
     ctx.close()
 
     free = None
