@@ -656,8 +656,8 @@ def main():
                 model = float(wl["S"]) * 2 * pass_bytes(wl["n"], wl["m"])
                 compare[cform]["roofline_model_frac"] = model / cdt / 1e9 / HBM_PEAK_GBS
                 compare[cform]["roofline_note"] = (
-                    "HBM-bound by random sector traffic: rocprofv3 counters on 4096 RMAT-16 sources read "
-                    "9.2e11 B (13x the model) at 3.6 TB/s, 0.45 of peak, 19% L2 hits")
+                    "bound by latency and the 8-byte atomics of the DAG arcs: a vertex's state is a byte in LDS, "
+                    "only arcs of the shortest-path DAG go to memory")
 
     cpu, accuracy = None, {}
     if not args.no_cpu_baseline:

@@ -93,6 +93,5 @@ bc_status lds_columns(bc_ctx *ctx, const std::vector<int32_t> &voff, const std::
     hipLaunchKernelGGL(k_pad_columns, dim3(ng), dim3(256), 0, ctx->stream, d_voff, d_rpoff, d_rp, ctx->col, out.brp,
                        out.boff, (uint4 *)out.bursts);
     BC_HIP(ctx, hipGetLastError());
-    BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return BC_OK;
 }
