@@ -132,10 +132,20 @@ bc_status bc_fail(bc_ctx *ctx, bc_status s, const std::string &msg) {
 }
 
 bc_status bc_hip(bc_ctx *ctx, hipError_t e, const char *what) {
+    bc_clear_error();
     std::string msg = std::string(what) + ": " + hipGetErrorString(e);
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) return bc_fail(ctx, BC_ERR_NOMEM, msg);
     if (ctx) ctx->poisoned = true;
     return bc_fail(ctx, BC_ERR_DEVICE, msg);
+}
+
+void bc_clear_error() { (void)hipGetLastError(); }
+
+void *bc_halloc(size_t bytes) {
+    void *p = nullptr;
+    if (hipHostMalloc(&p, bytes ? bytes : 256) == hipSuccess) return p;
+    bc_clear_error();
+    return nullptr;
 }
 
 void *bc_dalloc(bc_ctx *ctx, size_t bytes) {
@@ -148,10 +158,12 @@ void *bc_dalloc(bc_ctx *ctx, size_t bytes) {
     } else {
         if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
     }
-    if (p) {
-        ctx->owned.emplace_back(p, bytes);
-        ctx->device_bytes += (int64_t)bytes;
+    if (!p) { // also an allocator's own failed call
+        bc_clear_error();
+        return nullptr;
     }
+    ctx->owned.emplace_back(p, bytes);
+    ctx->device_bytes += (int64_t)bytes;
     return p;
 }
 
@@ -175,7 +187,10 @@ hipEvent_t bc_event_get(bc_ctx *ctx) {
         return e;
     }
     hipEvent_t e = nullptr;
-    if (hipEventCreateWithFlags(&e, hipEventDisableSystemFence) != hipSuccess) return nullptr;
+    if (hipEventCreateWithFlags(&e, hipEventDisableSystemFence) != hipSuccess) {
+        bc_clear_error();
+        return nullptr;
+    }
     return e;
 }
 
@@ -426,7 +441,8 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
         ctx->new_of_old = (int32_t *)bc_dalloc(ctx, sizeof(int32_t) * (size_t)n);
         if (!ctx->new_of_old) return bail(BC_ERR_NOMEM, "device allocation failed");
     }
-    if (hipHostMalloc((void **)&ctx->status_host, 256) != hipSuccess) return bail(BC_ERR_NOMEM, "pinned allocation failed");
+    ctx->status_host = (uint32_t *)bc_halloc(256);
+    if (!ctx->status_host) return bail(BC_ERR_NOMEM, "pinned allocation failed");
     // Connected components (internal numbering): a source reaches exactly the
     // vertices of its own, which lets a batch know when its search is over.
     std::vector<int32_t> csize((size_t)std::max(n, 1), 0);
@@ -585,8 +601,8 @@ bc_status bc_create_many(const bc_graph *gs, int32_t count, const bc_options *op
     ctx->bc = (double *)bc_dalloc(ctx, sizeof(double) * nn);
     ctx->bc_scratch = (double *)bc_dalloc(ctx, sizeof(double) * nn);
     ctx->status = (uint32_t *)bc_dalloc(ctx, 256);
-    if (!ctx->col || !ctx->bc || !ctx->bc_scratch || !ctx->status ||
-        hipHostMalloc((void **)&ctx->status_host, 256) != hipSuccess)
+    ctx->status_host = (uint32_t *)bc_halloc(256);
+    if (!ctx->col || !ctx->bc || !ctx->bc_scratch || !ctx->status || !ctx->status_host)
         return bail(BC_ERR_NOMEM, "device allocation failed");
     if ((total_arcs > 0 &&
          hipMemcpy(ctx->col, col.data(), sizeof(int32_t) * (size_t)total_arcs, hipMemcpyHostToDevice) != hipSuccess) ||

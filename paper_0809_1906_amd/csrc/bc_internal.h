@@ -309,7 +309,13 @@ bc_status bc_check_usable(bc_ctx *ctx);
 bc_status bc_status_save(bc_ctx *ctx, uint32_t *before);
 bc_status bc_status_restore(bc_ctx *ctx, uint32_t before, uint32_t *now);
 bc_status bc_hip(bc_ctx *ctx, hipError_t e, const char *what);
+// The thread's HIP error stays set until it is read: whoever takes a failed
+// call in clears it, or a later launch check reports it as its own.
+void bc_clear_error();
+// Device memory (freed by bc_dfree or with the context) and pinned host memory
+// (hipHostFree); nullptr, and no HIP error left, where there is none.
 void *bc_dalloc(bc_ctx *ctx, size_t bytes);
+void *bc_halloc(size_t bytes);
 void bc_dfree(bc_ctx *ctx, void *p);
 // Timing events from the context's pool (created without the system-scope
 // fence: they only time work on the stream); nullptr if creation fails.

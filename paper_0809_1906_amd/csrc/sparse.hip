@@ -1042,8 +1042,8 @@ bc_status ensure_levels(bc_ctx *ctx, int32_t need) {
     uint32_t *na = (uint32_t *)bc_dalloc(ctx, (size_t)cap * aw * sizeof(uint32_t));
     unsigned long long *nm = (unsigned long long *)bc_dalloc(ctx, (size_t)cap * sizeof(unsigned long long));
     uint32_t *nl = (uint32_t *)bc_dalloc(ctx, (size_t)cap * sizeof(uint32_t));
-    uint32_t *nh = nullptr;
-    if (!nf || !na || !nm || !nl || hipHostMalloc((void **)&nh, (size_t)cap * aw * sizeof(uint32_t)) != hipSuccess) {
+    uint32_t *nh = nf && na && nm && nl ? (uint32_t *)bc_halloc((size_t)cap * aw * sizeof(uint32_t)) : nullptr;
+    if (!nh) {
         bc_dfree(ctx, nf);
         bc_dfree(ctx, na);
         bc_dfree(ctx, nm);
@@ -1714,6 +1714,7 @@ bool lane_streams_take(bc_ctx *ctx) {
     while ((int)p.streams.size() < MAX_LANES) {
         hipStream_t q = nullptr;
         if (hipStreamCreateWithFlags(&q, hipStreamNonBlocking) != hipSuccess) {
+            bc_clear_error();
             if (p.users == 0) {
                 for (hipStream_t s : p.streams) hipStreamDestroy(s);
                 p.streams.clear();
@@ -1768,7 +1769,8 @@ bc_status lane_prepare(bc_ctx *t, const bc_ctx *ctx) {
     t->form = ctx->form;
     t->fold = ctx->fold;
     t->status = (uint32_t *)bc_dalloc(t, 256);
-    if (!t->status || hipHostMalloc((void **)&t->status_host, 256) != hipSuccess)
+    t->status_host = (uint32_t *)bc_halloc(256);
+    if (!t->status || !t->status_host)
         return bc_fail(t, BC_ERR_NOMEM, "batch lane: allocation failed");
     BC_HIP(t, hipMemsetAsync(t->status, 0, 256, t->stream));
     bc_status st = sparse_prepare(t, ctx->sp.batch, ctx->sp.split);
@@ -1781,7 +1783,10 @@ bc_status lane_prepare(bc_ctx *t, const bc_ctx *ctx) {
 bool ensure_lanes(bc_ctx *ctx, int lanes) {
     while (ctx->lane_events.size() < 1 + MAX_LANES) {
         hipEvent_t e = nullptr;
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return false;
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+            bc_clear_error();
+            return false;
+        }
         ctx->lane_events.push_back(e);
     }
     if (!lane_streams_take(ctx)) return false;

@@ -762,7 +762,8 @@ bc_status weighted_prepare(bc_ctx *ctx) {
     w.retry_count = (uint32_t *)bc_dalloc(ctx, 256);
     w.retry = (int32_t *)bc_dalloc(ctx, (size_t)RETRY_CAP * 4);
     w.again = (int32_t *)bc_dalloc(ctx, (size_t)RETRY_CAP * 8);
-    if (!w.next || !w.retry_count || !w.retry || !w.again || hipHostMalloc((void **)&w.host, 256) != hipSuccess)
+    w.host = (uint32_t *)bc_halloc(256);
+    if (!w.next || !w.retry_count || !w.retry || !w.again || !w.host)
         return bc_fail(ctx, BC_ERR_NOMEM, "weighted form: allocation failed");
     return BC_OK;
 }
