@@ -1132,28 +1132,19 @@ bc_status algebraic_backward_level(bc_ctx *ctx, bool wide, const uint64_t *fcur,
                 : algebraic_backward_level_t<uint32_t>(ctx, fcur, fnext, deeper, delta_dump, accumulate, gate);
 }
 
-int64_t algebraic_planes_issued(bc_ctx *ctx) {
+bool algebraic_counts(bc_ctx *ctx, int64_t (&out)[5]) {
     AlgebraicState &a = ctx->al;
-    if (!a.planes_issued) return 0;
-    unsigned long long v = 0;
-    if (hipMemcpyAsync(&v, a.planes_issued, sizeof v, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
-        hipStreamSynchronize(ctx->stream) != hipSuccess)
-        return -1;
-    return (int64_t)v;
-}
-
-bool algebraic_ktiles(bc_ctx *ctx, int64_t *run, int64_t *dense, int64_t *run_fwd, int64_t *dense_fwd) {
-    AlgebraicState &a = ctx->al;
-    *run = *dense = *run_fwd = *dense_fwd = 0;
+    std::fill(std::begin(out), std::end(out), 0);
     if (!a.planes_issued) return true;
-    unsigned long long v[4] = {0, 0, 0, 0};
-    if (hipMemcpyAsync(v, a.planes_issued + 1, sizeof v, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+    unsigned long long v[5] = {};
+    if (hipMemcpyAsync(v, a.planes_issued, sizeof v, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
         hipStreamSynchronize(ctx->stream) != hipSuccess)
         return false;
-    *run_fwd = (int64_t)v[0];
-    *dense_fwd = (int64_t)v[1];
-    *run = (int64_t)(v[0] + v[2]);
-    *dense = (int64_t)(v[1] + v[3]);
+    out[0] = (int64_t)v[0];
+    out[1] = (int64_t)(v[1] + v[3]);
+    out[2] = (int64_t)(v[2] + v[4]);
+    out[3] = (int64_t)v[1];
+    out[4] = (int64_t)v[2];
     return true;
 }
 

@@ -160,7 +160,7 @@ void *bc_dalloc(bc_ctx *ctx, size_t bytes) {
     }
     if (!p) { // also an allocator's own failed call
         bc_clear_error();
-        return nullptr;
+        return lanes_give_room(ctx) ? bc_dalloc(ctx, bytes) : nullptr;
     }
     ctx->owned.emplace_back(p, bytes);
     ctx->device_bytes += (int64_t)bytes;
@@ -698,7 +698,7 @@ static bc_status check_overflow(bc_ctx *ctx) {
         BC_HIP(ctx, hipMemcpyAsync(ctx->status_host + 2 + i, ctx->lanes[i]->status, sizeof(uint32_t),
                                    hipMemcpyDeviceToHost, ctx->stream));
     BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    uint32_t bits = *ctx->status_host;
+    uint32_t bits = *ctx->status_host | ctx->lane_status;
     for (size_t i = 0; i < ctx->lanes.size(); ++i) bits |= ctx->status_host[2 + i];
     if (bits & BC_DEV_SIGMA_OVERFLOW) {
         ctx->overflow_seen = true;
@@ -776,6 +776,9 @@ bc_status bc_reset(bc_ctx *ctx) {
         BC_HIP(ctx, hipMemsetAsync(t->status, 0, 256, ctx->stream));
         algebraic_reset_counters(t);
     }
+    ctx->lane_limit = 1 << 30;
+    ctx->lane_status = 0;
+    std::fill(std::begin(ctx->lane_products), std::end(ctx->lane_products), 0);
     BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     bc_timers_clear(ctx);
     algebraic_reset_counters(ctx);
@@ -929,21 +932,24 @@ bc_status bc_get_info(const bc_ctx *ctx, bc_info *out) {
     out->mfma_density_bwd = every ? 0.0 : hybrid ? ctx->hy.theta_bwd : 2.0;
     out->tune_source = ctx->hy.tune_source;
     out->mfma_fwd_rows = every || hybrid ? ctx->al.fwd_rows : 0;
-    out->mfma_planes = ctx->poisoned ? 0 : algebraic_planes_issued(const_cast<bc_ctx *>(ctx));
-    out->mfma_ktiles_run = out->mfma_ktiles_dense = out->mfma_ktiles_run_fwd = out->mfma_ktiles_dense_fwd = 0;
-    if (!ctx->poisoned && !algebraic_ktiles(const_cast<bc_ctx *>(ctx), &out->mfma_ktiles_run, &out->mfma_ktiles_dense,
-                                            &out->mfma_ktiles_run_fwd, &out->mfma_ktiles_dense_fwd))
-        out->mfma_ktiles_run = out->mfma_ktiles_dense = out->mfma_ktiles_run_fwd = out->mfma_ktiles_dense_fwd = -1;
-    for (bc_ctx *t : ctx->lanes) {
-        out->device_bytes += t->device_bytes;
-        int64_t run = 0, dense = 0, run_fwd = 0, dense_fwd = 0;
-        if (ctx->poisoned || !algebraic_ktiles(t, &run, &dense, &run_fwd, &dense_fwd)) continue;
-        out->mfma_planes += algebraic_planes_issued(t);
-        out->mfma_ktiles_run += run;
-        out->mfma_ktiles_dense += dense;
-        out->mfma_ktiles_run_fwd += run_fwd;
-        out->mfma_ktiles_dense_fwd += dense_fwd;
+    int64_t sum[5] = {};
+    if (!ctx->poisoned) {
+        std::vector<bc_ctx *> all{const_cast<bc_ctx *>(ctx)};
+        all.insert(all.end(), ctx->lanes.begin(), ctx->lanes.end());
+        std::copy(std::begin(ctx->lane_products), std::end(ctx->lane_products), sum);
+        bool known = true;
+        for (bc_ctx *t : all) {
+            int64_t own[5];
+            known = known && algebraic_counts(t, own);
+            for (int i = 0; i < 5; ++i) sum[i] = known ? sum[i] + own[i] : -1;
+        }
     }
+    for (bc_ctx *t : ctx->lanes) out->device_bytes += t->device_bytes;
+    out->mfma_planes = sum[0];
+    out->mfma_ktiles_run = sum[1];
+    out->mfma_ktiles_dense = sum[2];
+    out->mfma_ktiles_run_fwd = sum[3];
+    out->mfma_ktiles_dense_fwd = sum[4];
     return BC_OK;
 }
 

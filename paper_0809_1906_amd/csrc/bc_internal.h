@@ -278,7 +278,9 @@ struct bc_ctx {
     std::vector<bc_ctx *> lanes;
     std::vector<hipStream_t> lane_streams; // the device's, shared by its contexts
     std::vector<hipEvent_t> lane_events; // the fork, then each lane's join
-    bool lanes_refused = false;          // their memory was not to be had
+    int lane_limit = 1 << 30;            // as many as their memory could be had for (until bc_reset)
+    uint32_t lane_status = 0;            // what lanes given up since bc_reset had found: status bits,
+    int64_t lane_products[5] = {};       // and products as bc_info counts them
 
     // bookkeeping
     int64_t sources_run = 0;
@@ -414,10 +416,9 @@ bc_status algebraic_backward_level(bc_ctx *ctx, bool wide, const uint64_t *fcur,
                                    const uint32_t *gate = nullptr);
 // A lane's products: `from`'s adjacency bits, buffers of its own.
 bc_status algebraic_share(bc_ctx *ctx, const bc_ctx *from);
-int64_t algebraic_planes_issued(bc_ctx *ctx); // synchronises; -1 on a device error
-// k-tiles the products multiplied and those a dense product would have;
-// synchronises; false on a device error
-bool algebraic_ktiles(bc_ctx *ctx, int64_t *run, int64_t *dense, int64_t *run_fwd, int64_t *dense_fwd);
+// One context's own products: planes issued, k-tiles run and dense, of those the
+// forward's; synchronises; false on a device error.
+bool algebraic_counts(bc_ctx *ctx, int64_t (&out)[5]);
 void algebraic_reset_counters(bc_ctx *ctx);
 bc_status sparse_release(bc_ctx *ctx);
 bc_status algebraic_release(bc_ctx *ctx);
@@ -432,6 +433,10 @@ bc_status order_prepare(bc_ctx *ctx, const int32_t *h_col, const std::vector<int
 // pending.  Every entry point calls it before touching the context's state.
 bc_status sparse_settle(bc_ctx *ctx);
 void lanes_release(bc_ctx *ctx); // synchronises
+// Frees the lanes for the memory another request could not be given; false
+// where there are none, or they have replays whose checks the host has not
+// read.  Synchronises.
+bool lanes_give_room(bc_ctx *ctx);
 // Destroys the recorded batch graphs and their capture stream; synchronises.
 void sparse_graphs_release(bc_ctx *ctx);
 // delta_dump = nullptr runs the forward only (distances and counts).

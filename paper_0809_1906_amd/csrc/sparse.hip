@@ -1680,12 +1680,14 @@ constexpr int MAX_LANES = 3;
 // batches goes without.  Timed and weighted batches are driven from the host,
 // one at a time.
 int lanes_for(const bc_ctx *ctx, int64_t nb) {
-    if (ctx->timing == 1 || ctx->weighted || ctx->host_driven || ctx->lanes_refused) return 1;
+    if (ctx->timing == 1 || ctx->weighted || ctx->host_driven) return 1;
     if (nb < (ctx->lanes.empty() ? 4 : 2)) return 1;
     const size_t cells = (size_t)ctx->n * ctx->sp.batch;
-    if (cells * 12 > size_t(8) << 30) return 1; // its memory
+    // its memory: counts and c, and a bitmap per level
+    const size_t levels = (size_t)std::max(ctx->sp.depth_max + 1, 16);
+    if (cells * 12 > size_t(8) << 30 || levels * (cells / 8) > size_t(16) << 30) return 1;
     const size_t written = cells * 8 + cells / 8 * 8 + (ctx->al.planes ? cells * 6 : 0);
-    return (int)std::min<int64_t>(nb, 3 * written <= size_t(256) << 20 ? 3 : 2);
+    return (int)std::min<int64_t>({nb, ctx->lane_limit, 3 * written <= size_t(256) << 20 ? 3 : 2});
 }
 
 // The streams lanes run on, one set per device, shared by its contexts and
@@ -1778,36 +1780,52 @@ bc_status lane_prepare(bc_ctx *t, const bc_ctx *ctx) {
     return st;
 }
 
-// `lanes` lanes, this context's state being the first; false (and none kept
-// from this call) when their memory or streams cannot be had.
-bool ensure_lanes(bc_ctx *ctx, int lanes) {
+// Frees the lanes beyond the first `keep`; what they counted stays with the
+// context.
+void lanes_retire(bc_ctx *ctx, size_t keep) {
+    if (ctx->lanes.size() <= keep) return;
+    hipError_t e = hipStreamSynchronize(ctx->stream); // their work is joined to it
+    while (ctx->lanes.size() > keep) {
+        bc_ctx *t = ctx->lanes.back();
+        uint32_t bits = 0;
+        int64_t own[5] = {};
+        if (e == hipSuccess) e = hipMemcpy(&bits, t->status, sizeof bits, hipMemcpyDeviceToHost);
+        if (e == hipSuccess && !algebraic_counts(t, own)) e = hipErrorUnknown;
+        ctx->lane_status |= bits;
+        for (int i = 0; i < 5; ++i) ctx->lane_products[i] += own[i];
+        ctx->lanes.pop_back();
+        lane_free(t);
+    }
+    if (e != hipSuccess) (void)bc_hip(ctx, e, "batch lanes: reading their counters");
+}
+
+// Up to `lanes` lanes, this context's state being the first, as far as memory
+// and streams can be had; returns how many.
+int ensure_lanes(bc_ctx *ctx, int lanes) {
     while (ctx->lane_events.size() < 1 + MAX_LANES) {
         hipEvent_t e = nullptr;
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
             bc_clear_error();
-            return false;
+            return ctx->lane_limit = 1;
         }
         ctx->lane_events.push_back(e);
     }
-    if (!lane_streams_take(ctx)) return false;
+    if (!lane_streams_take(ctx)) return ctx->lane_limit = 1;
     while ((int)ctx->lanes.size() < lanes - 1) {
         bc_ctx *t = new (std::nothrow) bc_ctx();
-        if (!t) return false;
-        if (lane_prepare(t, ctx) != BC_OK) {
-            if (t->poisoned) lane_failed(ctx, t);
-            lane_free(t);
-            return false;
+        if (!t || lane_prepare(t, ctx) != BC_OK) {
+            if (t && t->poisoned) lane_failed(ctx, t);
+            if (t) lane_free(t);
+            return ctx->lane_limit = 1 + (int)ctx->lanes.size();
         }
         ctx->lanes.push_back(t);
     }
-    return true;
+    return lanes;
 }
 
-// The recorded batch is ready and the device holds the run's control block.
-bc_status start_replays(bc_ctx *ctx, const int32_t *d_src, int64_t count, hipStream_t stream) {
+// Everything replays of up to nb batches need, allocated and recorded.
+bc_status prepare_replays(bc_ctx *ctx, int64_t nb) {
     SparseState &s = ctx->sp;
-    const int64_t leafy = s.wt_off ? std::max<int64_t>(ctx->fold.src + ctx->fold.leafy - d_src, 0) : 0;
-    const int64_t nb = (count + s.batch - 1) / s.batch;
     if (nb > s.redo_cap) {
         int32_t *r = (int32_t *)bc_dalloc(ctx, (size_t)nb * sizeof(int32_t));
         if (!r) return bc_fail(ctx, BC_ERR_NOMEM, "sparse form: allocation of the handed-back list failed");
@@ -1815,8 +1833,13 @@ bc_status start_replays(bc_ctx *ctx, const int32_t *d_src, int64_t count, hipStr
         s.redo = r;
         s.redo_cap = nb;
     }
-    bc_status st = ensure_replay(ctx);
-    if (st != BC_OK) return st;
+    return ensure_replay(ctx);
+}
+
+// The device holds the run's control block.
+bc_status start_replays(bc_ctx *ctx, const int32_t *d_src, int64_t count, hipStream_t stream) {
+    SparseState &s = ctx->sp;
+    const int64_t leafy = s.wt_off ? std::max<int64_t>(ctx->fold.src + ctx->fold.leafy - d_src, 0) : 0;
     hipLaunchKernelGGL(k_run_init, dim3(1), dim3(64), 0, stream, s.ctl, d_src, (int32_t)count, s.redo,
                        s.wt_off, (int32_t)(std::min(leafy, count) / s.batch));
     BC_HIP(ctx, hipGetLastError());
@@ -1828,21 +1851,15 @@ bc_status start_replays(bc_ctx *ctx, const int32_t *d_src, int64_t count, hipStr
 // that have been run.
 bc_status run_lanes(bc_ctx *ctx, int lanes, const int32_t *d_src, int64_t count, const std::vector<uint8_t> &done) {
     const int64_t B = ctx->sp.batch, nb = (count + B - 1) / B;
-    if (!ensure_lanes(ctx, lanes)) {
-        if (ctx->poisoned) return BC_ERR_DEVICE;
-        ctx->lanes_refused = ctx->lanes.empty();
-        lanes = 1 + (int)ctx->lanes.size();
-    }
-    std::vector<bc_ctx *> all{ctx};
-    all.insert(all.end(), ctx->lanes.begin(), ctx->lanes.begin() + (lanes - 1));
-    std::vector<int64_t> first((size_t)lanes + 1);
-    for (int i = 0; i <= lanes; ++i) first[(size_t)i] = nb * i / lanes;
-    auto stream = [&](int i) { return lanes > 1 ? ctx->lane_streams[(size_t)i] : ctx->stream; };
-    const int forked = lanes > 1 ? lanes : 0;
     // What a lane needs is allocated and recorded before the fork, in the order
-    // of the context's own stream.
-    for (int i = 1; i < lanes; ++i) {
-        bc_ctx *t = all[(size_t)i];
+    // of the context's own stream, and before the shares are dealt: without the
+    // memory for a lane there is one fewer.  This context's own batch first, for
+    // which the others may have to go (bc_dalloc).
+    bc_status st = prepare_replays(ctx, nb);
+    if (st != BC_OK) return st;
+    lanes = ensure_lanes(ctx, lanes);
+    for (int i = 1; i < lanes && !ctx->poisoned; ++i) {
+        bc_ctx *t = ctx->lanes[(size_t)i - 1];
         t->sp.depth_max = ctx->sp.depth_max;
         t->sp.depth_guess = ctx->sp.depth_guess;
         t->sp.wide = ctx->sp.wide;
@@ -1853,10 +1870,25 @@ bc_status run_lanes(bc_ctx *ctx, int lanes, const int32_t *d_src, int64_t count,
         t->hy.prev_density = ctx->hy.prev_density;
         t->al.every_level = ctx->al.every_level;
         t->al.fwd_rows = ctx->al.fwd_rows;
+        st = prepare_replays(t, nb);
+        if (st == BC_ERR_NOMEM) {
+            lanes_retire(ctx, (size_t)i - 1);
+            ctx->lane_limit = lanes = i;
+        } else if (st != BC_OK) {
+            lane_failed(ctx, t);
+            return st;
+        }
     }
+    if (ctx->poisoned) return BC_ERR_DEVICE;
+    std::vector<bc_ctx *> all{ctx};
+    all.insert(all.end(), ctx->lanes.begin(), ctx->lanes.begin() + (lanes - 1));
+    std::vector<int64_t> first((size_t)lanes + 1);
+    for (int i = 0; i <= lanes; ++i) first[(size_t)i] = nb * i / lanes;
+    auto stream = [&](int i) { return lanes > 1 ? ctx->lane_streams[(size_t)i] : ctx->stream; };
+    const int forked = lanes > 1 ? lanes : 0;
     for (int i = 0; i < lanes; ++i) {
         const int64_t b = first[(size_t)i] * B, e = std::min(first[(size_t)i + 1] * B, count);
-        const bc_status st = start_replays(all[(size_t)i], d_src + b, e - b, ctx->stream);
+        st = start_replays(all[(size_t)i], d_src + b, e - b, ctx->stream);
         if (st != BC_OK) {
             if (i > 0) lane_failed(ctx, all[(size_t)i]);
             return st;
@@ -1888,28 +1920,16 @@ bc_status run_lanes(bc_ctx *ctx, int lanes, const int32_t *d_src, int64_t count,
     return BC_OK;
 }
 
-// Takes in what a lane's replays found (c, read from its control block) and
-// runs the batches they handed back.
-bc_status settle_one(bc_ctx *ctx, const BatchCtl &c) {
-    SparseState &s = ctx->sp;
-    s.depth_max = std::max(s.depth_max, (int32_t)c.max_nlev);
-    s.depth_guess = std::max(s.depth_guess, (int32_t)c.max_nlev);
-    ctx->max_levels = std::max(ctx->max_levels, (int32_t)c.seen);
-    if (c.redo_count == 0) return BC_OK;
-    std::vector<int32_t> redo(c.redo_count);
-    BC_HIP(ctx, hipMemcpy(redo.data(), s.redo, redo.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-    if (c.need_wide) s.wide = true; // sticky, as on the host-driven path
-    s.wt_off = c.wt_off;
-    bc_status st = BC_OK;
-    for (const int32_t b0 : redo) {
-        int32_t nlev = 0;
-        if (st == BC_OK) st = run_batch(ctx, c.src + b0, std::min(s.batch, c.total - b0), true, &nlev);
-    }
-    s.wt_off = 0;
-    return st;
-}
-
 } // namespace
+
+bool lanes_give_room(bc_ctx *ctx) {
+    if (ctx->lanes.empty() || ctx->poisoned) return false;
+    for (const bc_ctx *t : ctx->lanes)
+        if (t->sp.g_pending) return false;
+    lanes_retire(ctx, 0);
+    ctx->lane_limit = 1;
+    return !ctx->poisoned;
+}
 
 void lanes_release(bc_ctx *ctx) {
     hipStreamSynchronize(ctx->stream); // the lanes' work is joined to it
@@ -1967,7 +1987,8 @@ static bc_status run_list(bc_ctx *ctx, const int32_t *d_src, int64_t count) {
         }
         return run_lanes(ctx, lanes, d_src, count, done);
     }
-    bc_status st = start_replays(ctx, d_src, count, ctx->stream);
+    bc_status st = prepare_replays(ctx, nb);
+    if (st == BC_OK) st = start_replays(ctx, d_src, count, ctx->stream);
     if (st != BC_OK) return st;
     for (int64_t i = 0; i < nb; ++i) {
         bc_timing_batch(ctx);
@@ -2090,23 +2111,36 @@ bc_status sparse_settle(bc_ctx *ctx) {
     }
     if (!pending) return BC_OK;
     BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    BatchCtl ctls[MAX_LANES];
-    for (size_t i = 0; i < all.size(); ++i) std::memcpy(&ctls[i], ctx->status_host + 16 * (i + 1), sizeof(BatchCtl));
-    bc_status st = BC_OK;
+    // what every lane found; its handed-back batches then run on the context's
+    // own state, which may need the lanes' memory (bc_dalloc)
+    struct HandedBack {
+        const int32_t *src;
+        int32_t count;
+        int64_t wt_off;
+    };
+    std::vector<HandedBack> back;
+    SparseState &s = ctx->sp;
     for (size_t i = 0; i < all.size(); ++i) {
         if (!all[i]->sp.g_pending) continue;
         all[i]->sp.g_pending = false;
-        const bc_status one = settle_one(all[i], ctls[i]);
-        if (i > 0) {
-            SparseState &s = ctx->sp;
-            s.depth_max = std::max(s.depth_max, all[i]->sp.depth_max);
-            s.depth_guess = std::max(s.depth_guess, all[i]->sp.depth_guess);
-            s.wide = s.wide || all[i]->sp.wide;
-            ctx->max_levels = std::max(ctx->max_levels, all[i]->max_levels);
-            if (one != BC_OK) lane_failed(ctx, all[i]);
-        }
-        if (st == BC_OK) st = one;
+        BatchCtl c;
+        std::memcpy(&c, ctx->status_host + 16 * (i + 1), sizeof c);
+        s.depth_max = std::max(s.depth_max, (int32_t)c.max_nlev);
+        s.depth_guess = std::max(s.depth_guess, (int32_t)c.max_nlev);
+        ctx->max_levels = std::max(ctx->max_levels, (int32_t)c.seen);
+        if (c.redo_count == 0) continue;
+        std::vector<int32_t> redo(c.redo_count);
+        BC_HIP(ctx, hipMemcpy(redo.data(), all[i]->sp.redo, redo.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+        if (c.need_wide) s.wide = true; // sticky, as on the host-driven path
+        for (const int32_t b0 : redo) back.push_back({c.src + b0, std::min(s.batch, c.total - b0), c.wt_off});
     }
+    bc_status st = BC_OK;
+    for (const HandedBack &h : back) {
+        int32_t nlev = 0;
+        s.wt_off = h.wt_off;
+        if (st == BC_OK) st = run_batch(ctx, h.src, h.count, true, &nlev);
+    }
+    s.wt_off = 0;
     return st;
 }
 

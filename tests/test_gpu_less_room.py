@@ -96,3 +96,111 @@ def test_all_pairs_without_the_far_matrices(gpu_lib):
     assert a.refused == 1 and rel_err(out, want) <= 1e-12
     B.load().bc_destroy(ctx)
     assert not a.live
+
+
+def up256(nbytes):
+    return -(-nbytes // 256) * 256
+
+
+@pytest.mark.parametrize("granted", [0, 1])
+def test_lanes_without_their_levels(gpu_lib, granted):
+    """A further lane has its state but not the bitmaps of a deep graph's levels."""
+    g = gg.watts_strogatz(9000, 4, 0.002, 3)
+    want = oracle.bc(g, threads=8)
+    level = g.n * 8
+    a, ctx = context(g, "sparse", 64)
+    asked = []
+
+    def refuse(nbytes):
+        # the first state's storage doubles from 16 levels as its search goes on; a
+        # lane's is made in one go for the depth that is known by then
+        if nbytes > up256(32 * level) and nbytes not in [up256(k * level) for k in (64, 128, 256, 512, 1024, 2048)]:
+            asked.append(nbytes)
+            return len(asked) > granted
+        return False
+
+    a.refuse = refuse
+    print(f"less_room levels granted={granted}", flush=True)
+    for times in (1, 2):
+        assert B.load().bc_run(ctx, None, -1, B.BC_MEM_HOST) == B.BC_OK
+        assert rel_err(read(ctx, g.n), times * want) <= 1e-5
+    assert a.refused > 0
+    B.load().bc_destroy(ctx)
+    assert not a.live
+
+
+def test_lanes_give_way_to_deeper_levels(gpu_lib):
+    """A state that has to grow past what is left takes the lanes' memory."""
+    star = 7200
+    g = gg.disjoint_union(gg.star(star), gg.path(250))
+    shallow = np.arange(1, 8 * 64 + 1, dtype=np.int32)
+    deep = np.arange(star, g.n, dtype=np.int32)
+    a, ctx = context(g, "sparse", 64)
+    lib = B.load()
+    print("less_room give way", flush=True)
+    assert lib.bc_run(ctx, shallow.ctypes.data, shallow.size, B.BC_MEM_HOST) == B.BC_OK
+    want = oracle.bc(g, sources=shallow)
+    assert rel_err(read(ctx, g.n), want) <= 1e-5
+    # room for a growth to 256 levels beside the 128 before only without the lanes,
+    # of which each holds 12 bytes for a vertex and source
+    room = sum(a.live.values()) + 16 * g.n * 64 * 2
+    a.refuse = lambda nbytes: sum(a.live.values()) + nbytes > room
+    assert lib.bc_run(ctx, deep.ctypes.data, deep.size, B.BC_MEM_HOST) == B.BC_OK
+    want += oracle.bc(g, sources=deep)
+    assert rel_err(read(ctx, g.n), want) <= 1e-5
+    assert a.refused > 0
+    a.refuse = lambda nbytes: False
+    lib.bc_destroy(ctx)
+    assert not a.live
+
+
+def refuse_next(a):
+    """Refuses one request."""
+    left = [True]
+    a.refuse = lambda nbytes: left.pop() if left else False
+
+
+def readout(ctx, n):
+    src, dist = np.zeros(1, np.int32), np.zeros((1, n), np.int32)
+    return B.load().bc_read_sssp(ctx, src.ctypes.data, 1, dist.ctypes.data, None, None)
+
+
+def test_lanes_given_up_leave_their_overflow(gpu_lib):
+    g = gg.disjoint_union(gg.star(7200), gg.grid(35, 35))  # C(68,34) > 2^64 - 1
+    corners = np.tile(np.array([7200, g.n - 1], np.int32), 4 * 64)
+    a, ctx = context(g, "sparse", 64)
+    lib = B.load()
+    print("less_room overflow", flush=True)
+    for _ in range(2):  # the second run's counts are 64 bits wide from the start
+        assert lib.bc_reset(ctx) == B.BC_OK
+        assert lib.bc_run(ctx, corners.ctypes.data, corners.size, B.BC_MEM_HOST) == B.BC_OK
+    refuse_next(a)
+    assert readout(ctx, g.n) == B.BC_OK and a.refused == 1
+    out = np.zeros(g.n)
+    assert lib.bc_read(ctx, out.ctypes.data, B.BC_MEM_HOST) == B.BC_ERR_OVERFLOW
+    assert lib.bc_reset(ctx) == B.BC_OK
+    assert not np.any(read(ctx, g.n))
+    lib.bc_destroy(ctx)
+    assert not a.live
+
+
+def test_lanes_given_up_leave_their_products(gpu_lib):
+    g = gg.er_plus_tree(2500, 20.0, 4)
+    lib = B.load()
+    seen = []
+    for give_up in (False, True):
+        print(f"less_room products give_up={give_up}", flush=True)
+        a, ctx = context(g, "algebraic", 256)
+        for _ in range(2):
+            assert lib.bc_run(ctx, None, -1, B.BC_MEM_HOST) == B.BC_OK
+        held = B.bc_get_info(ctx).device_bytes
+        if give_up:
+            refuse_next(a)
+        assert readout(ctx, g.n) == B.BC_OK and a.refused == give_up
+        info = B.bc_get_info(ctx)
+        assert (info.device_bytes < held) == give_up
+        seen.append((info.mfma_planes, info.mfma_ktiles_run, info.mfma_ktiles_dense, info.mfma_ktiles_run_fwd,
+                     info.mfma_ktiles_dense_fwd))
+        lib.bc_destroy(ctx)
+        assert not a.live
+    assert seen[0] == seen[1] and min(seen[0]) > 0
