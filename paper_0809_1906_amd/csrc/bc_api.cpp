@@ -768,6 +768,10 @@ bc_status bc_read_edges(bc_ctx *ctx, double *eb_out, bc_mem mem) {
 bc_status bc_reset(bc_ctx *ctx) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     bc_status s = bc_check_usable(ctx);
+    if (s == BC_ERR_NOMEM) { // batches still to run: their sums are dropped here
+        ctx->handed_back.clear();
+        s = bc_check_usable(ctx);
+    }
     if (s != BC_OK) return s;
     BC_HIP(ctx, hipMemsetAsync(ctx->bc, 0, sizeof(double) * (size_t)std::max(ctx->n, 1), ctx->stream));
     if (ctx->eb) BC_HIP(ctx, hipMemsetAsync(ctx->eb, 0, sizeof(double) * (size_t)std::max(ctx->nnz, 1), ctx->stream));

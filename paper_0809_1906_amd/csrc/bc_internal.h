@@ -223,6 +223,13 @@ struct PlainState {
     uint32_t *next = nullptr; // work counter
 };
 
+// A batch that its replay could not finish, to be run from the host.
+struct HandedBack {
+    const int32_t *src;
+    int32_t count;
+    int64_t wt_off;
+};
+
 struct bc_ctx {
     // graph (host copy of the shape only)
     int32_t n = 0, nnz = 0;
@@ -281,6 +288,8 @@ struct bc_ctx {
     int lane_limit = 1 << 30;            // as many as their memory could be had for (until bc_reset)
     uint32_t lane_status = 0;            // what lanes given up since bc_reset had found: status bits,
     int64_t lane_products[5] = {};       // and products as bc_info counts them
+
+    std::vector<HandedBack> handed_back; // read from the control blocks, not run yet
 
     // bookkeeping
     int64_t sources_run = 0;
@@ -431,6 +440,7 @@ bc_status order_prepare(bc_ctx *ctx, const int32_t *h_col, const std::vector<int
 // Reads back what replayed batches found and re-runs the batches they handed
 // back (on the host-driven path); synchronises.  A no-op when nothing is
 // pending.  Every entry point calls it before touching the context's state.
+// BC_ERR_NOMEM leaves the batches that did not run to the next call.
 bc_status sparse_settle(bc_ctx *ctx);
 void lanes_release(bc_ctx *ctx); // synchronises
 // Frees the lanes for the memory another request could not be given; false

@@ -2109,16 +2109,10 @@ bc_status sparse_settle(bc_ctx *ctx) {
         BC_HIP(ctx, hipMemcpyAsync(ctx->status_host + 16 * (i + 1), all[i]->sp.ctl, sizeof(BatchCtl),
                                    hipMemcpyDeviceToHost, ctx->stream));
     }
-    if (!pending) return BC_OK;
-    BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    if (!pending && ctx->handed_back.empty()) return BC_OK;
+    if (pending) BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     // what every lane found; its handed-back batches then run on the context's
     // own state, which may need the lanes' memory (bc_dalloc)
-    struct HandedBack {
-        const int32_t *src;
-        int32_t count;
-        int64_t wt_off;
-    };
-    std::vector<HandedBack> back;
     SparseState &s = ctx->sp;
     for (size_t i = 0; i < all.size(); ++i) {
         if (!all[i]->sp.g_pending) continue;
@@ -2132,15 +2126,20 @@ bc_status sparse_settle(bc_ctx *ctx) {
         std::vector<int32_t> redo(c.redo_count);
         BC_HIP(ctx, hipMemcpy(redo.data(), all[i]->sp.redo, redo.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
         if (c.need_wide) s.wide = true; // sticky, as on the host-driven path
-        for (const int32_t b0 : redo) back.push_back({c.src + b0, std::min(s.batch, c.total - b0), c.wt_off});
+        for (const int32_t b0 : redo) ctx->handed_back.push_back({c.src + b0, std::min(s.batch, c.total - b0), c.wt_off});
     }
     bc_status st = BC_OK;
-    for (const HandedBack &h : back) {
+    size_t ran = 0;
+    for (; ran < ctx->handed_back.size() && st == BC_OK; ran += st == BC_OK) {
+        const HandedBack &h = ctx->handed_back[ran];
         int32_t nlev = 0;
         s.wt_off = h.wt_off;
-        if (st == BC_OK) st = run_batch(ctx, h.src, h.count, true, &nlev);
+        st = run_batch(ctx, h.src, h.count, true, &nlev);
     }
     s.wt_off = 0;
+    // a batch without memory for its levels has added nothing yet
+    if (st != BC_ERR_NOMEM) ran = ctx->handed_back.size();
+    ctx->handed_back.erase(ctx->handed_back.begin(), ctx->handed_back.begin() + (long)ran);
     return st;
 }
 

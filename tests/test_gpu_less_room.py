@@ -204,3 +204,36 @@ def test_lanes_given_up_leave_their_products(gpu_lib):
         lib.bc_destroy(ctx)
         assert not a.live
     assert seen[0] == seen[1] and min(seen[0]) > 0
+
+
+def test_handed_back_batches_wait_for_memory(gpu_lib):
+    """A call without the memory for handed-back batches leaves them to the next."""
+    import torch
+    # K2s come last in the order of the sources, so the first batch is shallow
+    # and the path's are handed back
+    g = gg.disjoint_union(gg.star(7200), gg.path(250), *[gg.path(2)] * 60)
+    want = oracle.bc(g)
+    src = np.array([0, 7300], np.int32)
+    dist = torch.empty((2, g.n), dtype=torch.int32, device="cuda:0")
+    print("less_room handed back", flush=True)
+    with gpu_lib.BC(g, form="sparse", batch=64) as ctx:
+        ctx.run()
+        for _ in range(2):
+            with pytest.raises(gpu_lib.BCError) as ei:
+                ctx.sssp_noalloc(src, dist=dist)
+            assert ei.value.status == gpu_lib.BC_ERR_NOMEM
+        assert rel_err(ctx.read(), want) <= 1e-5
+    # a reset while they wait
+    a, ctx = context(g, "sparse", 64)
+    lib = B.load()
+    assert lib.bc_run(ctx, None, -1, B.BC_MEM_HOST) == B.BC_OK
+    a.refuse = lambda nbytes: True
+    out = np.zeros(g.n)
+    assert lib.bc_read(ctx, out.ctypes.data, B.BC_MEM_HOST) == B.BC_ERR_NOMEM
+    assert lib.bc_reset(ctx) == B.BC_OK
+    assert lib.bc_read(ctx, out.ctypes.data, B.BC_MEM_HOST) == B.BC_OK and not np.any(out)
+    a.refuse = lambda nbytes: False
+    assert lib.bc_run(ctx, None, -1, B.BC_MEM_HOST) == B.BC_OK
+    assert rel_err(read(ctx, g.n), want) <= 1e-5
+    lib.bc_destroy(ctx)
+    assert not a.live
