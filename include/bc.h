@@ -403,8 +403,10 @@ typedef struct {
                                 context has no products */
 } bc_info;
 
-/* Fills *out; synchronises the context's stream (mfma_planes and the k-tile
- * counts are read from the device). */
+/* Fills *out; synchronises the context's stream (max_levels, mfma_planes and
+ * the k-tile counts are read from the device).  While that stream is being
+ * captured into a HIP graph nothing is read: max_levels is then the last known,
+ * and the products' counts are -1 where the context has products. */
 bc_status bc_get_info(const bc_ctx *ctx, bc_info *out);
 
 /*
@@ -419,6 +421,7 @@ bc_status bc_get_info(const bc_ctx *ctx, bc_info *out);
  * batches' totals and launch counts to all batches; forms without batches
  * time every launch.  Unknown names give zero.
  * Synchronises the stream.  bc_create refuses a negative k.
+ * Errors: BC_ERR_STATE for a known name while the stream is being captured.
  */
 bc_status bc_get_timing(bc_ctx *ctx, const char *kernel, double *total_ms, int64_t *launches);
 

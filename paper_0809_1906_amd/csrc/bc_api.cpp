@@ -675,16 +675,17 @@ static bc_status stage_sources(bc_ctx *ctx, const int32_t *sources, int64_t coun
 
 } // extern "C"
 
+// Synchronising a stream under graph capture, or reading back on it, ends the
+// capture; nothing is recorded.
+static bool capturing(const bc_ctx *ctx) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return ctx->stream && hipStreamIsCapturing(ctx->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+}
+
 bc_status bc_check_usable(bc_ctx *ctx) {
     if (ctx->poisoned) return bc_fail(ctx, BC_ERR_STATE, "context poisoned by an earlier device error");
     if (hipSetDevice(ctx->device) != hipSuccess) return bc_hip(ctx, hipErrorInvalidDevice, "hipSetDevice");
-    // Every call may synchronise the stream or read results back, which a
-    // stream under graph capture does not allow; nothing is recorded.
-    if (ctx->stream) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(ctx->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
-            return bc_fail(ctx, BC_ERR_STATE, "the context's stream is being captured into a HIP graph");
-    }
+    if (capturing(ctx)) return bc_fail(ctx, BC_ERR_STATE, "the context's stream is being captured into a HIP graph");
     // batches replayed by an earlier bc_run: read their checks, re-run what
     // they handed back
     return sparse_settle(ctx);
@@ -917,9 +918,14 @@ bc_status bc_sampled_distances(bc_ctx *ctx, const int32_t *sources, int32_t coun
     return sampled_distances(ctx, sources, count, sample, nsample, limit, dist_out, mem == BC_MEM_DEVICE);
 }
 
-bc_status bc_get_info(const bc_ctx *ctx, bc_info *out) {
-    if (!ctx || !out) return BC_ERR_INVALID_ARG;
-    if (!ctx->poisoned) (void)sparse_settle(const_cast<bc_ctx *>(ctx)); // replays' depth and sources
+bc_status bc_get_info(const bc_ctx *c, bc_info *out) {
+    if (!c || !out) return BC_ERR_INVALID_ARG;
+    bc_ctx *ctx = const_cast<bc_ctx *>(c);
+    const bool live = !ctx->poisoned && !capturing(ctx); // else what the host knows
+    if (live) {
+        (void)sparse_settle(ctx); // replays' depth and sources
+        ctx->max_levels = std::max(ctx->max_levels, small_levels(ctx, 1));
+    }
     memset(out, 0, sizeof(*out));
     out->n = ctx->n;
     out->m = ctx->nnz / 2;
@@ -927,7 +933,7 @@ bc_status bc_get_info(const bc_ctx *ctx, bc_info *out) {
     out->weighted = ctx->weighted ? 1 : 0;
     out->form = ctx->form;
     out->batch = ctx->many ? ctx->mg.chunk : ctx->form == BC_FORM_PLAIN_FP64 ? 1 : ctx->sp.batch;
-    out->max_levels = std::max(ctx->max_levels, ctx->poisoned ? 0 : small_levels(const_cast<bc_ctx *>(ctx), 1));
+    out->max_levels = ctx->max_levels;
     out->sources_run = ctx->sources_run;
     out->device_bytes = ctx->device_bytes;
     const bool every = ctx->form == BC_FORM_ALGEBRAIC;
@@ -938,13 +944,13 @@ bc_status bc_get_info(const bc_ctx *ctx, bc_info *out) {
     out->mfma_fwd_rows = every || hybrid ? ctx->al.fwd_rows : 0;
     int64_t sum[5] = {};
     if (!ctx->poisoned) {
-        std::vector<bc_ctx *> all{const_cast<bc_ctx *>(ctx)};
+        std::vector<bc_ctx *> all{ctx};
         all.insert(all.end(), ctx->lanes.begin(), ctx->lanes.end());
         std::copy(std::begin(ctx->lane_products), std::end(ctx->lane_products), sum);
         bool known = true;
         for (bc_ctx *t : all) {
             int64_t own[5];
-            known = known && algebraic_counts(t, own);
+            known = known && (live || !t->al.planes_issued) && algebraic_counts(t, own);
             for (int i = 0; i < 5; ++i) sum[i] = known ? sum[i] + own[i] : -1;
         }
     }
@@ -961,9 +967,11 @@ bc_status bc_get_timing(bc_ctx *ctx, const char *kernel, double *total_ms, int64
     if (!ctx || !kernel || !total_ms || !launches) return BC_ERR_INVALID_ARG;
     *total_ms = 0.0;
     *launches = 0;
-    if (!ctx->poisoned) (void)sparse_settle(ctx); // replays' handed-back batches are counted too
+    const bool captured = capturing(ctx);
+    if (!ctx->poisoned && !captured) (void)sparse_settle(ctx); // replays' handed-back batches are counted too
     auto it = ctx->timers.find(kernel);
     if (it == ctx->timers.end()) return BC_OK;
+    if (captured) return bc_fail(ctx, BC_ERR_STATE, "the context's stream is being captured into a HIP graph");
     BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     for (auto &pr : it->second.pending) {
         float ms = 0.f;
