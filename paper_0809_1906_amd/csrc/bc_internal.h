@@ -413,6 +413,9 @@ void noalloc_init_device(int device);
 // That address, or nullptr if the lookup failed.
 unsigned char *noalloc_scratch(int device);
 
+// Checks and sets the batch width and row split; sparse_prepare also the batch
+// state.
+bc_status sparse_shape(bc_ctx *ctx, int32_t batch, int32_t split_degree);
 bc_status sparse_prepare(bc_ctx *ctx, int32_t batch, int32_t split_degree);
 bc_status algebraic_prepare(bc_ctx *ctx);
 // Forward level l -> l+1 by products (front, counts, any and lvmax of level l+1).

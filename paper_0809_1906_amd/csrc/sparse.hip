@@ -1565,13 +1565,20 @@ __global__ void k_ctl_skip(BatchCtl *ctl) {
 
 } // namespace
 
-bc_status sparse_prepare(bc_ctx *ctx, int32_t batch, int32_t split_degree) {
+bc_status sparse_shape(bc_ctx *ctx, int32_t batch, int32_t split_degree) {
     SparseState &s = ctx->sp;
     if (batch != 64 && batch != 128 && batch != 256 && batch != 512)
         return bc_fail(ctx, BC_ERR_INVALID_ARG, "sparse form: batch must be 64, 128, 256 or 512");
     s.batch = batch;
     s.words = batch / 64;
     s.split = split_degree > 0 ? split_degree : 128;
+    return BC_OK;
+}
+
+bc_status sparse_prepare(bc_ctx *ctx, int32_t batch, int32_t split_degree) {
+    const bc_status st = sparse_shape(ctx, batch, split_degree);
+    if (st != BC_OK) return st;
+    SparseState &s = ctx->sp;
     {
         // launch shapes of the pulls: at most 32 blocks of four waves per
         // compute unit, each wave striding over the items; 16 and 64 were

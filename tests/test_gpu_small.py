@@ -112,3 +112,19 @@ def test_small_overflow(gpu_lib, form):
         ctx.reset()
         ctx.run(np.array([600], np.int32))  # near the middle: counts fit
         assert rel_err(ctx.read(), oracle.bc(g, sources=np.array([600], np.int32))) <= 1e-5
+
+
+@pytest.mark.parametrize("form,batch", [("auto", 0), ("sparse", 512), ("hybrid", 256)])
+def test_small_contexts_hold_no_batch_state(gpu_lib, form, batch):
+    g = gg.er_plus_tree(300, 6.0, 3)
+    print(f"small state {form}", flush=True)
+    with gpu_lib.BC(g, form=form, batch=batch) as ctx:
+        # a batch's counts alone: 8 bytes for every vertex and source
+        assert ctx.info().device_bytes < 8 * g.n * ctx.info().batch
+        ctx.run()
+        assert rel_err(ctx.read(), oracle.bc(g)) <= 1e-5
+        assert ctx.info().batch == (batch or 256)
+    for bad in (192, 1024):
+        with pytest.raises(gpu_lib.BCError) as ei:
+            gpu_lib.BC(g, form="sparse", batch=bad)
+        assert ei.value.status == gpu_lib.BC_ERR_INVALID_ARG
