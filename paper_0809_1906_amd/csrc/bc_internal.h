@@ -159,7 +159,9 @@ struct WeightedState {
     WeightedBuffers lds;          // the sweep with its distances in LDS
     int32_t lds_threads = 0;      // its threads per workgroup; 0: the distances do not fit
     int32_t lds_few = 0;          // up to this many sources its workgroups have 1024 threads
-    bool lds_off = false;         // most sources' distances pass 16 bits
+    int64_t lds_tried = 0;        // sources given to it
+    int64_t lds_back = 0;         // of those, handed back: a distance past 16 bits, DAG arcs past
+                                  // their room or a count near 2^64
     WeightedBuffers main;         // many workgroups, arena of max(4n, 2^16)
     WeightedBuffers big;          // few workgroups, arena of nnz (allocated on first need)
     uint32_t *next = nullptr;

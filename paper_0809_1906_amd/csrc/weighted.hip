@@ -831,12 +831,18 @@ bc_status weighted_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, boo
         const size_t row = (size_t)c0 * ctx->n;
         const Outputs o{accumulate, delta_dump ? delta_dump + row : nullptr, dist_dump ? dist_dump + row : nullptr,
                         sigma_dump ? sigma_dump + row : nullptr};
-        const bool lds = w.lds_threads && !w.lds_off;
+        // A graph most of whose sources are handed back goes to the other sweep
+        // straight away, once enough of them have said so: one source, or a
+        // readout of a far component, tells nothing about the others.
+        const bool lds = w.lds_threads && (w.lds_tried < 256 || 2 * w.lds_back <= w.lds_tried);
         uint32_t left = 0;
         bc_status st = launch(ctx, lds ? w.lds : w.main, src, nullptr, cnt, o, &left);
         if (st != BC_OK) return st;
+        if (lds) {
+            w.lds_tried += cnt;
+            w.lds_back += left;
+        }
         if (left && lds) {
-            w.lds_off = 2 * (int64_t)left > cnt; // long distances: the other sweep straight away from now on
             if ((st = gather_left(ctx, src, cnt, left)) != BC_OK) return st;
             if ((st = launch(ctx, w.main, w.again, w.again + left, left, o, &left)) != BC_OK) return st;
         }

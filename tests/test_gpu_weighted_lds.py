@@ -72,3 +72,21 @@ def test_weighted_lds_overflow(gpu_lib):
         ctx.reset()
         ctx.run(np.array([5], np.int32))
         assert rel_err(ctx.read(), oracle.bc(g, sources=np.array([5], np.int32))) <= 1e-12
+
+
+def test_a_few_far_sources_decide_nothing(gpu_lib):
+    """A far source takes a launch of either sweep, until most of at least 256
+    sources were far; a near one takes one launch."""
+    g = union(255, gg.path(600), gg.star(300))  # a path's vertices are up to 152745 apart
+    far, near = np.arange(100, dtype=np.int32), np.arange(600, 650, dtype=np.int32)
+    sums, launches = np.zeros(g.n), 0
+    with gpu_lib.BC(g, timing=1) as ctx:
+        # by the last far hundred 202 of 302 sources have been far
+        for src, new in ((far[:1], 2), (far[:1], 2), (near, 1), (far, 2), (near, 1), (far, 2), (far[:1], 1),
+                         (near, 1), (far, 1)):
+            print(f"weighted_lds far={src.size and src[0] < 600} count={src.size}", flush=True)
+            ctx.run(src)
+            launches += new
+            assert ctx.timing("weighted_sweep")[1] == launches
+            sums += oracle.bc(g, sources=src)
+        assert rel_err(ctx.read(), sums) <= 1e-12
