@@ -73,7 +73,6 @@ struct SparseState {
     int32_t *heavy_nseg = nullptr; // [nheavy] segments per heavy row
     uint32_t *arrive = nullptr;  // [nheavy] segment arrival counters (per row)
     uint32_t *arrive_w = nullptr;// [nheavy][words] segment arrival counters (per row and word)
-    bool bwd_per_word = true;    // backward: one wave per (row, word) instead of per row
     int32_t bwd_grid = 0;        // per-word backward: blocks per launch (0 = one wave per item)
     int32_t fwd_grid = 0;        // forward pull: blocks per launch (0 = one wave per row or segment)
     int32_t depth_guess = 8;     // forward levels launched before the first check

@@ -247,55 +247,6 @@ __device__ __forceinline__ void fwd_scan(const Topo &t, int32_t beg, int32_t end
     }
 }
 
-// acc[q] += sum over arcs [beg, end) of c(w, 64q+lane) for neighbours w whose
-// word q of the level-(l+1) frontier meets F[q] at this lane.
-template <int NW>
-__device__ __forceinline__ void bwd_scan(const Topo &t, int32_t beg, int32_t end, const uint64_t (&F)[NW],
-                                         const uint32_t *__restrict__ any_next, const uint64_t *__restrict__ fnext,
-                                         const float *__restrict__ cval, int lane, double (&acc)[NW]) {
-    constexpr int ARCS = NW >= GDEPTH ? 1 : GDEPTH / NW;
-    for (int32_t base = beg; base < end; base += 64) {
-        const int32_t e = base + lane;
-        int32_t w = 0;
-        uint64_t g[NW];
-#pragma unroll
-        for (int q = 0; q < NW; ++q) g[q] = 0;
-        if (e < end) {
-            w = t.col[e];
-            if ((any_next[w >> 5] >> (w & 31)) & 1) {
-#pragma unroll
-                for (int q = 0; q < NW; ++q) g[q] = fnext[(size_t)w * NW + q] & F[q];
-            }
-        }
-        uint64_t nz = 0;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) nz |= g[q];
-        uint64_t act = __ballot(nz != 0);
-        while (act) {
-            float x[ARCS][NW];
-#pragma unroll
-            for (int a = 0; a < ARCS; ++a) {
-#pragma unroll
-                for (int q = 0; q < NW; ++q) x[a][q] = 0.f;
-                if (act) {
-                    const int j = pop_lowest(act);
-                    const size_t row = (size_t)rl32(w, j) * t.B;
-#pragma unroll
-                    for (int q = 0; q < NW; ++q) {
-                        const uint64_t gj = rl64(g[q], j);
-                        if (gj != 0 && in_mask(gj)) x[a][q] = at_lane(cval + row + (size_t)q * 64, lane);
-                    }
-                }
-            }
-#pragma unroll
-            for (int a = 0; a < ARCS; ++a) {
-#pragma unroll
-                for (int q = 0; q < NW; ++q) acc[q] += (double)x[a][q];
-            }
-        }
-    }
-}
-
 // For every word with sources at this level: delta(v,b) = sigma(v,b) * acc,
 // c(v,b) = (1 + delta) / sigma; BC(v) += sum of delta, times the source's
 // weight (behind the B sources), over lanes whose source is not v (one atomic
@@ -654,64 +605,6 @@ __global__ __launch_bounds__(SB) void k_fwd_pull_row(
                               lvmax_next, threadIdx.x & 63);
 }
 
-// Backward level l.  Light rows complete in their wave; split rows in the last
-// segment wave to arrive.  fnext = nullptr at the deepest level.
-template <int NW, typename S>
-__global__ __launch_bounds__(SB) void k_bwd_pull(Topo t, const uint64_t *__restrict__ fcur,
-                                                 const uint32_t *__restrict__ any_next,
-                                                 const uint64_t *__restrict__ fnext, const S *__restrict__ sigma,
-                                                 float *__restrict__ cval, const int32_t *__restrict__ src_lane,
-                                                 double *__restrict__ bc, double *__restrict__ hacc,
-                                                 uint32_t *__restrict__ arrive, double *__restrict__ delta_dump,
-                                                 int accumulate, const uint32_t *__restrict__ lvf) {
-    // replayed batches: lvf[0] says level l holds a vertex (cleared for a
-    // batch handed back), lvf[1] level l+1 (else fnext is not read)
-    if (lvf) {
-        if (lvf[0] == 0) return;
-        if (lvf[1] == 0) fnext = nullptr;
-    }
-    const int lane = threadIdx.x & 63;
-    const int64_t wid = (int64_t)blockIdx.x * WPB + (threadIdx.x >> 6);
-    Item it;
-    if (!item_of(t, wid, it)) return;
-    const int32_t v = it.v;
-    uint64_t F[NW];
-    load_words<NW>(fcur + (size_t)v * NW, lane, F);
-    uint64_t anyF = 0;
-#pragma unroll
-    for (int q = 0; q < NW; ++q) anyF |= F[q];
-    if (anyF == 0) return;
-    double acc[NW];
-#pragma unroll
-    for (int q = 0; q < NW; ++q) acc[q] = 0.0;
-    if (!fnext) {
-        // the deepest level: no successor, so delta = 0 and c = 1 / lambda;
-        // the row's first segment finalizes it, no partial sums are needed
-        if (it.first) bwd_finalize<NW, S>(v, F, acc, lane, t.B, t.n, sigma, cval, src_lane, bc, delta_dump, accumulate);
-        return;
-    }
-    bwd_scan<NW>(t, it.beg, it.end, F, any_next, fnext, cval, lane, acc);
-    if (it.h < 0) {
-        bwd_finalize<NW, S>(v, F, acc, lane, t.B, t.n, sigma, cval, src_lane, bc, delta_dump, accumulate);
-        return;
-    }
-    double *hrow = hacc + (size_t)it.h * t.B + lane;
-#pragma unroll
-    for (int q = 0; q < NW; ++q)
-        if (acc[q] != 0.0) unsafeAtomicAdd(&hrow[q * 64], acc[q]);
-    if (last_arriver(&arrive[it.h], t.heavy_nseg[it.h], lane)) {
-#pragma unroll
-        for (int q = 0; q < NW; ++q) {
-            acc[q] = 0.0;
-            if ((F[q] >> lane) & 1) {
-                acc[q] = __hip_atomic_load(&hrow[q * 64], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (acc[q] != 0.0) __hip_atomic_store(&hrow[q * 64], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        bwd_finalize<NW, S>(v, F, acc, lane, t.B, t.n, sigma, cval, src_lane, bc, delta_dump, accumulate);
-    }
-}
-
 // Backward level l, one item per (row or row segment, word q): at the fat
 // levels this keeps NW times more waves in flight than a wave per row, and a
 // word with no sources at this level costs its wave a single load.
@@ -856,7 +749,8 @@ __global__ __launch_bounds__(SB) __attribute__((amdgpu_waves_per_eu(8))) void k_
     Topo t, const uint64_t *__restrict__ fcur, const uint64_t *__restrict__ fnext, const S *__restrict__ sigma, float *__restrict__ cval,
     const int32_t *__restrict__ src_lane, double *__restrict__ bc, double *__restrict__ hacc,
     uint32_t *__restrict__ arrive, double *__restrict__ delta_dump, int accumulate, const uint32_t *__restrict__ lvf, int C) {
-    // lvf as in k_bwd_pull
+    // replayed batches: lvf[0] says level l holds a vertex (cleared for a
+    // batch handed back), lvf[1] level l+1 (else fnext is not read)
     if (lvf) {
         if (lvf[0] == 0) return;
         if (lvf[1] == 0) fnext = nullptr;
@@ -1188,7 +1082,6 @@ bc_status launch_bwd_level(bc_ctx *ctx, const BatchShape &b, int32_t lv, bool pr
     SparseState &s = ctx->sp;
     const uint64_t *fcur = s.front + (size_t)lv * b.words;
     const uint64_t *fnext = flags || deeper ? s.front + (size_t)(lv + 1) * b.words : nullptr;
-    const uint32_t *anext = fnext ? s.any + (size_t)(lv + 1) * b.aw : nullptr;
     const uint32_t *lvf = flags ? s.lvflag + lv : nullptr;
     if (products) return algebraic_backward_level(ctx, sizeof(S) == 8, fcur, fnext, 1, ddump, accumulate, lvf);
     LaunchTimer tm(ctx, "bwd_pull");
@@ -1196,13 +1089,11 @@ bc_status launch_bwd_level(bc_ctx *ctx, const BatchShape &b, int32_t lv, bool pr
     if (ctx->edges && accumulate) // edge terms come from the per-word pull, one wave per item
         hipLaunchKernelGGL((k_bwd_pull_we<NW, S>), dim3(b.word_blocks), dim3(SB), 0, ctx->stream, b.t, fcur, fnext,
                            sigma, s.cval, s.src, ctx->bc, s.hacc, s.arrive_w, ddump, 1, ctx->eb, lvf);
-    else if (s.bwd_per_word || ctx->edges) {
+    else {
         const int grid = s.bwd_grid > 0 ? std::min(b.word_blocks, s.bwd_grid) : b.word_blocks;
         hipLaunchKernelGGL((k_bwd_pull_w<NW, S>), dim3(grid), dim3(SB), 0, ctx->stream, b.t, fcur, fnext, sigma,
                            s.cval, s.src, ctx->bc, s.hacc, s.arrive_w, ddump, accumulate ? 1 : 0, lvf, at_once((int64_t)ctx->n * NW, 64, 8192));
-    } else
-        hipLaunchKernelGGL((k_bwd_pull<NW, S>), dim3(b.pull_blocks), dim3(SB), 0, ctx->stream, b.t, fcur, anext, fnext,
-                           sigma, s.cval, s.src, ctx->bc, s.hacc, s.arrive, ddump, accumulate ? 1 : 0, lvf);
+    }
     tm.done();
     return BC_OK;
 }
