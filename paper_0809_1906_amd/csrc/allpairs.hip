@@ -363,6 +363,10 @@ bc_status allpairs_bc(bc_ctx *ctx, double *bc_internal) {
         return bc_hip(ctx, pe, "all pairs: preparation");
     }
     bool near = D8 && deepest <= MAX8;
+    if (!near) { // the triple sum alone needs no D8
+        bc_dfree(ctx, D8);
+        D8 = nullptr;
+    }
     LaunchTimer tm(ctx, "all_pairs");
     if (near) {
         const int32_t xcds = 8, tiles = l8 / 256;

@@ -98,6 +98,25 @@ def test_all_pairs_without_the_far_matrices(gpu_lib):
     assert not a.live
 
 
+@pytest.mark.parametrize("form", ["sparse", "plain"])
+@pytest.mark.parametrize("name", ["deep", "near"])
+def test_all_pairs_in_24_bytes_a_pair(gpu_lib, name, form):
+    """Distances past a byte leave every triple to the triple sum; so do near
+    ones where there is no more memory."""
+    g = gg.path(512) if name == "deep" else gg.watts_strogatz(512, 4, 0.05, 9)
+    a, ctx = context(g, form, 0 if form == "plain" else 64)
+    held = sum(a.live.values())
+    room = held + 24 * g.n * g.n + 8 * g.n + 8192  # the result, the sources
+    a.refuse = lambda nbytes: sum(a.live.values()) + nbytes > room
+    print(f"less_room all_pairs {name} {form}", flush=True)
+    out = np.zeros(g.n)
+    assert B.load().bc_all_pairs(ctx, out.ctypes.data, B.BC_MEM_HOST) == B.BC_OK
+    assert rel_err(out, oracle.bc(g)) <= 1e-12
+    assert sum(a.live.values()) == held
+    B.load().bc_destroy(ctx)
+    assert not a.live
+
+
 def up256(nbytes):
     return -(-nbytes // 256) * 256
 
