@@ -349,6 +349,11 @@ struct LaunchTimer {
     const char *name;
     hipEvent_t a = nullptr, b = nullptr;
     LaunchTimer(bc_ctx *c, const char *nm);
+    LaunchTimer(const LaunchTimer &) = delete;
+    ~LaunchTimer() { // not done: an error on the way
+        bc_event_put(ctx, a);
+        bc_event_put(ctx, b);
+    }
     void done();
 };
 
