@@ -168,11 +168,15 @@ typedef struct {
                              workgroups, each running one source at a time;
                              0 = default: sweeps whose state fits the compute
                              units' LDS where it does, as many workgroups as
-                             fit; else, and with a grid, the sweeps with their
-                             state in memory (the most workgroups that fit a
-                             workspace budget, at most 2048 unweighted, 1024
-                             weighted; the budget is 16 GB unweighted, 96 GB
-                             weighted, 192 GB weighted with an explicit grid) */
+                             fit; else the sweeps with their state in memory
+                             (the most workgroups that fit a workspace budget,
+                             at most 2048 unweighted, 1024 weighted; the budget
+                             is 16 GB unweighted, 96 GB weighted, 192 GB
+                             weighted with an explicit grid).  With a grid,
+                             integer weights always take the sweep with its
+                             state in memory; unit weights take one source per
+                             workgroup at any size, its vertices' states in LDS
+                             where they fit */
     int32_t edges;        /* nonzero: also accumulate edge betweenness (read with
                              bc_read_edges).  Plain, sparse and hybrid forms
                              (the hybrid form then takes every backward level
