@@ -468,7 +468,10 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
     }
     ctx->comp_size = (int32_t *)bc_dalloc(ctx, sizeof(int32_t) * (size_t)std::max(n, 1));
     if (!ctx->comp_size) return bail(BC_ERR_NOMEM, "device allocation failed");
-    // Host arrays (the caller's or the relabelled copies) go up synchronously.
+    // Host arrays (the caller's or the relabelled copies) go up synchronously,
+    // on the null stream: after what the stream still does with the memory that
+    // a stream-ordered allocator has handed over.
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return bail(BC_ERR_DEVICE, "stream synchronisation failed");
     const bool direct_device = !relabel && g->mem == BC_MEM_DEVICE;
     hipMemcpyKind kind = direct_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     if (hipMemcpy(ctx->row_ptr, urp, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyHostToDevice) != hipSuccess ||
@@ -604,6 +607,8 @@ bc_status bc_create_many(const bc_graph *gs, int32_t count, const bc_options *op
     ctx->status_host = (uint32_t *)bc_halloc(256);
     if (!ctx->col || !ctx->bc || !ctx->bc_scratch || !ctx->status || !ctx->status_host)
         return bail(BC_ERR_NOMEM, "device allocation failed");
+    // as in bc_create: the uploads wait for the memory's last use
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return bail(BC_ERR_DEVICE, "stream synchronisation failed");
     if ((total_arcs > 0 &&
          hipMemcpy(ctx->col, col.data(), sizeof(int32_t) * (size_t)total_arcs, hipMemcpyHostToDevice) != hipSuccess) ||
         hipMemsetAsync(ctx->bc, 0, sizeof(double) * nn, ctx->stream) != hipSuccess ||
