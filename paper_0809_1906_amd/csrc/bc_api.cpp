@@ -313,6 +313,9 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
     const int32_t *hrp = g->row_ptr, *hcol = g->col;
     const uint32_t *hw = g->weight;
     if (g->mem == BC_MEM_DEVICE) {
+        // the arrays as the stream leaves them: the copies below are on the null stream
+        if (hipStreamSynchronize((hipStream_t)opt.stream) != hipSuccess)
+            return fail_create(BC_ERR_DEVICE, "stream synchronisation failed");
         rp.resize((size_t)n + 1);
         col.resize((size_t)std::max(nnz, 1));
         if (hipMemcpy(rp.data(), g->row_ptr, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToHost) != hipSuccess ||
@@ -645,7 +648,9 @@ static bc_status stage_sources(bc_ctx *ctx, const int32_t *sources, int64_t coun
     const int32_t *hs = sources;
     if (mem == BC_MEM_DEVICE) {
         host.resize((size_t)count);
-        BC_HIP(ctx, hipMemcpy(host.data(), sources, sizeof(int32_t) * (size_t)count, hipMemcpyDeviceToHost));
+        BC_HIP(ctx, hipMemcpyAsync(host.data(), sources, sizeof(int32_t) * (size_t)count, hipMemcpyDeviceToHost,
+                                   ctx->stream));
+        BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
         hs = host.data();
     }
     for (int64_t i = 0; i < count; ++i)
