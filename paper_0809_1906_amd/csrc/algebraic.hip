@@ -948,9 +948,12 @@ static bc_status algebraic_scratch(bc_ctx *ctx) {
     a.part = (uint64_t *)bc_dalloc(ctx, (size_t)a.npad * B * sizeof(uint64_t));
     a.kflags = (uint32_t *)bc_dalloc(ctx, (K / GK) * (B / GN) * sizeof(uint32_t));
     a.planes_issued = (unsigned long long *)bc_dalloc(ctx, 256);
-    // Forward products with fewer tiles than the compute units hold blocks at
-    // once (256 units, two blocks each): two blocks per tile, each over every
-    // second stage (the sums are exact integers, so any split gives the same).
+    int cus = 0;
+    BC_HIP(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    const bool idle = (size_t)(a.npad / 128) * (B / GN) <= (size_t)std::max(cus, 1); // a tile per unit at most
+    // Forward products with fewer tiles than the compute units (256 here) hold
+    // blocks at once, two each: two blocks per tile, each over every second
+    // stage (the sums are exact integers, so any split gives the same).
     // Up to 256 tiles and from K = 4096 they gain 1 to 4% of a run over all
     // sources (G(5003, 128/5002), weights 1..4, batch 512: 13.5 -> 13.2 ms;
     // G(12000, 150/11999), batch 256: 46.5 -> 44.8); with 376 tiles they lose 5%,
@@ -958,14 +961,14 @@ static bc_status algebraic_scratch(bc_ctx *ctx) {
     // (tiles halve as the blocks per unit do); the workspace takes the larger
     // of the two (grids are rounded up to whole rounds of the eight XCDs).
     const size_t ntiles = grid_blocks<128>(a.npad, B), ntiles256 = grid_blocks<256>(a.npad, B);
-    a.ksplit = (size_t)(a.npad / 128) * (B / GN) <= 256 && K >= 4096 ? 2 : 1;
+    a.ksplit = idle && K >= 4096 ? 2 : 1;
     // Backward blocks of 64 rows up to 256 tiles of 128 x 128: twice the blocks
     // where a unit would hold one, the same sums in the same order.  All
     // sources, ms with 128 / 64 rows, batch 512: G(5003, 128/5002) weights 1..4
     // 13.2 / 12.0, G(5003, 50/5002) 5.8 / 5.0, G(8000, 80/7999) (256 tiles) 12.5 /
     // 11.1, G(12000, 150/11999) (376) 30.4 / 30.9; batch 256: 25.2 / 20.1, 11.0 /
     // 8.7 and 23.2 / 18.4 for the first three.
-    a.bwd_rows = (size_t)(a.npad / 128) * (B / GN) <= 256 ? 64 : 128;
+    a.bwd_rows = idle ? 64 : 128;
     const size_t per_tile = (size_t)(RT * 2 * 16) * sizeof(float); // one thread's sums
     const size_t ws = a.ksplit > 1 ? (size_t)10 * a.ksplit * per_tile * std::max(ntiles * 256, ntiles256 * 512) : 0;
     const size_t narrive = (size_t)10 * std::max(ntiles, ntiles256);

@@ -92,9 +92,9 @@ __global__ __launch_bounds__(256) void k_alg2_far(int32_t n, int32_t ld, const i
 // rows u (n bytes per arc, and 8 n where distances grow), so the blocks of one
 // XCD (every eighth) take one column range after the other: 256 columns of
 // every row of D8 fit its L2 up to n = 16384.  Whole call, against the triple
-// sum alone: G(6001, 64/6000), distances up to 3, 7.3 against 90.4 ms (this
-// kernel 2.4); G(16384, 256/16383) 77 against 492; where far triples remain,
-// G(6001, 8/6000) 41 against 57 and RMAT-13 70 against 111.
+// sum alone: G(6001, 64/6000), distances up to 3, 5.3 against 88 ms (this
+// kernel 2.4); G(16384, 256/16383) 75.4 against 492 (58.2); where far triples
+// remain, G(6001, 8/6000) 41 against 57 and RMAT-13 70 against 111.
 __global__ __launch_bounds__(256) void k_alg2_near(int32_t n, int32_t l8, const int32_t *__restrict__ rp,
                                                    const int32_t *__restrict__ col, const uint8_t *__restrict__ D8,
                                                    const double *__restrict__ R, const uint64_t *__restrict__ Lam,

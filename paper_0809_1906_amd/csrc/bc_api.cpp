@@ -1,6 +1,6 @@
 // The C ABI of include/bc.h: host-side validation, device memory, streams,
-// and dispatch to the forms.  Every device step runs in the HIP kernels of
-// plain.hip and sparse.hip.
+// and dispatch to the forms, whose device steps are the HIP kernels of the
+// other files.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -198,8 +198,8 @@ struct MultiState {
     int32_t ngraphs = 0, nunits = 0, chunk = 64, grid = 0;
     int32_t nbig = 0, nsmall = 0;     // units [0, nbig) and the next nsmall go to the group sweep
     int32_t *voff = nullptr, *rpoff = nullptr, *rp = nullptr, *units = nullptr;
-    int32_t *redo = nullptr;          // group-sweep units handed back to the full sweep
-    unsigned int *next = nullptr;     // queue counters: big, full, redo; [3] = redo count; [4] = small
+    int32_t *redo = nullptr;          // group-sweep units to run again with 64-bit counts
+    unsigned int *next = nullptr;     // queue counters: big, full, again; [3] = units to run again; [4] = small
     std::vector<int32_t> h_voff;
     std::vector<int32_t> h_arcs;      // arcs of each graph
     std::vector<uint8_t> h_group;     // graphs the group sweep takes
@@ -456,7 +456,7 @@ void lanes_release(bc_ctx *ctx); // synchronises
 // where there are none, or they have replays whose checks the host has not
 // read.  Synchronises.
 bool lanes_give_room(bc_ctx *ctx);
-// Destroys the recorded batch graphs and their capture stream; synchronises.
+// Destroys the recorded batch graph; synchronises.
 void sparse_graphs_release(bc_ctx *ctx);
 // delta_dump = nullptr runs the forward only (distances and counts).
 bc_status sparse_dump(bc_ctx *ctx, const int32_t *d_sources, int32_t count,

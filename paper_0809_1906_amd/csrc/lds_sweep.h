@@ -1,5 +1,5 @@
 // Per-source sweeps of a small graph with all per-source state in LDS, K
-// sources at once in one workgroup (multigraph.hip).
+// sources at once in one workgroup (multigraph.hip, small.hip).
 //
 // Brandes's algorithm (Sec. 1.1) for the sources of a group together: an entry
 // id = k (n + 1) + v stands for vertex v of the group's k-th source, and one

@@ -34,8 +34,8 @@ constexpr int32_t MG_INF = 0x7FFFFFFF;
 constexpr int ABURST = 8;        // column reads issued together per vertex
 constexpr int32_t COL_CAP = 16320; // 16-bit columns staged in LDS
 constexpr int LEVCAP = 1024;       // levels per source in the group sweep
-// The group sweep is bound by VALU and LDS issue about equally (counters: each
-// busy 45-50% of the time, the rest barriers and latency), and gains from
+// The group sweep is bound by VALU and LDS issue about equally (counters over
+// 256 Watts-Strogatz graphs: each busy half of the time), and gains from
 // every source that shares a barrier: one workgroup of 1024 threads with the
 // whole LDS (K = 4 at n = 4096).  256 Watts-Strogatz graphs, n = 64..4096:
 // 20.0 ms, against 23.0 with two workgroups of 512 and half the LDS each, and
@@ -62,7 +62,7 @@ struct MultiArgs {
     const int64_t *boff;   // [ngraphs] first burst of each graph (-1: not in the group sweep)
     const uint32_t *safe;  // [ngraphs] (2^32 - 1) / largest degree
     const uint4 *bursts;   // columns as 16-bit ids, eight per burst
-    int32_t *redo;         // group sweep: units handed to the full sweep
+    int32_t *redo;         // group sweep with 32-bit counts: units to run again in 64 bits
     unsigned int *redo_count;
     double *bc;            // [sum n]
     uint32_t *status;

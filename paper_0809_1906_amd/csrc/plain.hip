@@ -1,6 +1,7 @@
-// Plain FP64 form: one workgroup per source, per-source state in HBM.  Graphs
-// whose state fits the LDS go to small.hip instead, unless the caller asks for
-// a grid of workgroups or for edge terms.
+// Plain FP64 form: one workgroup per source, the vertices' states in LDS where
+// they fit, counts and sums in HBM.  Graphs whose whole state fits the LDS go to
+// small.hip instead, unless the caller asks for a grid of workgroups or for edge
+// terms.
 //
 // For each source s (Brandes's algorithm, Sec. 1.1):
 //   forward   level-synchronous breadth-first search from s (the parallel BFS
@@ -404,8 +405,9 @@ bc_status plain_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool a
         // up to a source per compute unit: all the threads one can have
         const bool wide = p.threads == WIDE_T ||
                           (count <= p.cus && fixed_lds<WIDE_T>() + state_lds(ctx->n) <= LDS_BYTES);
-        hipLaunchKernelGGL(wide ? k_plain_state<WIDE_T> : k_plain_state<ST_T>, dim3(grid), dim3(wide ? WIDE_T : ST_T), state_lds(ctx->n), ctx->stream, ctx->n, ctx->row_ptr, ctx->col,
-                           d_sources, count, (unsigned long long *)p.next, p.sigma, p.queue, p.lev, ctx->bc,
+        hipLaunchKernelGGL(wide ? k_plain_state<WIDE_T> : k_plain_state<ST_T>, dim3(grid),
+                           dim3(wide ? WIDE_T : ST_T), state_lds(ctx->n), ctx->stream, ctx->n, ctx->row_ptr,
+                           ctx->col, d_sources, count, (unsigned long long *)p.next, p.sigma, p.queue, p.lev, ctx->bc,
                            ctx->status, accumulate ? 1 : 0, delta_dump, dist_dump, sigma_dump, eb);
     } else {
         hipLaunchKernelGGL(k_plain_sweep, dim3(grid), dim3(PB), 0, ctx->stream, ctx->n, ctx->row_ptr, ctx->col,

@@ -1397,7 +1397,7 @@ void destroy_graphs(bc_ctx *ctx) {
     s.gexec = nullptr;
 }
 
-// Records one batch on the private capture stream (nothing runs) and
+// Records one batch on a private stream (nothing runs) and
 // instantiates it.
 bc_status capture_batch(bc_ctx *ctx, int32_t L, const std::vector<uint8_t> &plan) {
     SparseState &s = ctx->sp;

@@ -344,7 +344,8 @@ __global__ __launch_bounds__(PB) void k_weighted_sweep(
 // 19.4 against 12.9 / 25.7, up to 10 2.5 / 13.3 against 10.8 / 23.5; RMAT-13 1.7 /
 // 4.2 against 3.2 / 5.7; G(60000, 10/59999) 5.2 / 23.1 against 11.0 / 28.9.
 // What bounds the sweep is each phase's chain of dependent accesses and its
-// barriers (counters: waves wait 67% of their time, vector units busy 47%), so:
+// barriers (counters, RMAT-16, weights up to 255, 1024 sources: waves wait 74%
+// of their time, vector instructions issue in 32% of it), so:
 //   - a phase finds its vertices, and the least distance above its own, by a
 //     scan of the distances (two per instruction): no bins to read, search and
 //     file in memory, and no phase without a vertex.  The thread that finds a
@@ -710,10 +711,11 @@ WeightedWork work_of(bc_ctx *ctx, const WeightedBuffers &b) {
 } // namespace
 
 // The sweep with its distances in LDS takes every source first, where it
-// applies; what it hands back goes to the main workspace.  Workgroups get an arena ring of max(4n, 2^16) entries (rounded up to a power
-// of two); a source whose live bins outgrow it is re-run with an arena of nnz
-// entries, which always suffices (a vertex settles once, so at most one entry
-// per arc is ever filed).
+// applies; what it hands back goes to the main workspace.  Workgroups get an
+// arena ring of max(4n, 2^16) entries (rounded up to a power of two); a source
+// whose live bins outgrow it is re-run with an arena of nnz entries, which
+// always suffices (a vertex settles once, so at most one entry per arc is ever
+// filed).
 bc_status weighted_prepare(bc_ctx *ctx) {
     WeightedState &w = ctx->wt;
     if (ctx->max_weight > 255)
@@ -729,8 +731,9 @@ bc_status weighted_prepare(bc_ctx *ctx) {
     // The sweep with its distances in LDS, unless a grid or an arena of the
     // other was asked for: 512 threads where two workgroups' distances fit a
     // compute unit, else 1024, and 1024 up to a source per compute unit.  ms
-    // with 512 / 1024 threads: RMAT-15, 1024 sources 10.3 / 13.8, one 4.4 / 3.5 (9.4 and 3.0 by now);
-    // RMAT-13 with weights up to 10, 1024 sources 1.8 / 2.1, one 0.70 / 0.51.
+    // with 512 / 1024 threads, before one owner search served a wave: RMAT-15,
+    // 1024 sources 10.3 / 13.8, one 4.4 / 3.5; RMAT-13 with weights up to 10,
+    // 1024 sources 1.8 / 2.1, one 0.70 / 0.51.
     if (w.grid == 0 && w.arena_log2 == 0 && ctx->n > 0) {
         int cus = 0;
         BC_HIP(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
