@@ -188,7 +188,8 @@ struct SmallState {
     LdsColumns cols;
     uint32_t *count = nullptr;  // [0] units handed back by the 32-bit sweep, [1] most levels seen,
                                 // [2] by the last allocation-free call
-    int32_t *redo = nullptr;    // those units (the first list: behind count)
+    int32_t *redo = nullptr;    // those units
+    int32_t *first_redo = nullptr; // the first list, part of count's allocation
     int64_t redo_cap = 0;
 };
 
@@ -378,11 +379,14 @@ bc_status plain_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool a
                     double *delta_dump, int32_t *dist_dump, uint64_t *sigma_dump);
 
 // Padded columns of `voff.size() - 1` graphs; taken[g] says whether graph g's
-// bursts fit 16-bit indices.  voff, rpoff and rp as in a many-graph context.
-// d_voff, d_rpoff: voff and rpoff on the device, or null.
+// bursts fit 16-bit indices.  voff, rpoff and rp as in a many-graph context, and
+// on the device.
 bc_status lds_columns(bc_ctx *ctx, const std::vector<int32_t> &voff, const std::vector<int32_t> &rpoff,
                       const std::vector<int32_t> &rp, const int32_t *d_voff, const int32_t *d_rpoff,
                       const int32_t *d_rp, LdsColumns &out, std::vector<uint8_t> &taken);
+// Padded columns of the context's own graph, of fewer than 65536 bursts, by one
+// launch that also clears `words` (at most 256) of `zero`.
+bc_status lds_columns_of(bc_ctx *ctx, uint16_t *brp, void *bursts, uint32_t *zero, int words);
 // Small unweighted graphs without edge terms: can the LDS hold a source's state?
 bool small_fits(const bc_ctx *ctx);
 // Do the sparse and hybrid forms run their sources that way?

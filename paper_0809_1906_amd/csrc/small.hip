@@ -117,13 +117,17 @@ void launch(bc_ctx *ctx, const SmallArgs &a, bool heavy, bool dump, int grid) {
 
 } // namespace
 
-bool small_fits(const bc_ctx *ctx) {
-    if (ctx->weighted || ctx->edges || ctx->n < 1) return false;
-    if (lds_sweep::bytes_for<uint64_t>((size_t)ctx->n, 1, (size_t)ctx->n) > ST_BYTES) return false;
+static int64_t bursts_of(const bc_ctx *ctx) {
     int64_t bursts = 0;
     for (int32_t v = 0; v < ctx->n; ++v)
         bursts += (ctx->h_row_ptr[(size_t)v + 1] - ctx->h_row_ptr[(size_t)v] + lds_sweep::BURST - 1) / lds_sweep::BURST;
-    return bursts < 65536;
+    return bursts;
+}
+
+bool small_fits(const bc_ctx *ctx) {
+    if (ctx->weighted || ctx->edges || ctx->n < 1) return false;
+    if (lds_sweep::bytes_for<uint64_t>((size_t)ctx->n, 1, (size_t)ctx->n) > ST_BYTES) return false;
+    return bursts_of(ctx) < 65536;
 }
 
 // The sparse and hybrid forms' line.  A batch pays two launches per level and
@@ -169,17 +173,23 @@ bc_status small_check_room(bc_ctx *ctx) {
 
 bc_status small_prepare(bc_ctx *ctx) {
     SmallState &m = ctx->sm;
-    const std::vector<int32_t> voff{0, ctx->n}, rpoff{0};
+    // a small context's preparation is mostly allocations and copies: one
+    // allocation (the counts, the columns, the first list, the row starts) and one
+    // launch.  Creating a plain context of 300 vertices takes 145 us; with the
+    // tables made on the host and uploaded 185.
+    const size_t columns = (size_t)bursts_of(ctx) * sizeof(uint4);
     m.redo_cap = std::max(ctx->n, 4096);
-    m.count = (uint32_t *)bc_dalloc(ctx, 256 + (size_t)m.redo_cap * sizeof(int32_t)); // and the first list
-    if (!m.count) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation failed");
-    m.redo = (int32_t *)(m.count + 64);
-    BC_HIP(ctx, hipMemsetAsync(m.count, 0, 256, ctx->stream));
-    std::vector<uint8_t> taken;
-    bc_status st = lds_columns(ctx, voff, rpoff, ctx->h_row_ptr, nullptr, nullptr, ctx->row_ptr, m.cols, taken);
+    char *d = (char *)bc_dalloc(ctx, 256 + columns + (size_t)m.redo_cap * sizeof(int32_t) +
+                                         ((size_t)ctx->n + 1) * sizeof(uint16_t));
+    if (!d) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation failed");
+    m.count = (uint32_t *)d;
+    m.cols.bursts = d + 256;
+    m.redo = m.first_redo = (int32_t *)(d + 256 + columns);
+    m.cols.brp = (uint16_t *)(m.redo + m.redo_cap);
+    bc_status st = lds_columns_of(ctx, m.cols.brp, m.cols.bursts, m.count, 64);
     if (st != BC_OK) return st;
     BC_HIP(ctx, hipDeviceGetAttribute(&m.cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
-    m.on = taken[0] != 0;
+    m.on = true;
     return BC_OK;
 }
 
@@ -218,7 +228,7 @@ bc_status small_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool w
     if (a.nunits > m.redo_cap) {
         int32_t *r = (int32_t *)bc_dalloc(ctx, (size_t)a.nunits * sizeof(int32_t));
         if (!r) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation of the handed-back list failed");
-        if (m.redo != (int32_t *)(m.count + 64)) bc_dfree(ctx, m.redo);
+        if (m.redo != m.first_redo) bc_dfree(ctx, m.redo);
         m.redo = r;
         m.redo_cap = a.nunits;
     }
