@@ -128,3 +128,23 @@ def test_small_contexts_hold_no_batch_state(gpu_lib, form, batch):
         with pytest.raises(gpu_lib.BCError) as ei:
             gpu_lib.BC(g, form="sparse", batch=bad)
         assert ei.value.status == gpu_lib.BC_ERR_INVALID_ARG
+
+
+COLUMNS = {f"er{n}": (lambda n=n: gg.er_plus_tree(n, 9.0, n)) for n in (255, 256, 257, 512, 513)}
+COLUMNS |= {
+    "star2049": lambda: gg.star(2050),  # 257 bursts in one row
+    "late-hub": lambda: gg.disjoint_union(gg.path(600), gg.star(900)),
+    "gaps": lambda: gg.disjoint_union(*[gg.path(1)] * 300, gg.complete(40), *[gg.path(1)] * 300),
+}
+
+
+@pytest.mark.parametrize("order", ["degree", "input"])
+@pytest.mark.parametrize("name", list(COLUMNS))
+def test_padded_columns(gpu_lib, name, order):
+    """Row counts around a workgroup's 256, rows of none and of many bursts, in
+    the order of their degrees and as given."""
+    g = COLUMNS[name]()
+    print(f"small columns {name} {order} n={g.n}", flush=True)
+    with gpu_lib.BC(g, form="plain", vertex_order=order) as ctx:
+        ctx.run()
+        assert rel_err(ctx.read(), oracle.bc(g, threads=8)) <= 1e-12  # FP64 throughout
