@@ -285,8 +285,10 @@ struct bc_ctx {
     // graph, BC and stream; only its recorded batches run on its own stream,
     // between the fork and the join of a run.
     std::vector<bc_ctx *> lanes;
+    bool lane = false;                     // this is one
     std::vector<hipStream_t> lane_streams; // the device's, shared by its contexts
     std::vector<hipEvent_t> lane_events; // the fork, then each lane's join
+    double lane_saving = 0.0;            // microseconds that runs without lanes would have saved with them
     int lane_limit = 1 << 30;            // as many as their memory could be had for (until bc_reset)
     uint32_t lane_status = 0;            // what lanes given up since bc_reset had found: status bits,
     int64_t lane_products[5] = {};       // and products as bc_info counts them
@@ -427,6 +429,9 @@ unsigned char *noalloc_scratch(int device);
 // state.
 bc_status sparse_shape(bc_ctx *ctx, int32_t batch, int32_t split_degree);
 bc_status sparse_prepare(bc_ctx *ctx, int32_t batch, int32_t split_degree);
+// A lane's batch state: `from`'s rows and segments, buffers of its own (levels
+// when they are known).
+bc_status sparse_share(bc_ctx *ctx, const bc_ctx *from);
 bc_status algebraic_prepare(bc_ctx *ctx);
 // Forward level l -> l+1 by products (front, counts, any and lvmax of level l+1).
 bc_status algebraic_forward_level(bc_ctx *ctx, bool wide, int32_t l);

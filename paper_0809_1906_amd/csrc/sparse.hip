@@ -936,8 +936,11 @@ bc_status ensure_levels(bc_ctx *ctx, int32_t need) {
     uint32_t *na = (uint32_t *)bc_dalloc(ctx, (size_t)cap * aw * sizeof(uint32_t));
     unsigned long long *nm = (unsigned long long *)bc_dalloc(ctx, (size_t)cap * sizeof(unsigned long long));
     uint32_t *nl = (uint32_t *)bc_dalloc(ctx, (size_t)cap * sizeof(uint32_t));
-    uint32_t *nh = nf && na && nm && nl ? (uint32_t *)bc_halloc((size_t)cap * aw * sizeof(uint32_t)) : nullptr;
-    if (!nh) {
+    bool got = nf && na && nm && nl;
+    uint32_t *nh = nullptr;
+    if (got && !ctx->lane) // a lane's batches are never driven from the host
+        got = (nh = (uint32_t *)bc_halloc((size_t)cap * aw * sizeof(uint32_t))) != nullptr;
+    if (!got) {
         bc_dfree(ctx, nf);
         bc_dfree(ctx, na);
         bc_dfree(ctx, nm);
@@ -956,13 +959,13 @@ bc_status ensure_levels(bc_ctx *ctx, int32_t need) {
     BC_HIP(ctx, hipMemsetAsync(na + (size_t)old * aw, 0, (size_t)(cap - old) * aw * sizeof(uint32_t), ctx->stream));
     BC_HIP(ctx, hipMemsetAsync(nm + old, 0, (size_t)(cap - old) * sizeof(unsigned long long), ctx->stream));
     BC_HIP(ctx, hipMemsetAsync(nl + old, 0, (size_t)(cap - old) * sizeof(uint32_t), ctx->stream));
-    BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (s.front) {
+        BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
         bc_dfree(ctx, s.front);
         bc_dfree(ctx, s.any);
         bc_dfree(ctx, s.lvmax);
         bc_dfree(ctx, s.lvflag);
-        hipHostFree(s.any_host);
+        if (s.any_host) hipHostFree(s.any_host);
     }
     s.front = nf;
     s.any = na;
@@ -1466,6 +1469,45 @@ bc_status sparse_shape(bc_ctx *ctx, int32_t batch, int32_t split_degree) {
     return BC_OK;
 }
 
+// The buffers a batch in flight writes.
+static bc_status sparse_scratch(bc_ctx *ctx) {
+    SparseState &s = ctx->sp;
+    const size_t nn = (size_t)std::max(ctx->n, 1), nh = (size_t)std::max(s.nheavy, 1), batch = (size_t)s.batch;
+    s.arrive = (uint32_t *)bc_dalloc(ctx, nh * sizeof(uint32_t));
+    s.arrive_w = (uint32_t *)bc_dalloc(ctx, nh * s.words * sizeof(uint32_t));
+    s.hacc = (double *)bc_dalloc(ctx, nh * batch * sizeof(double));
+    s.visited = (uint64_t *)bc_dalloc(ctx, nn * s.words * sizeof(uint64_t));
+    s.sigma = (uint64_t *)bc_dalloc(ctx, nn * batch * sizeof(uint64_t));
+    s.cval = (float *)bc_dalloc(ctx, nn * batch * sizeof(float));
+    s.src = (int32_t *)bc_dalloc(ctx, 2 * batch * sizeof(int32_t));
+    s.ctl = (BatchCtl *)bc_dalloc(ctx, sizeof(BatchCtl));
+    s.reach = (unsigned long long *)bc_dalloc(ctx, 256);
+    if (!s.arrive || !s.arrive_w || !s.hacc || !s.visited || !s.sigma || !s.cval || !s.src || !s.ctl || !s.reach)
+        return bc_fail(ctx, BC_ERR_NOMEM, "sparse form: state allocation failed");
+    BC_HIP(ctx, hipMemsetAsync(s.arrive, 0, nh * sizeof(uint32_t), ctx->stream));
+    BC_HIP(ctx, hipMemsetAsync(s.arrive_w, 0, nh * s.words * sizeof(uint32_t), ctx->stream));
+    BC_HIP(ctx, hipMemsetAsync(s.hacc, 0, nh * batch * sizeof(double), ctx->stream));
+    return BC_OK;
+}
+
+bc_status sparse_share(bc_ctx *ctx, const bc_ctx *from) {
+    SparseState &s = ctx->sp;
+    const SparseState &f = from->sp;
+    s.batch = f.batch;
+    s.words = f.words;
+    s.split = f.split;
+    s.bwd_grid = f.bwd_grid;
+    s.fwd_grid = f.fwd_grid;
+    s.nheavy = f.nheavy;
+    s.nseg = f.nseg;
+    s.heavy_id = f.heavy_id;
+    s.heavy_nseg = f.heavy_nseg;
+    s.seg_v = f.seg_v;
+    s.seg_beg = f.seg_beg;
+    s.seg_end = f.seg_end;
+    return sparse_scratch(ctx);
+}
+
 bc_status sparse_prepare(bc_ctx *ctx, int32_t batch, int32_t split_degree) {
     const bc_status st = sparse_shape(ctx, batch, split_degree);
     if (st != BC_OK) return st;
@@ -1501,21 +1543,13 @@ bc_status sparse_prepare(bc_ctx *ctx, int32_t batch, int32_t split_degree) {
     const size_t nh = std::max<size_t>((size_t)nheavy, 1), ns = std::max<size_t>(seg_v.size(), 1);
     s.heavy_id = (int32_t *)bc_dalloc(ctx, nn * sizeof(int32_t));
     s.heavy_nseg = (int32_t *)bc_dalloc(ctx, nh * sizeof(int32_t));
-    s.arrive = (uint32_t *)bc_dalloc(ctx, nh * sizeof(uint32_t));
-    s.arrive_w = (uint32_t *)bc_dalloc(ctx, nh * s.words * sizeof(uint32_t));
     s.seg_v = (int32_t *)bc_dalloc(ctx, ns * sizeof(int32_t));
     s.seg_beg = (int32_t *)bc_dalloc(ctx, ns * sizeof(int32_t));
     s.seg_end = (int32_t *)bc_dalloc(ctx, ns * sizeof(int32_t));
-    s.hacc = (double *)bc_dalloc(ctx, nh * batch * sizeof(double));
-    s.visited = (uint64_t *)bc_dalloc(ctx, nn * s.words * sizeof(uint64_t));
-    s.sigma = (uint64_t *)bc_dalloc(ctx, nn * batch * sizeof(uint64_t));
-    s.cval = (float *)bc_dalloc(ctx, nn * batch * sizeof(float));
-    s.src = (int32_t *)bc_dalloc(ctx, 2 * batch * sizeof(int32_t));
-    s.ctl = (BatchCtl *)bc_dalloc(ctx, sizeof(BatchCtl));
-    s.reach = (unsigned long long *)bc_dalloc(ctx, 256);
-    if (!s.heavy_id || !s.heavy_nseg || !s.arrive || !s.arrive_w || !s.seg_v || !s.seg_beg || !s.seg_end || !s.hacc || !s.visited ||
-        !s.sigma || !s.cval || !s.src || !s.ctl || !s.reach)
+    if (!s.heavy_id || !s.heavy_nseg || !s.seg_v || !s.seg_beg || !s.seg_end)
         return bc_fail(ctx, BC_ERR_NOMEM, "sparse form: state allocation failed");
+    const bc_status sc = sparse_scratch(ctx);
+    if (sc != BC_OK) return sc;
     if (n > 0)
         BC_HIP(ctx, hipMemcpyAsync(s.heavy_id, heavy_id.data(), nn * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
     if (nheavy) {
@@ -1525,9 +1559,6 @@ bc_status sparse_prepare(bc_ctx *ctx, int32_t batch, int32_t split_degree) {
         BC_HIP(ctx, hipMemcpyAsync(s.seg_beg, seg_beg.data(), seg_v.size() * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
         BC_HIP(ctx, hipMemcpyAsync(s.seg_end, seg_end.data(), seg_v.size() * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
     }
-    BC_HIP(ctx, hipMemsetAsync(s.arrive, 0, nh * sizeof(uint32_t), ctx->stream));
-    BC_HIP(ctx, hipMemsetAsync(s.arrive_w, 0, nh * s.words * sizeof(uint32_t), ctx->stream));
-    BC_HIP(ctx, hipMemsetAsync(s.hacc, 0, nh * batch * sizeof(double), ctx->stream));
     if (ctx->timing) {
         // a process's first launch loads the code: 3 ms that no timed launch should count
         hipLaunchKernelGGL(k_ctl_skip, dim3(1), dim3(64), 0, ctx->stream, s.ctl);
@@ -1574,12 +1605,25 @@ constexpr int MAX_LANES = 3;
 // / 6.5, batch 512 9.7 / 6.9 / 6.1; RMAT-16 (108 MB a lane) 94 / 67.5 / 66.0;
 // a ring lattice of 20000 204 / 136 / 116; G(5003, 50/5002) by products, batch
 // 512, 5.0 / 3.3 / 3.2; G(16384, 256/16383) (117 MB) 52.9 / 51.3 / 53.6.  Setting
-// a lane up costs about a millisecond once, so a first run of fewer than four
-// batches goes without.  Timed and weighted batches are driven from the host,
-// one at a time.
-int lanes_for(const bc_ctx *ctx, int64_t nb) {
+// two lanes up takes half a millisecond and a few microseconds per recorded
+// launch, so a context's runs go without until they would have saved as much: a
+// third of their time, a launch taken as 4.5 us, a launch of products as 25 more
+// and an arc and word as 0.1 ns (the batches of RMAT-13 to RMAT-16 take as long,
+// to a fifth).  A context's first run, us with lanes / without: a star of 9000,
+// 1500 sources, batch 256, 1210 / 720; K(1200), 300 sources, batch 64, 1170 / 495;
+// RMAT-14, 1500 sources, batch 256, 2150 / 2080; G(3000) of degree 64 by products,
+// all sources, batch 256, 2650 / 4320.  Timed and weighted batches are driven from
+// the host, one at a time.
+int lanes_for(bc_ctx *ctx, int64_t nb) {
     if (ctx->timing == 1 || ctx->weighted || ctx->host_driven) return 1;
     if (nb < (ctx->lanes.empty() ? 4 : 2)) return 1;
+    if (ctx->lanes.empty()) {
+        const double launches = 2.0 * ctx->sp.depth_max + 4.0;
+        const bool products = ctx->hy.products ? std::min(ctx->hy.theta_fwd, ctx->hy.theta_bwd) <= 1.0 : ctx->al.every_level;
+        const double batch = (products ? 29.5 : 4.5) * launches + 1e-4 * (double)ctx->nnz * ctx->sp.words;
+        ctx->lane_saving += (double)nb * batch / 3.0;
+        if (ctx->lane_saving < 500.0 + 4.0 * launches) return 1;
+    }
     const size_t cells = (size_t)ctx->n * ctx->sp.batch;
     // its memory: counts and c, and a bitmap per level
     const size_t levels = (size_t)std::max(ctx->sp.depth_max + 1, 16);
@@ -1647,8 +1691,6 @@ void lane_free(bc_ctx *t) {
     sparse_graphs_release(t);
     auto owned = t->owned;
     for (auto &pr : owned) bc_dfree(t, pr.first);
-    if (t->sp.any_host) hipHostFree(t->sp.any_host);
-    if (t->status_host) hipHostFree(t->status_host);
     delete t;
 }
 
@@ -1656,7 +1698,7 @@ bc_status lane_prepare(bc_ctx *t, const bc_ctx *ctx) {
     t->n = ctx->n;
     t->nnz = ctx->nnz;
     t->max_degree = ctx->max_degree;
-    t->h_row_ptr = ctx->h_row_ptr;
+    t->lane = true;
     t->device = ctx->device;
     t->stream = ctx->stream;
     t->alloc = ctx->alloc;
@@ -1669,11 +1711,10 @@ bc_status lane_prepare(bc_ctx *t, const bc_ctx *ctx) {
     t->form = ctx->form;
     t->fold = ctx->fold;
     t->status = (uint32_t *)bc_dalloc(t, 256);
-    t->status_host = (uint32_t *)bc_halloc(256);
-    if (!t->status || !t->status_host)
+    if (!t->status)
         return bc_fail(t, BC_ERR_NOMEM, "batch lane: allocation failed");
     BC_HIP(t, hipMemsetAsync(t->status, 0, 256, t->stream));
-    bc_status st = sparse_prepare(t, ctx->sp.batch, ctx->sp.split);
+    bc_status st = sparse_share(t, ctx);
     if (st == BC_OK && ctx->al.planes) st = algebraic_share(t, ctx);
     return st;
 }

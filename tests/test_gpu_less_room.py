@@ -157,8 +157,7 @@ def test_lanes_give_way_to_deeper_levels(gpu_lib):
     a, ctx = context(g, "sparse", 64)
     lib = B.load()
     print("less_room give way", flush=True)
-    assert lib.bc_run(ctx, shallow.ctypes.data, shallow.size, B.BC_MEM_HOST) == B.BC_OK
-    want = oracle.bc(g, sources=shallow)
+    want = run_until_lanes(ctx, a, shallow) * oracle.bc(g, sources=shallow)
     assert rel_err(read(ctx, g.n), want) <= 1e-5
     # room for a growth to 256 levels beside the 128 before only without the lanes,
     # of which each holds 12 bytes for a vertex and source
@@ -171,6 +170,17 @@ def test_lanes_give_way_to_deeper_levels(gpu_lib):
     a.refuse = lambda nbytes: False
     lib.bc_destroy(ctx)
     assert not a.live
+
+
+def run_until_lanes(ctx, a, src):
+    """Runs until the context has set its lanes up (more than a dozen requests
+    each); returns how often."""
+    for times in range(1, 100):
+        calls = a.calls
+        assert B.load().bc_run(ctx, src.ctypes.data, src.size, B.BC_MEM_HOST) == B.BC_OK
+        if a.calls >= calls + 20:
+            return times
+    raise AssertionError("no lanes")
 
 
 def refuse_next(a):
@@ -190,6 +200,7 @@ def test_lanes_given_up_leave_their_overflow(gpu_lib):
     a, ctx = context(g, "sparse", 64)
     lib = B.load()
     print("less_room overflow", flush=True)
+    run_until_lanes(ctx, a, np.arange(1, 8 * 64 + 1, dtype=np.int32))
     for _ in range(2):  # the second run's counts are 64 bits wide from the start
         assert lib.bc_reset(ctx) == B.BC_OK
         assert lib.bc_run(ctx, corners.ctypes.data, corners.size, B.BC_MEM_HOST) == B.BC_OK
@@ -207,11 +218,12 @@ def test_lanes_given_up_leave_their_products(gpu_lib):
     g = gg.er_plus_tree(2500, 20.0, 4)
     lib = B.load()
     seen = []
+    gpu_lib.BC(g, form="algebraic", batch=256).close()  # tuned: the contexts below start alike
     for give_up in (False, True):
         print(f"less_room products give_up={give_up}", flush=True)
         a, ctx = context(g, "algebraic", 256)
-        for _ in range(2):
-            assert lib.bc_run(ctx, None, -1, B.BC_MEM_HOST) == B.BC_OK
+        run_until_lanes(ctx, a, np.arange(g.n, dtype=np.int32))
+        assert lib.bc_run(ctx, None, -1, B.BC_MEM_HOST) == B.BC_OK
         held = B.bc_get_info(ctx).device_bytes
         if give_up:
             refuse_next(a)
