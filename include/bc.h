@@ -188,9 +188,10 @@ typedef struct {
                              level seen so far plus one) into a HIP graph once
                              and replays it for every batch, two or three
                              batches at a time on streams of the library's
-                             own, forked from the context's stream and joined
-                             to it, with no host
-                             synchronisation between batches; a batch that
+                             own (shared by the contexts of a device), forked
+                             from the context's stream and joined to it, with
+                             no host synchronisation between batches; a batch
+                             that
                              goes deeper, or whose counts need 64 bits, is
                              handed back and re-run when the context is next
                              used.  Nonzero: every batch is driven level by
@@ -352,7 +353,8 @@ bc_status bc_sampled_distances(bc_ctx *ctx, const int32_t *sources, int32_t coun
  * other allocation the context would need on the way (frontier levels for a
  * graph deeper than any batch run so far, a weighted source's larger arena,
  * the handed-back batches of an earlier replayed run) gives BC_ERR_NOMEM
- * instead; an ordinary call with the same sources first makes that room.
+ * instead; an ordinary call with the same sources first makes that room (and
+ * runs handed-back batches, which wait for it).
  * Every call on one GPU uses the same array, which keeps the last call's
  * contents: calls that overlap on one GPU (from several threads, or
  * contexts on other streams) race.  Synchronises.
