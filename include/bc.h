@@ -17,7 +17,9 @@
  * Pairs are ORDERED and nothing is halved: the unordered-pair value is BC/2.
  * Unreachable targets contribute nothing.
  *
- * Every entry point returns a bc_status; no exception crosses this boundary.
+ * Every entry point returns a bc_status; no exception crosses this boundary (a
+ * host allocation that fails inside a call gives BC_ERR_NOMEM, after which the
+ * context can only be destroyed).
  * All pointers are plain host or device pointers as stated per argument.
  * A context owns every device buffer it allocates until bc_destroy.  A context
  * is bound to one HIP stream and one device and is not thread-safe.
@@ -191,11 +193,10 @@ typedef struct {
                              own (shared by the contexts of a device), forked
                              from the context's stream and joined to it, with
                              no host synchronisation between batches; a batch
-                             that
-                             goes deeper, or whose counts need 64 bits, is
-                             handed back and re-run when the context is next
-                             used.  Nonzero: every batch is driven level by
-                             level from the host, one synchronisation per
+                             that goes deeper, or whose counts need 64 bits,
+                             is handed back and re-run when the context is
+                             next used.  Nonzero: every batch is driven level
+                             by level from the host, one synchronisation per
                              batch.  Results are the same. */
 } bc_options;
 

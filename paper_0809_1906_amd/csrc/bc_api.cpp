@@ -108,9 +108,7 @@ void release_all(bc_ctx *ctx) {
     bc_timers_clear(ctx);
     for (hipEvent_t e : ctx->event_pool) hipEventDestroy(e);
     ctx->event_pool.clear();
-    auto owned = ctx->owned;
-    for (auto &pr : owned) bc_dfree(ctx, pr.first);
-    ctx->owned.clear();
+    while (!ctx->owned.empty()) bc_dfree(ctx, ctx->owned.back().first);
     if (ctx->status_host) hipHostFree(ctx->status_host);
     if (ctx->sp.any_host) hipHostFree(ctx->sp.any_host);
     if (ctx->wt.host) hipHostFree(ctx->wt.host);
@@ -129,6 +127,15 @@ bc_status bc_fail(bc_ctx *ctx, bc_status s, const std::string &msg) {
     if (ctx) ctx->err = msg;
     else g_create_error = msg;
     return s;
+}
+
+bc_status bc_threw(bc_ctx *ctx, const char *what) noexcept {
+    if (ctx) ctx->poisoned = true; // the call stopped anywhere
+    try {
+        return bc_fail(ctx, BC_ERR_NOMEM, what);
+    } catch (...) {
+        return BC_ERR_NOMEM;
+    }
 }
 
 bc_status bc_hip(bc_ctx *ctx, hipError_t e, const char *what) {
@@ -274,7 +281,9 @@ const char *bc_last_error(const bc_ctx *ctx) {
     return ctx ? ctx->err.c_str() : g_create_error.c_str();
 }
 
-bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
+} // extern "C"
+
+static bc_status do_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out, bc_ctx *&made) {
     if (!out) return fail_create(BC_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     if (!g) return fail_create(BC_ERR_INVALID_ARG, "graph is NULL");
@@ -359,6 +368,7 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
     // ---- device side ----
     bc_ctx *ctx = new (std::nothrow) bc_ctx();
     if (!ctx) return fail_create(BC_ERR_NOMEM, "host allocation of the context failed");
+    made = ctx;
     ctx->n = n;
     ctx->nnz = nnz;
     ctx->max_degree = max_deg;
@@ -372,6 +382,7 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
 
     auto bail = [&](bc_status s, const std::string &m) {
         const std::string msg = m; // m may be ctx->err, which delete frees
+        made = nullptr;
         release_all(ctx);
         delete ctx;
         return fail_create(s, msg);
@@ -527,7 +538,7 @@ bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
 }
 
 
-bc_status bc_create_many(const bc_graph *gs, int32_t count, const bc_options *opt_in, bc_ctx **out) {
+static bc_status do_create_many(const bc_graph *gs, int32_t count, const bc_options *opt_in, bc_ctx **out, bc_ctx *&made) {
     if (!out) return fail_create(BC_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     if (count < 0 || (count > 0 && !gs)) return fail_create(BC_ERR_INVALID_ARG, "bad graph list");
@@ -580,6 +591,7 @@ bc_status bc_create_many(const bc_graph *gs, int32_t count, const bc_options *op
     }
     bc_ctx *ctx = new (std::nothrow) bc_ctx();
     if (!ctx) return fail_create(BC_ERR_NOMEM, "host allocation of the context failed");
+    made = ctx;
     ctx->n = (int32_t)total_n;
     ctx->nnz = (int32_t)total_arcs;
     ctx->max_degree = max_deg;
@@ -590,6 +602,7 @@ bc_status bc_create_many(const bc_graph *gs, int32_t count, const bc_options *op
     ctx->many = true;
     auto bail = [&](bc_status s, const std::string &m) {
         const std::string msg = m; // m may be ctx->err, which delete frees
+        made = nullptr;
         release_all(ctx);
         delete ctx;
         return fail_create(s, msg);
@@ -683,8 +696,6 @@ static bc_status stage_sources(bc_ctx *ctx, const int32_t *sources, int64_t coun
     return BC_OK;
 }
 
-} // extern "C"
-
 // Synchronising a stream under graph capture, or reading back on it, ends the
 // capture; nothing is recorded.
 static bool capturing(const bc_ctx *ctx) {
@@ -701,8 +712,6 @@ bc_status bc_check_usable(bc_ctx *ctx) {
     return sparse_settle(ctx);
 }
 
-extern "C" {
-
 static bc_status check_overflow(bc_ctx *ctx) {
     BC_HIP(ctx, hipMemcpyAsync(ctx->status_host, ctx->status, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
     for (size_t i = 0; i < ctx->lanes.size(); ++i)
@@ -718,7 +727,7 @@ static bc_status check_overflow(bc_ctx *ctx) {
     return BC_OK;
 }
 
-bc_status bc_run(bc_ctx *ctx, const int32_t *sources, int64_t count, bc_mem mem) {
+static bc_status do_run(bc_ctx *ctx, const int32_t *sources, int64_t count, bc_mem mem) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     bc_status s = bc_check_usable(ctx);
     if (s != BC_OK) return s;
@@ -743,7 +752,7 @@ bc_status bc_run(bc_ctx *ctx, const int32_t *sources, int64_t count, bc_mem mem)
     return s;
 }
 
-bc_status bc_read(bc_ctx *ctx, double *bc_out, bc_mem mem) {
+static bc_status do_read(bc_ctx *ctx, double *bc_out, bc_mem mem) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     if (!bc_out && ctx->n > 0) return bc_fail(ctx, BC_ERR_INVALID_ARG, "bc_out is NULL");
     bc_status s = bc_check_usable(ctx);
@@ -759,7 +768,7 @@ bc_status bc_read(bc_ctx *ctx, double *bc_out, bc_mem mem) {
     return BC_OK;
 }
 
-bc_status bc_read_edges(bc_ctx *ctx, double *eb_out, bc_mem mem) {
+static bc_status do_read_edges(bc_ctx *ctx, double *eb_out, bc_mem mem) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     if (!ctx->edges) return bc_fail(ctx, BC_ERR_UNSUPPORTED, "the context was created without edges");
     if (!eb_out && ctx->nnz > 0) return bc_fail(ctx, BC_ERR_INVALID_ARG, "eb_out is NULL");
@@ -776,7 +785,7 @@ bc_status bc_read_edges(bc_ctx *ctx, double *eb_out, bc_mem mem) {
     return BC_OK;
 }
 
-bc_status bc_reset(bc_ctx *ctx) {
+static bc_status do_reset(bc_ctx *ctx) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     bc_status s = bc_check_usable(ctx);
     if (s == BC_ERR_NOMEM) { // batches still to run: their sums are dropped here
@@ -805,8 +814,6 @@ bc_status bc_reset(bc_ctx *ctx) {
 // Calls that run sources without adding to BC (per-source dumps, all pairs)
 // share the device overflow flag with bc_run: they save it and clear it first,
 // then read what they raised and put the saved value back.
-} // extern "C"
-
 bc_status bc_status_save(bc_ctx *ctx, uint32_t *before) {
     BC_HIP(ctx, hipMemcpyAsync(ctx->status_host, ctx->status, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
     BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -825,9 +832,7 @@ bc_status bc_status_restore(bc_ctx *ctx, uint32_t before, uint32_t *now) {
     return BC_OK;
 }
 
-extern "C" {
-
-bc_status bc_read_sssp(bc_ctx *ctx, const int32_t *sources, int32_t count,
+static bc_status do_read_sssp(bc_ctx *ctx, const int32_t *sources, int32_t count,
                        int32_t *dist, uint64_t *sigma, double *delta) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     bc_status s = bc_check_usable(ctx);
@@ -872,7 +877,7 @@ bc_status bc_read_sssp(bc_ctx *ctx, const int32_t *sources, int32_t count,
     return BC_OK;
 }
 
-bc_status bc_all_pairs(bc_ctx *ctx, double *bc_out, bc_mem mem) {
+static bc_status do_all_pairs(bc_ctx *ctx, double *bc_out, bc_mem mem) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     if (!bc_out && ctx->n > 0) return bc_fail(ctx, BC_ERR_INVALID_ARG, "bc_out is NULL");
     bc_status s = bc_check_usable(ctx);
@@ -910,7 +915,7 @@ bc_status bc_all_pairs(bc_ctx *ctx, double *bc_out, bc_mem mem) {
     return s;
 }
 
-bc_status bc_sampled_distances(bc_ctx *ctx, const int32_t *sources, int32_t count, const int32_t *sample,
+static bc_status do_sampled_distances(bc_ctx *ctx, const int32_t *sources, int32_t count, const int32_t *sample,
                                int32_t nsample, int32_t limit, int32_t *dist_out, bc_mem mem) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     bc_status s = bc_check_usable(ctx);
@@ -928,7 +933,7 @@ bc_status bc_sampled_distances(bc_ctx *ctx, const int32_t *sources, int32_t coun
     return sampled_distances(ctx, sources, count, sample, nsample, limit, dist_out, mem == BC_MEM_DEVICE);
 }
 
-bc_status bc_get_info(const bc_ctx *c, bc_info *out) {
+static bc_status do_get_info(const bc_ctx *c, bc_info *out) {
     if (!c || !out) return BC_ERR_INVALID_ARG;
     bc_ctx *ctx = const_cast<bc_ctx *>(c);
     const bool live = !ctx->poisoned && !capturing(ctx); // else what the host knows
@@ -973,7 +978,7 @@ bc_status bc_get_info(const bc_ctx *c, bc_info *out) {
     return BC_OK;
 }
 
-bc_status bc_get_timing(bc_ctx *ctx, const char *kernel, double *total_ms, int64_t *launches) {
+static bc_status do_get_timing(bc_ctx *ctx, const char *kernel, double *total_ms, int64_t *launches) {
     if (!ctx || !kernel || !total_ms || !launches) return BC_ERR_INVALID_ARG;
     *total_ms = 0.0;
     *launches = 0;
@@ -1002,9 +1007,77 @@ bc_status bc_get_timing(bc_ctx *ctx, const char *kernel, double *total_ms, int64
     return BC_OK;
 }
 
+// ---------------------------------------------------------------------------
+// the C entries: no exception crosses them
+// ---------------------------------------------------------------------------
+
+template <typename F>
+static bc_status create_guarded(F &&create, bc_ctx **out) {
+    bc_ctx *made = nullptr;
+    const bc_status s = bc_guard(nullptr, [&] { return create(made); });
+    if (s != BC_OK && made) { // an exception on the way
+        release_all(made);
+        delete made;
+        *out = nullptr;
+    }
+    return s;
+}
+
+extern "C" {
+
+bc_status bc_create(const bc_graph *g, const bc_options *opt_in, bc_ctx **out) {
+    return create_guarded([&](bc_ctx *&made) { return do_create(g, opt_in, out, made); }, out);
+}
+
+bc_status bc_create_many(const bc_graph *gs, int32_t count, const bc_options *opt_in, bc_ctx **out) {
+    return create_guarded([&](bc_ctx *&made) { return do_create_many(gs, count, opt_in, out, made); }, out);
+}
+
+bc_status bc_run(bc_ctx *ctx, const int32_t *sources, int64_t count, bc_mem mem) {
+    return bc_guard(ctx, [&] { return do_run(ctx, sources, count, mem); });
+}
+
+bc_status bc_read(bc_ctx *ctx, double *bc_out, bc_mem mem) {
+    return bc_guard(ctx, [&] { return do_read(ctx, bc_out, mem); });
+}
+
+bc_status bc_read_edges(bc_ctx *ctx, double *eb_out, bc_mem mem) {
+    return bc_guard(ctx, [&] { return do_read_edges(ctx, eb_out, mem); });
+}
+
+bc_status bc_reset(bc_ctx *ctx) {
+    return bc_guard(ctx, [&] { return do_reset(ctx); });
+}
+
+bc_status bc_read_sssp(bc_ctx *ctx, const int32_t *sources, int32_t count, int32_t *dist, uint64_t *sigma,
+                       double *delta) {
+    return bc_guard(ctx, [&] { return do_read_sssp(ctx, sources, count, dist, sigma, delta); });
+}
+
+bc_status bc_all_pairs(bc_ctx *ctx, double *bc_out, bc_mem mem) {
+    return bc_guard(ctx, [&] { return do_all_pairs(ctx, bc_out, mem); });
+}
+
+bc_status bc_sampled_distances(bc_ctx *ctx, const int32_t *sources, int32_t count, const int32_t *sample,
+                               int32_t nsample, int32_t limit, int32_t *dist_out, bc_mem mem) {
+    return bc_guard(ctx,
+                    [&] { return do_sampled_distances(ctx, sources, count, sample, nsample, limit, dist_out, mem); });
+}
+
+bc_status bc_get_info(const bc_ctx *c, bc_info *out) {
+    return bc_guard(const_cast<bc_ctx *>(c), [&] { return do_get_info(c, out); });
+}
+
+bc_status bc_get_timing(bc_ctx *ctx, const char *kernel, double *total_ms, int64_t *launches) {
+    return bc_guard(ctx, [&] { return do_get_timing(ctx, kernel, total_ms, launches); });
+}
+
 void bc_destroy(bc_ctx *ctx) {
     if (!ctx) return;
-    release_all(ctx);
+    (void)bc_guard(nullptr, [&] {
+        release_all(ctx);
+        return BC_OK;
+    });
     delete ctx;
 }
 

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <exception>
 #include <map>
 #include <string>
 #include <vector>
@@ -324,6 +325,19 @@ bc_status bc_check_usable(bc_ctx *ctx);
 bc_status bc_status_save(bc_ctx *ctx, uint32_t *before);
 bc_status bc_status_restore(bc_ctx *ctx, uint32_t before, uint32_t *now);
 bc_status bc_hip(bc_ctx *ctx, hipError_t e, const char *what);
+// A C entry's body: a host allocation that fails in it, or any other exception,
+// ends the call with BC_ERR_NOMEM, and the context can only be destroyed.
+bc_status bc_threw(bc_ctx *ctx, const char *what) noexcept;
+template <typename F>
+bc_status bc_guard(bc_ctx *ctx, F &&body) noexcept {
+    try {
+        return body();
+    } catch (const std::exception &e) {
+        return bc_threw(ctx, e.what());
+    } catch (...) {
+        return bc_threw(ctx, "unexpected exception");
+    }
+}
 // The thread's HIP error stays set until it is read: whoever takes a failed
 // call in clears it, or a later launch check reports it as its own.
 void bc_clear_error();

@@ -45,8 +45,8 @@ struct NoAllocScope {
     ~NoAllocScope() { ctx->no_alloc = false; }
 };
 
-extern "C" bc_status bc_read_sssp_noalloc(bc_ctx *ctx, const int32_t *sources, int32_t count, int32_t *dist,
-                                          uint64_t *sigma, double *delta) {
+static bc_status do_read_sssp_noalloc(bc_ctx *ctx, const int32_t *sources, int32_t count, int32_t *dist,
+                                      uint64_t *sigma, double *delta) {
     if (!ctx) return BC_ERR_INVALID_ARG;
     NoAllocScope scope(ctx);
     bc_status s = bc_check_usable(ctx);
@@ -94,4 +94,9 @@ extern "C" bc_status bc_read_sssp_noalloc(bc_ctx *ctx, const int32_t *sources, i
     }
     BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return BC_OK;
+}
+
+extern "C" bc_status bc_read_sssp_noalloc(bc_ctx *ctx, const int32_t *sources, int32_t count, int32_t *dist,
+                                          uint64_t *sigma, double *delta) {
+    return bc_guard(ctx, [&] { return do_read_sssp_noalloc(ctx, sources, count, dist, sigma, delta); });
 }

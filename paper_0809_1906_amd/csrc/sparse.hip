@@ -1689,8 +1689,7 @@ void lane_failed(bc_ctx *ctx, const bc_ctx *lane) {
 
 void lane_free(bc_ctx *t) {
     sparse_graphs_release(t);
-    auto owned = t->owned;
-    for (auto &pr : owned) bc_dfree(t, pr.first);
+    while (!t->owned.empty()) bc_dfree(t, t->owned.back().first);
     delete t;
 }
 
