@@ -126,6 +126,17 @@ struct HeavyRows {
     }
 };
 
+// The entries of a level that a wave takes: its first, the step from lane to
+// lane, and so on every T-th.  A wave's lanes have entries next to each other,
+// whose rows are of like lengths; or (spread) the workgroup's waves take turns,
+// so that the heavy rows, which come together too, are dealt to all of them.
+template <int T, bool HV>
+struct Deal {
+    int32_t first, step;
+    __device__ explicit Deal(bool spread)
+        : first(HV && spread ? threadIdx.x >> 6 : threadIdx.x & ~63u), step(HV && spread ? T / 64 : 1) {}
+};
+
 // Forward sweep of the group from sources src(0) .. src(K - 1) by the T
 // threads of the workgroup; cnt[0..2] is LDS scratch.  Returns the number of
 // levels, or -1 when there were more than a.levels.  *ovf in LDS is set when a
@@ -136,9 +147,10 @@ struct HeavyRows {
 // such vertices would not do: a small count can be the one that wraps.)
 template <typename ST, int T, bool HV, typename Src>
 __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__restrict__ cols, Src src, ST safe,
-                                           int32_t *cnt, uint32_t *ovf) {
+                                           int32_t *cnt, uint32_t *ovf, bool spread) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int32_t n1 = a.n + 1, E = a.K * n1;
+    const Deal<T, HV> deal(spread);
     {
         uint32_t *st4 = reinterpret_cast<uint32_t *>(a.st);
         for (int32_t i = tid; i < (E >> 2); i += T) st4[i] = 0x01010101u * UNREACHED;
@@ -218,9 +230,10 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
             }
         };
         bool large = false;
-        for (int32_t i0 = qb + (tid & ~63); i0 < qe; i0 += T) {
-            const bool act = i0 + lane < qe;
-            const int32_t id = act ? (int32_t)a.queue[i0 + lane] : 0;
+        for (int32_t i0 = qb + deal.first; i0 < qe; i0 += T) {
+            const int32_t i = i0 + lane * deal.step;
+            const bool act = i < qe;
+            const int32_t id = act ? (int32_t)a.queue[i] : 0;
             const int32_t base = a.source_of(id) * n1;
             const int32_t v = id - base;
             const ST sv = a.sc[id];
@@ -267,9 +280,10 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
 // every level but 0.  put(k, v, delta) receives every dependency.
 template <typename ST, int T, bool HV, bool F32, typename Put>
 __device__ __forceinline__ void backward(const Arrays<ST> &a, const uint4 *__restrict__ cols, int32_t nlev,
-                                         int32_t lowest, Put put) {
-    const int tid = threadIdx.x, lane = tid & 63;
+                                         int32_t lowest, bool spread, Put put) {
+    const int lane = threadIdx.x & 63;
     const int32_t n1 = a.n + 1;
+    const Deal<T, HV> deal(spread);
     for (int32_t l = nlev - 1; l >= lowest; --l) {
         const uint32_t next = level_bit(l + 1);
         const int32_t lb = a.lev[l], le = a.lev[l + 1];
@@ -289,9 +303,10 @@ __device__ __forceinline__ void backward(const Arrays<ST> &a, const uint4 *__res
 #pragma unroll
             for (int j = 0; j < BURST; ++j) sum += coef(t[j] & next ? x[j] : (ST)0);
         };
-        for (int32_t i0 = lb + (tid & ~63); i0 < le; i0 += T) {
-            const bool act = i0 + lane < le;
-            const int32_t id = act ? (int32_t)a.queue[i0 + lane] : 0;
+        for (int32_t i0 = lb + deal.first; i0 < le; i0 += T) {
+            const int32_t i = i0 + lane * deal.step;
+            const bool act = i < le;
+            const int32_t id = act ? (int32_t)a.queue[i] : 0;
             const int32_t k = a.source_of(id), base = k * n1;
             const int32_t v = id - base;
             double acc = 0.0;

@@ -148,3 +148,31 @@ def test_padded_columns(gpu_lib, name, order):
     with gpu_lib.BC(g, form="plain", vertex_order=order) as ctx:
         ctx.run()
         assert rel_err(ctx.read(), oracle.bc(g, threads=8)) <= 1e-12  # FP64 throughout
+
+
+DEALT = {
+    "all-heavy": lambda: gg.er_plus_tree(500, 100.0, 1),
+    "few-heavy": lambda: gg.er_plus_tree(1500, 50.0, 2),  # their entries stay together
+    "bipartite": lambda: gg.complete_bipartite(900, 20),
+    "one-heavy": lambda: gg.disjoint_union(gg.star(66), gg.path(500), gg.star(1200)),
+    "hubs": lambda: gg.rmat(11, 16, 5),
+}
+
+
+@pytest.mark.parametrize("form,tol", [("plain", 1e-12), ("sparse", 1e-5)])
+@pytest.mark.parametrize("name", list(DEALT))
+def test_heavy_rows_dealt(gpu_lib, name, form, tol):
+    """Levels of one to more than a workgroup's entries, one source and several
+    a group, with the heavy rows dealt to the waves and without."""
+    g = DEALT[name]()
+    print(f"small dealt {name} {form} n={g.n} heavy={int((g.degrees() > 64).sum())}", flush=True)
+    with gpu_lib.BC(g, form=form, batch=64 if form == "sparse" else 0) as ctx:
+        for src in (np.arange(g.n, dtype=np.int32), gg.sample_sources(g.n, 20, 3)):
+            ctx.reset()
+            ctx.run(src)
+            assert rel_err(ctx.read(), oracle.bc(g, sources=src, threads=8)) <= tol
+        dist, sigma, delta = ctx.sssp(src[:3])
+    for i in range(3):
+        d, sg, dl = oracle.sssp_u64(g, int(src[i]))
+        assert np.array_equal(dist[i], d) and np.array_equal(sigma[i], sg)
+        assert rel_err(delta[i], dl) <= tol
