@@ -185,7 +185,7 @@ struct LdsColumns {
 // State of a small graph's LDS sweeps (small.hip).
 struct SmallState {
     bool on = false;
-    bool spread = false;        // heavy rows hold much of the arcs: dealt to all waves
+    int rows = 0;               // where its arcs are (lds_sweep::Rows)
     int cus = 0;
     LdsColumns cols;
     uint32_t *count = nullptr;  // [0] units handed back by the 32-bit sweep, [1] most levels seen,

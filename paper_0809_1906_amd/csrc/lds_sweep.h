@@ -126,15 +126,27 @@ struct HeavyRows {
     }
 };
 
+// Where a graph's arcs are (small.hip): few in heavy rows; many, in rows far
+// longer than others (hubs); many, in rows of like lengths, of twice HEAVY bursts
+// or more on average (long).
+enum Rows { FEW_HEAVY, HUBS, ALIKE_LONG, ALIKE };
+
 // The entries of a level that a wave takes: its first, the step from lane to
-// lane, and so on every T-th.  A wave's lanes have entries next to each other,
-// whose rows are of like lengths; or (spread) the workgroup's waves take turns,
-// so that the heavy rows, which come together too, are dealt to all of them.
+// lane, and so on every T-th; and the bursts up to which a row is one lane's.  A
+// wave's lanes have entries next to each other, whose rows are of like lengths.
+// Or the workgroup's waves take turns, so that the heavy rows, which come
+// together too, are dealt to all of them: where there are hubs, and at levels
+// that leave waves without entries.  At other levels rows of like lengths, not
+// long ones, keep a wave's lanes busy up to twice the bursts.
 template <int T, bool HV>
 struct Deal {
-    int32_t first, step;
-    __device__ explicit Deal(bool spread)
-        : first(HV && spread ? threadIdx.x >> 6 : threadIdx.x & ~63u), step(HV && spread ? T / 64 : 1) {}
+    int32_t first, step, limit;
+    __device__ Deal(Rows rows, int32_t entries) {
+        const bool turns = HV && (rows == HUBS || (rows >= ALIKE_LONG && entries < T / 2));
+        first = turns ? threadIdx.x >> 6 : threadIdx.x & ~63u;
+        step = turns ? T / 64 : 1;
+        limit = HV && rows == ALIKE && entries >= T / 2 ? 2 * HEAVY : HEAVY;
+    }
 };
 
 // Forward sweep of the group from sources src(0) .. src(K - 1) by the T
@@ -147,10 +159,9 @@ struct Deal {
 // such vertices would not do: a small count can be the one that wraps.)
 template <typename ST, int T, bool HV, typename Src>
 __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__restrict__ cols, Src src, ST safe,
-                                           int32_t *cnt, uint32_t *ovf, bool spread) {
+                                           int32_t *cnt, uint32_t *ovf, Rows rows) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int32_t n1 = a.n + 1, E = a.K * n1;
-    const Deal<T, HV> deal(spread);
     {
         uint32_t *st4 = reinterpret_cast<uint32_t *>(a.st);
         for (int32_t i = tid; i < (E >> 2); i += T) st4[i] = 0x01010101u * UNREACHED;
@@ -230,6 +241,7 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
             }
         };
         bool large = false;
+        const Deal<T, HV> deal(rows, qe - qb);
         for (int32_t i0 = qb + deal.first; i0 < qe; i0 += T) {
             const int32_t i = i0 + lane * deal.step;
             const bool act = i < qe;
@@ -240,8 +252,8 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
             int32_t b = act ? (int32_t)a.rp[v] : 0;
             const int32_t e = act ? (int32_t)a.rp[v + 1] : 0;
             large |= act && sv > safe;
-            uint64_t heavy = HV ? __ballot(e - b > HEAVY) : 0;
-            const bool light = !HV || e - b <= HEAVY;
+            uint64_t heavy = HV ? __ballot(e - b > deal.limit) : 0;
+            const bool light = !HV || e - b <= deal.limit;
             while (__any(light && b < e)) {
                 const bool more = light && b < e;
                 uint4 c = make_uint4(0, 0, 0, 0);
@@ -280,10 +292,9 @@ __device__ __forceinline__ int32_t forward(const Arrays<ST> &a, const uint4 *__r
 // every level but 0.  put(k, v, delta) receives every dependency.
 template <typename ST, int T, bool HV, bool F32, typename Put>
 __device__ __forceinline__ void backward(const Arrays<ST> &a, const uint4 *__restrict__ cols, int32_t nlev,
-                                         int32_t lowest, bool spread, Put put) {
+                                         int32_t lowest, Rows rows, Put put) {
     const int lane = threadIdx.x & 63;
     const int32_t n1 = a.n + 1;
-    const Deal<T, HV> deal(spread);
     for (int32_t l = nlev - 1; l >= lowest; --l) {
         const uint32_t next = level_bit(l + 1);
         const int32_t lb = a.lev[l], le = a.lev[l + 1];
@@ -303,6 +314,7 @@ __device__ __forceinline__ void backward(const Arrays<ST> &a, const uint4 *__res
 #pragma unroll
             for (int j = 0; j < BURST; ++j) sum += coef(t[j] & next ? x[j] : (ST)0);
         };
+        const Deal<T, HV> deal(rows, le - lb);
         for (int32_t i0 = lb + deal.first; i0 < le; i0 += T) {
             const int32_t i = i0 + lane * deal.step;
             const bool act = i < le;
@@ -313,8 +325,8 @@ __device__ __forceinline__ void backward(const Arrays<ST> &a, const uint4 *__res
             if (l + 1 < nlev) {
                 int32_t b = act ? (int32_t)a.rp[v] : 0;
                 const int32_t e = act ? (int32_t)a.rp[v + 1] : 0;
-                uint64_t heavy = HV ? __ballot(e - b > HEAVY) : 0;
-                if (!HV || e - b <= HEAVY)
+                uint64_t heavy = HV ? __ballot(e - b > deal.limit) : 0;
+                if (!HV || e - b <= deal.limit)
                     for (; b < e; ++b) burst(cols[b], base, acc);
                 while (HV && heavy) {
                     const HeavyRows r(heavy, lane);

@@ -267,9 +267,10 @@ __global__ __launch_bounds__(T) void k_mg_group(MultiArgs a) {
             for (int32_t k0 = s0; k0 < s1; k0 += K) {
                 s.K = min(K, s1 - k0);
                 const int32_t nlev = lds_sweep::forward<ST, T, HV>(
-                    s, cols, [&](int32_t k) { return k0 + k; }, (ST)safe, s_cnt, &s_fail, false);
+                    s, cols, [&](int32_t k) { return k0 + k; }, (ST)safe, s_cnt, &s_fail, lds_sweep::FEW_HEAVY);
                 if (nlev < 0 || (!WIDE && s_fail)) return false;
-                lds_sweep::backward<ST, T, HV, true>(s, cols, nlev, 1, false, [](int32_t, int32_t, double) {});
+                lds_sweep::backward<ST, T, HV, true>(s, cols, nlev, 1, lds_sweep::FEW_HEAVY,
+                                                                      [](int32_t, int32_t, double) {});
             }
             return true;
         };

@@ -32,7 +32,7 @@ struct SmallArgs {
     const uint32_t *list_count;
     int32_t *redo;          // 32-bit counts: units to run again in 64 bits
     uint32_t *redo_count;
-    bool spread;            // heavy rows are dealt to all waves
+    lds_sweep::Rows rows;   // where the arcs are
     uint64_t safe;          // largest count whose sums need no wrap test
     double *bc;
     uint32_t *status, *depth;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(ST_T) void k_small_sweep(SmallArgs a) {
         for (int64_t k0 = i0; k0 < i1; k0 += a.K) {
             s.K = (int32_t)min((int64_t)a.K, i1 - k0);
             const int32_t nlev = lds_sweep::forward<ST, ST_T, HV>(
-                s, a.bursts, [&](int32_t k) { return a.sources[k0 + k]; }, (ST)a.safe, s_cnt, &s_fail, a.spread);
+                s, a.bursts, [&](int32_t k) { return a.sources[k0 + k]; }, (ST)a.safe, s_cnt, &s_fail, a.rows);
             if (s_fail) { // uniform: the forward ends with a barrier
                 __syncthreads();
                 if (tid == 0) {
@@ -94,12 +94,12 @@ __global__ __launch_bounds__(ST_T) void k_small_sweep(SmallArgs a) {
                     }
                 __syncthreads(); // the backward overwrites the counts
                 if (!a.delta_dump) continue;
-                lds_sweep::backward<ST, ST_T, HV, F32>(s, a.bursts, nlev, 0, a.spread,
+                lds_sweep::backward<ST, ST_T, HV, F32>(s, a.bursts, nlev, 0, a.rows,
                                                        [&](int32_t k, int32_t v, double d) {
                     a.delta_dump[(size_t)(k0 + k) * n + v] = d;
                 });
             } else {
-                lds_sweep::backward<ST, ST_T, HV, F32>(s, a.bursts, nlev, 1, a.spread, [](int32_t, int32_t, double) {});
+                lds_sweep::backward<ST, ST_T, HV, F32>(s, a.bursts, nlev, 1, a.rows, [](int32_t, int32_t, double) {});
             }
         }
     }
@@ -133,15 +133,16 @@ bool small_fits(const bc_ctx *ctx) {
 }
 
 // The sparse and hybrid forms' line.  A batch pays two launches per level and
-// pulls every row at every level; the LDS sweep pays per arc and source.
-// Microseconds for one source / milliseconds for all, LDS against batches of
-// 256 (of 512 faster by a fifth): a path of 1000 1930 / 1.74 against 8350 /
-// 24.7; a ring lattice of 6001 295 / 2.3 against 1180 / 22; G(4000) degree 10
-// 170 / 0.38 against 274 / 1.75; RMAT-12 (97 thousand arcs) 293 / 1.10 against
-// 291 / 1.21; G(6500) degree 26 (170) 193 / 1.7 against 273 / 3.4.  Past the
-// line the batches catch up: R-MAT of 5960 vertices (135) 267 / 2.9 against 310
-// / 2.2, RMAT-13 (204) / 5.4 against / 2.6 and 2.1 at 512.  Hubs cost the LDS
-// sweep more, so the last stretch is for graphs without.
+// pulls every row at every level; the LDS sweep pays per arc and source.  A run
+// and its read, microseconds for one source / milliseconds for all, LDS against
+// batches of 256: a path of 1000 1177 / 1.73 against 4968 / 24.6; a ring lattice
+// of 6001 220 / 2.3 against 924 / 22.6; G(4000) degree 10 88 / 0.37 against 152 /
+// 1.74; RMAT-12 (97 thousand arcs) 135 / 1.02 against 182 / 1.21; G(6500) degree
+// 26 (170) 120 / 1.65 against 158 / 3.3; G(2500) degree 75 (194) 130 / 0.61
+// against 148 / 0.94.  Past the line the batches catch up: R-MAT of 5960 vertices
+// (135) 169 / 2.5 against 185 / 2.2, RMAT-13 (204) 212 / 4.1 against 210 / 2.6,
+// and 2.1 at 512.  Hubs cost the LDS sweep more, so the last stretch is for
+// graphs without.
 // Edge terms, kernel timing, host-driven batches and levels by products ask
 // for the batched kernels themselves.
 bool small_takes_batches(const bc_ctx *ctx) {
@@ -182,17 +183,24 @@ bc_status small_prepare(bc_ctx *ctx) {
     const size_t columns = (size_t)bursts_of(ctx) * sizeof(uint4);
     m.redo_cap = std::max(ctx->n, 4096);
     // Heavy rows come next to each other (by degree), a few waves' entries while
-    // the others wait: dealt to all waves where they hold a quarter of the arcs.
-    // Microseconds for one source / all, together / dealt: K(3000,20) 181 / 1204 and
-    // 91 / 566; RMAT-11 174 / 458 and 130 / 443; degree about 90 throughout, 2000
-    // vertices, 190 / 768 and 160 / 769.  Light rows' waves are mixed by it: G(4000)
-    // of degree 40, few rows heavy, 108 / 650 and 115 / 717.
+    // the others wait, so they are dealt to all waves where they hold a quarter of
+    // the arcs.  Microseconds for one source / all, a wave's entries together / as
+    // chosen: K(3000,20) 182 / 1204 and 91 / 458, RMAT-12 174 / 1094 and 135 / 1028; of
+    // like lengths, G(1700) of degree 75 196 / 682 and 113 / 313, a ring lattice of 1800
+    // and degree 72 1137 / 2205 and 271 / 1189.  (All sources of K(1000,60) lose: 304
+    // and 342.)  With few arcs in heavy rows the light ones would be mixed by it:
+    // G(4000) of degree 40 108 / 650 together, 115 / 717 dealt.
     int64_t heavy = 0;
     for (int32_t v = 0; v < ctx->n; ++v) {
         const int32_t deg = ctx->h_row_ptr[(size_t)v + 1] - ctx->h_row_ptr[(size_t)v];
         if (deg > lds_sweep::HEAVY * lds_sweep::BURST) heavy += deg;
     }
-    m.spread = 4 * heavy >= ctx->nnz && heavy > 0;
+    const bool alike = (int64_t)ctx->max_degree * ctx->n <= 2 * (int64_t)ctx->nnz;
+    const bool wide = ctx->nnz >= (int64_t)ctx->n * 2 * lds_sweep::HEAVY * lds_sweep::BURST;
+    m.rows = 4 * heavy < ctx->nnz ? lds_sweep::FEW_HEAVY
+             : !alike             ? lds_sweep::HUBS
+             : wide               ? lds_sweep::ALIKE_LONG
+                                  : lds_sweep::ALIKE;
     char *d = (char *)bc_dalloc(ctx, 256 + columns + (size_t)m.redo_cap * sizeof(int32_t) +
                                          ((size_t)ctx->n + 1) * sizeof(uint16_t));
     if (!d) return bc_fail(ctx, BC_ERR_NOMEM, "small graph: allocation failed");
@@ -219,16 +227,22 @@ bc_status small_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool w
     a.bursts = (const uint4 *)m.cols.bursts;
     a.sources = d_sources;
     a.count = count;
-    a.spread = m.spread;
+    a.rows = (lds_sweep::Rows)m.rows;
     a.bc = ctx->bc;
     a.status = ctx->status;
     a.depth = wide ? nullptr : m.count + (ctx->no_alloc ? 2 : 1);
     a.dist_dump = dist_dump;
     a.sigma_dump = sigma_dump;
     a.delta_dump = delta_dump;
-    // as many sources per group as fit, but no fewer groups than compute units
+    // As many sources per group as fit, but no fewer groups than compute units,
+    // and where they come in several rounds, groups that fill the last one too
+    // (G(2500) of degree 75, groups of 8 / of 5: 1860 / 1370 us for all sources).
     const int32_t even = (int32_t)std::min<int64_t>((count + cus - 1) / cus, 65535);
-    const int32_t k64 = lds_sweep::group_size<uint64_t>(ST_BYTES, n, n, even);
+    auto filled = [&](int32_t k) {
+        const int64_t rounds = (count + (int64_t)cus * k - 1) / ((int64_t)cus * k);
+        return (int32_t)((count + cus * rounds - 1) / (cus * rounds));
+    };
+    const int32_t k64 = filled(lds_sweep::group_size<uint64_t>(ST_BYTES, n, n, even));
     if (wide) {
         a.K = a.unit = k64;
         a.nunits = (count + a.unit - 1) / a.unit;
@@ -237,7 +251,7 @@ bc_status small_run(bc_ctx *ctx, const int32_t *d_sources, int64_t count, bool w
         BC_HIP(ctx, hipGetLastError());
         return BC_OK;
     }
-    a.K = a.unit = lds_sweep::group_size<uint32_t>(ST_BYTES, n, n, even);
+    a.K = a.unit = filled(lds_sweep::group_size<uint32_t>(ST_BYTES, n, n, even));
     a.nunits = (count + a.unit - 1) / a.unit;
     a.safe = 0xFFFFFFFFull / deg;
     if (a.nunits > m.redo_cap) {
