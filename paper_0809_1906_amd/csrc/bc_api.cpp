@@ -939,7 +939,7 @@ static bc_status do_get_info(const bc_ctx *c, bc_info *out) {
     const bool live = !ctx->poisoned && !capturing(ctx); // else what the host knows
     if (live) {
         (void)sparse_settle(ctx); // replays' depth and sources
-        ctx->max_levels = std::max(ctx->max_levels, small_levels(ctx, 1));
+        ctx->max_levels = std::max(ctx->max_levels, small_levels(ctx));
     }
     memset(out, 0, sizeof(*out));
     out->n = ctx->n;

@@ -409,9 +409,8 @@ bool small_fits(const bc_ctx *ctx);
 // Do the sparse and hybrid forms run their sources that way?
 bool small_takes_batches(const bc_ctx *ctx);
 bc_status small_prepare(bc_ctx *ctx);
-// Most levels any source had: slot 1 by ordinary calls, 2 in the last
-// allocation-free one (synchronises); 0 off this route.
-int32_t small_levels(bc_ctx *ctx, int slot);
+// Most levels any source of ordinary calls had (synchronises); 0 off this route.
+int32_t small_levels(bc_ctx *ctx);
 bc_status small_check_room(bc_ctx *ctx);
 // wide: 64-bit counts and FP64 c(v) throughout; else 32-bit counts and FP32
 // c(v), groups whose counts pass 32 bits again in 64 bits.  With dist_dump,

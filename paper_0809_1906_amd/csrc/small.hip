@@ -152,10 +152,10 @@ bool small_takes_batches(const bc_ctx *ctx) {
     return ctx->nnz <= 131072 || (ctx->nnz <= 196608 && ctx->max_degree <= 256);
 }
 
-int32_t small_levels(bc_ctx *ctx, int slot) {
+int32_t small_levels(bc_ctx *ctx) {
     if (!ctx->sm.on || ctx->form == BC_FORM_PLAIN_FP64) return 0;
     uint32_t x = 0;
-    if (hipMemcpyAsync(&x, ctx->sm.count + slot, sizeof x, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+    if (hipMemcpyAsync(&x, ctx->sm.count + 1, sizeof x, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
         hipStreamSynchronize(ctx->stream) != hipSuccess)
         return 0;
     return (int32_t)x;
@@ -166,7 +166,10 @@ int32_t small_levels(bc_ctx *ctx, int slot) {
 // more) is refused, as it is where those kernels run: whichever route a graph
 // takes, a context answers alike.
 bc_status small_check_room(bc_ctx *ctx) {
-    const int32_t seen = small_levels(ctx, 1), now = small_levels(ctx, 2);
+    uint32_t levels[2]; // of ordinary calls, of this one
+    BC_HIP(ctx, hipMemcpyAsync(levels, ctx->sm.count + 1, sizeof levels, hipMemcpyDeviceToHost, ctx->stream));
+    BC_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    const int32_t seen = (int32_t)levels[0], now = (int32_t)levels[1];
     int32_t cap = 16;
     while (cap < seen + 1) cap *= 2;
     if (now > seen && now + 2 > cap)
